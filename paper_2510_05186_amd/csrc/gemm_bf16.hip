@@ -355,27 +355,35 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
 // realises the LDS swizzle.  Requires K % 64 == 0 and operands below 4 GiB (checked on the host); rows or
 // columns past the operand read as zero through the buffer range check.
 //
+// What bounds them is power: the board holds its limit by lowering the clock, so time goes with the energy per flop.
+// v_mfma_f32_16x16x32_bf16 moves half the accumulator traffic per flop of v_mfma_f32_32x32x16_bf16 and runs 15 % faster in
+// a loop that does nothing else (2070 against 1806 TFLOP/s, operands drawn at random); in these kernels, 32x32x16 -> 16x16x32:
+// 4096 x 12288 x 4096 1358 -> 1479 TFLOP/s, 4096 x 4096 x 11008 1400 -> 1528, 4096 x 8192 x 28672 1430 -> 1503, the
+// grouped TN set of a hidden-8192 layer 1233 -> 1285 (fp32 store 1316 -> 1370).  The clock rises from 1.59 to 1.81 GHz, the matrix
+// pipe is busy 81 % of the cycles (88 % before).  Walking j to and fro (consecutive MFMAs share an operand) is worth 0.7 %.
+//
 //  NT (operands contiguous along k): a stage holds [256 rows][64 k]; the load for rows 8 q .. 8 q + 7 has lane i
-//     fetch row 8 q + i / 8, logical 16-byte chunk (i % 8) ^ swz(row); fragments are plain 16-byte reads.
+//     fetch row 8 q + i / 8, logical 16-byte chunk (i % 8) ^ swz(row); fragments are plain 16-byte reads: 16 rows by 4
+//     chunks, the 16 lanes of a pass on 16 rows of one chunk, which the swizzle spreads over all banks.
 //  TN (operands contiguous along their output index): a stage holds the tile as it lies in memory,
 //     [64 k][256 columns]; one load fills k-rows 2 b, 2 b + 1, lane i fetching k-row 2 b + i / 32, logical chunk
-//     (i % 32) ^ ((k & 3) << 2).  Fragments come from the transposing read ds_read_b64_tr_b16: in every 16-lane
-//     group lane 4 e + r reads 8 bytes of k-row e, columns 4 r .. 4 r + 3, and the instruction hands lane i the
-//     4 k values of column i; two of them make the 8 k of an MFMA operand.  The chunk XOR spreads the 4 k-rows
-//     of such a read over the four 64-byte bank groups.
+//     (i % 32) ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1).  Fragments come from the transposing read ds_read_b64_tr_b16: in
+//     every 16-lane group lane 4 e + r reads 8 bytes of k-row e, columns 4 r .. 4 r + 3, and the instruction hands lane i
+//     the 4 k values of column i; two of them make the 8 k of an MFMA operand.  The first XOR spreads the 4 k-rows of
+//     such a read over the four 64-byte bank groups, the second puts the two 16-lane groups of a pass, which read
+//     k-rows 8 apart, in the two halves of a group.
 //
 // With a single wave per SIMD nothing hides an instruction that waits, so the main loop is laid out by hand
 // (the scheduling barriers pin the order):
 //  * LDS is a ring of five 32 KB slots that the operand tiles take in the order A0 B0 A1 B1 A2 ...; a tile's
 //    operands may lie in any two of them, so the per-lane fragment addresses are rebuilt (one add each) for
-//    the next tile under MFMAs that have nothing else to issue; for TN the k-step is an immediate offset.
-//  * Fragment reads are issued ahead of every pair of MFMAs (k-step s + 1 is fetched under the MFMAs of
-//    k-step s); the fragments of the last k-step of a tile are requested early in the k-step before, so they
-//    have landed when the tile barrier is reached.
+//    the next tile under MFMAs that have nothing else to issue.
+//  * The fragments of k-step s + 1 are read under the MFMAs of k-step s; those of the last k-step of a tile are
+//    requested early in the k-step before, so they have landed when the tile barrier is reached.
 //  * The loop is rotated so that the one barrier per tile (next tile landed, two slots free to refill) sits at
 //    the top of the trip; it waits for all of this wave's loads but the newest eight, which belong to the tile
 //    after the next one.
-//  * One tile load goes out ahead of every fourth MFMA.  Issued back to back (16 loads by each of four waves at
+//  * One tile load goes out ahead of every eighth MFMA.  Issued back to back (16 loads by each of four waves at
 //    the same point of the loop) they fill the address queue of the texture unit, which blocks the waves that
 //    issue them and the MFMAs behind; the uneven request stream also cost a third more L2 misses.
 //  * A tile index past the end is fetched through a zero-length descriptor, which zero-fills its slot, so the
@@ -388,47 +396,44 @@ typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 
+// Accumulators of a wave of the direct kernels: 128 x 128 of the output as 8 x 8 MFMA tiles of 16 x 16.  Of tile (i, j)
+// this lane holds row 16 i + (lane & 15), columns 16 j + 4 (lane >> 4) .. + 3.
+typedef f32x4_t acc_tile_t[8][8];
+
 // Epilogue of the direct kernels for bf16 outputs: the wave converts its 128 x 128 accumulator tile to bf16
 // (after adding the residual, read in accumulator layout, when there is one), transposes it through its own
-// 32 KB of LDS ([128 rows][256 B], 16-byte chunks XOR-swizzled by the row) and writes whole 256-byte row
-// segments, 16 bytes per lane.  Rows 16..31 of every 32 keep the two 8-byte halves of a chunk swapped so that
-// a 32-lane 8-byte write touches all 64 banks once.
+// 32 KB of LDS ([128 rows][256 B], 16-byte chunks XOR-swizzled by the row: a 32-lane 8-byte write, 16 rows by the two
+// halves of a chunk, touches all 64 banks once) and writes whole 256-byte row segments, 16 bytes per lane.
 template <int EPI>
-__device__ __forceinline__ void epilogue_bf16_rows(f32x16_t (&acc)[4][4], char* smem, int wave, int lane, bf16_t* C,
+__device__ __forceinline__ void epilogue_bf16_rows(acc_tile_t& acc, char* smem, int wave, int lane, bf16_t* C,
                                                    const bf16_t* R, int M, int N, int ldc, int mw, int nw) {
   char* const wl = smem + wave * 32768;
-  const int khalf = lane >> 5;
+  const int g = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = i * 32 + (lane & 31);
-    const int hoff = ((khalf ^ ((row >> 4) & 1)) << 3);
-    bf16x4_t res[16];
+  for (int i = 0; i < 8; ++i) {
+    const int row = i * 16 + (lane & 15);
+    bf16x4_t res[8];
     if (EPI == EPI_RESID) {
       const int m = mw + row;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nw + j * 32 + g * 8 + khalf * 4;
-          bf16x4_t r = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
-          if (m < M && n < N) r = *reinterpret_cast<const bf16x4_t*>(R + (size_t)m * ldc + n);
-          res[j * 4 + g] = r;
-        }
+      for (int j = 0; j < 8; ++j) {
+        const int n = nw + j * 16 + g * 4;
+        bf16x4_t r = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+        if (m < M && n < N) r = *reinterpret_cast<const bf16x4_t*>(R + (size_t)m * ldc + n);
+        res[j] = r;
+      }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float v0 = acc[i][j][g * 4 + 0], v1 = acc[i][j][g * 4 + 1], v2 = acc[i][j][g * 4 + 2], v3 = acc[i][j][g * 4 + 3];
-        if (EPI == EPI_RESID) {
-          const bf16x4_t r = res[j * 4 + g];
-          v0 += (float)r[0]; v1 += (float)r[1]; v2 += (float)r[2]; v3 += (float)r[3];
-        }
-        bf16x4_t o;
-        o[0] = (bf16_t)v0; o[1] = (bf16_t)v1; o[2] = (bf16_t)v2; o[3] = (bf16_t)v3;
-        const int chunk = j * 4 + g;
-        *reinterpret_cast<bf16x4_t*>(wl + row * 256 + ((chunk ^ (row & 15)) << 4) + hoff) = o;
+    for (int j = 0; j < 8; ++j) {
+      f32x4_t v = acc[i][j];
+      if (EPI == EPI_RESID) {
+        v[0] += (float)res[j][0]; v[1] += (float)res[j][1]; v[2] += (float)res[j][2]; v[3] += (float)res[j][3];
       }
+      bf16x4_t o;
+      o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
+      const int chunk = j * 2 + (g >> 1);
+      *reinterpret_cast<bf16x4_t*>(wl + row * 256 + ((chunk ^ (row & 15)) << 4) + (g & 1) * 8) = o;
+    }
   }
   // every wave reads back only what it wrote itself: no workgroup barrier
   const int c = lane & 15, rsub = lane >> 4;
@@ -436,9 +441,7 @@ __device__ __forceinline__ void epilogue_bf16_rows(f32x16_t (&acc)[4][4], char* 
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
   auto fetch = [&](int row) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(wl + row * 256 + ((c ^ (row & 15)) << 4));
-    if (row & 16) { unsigned t0 = v[0], t1 = v[1]; v[0] = v[2]; v[1] = v[3]; v[2] = t0; v[3] = t1; }
-    return v;
+    return *reinterpret_cast<const u32x4*>(wl + row * 256 + ((c ^ (row & 15)) << 4));
   };
   if (mw + 128 <= M && nw + 128 <= N && (ldc & 7) == 0) {        // interior wave tile: 16-byte stores, no checks
     bf16_t* dst = C + (size_t)(mw + rsub) * ldc + n;
@@ -462,33 +465,69 @@ __device__ __forceinline__ void epilogue_bf16_rows(f32x16_t (&acc)[4][4], char* 
   }
 }
 
+// Epilogue of the direct kernels for fp32 outputs (C = product or C += product): 64 rows at a time go through the wave's
+// 32 KB of LDS ([64 rows][512 B], 16-byte chunks XOR-swizzled by the row) so that global memory sees whole 512-byte row
+// segments; the old values of a pass are requested before its transposition.  Rows are touched once: non-temporal.
+template <int EPI>
+__device__ __forceinline__ void epilogue_f32_rows(acc_tile_t& acc, char* smem, int wave, int lane, float* C, int M, int N, int ldc,
+                                                  int mw, int nw) {
+  char* const wl = smem + wave * 32768;
+  const int khalf = lane >> 5, c = lane & 31, n = nw + c * 4;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    f32x4_t old[EPI == EPI_ACCUM ? 32 : 1];
+    if (EPI == EPI_ACCUM) {
+#pragma unroll
+      for (int p2 = 0; p2 < 32; ++p2) {
+        const int m = mw + pass * 64 + 2 * p2 + khalf;
+        const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+        old[p2] = m < M && n < N ? __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(C + (size_t)m * ldc + n)) : z;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = i * 16 + (lane & 15);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        *reinterpret_cast<f32x4_t*>(wl + row * 512 + (((j * 4 + (lane >> 4)) ^ (row & 31)) << 4)) = acc[pass * 4 + i][j];
+    }
+#pragma unroll
+    for (int p2 = 0; p2 < 32; ++p2) {
+      const int row = 2 * p2 + khalf, m = mw + pass * 64 + row;
+      f32x4_t v = *reinterpret_cast<const f32x4_t*>(wl + row * 512 + ((c ^ (row & 31)) << 4));
+      if (m < M && n < N) {
+        if (EPI == EPI_ACCUM) { v[0] += old[p2][0]; v[1] += old[p2][1]; v[2] += old[p2][2]; v[3] += old[p2][3]; }
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(C + (size_t)m * ldc + n));
+      }
+    }
+  }
+}
+
 // Rotary embedding on the accumulators of a wave tile that is one attention head (128 columns starting at a multiple
-// of 128): column c < 64 pairs with column c + 64, which the same lane holds in the same register of acc[i][j + 2]
-// (j = 0, 1), so the rotation by position * theta_c happens in registers, in fp32, before the one conversion to bf16.
+// of 128): column c < 64 pairs with column c + 64, which the same lane holds in the same register of acc[i][j + 4]
+// (j = 0..3), so the rotation by position * theta_c happens in registers, in fp32, before the one conversion to bf16.
 // table[pos * 64 + c] = (cos, sin); pos = row % seq.  Every lane reads the 32-byte pieces of its own row's table row
 // straight from memory (the table stays in L2); staging the rows through LDS with coalesced loads measured slower.
-__device__ __forceinline__ void rope_rotate_acc(f32x16_t (&acc)[4][4], const float2* __restrict__ table, int seq, int M,
+__device__ __forceinline__ void rope_rotate_acc(acc_tile_t& acc, const float2* __restrict__ table, int seq, int M,
                                                 int mw, int lane) {
-  const int khalf = lane >> 5;
+  const int g = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int m = mw + i * 32 + (lane & 31);
+  for (int i = 0; i < 8; ++i) {
+    int m = mw + i * 16 + (lane & 15);
     m = m < M ? m : M - 1;                                 // rows past the end are never stored; keep the table read in bounds
     const float4* row = reinterpret_cast<const float4*>(table + (size_t)(m % seq) * 64);
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 4; ++j) {
+      const int c = j * 16 + g * 4;                        // this lane's 4 consecutive frequencies
+      const float4 t0 = row[c / 2], t1 = row[c / 2 + 1];   // (cos, sin) of c, c + 1 and of c + 2, c + 3
+      const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int c = j * 32 + g * 8 + khalf * 4;          // this lane's 4 consecutive frequencies
-        const float4 t0 = row[c / 2], t1 = row[c / 2 + 1]; // (cos, sin) of c, c + 1 and of c + 2, c + 3
-        const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = acc[i][j][g * 4 + e], hi = acc[i][j + 2][g * 4 + e];
-          acc[i][j][g * 4 + e] = lo * cs[e] - hi * sn[e];
-          acc[i][j + 2][g * 4 + e] = hi * cs[e] + lo * sn[e];
-        }
+      for (int e = 0; e < 4; ++e) {
+        const float lo = acc[i][j][e], hi = acc[i][j + 4][e];
+        acc[i][j][e] = lo * cs[e] - hi * sn[e];
+        acc[i][j + 4][e] = hi * cs[e] + lo * sn[e];
       }
+    }
   }
 }
 
@@ -497,27 +536,27 @@ __device__ __forceinline__ void rope_rotate_acc(f32x16_t (&acc)[4][4], const flo
 // the same indices: a = silu(gate) * up is formed from the fp32 accumulators.  Stored: gate and up (bf16) where the
 // plain [gate | up] layout has them (GU[m][base + c], GU[m][f + base + c]) and a (bf16) at A[m][base + c]; each of
 // the three is a 128-byte row segment.  32 rows at a time go through the wave's own LDS ([32][400 B]).
-__device__ __forceinline__ void epilogue_swiglu_rows(f32x16_t (&acc)[4][4], char* smem, int wave, int lane, bf16_t* GU,
+__device__ __forceinline__ void epilogue_swiglu_rows(acc_tile_t& acc, char* smem, int wave, int lane, bf16_t* GU,
                                                      bf16_t* Aout, int M, int f, int ldgu, int mw, int base) {
   char* const wl = smem + wave * 32768;
-  constexpr int RS = 400;                                  // row stride: 3 x 128 B + 16 (keeps 16-byte alignment)
-  const int khalf = lane >> 5, r = lane & 31;
+  constexpr int RS = 400;                                  // row stride: 3 x 128 B + 16 (16 rows start at 16 different chunks)
+  const int g = lane >> 4;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int j = 0; j < 4; ++j) {
         bf16x4_t og, ou, oa;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float gv = acc[i][j][g * 4 + e], uv = acc[i][j + 2][g * 4 + e];
+          const float gv = acc[2 * i + h][j][e], uv = acc[2 * i + h][j + 4][e];
           og[e] = (bf16_t)gv;
           ou[e] = (bf16_t)uv;
           // silu(g) u = g u / (1 + 2^(-g log2 e)): hardware exp2 and reciprocal (1 ulp each), far below bf16's 2^-9
           oa[e] = (bf16_t)(gv * uv * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896f * gv)));
         }
-        const int cb = (j * 32 + g * 8 + khalf * 4) * 2;   // byte offset of the 4 columns within a 128-byte segment
+        const int r = h * 16 + (lane & 15), cb = (j * 16 + g * 4) * 2;   // byte offset of the 4 columns within a 128-byte segment
         *reinterpret_cast<bf16x4_t*>(wl + r * RS + cb) = og;
         *reinterpret_cast<bf16x4_t*>(wl + r * RS + 128 + cb) = ou;
         *reinterpret_cast<bf16x4_t*>(wl + r * RS + 256 + cb) = oa;
@@ -548,19 +587,23 @@ __device__ __forceinline__ void for_range(F&& f) {
   for_range_impl<P0>(f, std::make_integer_sequence<int, P1 - P0>{});
 }
 
-// Issue position (0..63 within a trip of the main loop) of the trip's n-th tile load: one ahead of every fourth
-// MFMA; -1 = none at p
-__device__ constexpr int load_at(int p) { return (p & 3) == 1 ? p >> 2 : -1; }
+// Main loop of the direct kernels: position t (0..63) within a phase of 64 MFMAs.  Tile load n (0..7) of the phase goes
+// out ahead of position LOAD_POS[n]: every eighth, moved to t % 3 == 2, the positions that carry no fragment read
+__device__ constexpr int load_at(int t) {
+  constexpr int LOAD_POS[8] = {5, 14, 20, 29, 38, 44, 53, 62};
+  for (int n = 0; n < 8; ++n)
+    if (LOAD_POS[n] == t) return n;
+  return -1;
+}
 
 // One output tile.  TNL = false: A(m, k) at A[m * lda + k], B(n, k) at B[n * ldb + k].  TNL = true: A[k * lda + m],
-// B[k * ldb + n].  pid = position of the tile in the problem's tile sequence (groups of 8 tile rows, walked
-// column by column).
+// B[k * ldb + n]; there K may be anything (k-rows past it lie past the operand and read as zero), otherwise K % 64 == 0.
 template <bool TNL, int EPI>
 __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                             void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N, int K, int lda,
-                                            int ldb, int ldc, int tiles_m, int tiles_n, unsigned a_bytes, unsigned b_bytes,
-                                            int tile_m, int tile_n, bool b_slab = false, const GemmExtra& ex = GemmExtra()) {
-  constexpr int BM = 256, BN = 256, WM = 2, WN = 2, TM = 4, TN = 4;
+                                            int ldb, int ldc, unsigned a_bytes, unsigned b_bytes, int tile_m, int tile_n,
+                                            bool b_slab = false, const GemmExtra& ex = GemmExtra()) {
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 2;
   constexpr int OPB = 32768;                    // one operand of one stage
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -568,40 +611,39 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
 
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
-  f32x16_t acc[TM][TN];
+  acc_tile_t acc;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
-  // fragment q: 0..3 = A rows (i = q), 4..7 = B rows (j = q - 4).  Byte address of this lane's read within
-  // a slot: NT one per k-step, TN one (k-step and k-quad are immediates: 8192 and 2048 bytes)
-  constexpr int KS = TNL ? 1 : 4;
-  int faddr[8][KS];
+  // Fragment i (0..7) of an operand = its 16 rows 16 i .. (wave part of 128 rows); lane = row (lane & 15), k-group
+  // lane >> 4 of 8 k.  Byte address of this lane's read within a slot, without the wave part:
+  //  NT: faddr[(i & 3) * 2 + ks]; the swizzle repeats every 64 rows, so i + 4 is an immediate offset of 8192
+  //  TN: faddr[i]; k-step and k-quad are immediates (16384 and 2048 bytes)
+  int faddr[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const int first = q < 4 ? wm * (BM / WM) + q * 32 : wn * (BN / WN) + (q - 4) * 32;
+    const int g = lane >> 4;
     if (TNL) {
-      const int khalf = lane >> 5, cgrp = (lane >> 4) & 1, e = (lane >> 2) & 3, r = lane & 3;
-      const int c16 = (first + cgrp * 16 + r * 4) >> 3;
-      faddr[q][0] = (khalf * 8 + e) * 512 + ((c16 ^ (e << 2)) << 4) + (r & 1) * 8;
+      const int e = (lane >> 2) & 3, r = lane & 3;
+      faddr[q] = (g * 8 + e) * 512 + (((2 * q + (r >> 1)) ^ (e << 2) ^ ((g & 1) << 1)) << 4) + (r & 1) * 8;
     } else {
-      const int row = first + (lane & 31), khalf = lane >> 5;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) faddr[q][ks] = row * ROW_BYTES + (((ks * 2 + khalf) ^ swz(row)) << 4);
+      const int row = (q >> 1) * 16 + (lane & 15), ks = q & 1;
+      faddr[q] = row * ROW_BYTES + (((ks * 4 + g) ^ swz(row)) << 4);
     }
   }
   // tile loads: 16 per wave and tile, t even -> A, t odd -> B, each 1 KB of LDS; voff = this lane's byte offset
-  // within the k-tile (out of range for rows or columns past the operand), the k-tile offset is scalar
+  // within the k-tile (out of range for rows or columns past the operand); the k-tile moves the descriptor's base
   unsigned voff[16];
   unsigned a_tile, b_tile;
   if (TNL) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int k = 2 * (wave * 8 + j) + (lane >> 5);
-      const int c16 = (lane & 31) ^ ((k & 3) << 2);
+      const int c16 = (lane & 31) ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1);
       const int ca = m0 + c16 * 8, cb = n0 + c16 * 8;
       voff[2 * j] = ca < M ? (unsigned)k * (unsigned)lda * 2u + (unsigned)ca * 2u : 0xFFFFFF00u;
       voff[2 * j + 1] = cb < N ? (unsigned)k * (unsigned)ldb * 2u + (unsigned)cb * 2u : 0xFFFFFF00u;
@@ -622,168 +664,151 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     a_tile = BK * 2;
     b_tile = b_slab ? 32768u : BK * 2;
   }
-  auto make_desc = [](const void* p, unsigned bytes) {
-    const unsigned long long a = (unsigned long long)p;
+  const int nk = (K + BK - 1) / BK;
+  // Descriptor of an operand for k-tile `tile`: base and length both moved by the tile, so that what lies past the
+  // operand's end reads as zero whatever the range check makes of a scalar offset.  Past the last tile the length is
+  // zero (the load then moves nothing from memory and zero-fills its slot, so the count of loads in flight is the same
+  // on every trip).
+  auto desc_for = [&](const void* p, unsigned bytes, unsigned step, int tile) __attribute__((always_inline)) {
+    const unsigned off = (unsigned)tile * step;                        // below 4 GiB for every tile of the operand
+    const unsigned long long a = (unsigned long long)p + off;
     i32x4_t d;
     d[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)a);
     d[1] = __builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32) & 0xffff);
-    d[2] = (int)bytes;
+    d[2] = __builtin_amdgcn_readfirstlane(tile < nk ? (int)(bytes - off) : 0);
     d[3] = 0x00020000;
     return d;
   };
-  const i32x4_t ra = make_desc(A, a_bytes), rb = make_desc(B, b_bytes);
   const unsigned lds0 = (unsigned)(size_t)(lds_void_t*)smem;
-  // load idx (0..7) of this wave for one operand of k-tile `tile` into the ring slot whose address, plus this
-  // wave's 8 KB share, is `base`
-  auto issue_one = [&](i32x4_t desc, unsigned base, int tile, bool is_b, auto idx_c) __attribute__((always_inline)) {
+  // load idx (0..7) of this wave for one operand: set_m0 gives the ring slot's address plus this wave's 8 KB share as
+  // `base`; m0 = LDS address of the load, written one position ahead of the load (the hardware wants an instruction in between)
+  unsigned m0v;
+  auto set_m0 = [](unsigned base, auto idx_c) __attribute__((always_inline)) {
     constexpr int idx = decltype(idx_c)::value;
-    const unsigned soff = tile * (is_b ? b_tile : a_tile);
+    unsigned r;
+    asm volatile("s_add_u32 %0, %1, %2" : "={m0}"(r) : "s"(base), "n"(idx * 1024) : "scc");
+    return r;
+  };
+  auto issue_one = [&](i32x4_t desc, bool is_b, auto idx_c) __attribute__((always_inline)) {
+    constexpr int idx = decltype(idx_c)::value;
     const unsigned vo = voff[2 * idx + (is_b ? 1 : 0)];
-    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(base), "v"(vo), "s"(desc), "s"(soff), "n"(idx * 1024) : "memory", "m0", "scc");
+    const unsigned mm = m0v;
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" :: "v"(vo), "s"(desc), "{m0}"(mm) : "memory");
   };
   const unsigned lds_wave = lds0 + wave * 8192;
-  // descriptor of an operand for k-tile `tile`: past the last tile it has length zero (the load then moves nothing
-  // from memory and zero-fills its slot, so the count of loads in flight is the same on every trip)
-  auto desc_for = [&](i32x4_t d, int tile) __attribute__((always_inline)) {
-    d[2] = tile < K / BK ? d[2] : 0;
-    return d;
-  };
   // LDS is a ring of five 32 KB slots which the operands take in the order A0 B0 A1 B1 A2 ... (operand u in slot
   // u % 5).  While tile kt is computed its two slots are read, the two that tile kt - 1 has left are refilled with
   // B of tile kt + 1 and A of tile kt + 2, and A of tile kt + 1 sits in the fifth.  The sync at the top of tile kt
   // wants both operands of tile kt landed: every load but this wave's last 8 (A of tile kt + 1), which stay in
   // flight across the barrier, so the memory pipe never runs empty.  The slots of a tile change from trip to
-  // trip: cur[][] = LDS addresses of the fragments of the tile being read, rebuilt for the next tile
-  // under the MFMAs of the last k-step that reads nothing any more.
+  // trip: cur[] = LDS addresses of the fragments of the tile being read (0..7 A, 8..15 B), rebuilt for the next tile
+  // under the MFMAs that end the trip, when nothing reads the old ones any more.
   constexpr unsigned RING = 5 * OPB;
   auto two_on = [](unsigned off) __attribute__((always_inline)) { off += 2 * OPB; return off >= RING ? off - RING : off; };
-  int cur[8][KS];
-  i16x4_t fr[2][8][2];
-  // half 0 / 1: the two 8-byte halves of fragment q (TN: one transposing read each; NT: one 16-byte read at half 0)
-  auto load_half = [&](int set, int ks, int q, int half) __attribute__((always_inline)) {
-    if (TNL) {
-      fr[set][q][half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(unsigned)(cur[q][0] + ks * 8192 + half * 2048));
-    } else if (half == 0) {
-      typedef short i16x8_t __attribute__((ext_vector_type(8)));
-      typedef __attribute__((address_space(3))) i16x8_t lds_i16x8_t;
-      const i16x8_t v = *(const lds_i16x8_t*)(unsigned)cur[q][TNL ? 0 : ks];
-      fr[set][q][0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
-      fr[set][q][1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
-    }
+  constexpr int WPART = TNL ? 256 : 16384;           // the 128 rows (NT) or columns (TN) of a wave within a slot
+  const unsigned base_fa = lds0 + wm * WPART, base_fb = lds0 + wn * WPART;
+  int cur[16];
+  bf16x8_t fr[2][16];                                // [k-step parity][0..7 A, 8..15 B]
+  i16x4_t half0;                                     // TN: first half of the fragment being read
+  // TN: the two 8-byte halves of fragment q are one transposing read each; NT: one 16-byte read
+  auto read_nt = [&](int ks, int q) __attribute__((always_inline)) {
+    typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
+    const int i = q & 7;
+    fr[ks][q] = *(const lds_bf16x8_t*)(unsigned)(cur[(q & 8) + (i & 3) * 2 + ks] + (i >> 2) * 8192);
   };
-  auto frag = [&](int set, int q) __attribute__((always_inline)) {
-    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(fr[set][q][0], fr[set][q][1], 0, 1, 2, 3, 4, 5, 6, 7));
+  auto read_tn = [&](int ks, int q, int half) __attribute__((always_inline)) {
+    const i16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(unsigned)(cur[q] + ks * 16384 + half * 2048));
+    if (half == 0) half0 = v;
+    else fr[ks][q] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(half0, v, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  // fragments are read in the order a0 b0 a1 b1 ...; the MFMA order uses the ones read first first
-  constexpr int MI[16] = {0, 1, 0, 1, 2, 2, 0, 1, 2, 3, 3, 3, 0, 1, 2, 3};
-  constexpr int MJ[16] = {0, 0, 1, 1, 0, 1, 2, 2, 2, 0, 1, 2, 3, 3, 3, 3};
-  constexpr int LQ[8] = {0, 4, 1, 5, 2, 6, 3, 7};
+  // order in which a phase needs its fragments (MFMA t of a phase: i = t / 8, j walks to and fro, so that consecutive
+  // MFMAs share an operand): A0, B0 .. B7, A1 .. A7
+  constexpr int RQ[16] = {0, 8, 9, 10, 11, 12, 13, 14, 15, 1, 2, 3, 4, 5, 6, 7};
   auto mma_one = [&](int set, int t) __attribute__((always_inline)) {
-    acc[MI[t]][MJ[t]] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(set, 4 + MJ[t]), frag(set, MI[t]), acc[MI[t]][MJ[t]], 0, 0, 0);
+    const int i = t >> 3, j = (i & 1) ? 7 - (t & 7) : (t & 7);
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[set][8 + j], fr[set][i], acc[i][j], 0, 0, 0);
   };
-  // One trip of the loop = 64 MFMAs = 64 issue positions p: 0..15 are k-step 3 of the previous tile (fragment set
-  // 1, in registers), 16..63 k-steps 0..2 of tile kt.  An MFMA occupies the matrix pipe for 32 cycles, which is
-  // all the room there is for whatever the wave issues ahead of the next one; a tile load takes most of that by
-  // itself (three scalar instructions and a 64-lane address), so no position carries more than one expensive
-  // thing:
-  //  * fragment reads (k-step 0 of tile kt during positions 0..15, then step s + 1 during step s; the reads of
-  //    step 3 are all out by position 55), NT at even positions, TN one at every position;
-  //  * the 16 tile loads of the trip, n = 0..7 = B of tile kt + 1 into the slot at pa, 8..15 = A of tile kt + 2
-  //    into the slot at pb, at positions 1, 5, ..., 61 (for TN the read of such a position moves to the one before);
-  //  * the fragment addresses of the next tile, rebuilt at positions 56..63 when nothing reads the old ones.
-  // Loads issued back to back (16 by each of four waves at the same point) fill the address queue of the texture
-  // unit, which blocks the waves that issue them and the MFMAs behind, and cost a third more L2 misses.
-  auto reads_at = [&](int p, bool next) __attribute__((always_inline)) {
-    if (p < 16) {
-      if (!next) return;
-      if (TNL) load_half(0, 0, LQ[p >> 1], p & 1);
-      else if ((p & 1) == 0) load_half(0, 0, LQ[p >> 1], 0);
-      return;
-    }
-    const int ks = (p - 16) >> 4, t = (p - 16) & 15, q = t >> 1, set = ks & 1;
-    if (ks < 2) {
-      if (TNL) load_half(set ^ 1, ks + 1, LQ[q], t & 1);
-      else if ((t & 1) == 0) load_half(set ^ 1, ks + 1, LQ[q], 0);
-    } else if (q < 4) {                            // last reads of these slots: all requested in the first half
-      if (TNL) {
-        load_half(set ^ 1, ks + 1, LQ[t], 0);
-        load_half(set ^ 1, ks + 1, LQ[t], 1);
-      } else if ((t & 1) == 0) {
-        load_half(set ^ 1, ks + 1, LQ[t], 0);
-        load_half(set ^ 1, ks + 1, LQ[t + 1], 0);
-      }
-    }
-  };
-  auto position = [&](auto p_c, unsigned na, unsigned nb, i32x4_t db, i32x4_t da, unsigned base_b, unsigned base_a, int kt,
-                      bool refill, bool next) __attribute__((always_inline)) {
-    constexpr int p = decltype(p_c)::value;
-    constexpr int n = load_at(p), n1 = p < 63 ? load_at(p + 1) : -1;
+  // One trip of the loop = two phases of 64 MFMAs: phase 0 multiplies k-step 1 of the previous tile (fragment set 1, in
+  // registers) while the fragments of k-step 0 of tile kt are read, phase 1 multiplies k-step 0 of tile kt while those of
+  // k-step 1 are read.  An MFMA occupies the matrix pipe for 16 cycles, which is room for the issue of two or three other
+  // instructions, so no position carries more than one of:
+  //  * fragment reads, out by position 47 of the phase (t % 3 == 0, for TN, which has two per fragment, also 1), so that
+  //    they have landed when the tile barrier is reached;
+  //  * the 16 tile loads of the trip (t % 3 == 2): in phase 0 the 8 of B of tile kt + 1 into the slot at pa, in phase 1
+  //    those of A of tile kt + 2 into the slot at pb;
+  //  * the fragment addresses of the next tile, one each at positions 48..63 of phase 1.
+  auto position = [&](auto p_c, unsigned na, unsigned nb, const i32x4_t& desc, unsigned base_ld, bool refill, bool next)
+      __attribute__((always_inline)) {
+    constexpr int p = decltype(p_c)::value, ph = p >> 6, t = p & 63;
+    constexpr int n = load_at(t);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (n >= 0) {
-      if (refill) {
-        if constexpr (n < 8) issue_one(db, base_b, kt + 1, true, std::integral_constant<int, n>{});
-        else issue_one(da, base_a, kt + 2, false, std::integral_constant<int, n - 8>{});
-      }
+      if (refill) issue_one(desc, ph == 0, std::integral_constant<int, n>{});
     }
-    if (!(TNL && n >= 0)) reads_at(p, next);
-    if (TNL && n1 >= 0) reads_at(p + 1, next);
-    if (p >= 56) {
-      constexpr int PER = 8 * KS / 8;              // addresses per position
-#pragma unroll
-      for (int e = (p - 56) * PER; e < (p - 55) * PER; ++e) cur[e / KS][e % KS] = faddr[e / KS][e % KS] + (int)(lds0 + (e / KS < 4 ? na : nb));
+    if (next && t < 48) {
+      if (TNL) { if (t % 3 < 2) read_tn(ph, RQ[t / 3], t % 3); }
+      else if (t % 3 == 0) read_nt(ph, RQ[t / 3]);
+    }
+    if (ph == 1 && t >= 48) {
+      constexpr int q = t >= 48 ? t - 48 : 0;
+      cur[q] = faddr[q & 7] + (int)(q < 8 ? na : nb);
+    }
+    if constexpr (t < 63 && load_at(t + 1) >= 0) {
+      if (refill) m0v = set_m0(base_ld, std::integral_constant<int, load_at(t + 1)>{});
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (p < 16) mma_one(1, p); else mma_one(((p - 16) >> 4) & 1, (p - 16) & 15);
+    mma_one(ph ^ 1, t);
   };
-  // positions [p0, p1) of the trip of tile kt; pa, pb = byte offsets of the slots the previous tile has left
+  // phases [p0, p1) / 64 of the trip of tile kt; pa, pb = byte offsets of the slots the previous tile has left, na, nb =
+  // those of the next tile's operands
   auto trip = [&](auto p0, auto p1, unsigned pa, unsigned pb, unsigned na, unsigned nb, int kt, bool refill, bool next)
       __attribute__((always_inline)) {
-    const i32x4_t db = desc_for(rb, kt + 1), da = desc_for(ra, kt + 2);
-    const unsigned base_b = lds_wave + pa, base_a = lds_wave + pb;
-    for_range<decltype(p0)::value, decltype(p1)::value>(
-        [&](auto p) __attribute__((always_inline)) { position(p, na, nb, db, da, base_b, base_a, kt, refill, next); });
+    const i32x4_t db = desc_for(B, b_bytes, b_tile, kt + 1), da = desc_for(A, a_bytes, a_tile, kt + 2);
+    for_range<decltype(p0)::value, decltype(p1)::value>([&](auto p) __attribute__((always_inline)) {
+      constexpr bool first = decltype(p)::value < 64;
+      position(p, base_fa + na, base_fb + nb, first ? db : da, lds_wave + (first ? pa : pb), refill, next);
+    });
     __builtin_amdgcn_sched_barrier(0);
   };
   constexpr std::integral_constant<int, 0> P0{};
-  constexpr std::integral_constant<int, 16> P16{};
   constexpr std::integral_constant<int, 64> P64{};
+  constexpr std::integral_constant<int, 128> P128{};
 #define OPTSTAGE_TILE_SYNC(n) asm volatile("s_waitcnt vmcnt(" #n ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
-  const int nk = K / BK;
 #pragma unroll
   for (int u = 0; u < 5; ++u) {
-    const i32x4_t d = desc_for((u & 1) ? rb : ra, u >> 1);
-    for_range<0, 8>([&](auto idx) __attribute__((always_inline)) { issue_one(d, lds_wave + u * OPB, u >> 1, (u & 1) != 0, idx); });
+    const i32x4_t d = (u & 1) ? desc_for(B, b_bytes, b_tile, u >> 1) : desc_for(A, a_bytes, a_tile, u >> 1);
+    for_range<0, 8>([&](auto idx) __attribute__((always_inline)) { m0v = set_m0(lds_wave + u * OPB, idx); asm volatile("s_nop 0"); issue_one(d, (u & 1) != 0, idx); });
   }
 #pragma unroll
-  for (int q = 0; q < 8; ++q)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) cur[q][ks] = faddr[q][ks] + (int)(lds0 + (q < 4 ? 0 : OPB));
+  for (int q = 0; q < 16; ++q) cur[q] = faddr[q & 7] + (int)(q < 8 ? base_fa : base_fb + OPB);
   OPTSTAGE_TILE_SYNC(24);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) { load_half(0, 0, LQ[q], 0); load_half(0, 0, LQ[q], 1); }
+  for (int q = 0; q < 16; ++q) {
+    if (TNL) { read_tn(0, RQ[q], 0); read_tn(0, RQ[q], 1); }
+    else read_nt(0, RQ[q]);
+  }
   unsigned pa = 0, pb = OPB;                         // slots of the tile before tile kt
-  trip(P16, P64, 0, 0, two_on(pa), two_on(pb), 0, false, true);
+  trip(P64, P128, 0, 0, two_on(pa), two_on(pb), 0, false, true);
   for (int kt = 1; kt < nk; ++kt) {
     const unsigned oa = two_on(pa), ob = two_on(pb);
     OPTSTAGE_TILE_SYNC(8);
-    trip(P0, P64, pa, pb, two_on(oa), two_on(ob), kt, true, true);
+    trip(P0, P128, pa, pb, two_on(oa), two_on(ob), kt, true, true);
     pa = oa;
     pb = ob;
   }
-  trip(P0, P16, 0, 0, 0, 0, 0, false, false);
+  trip(P0, P64, 0, 0, 0, 0, 0, false, false);
   OPTSTAGE_TILE_SYNC(0);                             // every wave is done with the operand tiles, nothing in flight
 #undef OPTSTAGE_TILE_SYNC
-  if (EPI == EPI_ACCUM || EPI == EPI_STOREF) {
-    epilogue_via_lds<EPI, TM, TN, 4>(acc, smem, wave, lane, Cv, R, M, N, ldc, m0 + wm * (BM / WM), n0 + wn * (BN / WN));
-  } else if (EPI == EPI_SWIGLU) {
+  const int mw = m0 + wm * (BM / WM), nw = n0 + wn * (BN / WN);
+  if constexpr (EPI == EPI_ACCUM || EPI == EPI_STOREF) {
+    epilogue_f32_rows<EPI>(acc, smem, wave, lane, reinterpret_cast<float*>(Cv), M, N, ldc, mw, nw);
+  } else if constexpr (EPI == EPI_SWIGLU) {
     epilogue_swiglu_rows(acc, smem, wave, lane, reinterpret_cast<bf16_t*>(Cv), reinterpret_cast<bf16_t*>(ex.a_out), M, ex.f, ldc,
-                         m0 + wm * (BM / WM), tile_n * 128 + wn * 64);
+                         mw, tile_n * 128 + wn * 64);
   } else {
-    if (EPI == EPI_ROPE && n0 + wn * (BN / WN) < ex.rot_cols)      // this wave's 128 columns are a q or k head
-      rope_rotate_acc(acc, ex.table, ex.seq, M, m0 + wm * (BM / WM), lane);
-    epilogue_bf16_rows<(EPI == EPI_ROPE ? EPI_STORE : EPI)>(acc, smem, wave, lane, reinterpret_cast<bf16_t*>(Cv), R, M, N, ldc,
-                                                             m0 + wm * (BM / WM), n0 + wn * (BN / WN));
+    if (EPI == EPI_ROPE && nw < ex.rot_cols)         // this wave's 128 columns are a q or k head
+      rope_rotate_acc(acc, ex.table, ex.seq, M, mw, lane);
+    epilogue_bf16_rows<(EPI == EPI_ROPE ? EPI_STORE : EPI)>(acc, smem, wave, lane, reinterpret_cast<bf16_t*>(Cv), R, M, N, ldc, mw, nw);
   }
 }
 
@@ -835,8 +860,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(const bf16_t* __r
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int tile_m, tile_n;
   tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, order, tile_m, tile_n);
-  direct_tile<TNL, EPI>(smem, A, B, Cv, R, M, N, K, lda, ldb, ldc, tiles_m, tiles_n, a_bytes, b_bytes, tile_m, tile_n,
-                        !TNL && b_slab != 0, ex);
+  direct_tile<TNL, EPI>(smem, A, B, Cv, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, tile_m, tile_n, !TNL && b_slab != 0, ex);
 }
 
 // Several independent products with the same K in one launch (the weight-gradient GEMMs of a W op: four per
@@ -870,8 +894,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_direct_grouped_kernel(const Gro
     tile_m = first_m + in_grp % gsz;
     tile_n = in_grp / gsz;
   }
-  direct_tile<TNL, EPI>(smem, pr.A, pr.B, pr.C, pr.R, pr.M, pr.N, g.K, pr.lda, pr.ldb, pr.ldc, pr.tiles_m, pr.tiles_n,
-                        pr.a_bytes, pr.b_bytes, tile_m, tile_n);
+  direct_tile<TNL, EPI>(smem, pr.A, pr.B, pr.C, pr.R, pr.M, pr.N, g.K, pr.lda, pr.ldb, pr.ldc, pr.a_bytes, pr.b_bytes, tile_m, tile_n);
 }
 
 // Measured on the weight-gradient set of the grouped-query stage (8 products, one launch): order 1 1229 TFLOP/s against
