@@ -360,7 +360,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
 // a loop that does nothing else (2070 against 1806 TFLOP/s, operands drawn at random); in these kernels, 32x32x16 -> 16x16x32:
 // 4096 x 12288 x 4096 1358 -> 1479 TFLOP/s, 4096 x 4096 x 11008 1400 -> 1528, 4096 x 8192 x 28672 1430 -> 1503, the
 // grouped TN set of a hidden-8192 layer 1233 -> 1285 (fp32 store 1316 -> 1370).  The clock rises from 1.59 to 1.81 GHz, the matrix
-// pipe is busy 81 % of the cycles (88 % before).  Walking j to and fro (consecutive MFMAs share an operand) is worth 0.7 %.
+// pipe is busy 81 % of the cycles (88 % before); with the trip's scalar work spread between the MFMAs (below) the four reach
+// 1522, 1563, 1566 and 1331 (1427) on a box where the start gave 1355, 1377, 1413 and 1235 (1305).  Walking j to and fro (consecutive MFMAs share an operand) is worth 0.7 %.
 //
 //  NT (operands contiguous along k): a stage holds [256 rows][64 k]; the load for rows 8 q .. 8 q + 7 has lane i
 //     fetch row 8 q + i / 8, logical 16-byte chunk (i % 8) ^ swz(row); fragments are plain 16-byte reads: 16 rows by 4
@@ -386,6 +387,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
 //  * One tile load goes out ahead of every eighth MFMA.  Issued back to back (16 loads by each of four waves at
 //    the same point of the loop) they fill the address queue of the texture unit, which blocks the waves that
 //    issue them and the MFMAs behind; the uneven request stream also cost a third more L2 misses.
+//  * An MFMA leaves room for the issue of two or three other instructions, so the scalar work of a trip (descriptors, ring
+//    slots) and the address adds are pinned between MFMAs too, at the positions that carry no read: gathered at the top of
+//    the trip, as the compiler leaves them, they cost 4 %.
 //  * A tile index past the end is fetched through a zero-length descriptor, which zero-fills its slot, so the
 //    number of loads in flight is the same on every trip and the waits need no second code path.
 //  * The tile loads are written in assembly: issued through the compiler builtin, every later transposing
@@ -665,20 +669,44 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     b_tile = b_slab ? 32768u : BK * 2;
   }
   const int nk = (K + BK - 1) / BK;
-  // Descriptor of an operand for k-tile `tile`: base and length both moved by the tile, so that what lies past the
-  // operand's end reads as zero whatever the range check makes of a scalar offset.  Past the last tile the length is
-  // zero (the load then moves nothing from memory and zero-fills its slot, so the count of loads in flight is the same
-  // on every trip).
-  auto desc_for = [&](const void* p, unsigned bytes, unsigned step, int tile) __attribute__((always_inline)) {
-    const unsigned off = (unsigned)tile * step;                        // below 4 GiB for every tile of the operand
-    const unsigned long long a = (unsigned long long)p + off;
-    i32x4_t d;
-    d[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)a);
-    d[1] = __builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32) & 0xffff);
-    d[2] = __builtin_amdgcn_readfirstlane(tile < nk ? (int)(bytes - off) : 0);
-    d[3] = 0x00020000;
+  // Descriptor of an operand: base and length both move with the k-tile, so that what lies past the operand's end reads as
+  // zero whatever the range check makes of a scalar offset.  Past the last tile the length is zero (the load then moves
+  // nothing from memory and zero-fills its slot, so the count of loads in flight is the same on every trip).
+  // The scalar steps of the main loop are written in assembly so that they stay at the positions they are written at: left to
+  // the compiler they gather at the top of the trip, 40 instructions during which the matrix unit has nothing to do.
+  struct Desc { unsigned lo, hi, left, len; };          // left = bytes from the tile's base to the operand's end
+  auto start = [&](const void* p, unsigned bytes) __attribute__((always_inline)) {
+    const unsigned long long a = (unsigned long long)p;
+    Desc d;
+    d.lo = __builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    d.hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(a >> 32)) & 0xffff;
+    d.left = d.len = __builtin_amdgcn_readfirstlane((int)bytes);
     return d;
   };
+  auto move_base = [](Desc& d, unsigned step) __attribute__((always_inline)) {
+    asm volatile("s_add_u32 %0, %0, %2\n\ts_addc_u32 %1, %1, 0" : "+s"(d.lo), "+s"(d.hi) : "s"(step) : "scc");
+  };
+  auto move_end = [](Desc& d, unsigned step, int tile, int tiles) __attribute__((always_inline)) {
+    asm volatile("s_sub_u32 %0, %0, %2\n\ts_cmp_lt_i32 %3, %4\n\ts_cselect_b32 %1, %0, 0"
+                 : "+s"(d.left), "=&s"(d.len) : "s"(step), "s"(tile), "s"(tiles) : "scc");
+  };
+  auto add = [](unsigned& r, unsigned x, unsigned y) __attribute__((always_inline)) {
+    asm volatile("s_add_u32 %0, %1, %2" : "=s"(r) : "s"(x), "s"(y) : "scc");
+  };
+  // ring arithmetic on byte offsets of slots
+  auto slot_after = [](unsigned& r, unsigned x) __attribute__((always_inline)) {
+    asm volatile("s_add_u32 %0, %1, %2\n\ts_cmp_eq_u32 %0, %3\n\ts_cselect_b32 %0, 0, %0"
+                 : "=&s"(r) : "s"(x), "n"(32768), "n"(163840) : "scc");
+  };
+  auto slot_before = [](unsigned& r, unsigned x) __attribute__((always_inline)) {
+    asm volatile("s_sub_u32 %0, %1, %2\n\ts_cselect_b32 %0, %3, %0" : "=&s"(r) : "s"(x), "n"(32768), "n"(131072) : "scc");
+  };
+  auto slot_after_next = [](unsigned& x) __attribute__((always_inline)) {
+    unsigned y;
+    asm volatile("s_add_u32 %0, %0, %2\n\ts_sub_u32 %1, %0, %3\n\ts_cselect_b32 %0, %0, %1"
+                 : "+s"(x), "=&s"(y) : "n"(65536), "n"(163840) : "scc");
+  };
+  auto words = [](const Desc& d) __attribute__((always_inline)) { return i32x4_t{(int)d.lo, (int)d.hi, (int)d.len, 0x00020000}; };
   const unsigned lds0 = (unsigned)(size_t)(lds_void_t*)smem;
   // load idx (0..7) of this wave for one operand: set_m0 gives the ring slot's address plus this wave's 8 KB share as
   // `base`; m0 = LDS address of the load, written one position ahead of the load (the hardware wants an instruction in between)
@@ -703,8 +731,6 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
   // flight across the barrier, so the memory pipe never runs empty.  The slots of a tile change from trip to
   // trip: cur[] = LDS addresses of the fragments of the tile being read (0..7 A, 8..15 B), rebuilt for the next tile
   // under the MFMAs that end the trip, when nothing reads the old ones any more.
-  constexpr unsigned RING = 5 * OPB;
-  auto two_on = [](unsigned off) __attribute__((always_inline)) { off += 2 * OPB; return off >= RING ? off - RING : off; };
   constexpr int WPART = TNL ? 256 : 16384;           // the 128 rows (NT) or columns (TN) of a wave within a slot
   const unsigned base_fa = lds0 + wm * WPART, base_fb = lds0 + wn * WPART;
   int cur[16];
@@ -737,37 +763,55 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
   //  * the 16 tile loads of the trip (t % 3 == 2): in phase 0 the 8 of B of tile kt + 1 into the slot at pa, in phase 1
   //    those of A of tile kt + 2 into the slot at pb;
   //  * the fragment addresses of the next tile, one each at positions 48..63 of phase 1.
-  auto position = [&](auto p_c, unsigned na, unsigned nb, const i32x4_t& desc, unsigned base_ld, bool refill, bool next)
-      __attribute__((always_inline)) {
+  // The ring in the trip of tile kt, as byte offsets: pa = slot that A of tile kt - 1 has left, which takes B of kt + 1 (operand
+  // 2 kt + 3); the one after it takes A of kt + 2; the one before it holds A of kt + 1.
+  unsigned pa = 0, pb = 0, na = 0;
+  unsigned ld_b = 0, ld_a = 0;                       // LDS addresses (this wave's share) of the two slots to refill
+  unsigned at_a = base_fa + 2 * OPB, at_b = base_fb + 3 * OPB;   // where the next tile's fragments are
+  Desc da = start(A, a_bytes), db = start(B, b_bytes);
+  const int nk2 = nk - 2;
+  int kt = 0;
+  auto position = [&](auto p_c, bool refill, bool next) __attribute__((always_inline)) {
     constexpr int p = decltype(p_c)::value, ph = p >> 6, t = p & 63;
     constexpr int n = load_at(t);
     __builtin_amdgcn_sched_barrier(0);
+    // every fragment of this phase has landed (requested 16 MFMAs ago at the latest): said once, so that the compiler
+    // does not put a wait ahead of each fragment's first use (lgkmcnt(0), the other counters left alone)
+    if (t == 0) __builtin_amdgcn_s_waitcnt(0xC07F);
     if constexpr (n >= 0) {
-      if (refill) issue_one(desc, ph == 0, std::integral_constant<int, n>{});
+      if (refill) issue_one(words(ph == 0 ? db : da), ph == 0, std::integral_constant<int, n>{});
     }
     if (next && t < 48) {
       if (TNL) { if (t % 3 < 2) read_tn(ph, RQ[t / 3], t % 3); }
       else if (t % 3 == 0) read_nt(ph, RQ[t / 3]);
     }
+    if (next && ph == 0) {                           // for phase 1: A's descriptor and slot, the next tile's fragments
+      if (t == 48) move_base(da, a_tile);
+      if (t == 49) move_end(da, a_tile, kt, nk2);
+      if (t == 50) slot_after(pb, pa);
+      if (t == 51) add(ld_a, lds_wave, pb);
+      if (t == 54) slot_before(na, pa);
+      if (t == 55) { add(at_a, base_fa, na); add(at_b, base_fb, pa); }
+      if (t == 56) slot_after_next(pa);
+    }
+    if (next && ph == 1) {                           // for the next trip: B's descriptor and slot
+      if (t == 48) move_base(db, b_tile);
+      if (t == 49) move_end(db, b_tile, kt, nk2);
+      if (t == 50) add(ld_b, lds_wave, pa);
+    }
     if (ph == 1 && t >= 48) {
       constexpr int q = t >= 48 ? t - 48 : 0;
-      cur[q] = faddr[q & 7] + (int)(q < 8 ? na : nb);
+      cur[q] = faddr[q & 7] + (int)(q < 8 ? at_a : at_b);
+      asm volatile("" : "+v"(cur[q]));               // here, not where the address is first used
     }
     if constexpr (t < 63 && load_at(t + 1) >= 0) {
-      if (refill) m0v = set_m0(base_ld, std::integral_constant<int, load_at(t + 1)>{});
+      if (refill) m0v = set_m0(ph == 0 ? ld_b : ld_a, std::integral_constant<int, load_at(t + 1)>{});
     }
     __builtin_amdgcn_sched_barrier(0);
     mma_one(ph ^ 1, t);
   };
-  // phases [p0, p1) / 64 of the trip of tile kt; pa, pb = byte offsets of the slots the previous tile has left, na, nb =
-  // those of the next tile's operands
-  auto trip = [&](auto p0, auto p1, unsigned pa, unsigned pb, unsigned na, unsigned nb, int kt, bool refill, bool next)
-      __attribute__((always_inline)) {
-    const i32x4_t db = desc_for(B, b_bytes, b_tile, kt + 1), da = desc_for(A, a_bytes, a_tile, kt + 2);
-    for_range<decltype(p0)::value, decltype(p1)::value>([&](auto p) __attribute__((always_inline)) {
-      constexpr bool first = decltype(p)::value < 64;
-      position(p, base_fa + na, base_fb + nb, first ? db : da, lds_wave + (first ? pa : pb), refill, next);
-    });
+  auto trip = [&](auto p0, auto p1, bool refill, bool next) __attribute__((always_inline)) {
+    for_range<decltype(p0)::value, decltype(p1)::value>([&](auto p) __attribute__((always_inline)) { position(p, refill, next); });
     __builtin_amdgcn_sched_barrier(0);
   };
   constexpr std::integral_constant<int, 0> P0{};
@@ -776,8 +820,13 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
 #define OPTSTAGE_TILE_SYNC(n) asm volatile("s_waitcnt vmcnt(" #n ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
 #pragma unroll
   for (int u = 0; u < 5; ++u) {
-    const i32x4_t d = (u & 1) ? desc_for(B, b_bytes, b_tile, u >> 1) : desc_for(A, a_bytes, a_tile, u >> 1);
-    for_range<0, 8>([&](auto idx) __attribute__((always_inline)) { m0v = set_m0(lds_wave + u * OPB, idx); asm volatile("s_nop 0"); issue_one(d, (u & 1) != 0, idx); });
+    Desc& d = u & 1 ? db : da;
+    if (u >= 2) { move_base(d, u & 1 ? b_tile : a_tile); move_end(d, u & 1 ? b_tile : a_tile, u >> 1, nk); }
+    for_range<0, 8>([&](auto idx) __attribute__((always_inline)) {
+      m0v = set_m0(lds_wave + u * OPB, idx);
+      asm volatile("s_nop 0");
+      issue_one(words(d), (u & 1) != 0, idx);
+    });
   }
 #pragma unroll
   for (int q = 0; q < 16; ++q) cur[q] = faddr[q & 7] + (int)(q < 8 ? base_fa : base_fb + OPB);
@@ -787,16 +836,12 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     if (TNL) { read_tn(0, RQ[q], 0); read_tn(0, RQ[q], 1); }
     else read_nt(0, RQ[q]);
   }
-  unsigned pa = 0, pb = OPB;                         // slots of the tile before tile kt
-  trip(P64, P128, 0, 0, two_on(pa), two_on(pb), 0, false, true);
-  for (int kt = 1; kt < nk; ++kt) {
-    const unsigned oa = two_on(pa), ob = two_on(pb);
+  trip(P64, P128, false, true);
+  for (kt = 1; kt < nk; ++kt) {
     OPTSTAGE_TILE_SYNC(8);
-    trip(P0, P128, pa, pb, two_on(oa), two_on(ob), kt, true, true);
-    pa = oa;
-    pb = ob;
+    trip(P0, P128, true, true);
   }
-  trip(P0, P64, 0, 0, 0, 0, 0, false, false);
+  trip(P0, P64, false, false);
   OPTSTAGE_TILE_SYNC(0);                             // every wave is done with the operand tiles, nothing in flight
 #undef OPTSTAGE_TILE_SYNC
   const int mw = m0 + wm * (BM / WM), nw = n0 + wn * (BN / WN);
