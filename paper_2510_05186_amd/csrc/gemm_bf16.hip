@@ -3,19 +3,16 @@
 // These are the three linear maps of a stage (paper Sec. 2.2): forward Y = X W^T (NT), backward for
 // activations dX = dY W (NT against the transposed weight copy), backward for weights dW += dY^T X (TN).
 //
-// Design (CDNA4): one workgroup of 4 or 8 waves owns a BM x BN output tile (256 x 256 for large problems);
-// the K loop advances 64 elements at a time through LDS tiles (two buffers in the register-staged kernel, a ring
-// of five operand slots in the direct kernels) with one barrier per step.
-// Large problems with K % 64 == 0 load their tiles straight from global memory into LDS (no registers, no
-// ds_write; see the direct kernels below); everything else stages tiles global -> registers -> LDS.  LDS tiles
-// are always [row][64 k] with the 16-byte chunk index XOR-swizzled by the row so that both the 16-byte operand reads
-// of v_mfma_f32_32x32x16_bf16 and the tile writes are bank-conflict
-// free.  Operands that are contiguous along their output index (TN) are transposed in registers on the
-// way into LDS (each thread gathers a KV x 8 patch and writes 8 k-contiguous pieces), so the MFMA read
-// path is identical for every layout.  The MFMA is issued with the B fragment as its first operand:
-// each lane then owns 4 consecutive n of one m, which gives 8-byte (bf16) / 16-byte (fp32) row-major
-// global accesses in the epilogue.  Workgroup ids are remapped so that the tiles resident on one XCD
-// (ids congruent mod 8) form a compact patch of the output and share A/B panels in that XCD's L2.
+// Design (CDNA4): three kernels by size (launch_layout).  Large products take the direct kernels below: one workgroup of
+// 4 waves per tile, the K loop advances 64 elements at a time, operand tiles go straight from global memory into a ring of
+// five LDS slots, one barrier per step.  Smaller products run on tiles of 128 or 64 (gemm_bf16_small.hip).  What neither can
+// address (rows of one tile spread over more than 32-bit offsets) goes through the register-staged kernel: 128 x 128 tiles, global
+// -> registers -> LDS, two buffers, operands that are contiguous along their output index (TN) transposed in registers on the
+// way into LDS.  Everywhere the LDS tiles' 16-byte chunk index is XOR-swizzled by the row so that operand reads and tile writes
+// are free of bank conflicts, and the MFMA is issued with the B fragment as its first operand: each lane then owns
+// 4 consecutive n of one m, which gives 8-byte (bf16) / 16-byte (fp32) row-major global accesses in the epilogue.  Workgroup
+// ids are remapped so that the tiles resident on one XCD (ids congruent mod 8) form a compact patch of the output and share
+// A/B panels in that XCD's L2.
 #include <utility>
 
 #include "common.h"
@@ -57,18 +54,14 @@ template <int R_T, int NTH> struct StageKC {
 // Row-contiguous operand: element (r, k) at p[k * ld + r].  Thread gathers KV k-rows x 8 r and writes
 // 8 pieces of KV k-contiguous elements.
 template <int R_T, int NTH> struct StageRC {
-  static constexpr int KV = R_T * 8 / NTH;   // k-rows per thread: 8 (16-byte LDS stores) or 4 (8-byte stores)
-  static_assert(KV == 8 || KV == 4, "unsupported tile / thread-count combination");
+  static constexpr int KV = R_T * 8 / NTH;   // k-rows per thread
+  static_assert(KV == 4, "unsupported tile / thread-count combination");
   uint4 reg[KV];
+  // 8-byte LDS stores: lanes 0-7 vary the row chunk, lane bit 3 the half of the 16-byte chunk
   __device__ __forceinline__ static void coords(int tid, int& rc, int& kg) {
-    if (KV == 8) {          // R_T / 8 row chunks x 8 k-groups; 8 consecutive lanes hit 8 distinct 16-byte chunks
-      rc = tid % (R_T / 8);
-      kg = tid / (R_T / 8);
-    } else {                // 8-byte stores: lanes 0-7 vary the row chunk, lane bit 3 the half of the 16-byte chunk
-      const int hi = tid >> 4;
-      rc = (tid & 7) | ((hi % (R_T / 64)) << 3);
-      kg = ((tid >> 3) & 1) | ((hi / (R_T / 64)) << 1);
-    }
+    const int hi = tid >> 4;
+    rc = (tid & 7) | ((hi % (R_T / 64)) << 3);
+    kg = ((tid >> 3) & 1) | ((hi / (R_T / 64)) << 1);
   }
   __device__ __forceinline__ void load(const bf16_t* p, int ld, int row0, int rows, int k0, int K, int tid) {
     int rc, kg;
@@ -98,10 +91,7 @@ template <int R_T, int NTH> struct StageRC {
       int row = rc * 8 + i;
       int koff = kg * KV;
       char* dst = lds + row * ROW_BYTES + ((((koff >> 3)) ^ swz(row)) << 4) + (koff & 7) * 2;
-      if (KV == 8)
-        *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2 % (KV / 2)], out[3 % (KV / 2)]);
-      else
-        *reinterpret_cast<uint2*>(dst) = make_uint2(out[0], out[1]);
+      *reinterpret_cast<uint2*>(dst) = make_uint2(out[0], out[1]);
     }
   }
 };
@@ -109,93 +99,14 @@ template <int R_T, int NTH> struct StageRC {
 template <int R_T, int NTH, bool RC> struct StageSel { typedef StageKC<R_T, NTH> type; };
 template <int R_T, int NTH> struct StageSel<R_T, NTH, true> { typedef StageRC<R_T, NTH> type; };
 
-// Epilogue through LDS for 256 x 256 workgroup tiles: each wave transposes its accumulator tile (32 TM rows
-// x 128 columns), 32 * 128 KB / (NWAVES * 16 KB) rows at a time, through a private slice of the 128 KB of
-// LDS (16-byte chunks XOR-swizzled by the row, conflict free both ways), so that global memory sees whole
-// 512-byte row segments instead of 16-byte pieces of 32 different rows.  The caller has made sure that no
-// wave still reads operand tiles.
-template <int EPI, int TM, int TN, int NWAVES>
-__device__ __forceinline__ void epilogue_via_lds(f32x16_t (&acc)[TM][TN], char* smem, int wave, int lane, void* Cv,
-                                                 const bf16_t* R, int M, int N, int ldc, int mw, int nw) {
-  static_assert(TN == 4, "a wave tile is 128 columns wide");
-  constexpr int SLICE = 131072 / NWAVES, IPP = SLICE / 16384;     // MFMA tile rows (32 matrix rows) per pass
-  static_assert(IPP >= 1 && TM % IPP == 0, "wave tile must split into whole passes");
-  constexpr int NIT = 16 * IPP;                                   // row pairs per pass
-  char* const wl = smem + wave * SLICE;
-  const int khalf = lane >> 5;
-  const int c = lane & 31;
-  const int n = nw + c * 4;
-#pragma unroll
-  for (int pass = 0; pass < TM / IPP; ++pass) {
-    // accumulate / residual: request this pass's rows of the old values first, so that their latency runs
-    // under the LDS transposition
-    // (only where the register budget allows it: 4-wave kernels)
-    constexpr bool PRE = NWAVES == 4;
-    f32x4_t cold[EPI == EPI_ACCUM && PRE ? NIT : 1];
-    bf16x4_t rold[EPI == EPI_RESID && PRE ? NIT : 1];
-    if ((EPI == EPI_ACCUM || EPI == EPI_RESID) && PRE) {
-#pragma unroll
-      for (int p2 = 0; p2 < NIT; ++p2) {
-        const int m = mw + pass * IPP * 32 + 2 * p2 + khalf;
-        const bool ok = m < M && n < N;
-        const size_t off = (size_t)m * ldc + n;
-        if (EPI == EPI_ACCUM) {
-          f32x4_t z = {0.f, 0.f, 0.f, 0.f};
-          cold[p2] = ok ? __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(Cv) + off)) : z;
-        } else {
-          bf16x4_t z = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
-          rold[p2] = ok ? *reinterpret_cast<const bf16x4_t*>(R + off) : z;
-        }
-      }
-    }
-#pragma unroll
-    for (int i2 = 0; i2 < IPP; ++i2) {
-      const int row = i2 * 32 + (lane & 31);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int chunk = j * 8 + g * 2 + khalf;
-          f32x4_t v;
-          v[0] = acc[pass * IPP + i2][j][g * 4 + 0]; v[1] = acc[pass * IPP + i2][j][g * 4 + 1];
-          v[2] = acc[pass * IPP + i2][j][g * 4 + 2]; v[3] = acc[pass * IPP + i2][j][g * 4 + 3];
-          *reinterpret_cast<f32x4_t*>(wl + row * 512 + ((chunk ^ (row & 31)) << 4)) = v;
-        }
-    }
-#pragma unroll
-    for (int p2 = 0; p2 < NIT; ++p2) {
-      const int row = 2 * p2 + khalf;
-      const int m = mw + pass * IPP * 32 + row;
-      f32x4_t v = *reinterpret_cast<const f32x4_t*>(wl + row * 512 + ((c ^ (row & 31)) << 4));
-      if (m < M && n < N) {
-        const size_t off = (size_t)m * ldc + n;
-        if (EPI == EPI_STOREF) {
-          __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(Cv) + off));
-        } else if (EPI == EPI_ACCUM) {
-          const f32x4_t o = PRE ? cold[PRE ? p2 : 0] : *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(Cv) + off);
-          v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
-          __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(Cv) + off));
-        } else {
-          if (EPI == EPI_RESID) {
-            const bf16x4_t r = PRE ? rold[PRE ? p2 : 0] : *reinterpret_cast<const bf16x4_t*>(R + off);
-            v[0] += (float)r[0]; v[1] += (float)r[1]; v[2] += (float)r[2]; v[3] += (float)r[3];
-          }
-          bf16x4_t o;
-          o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
-          *reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16_t*>(Cv) + off) = o;
-        }
-      }
-    }
-  }
-}
-
 // ---- kernel ---------------------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, bool A_RC, bool B_RC, int EPI>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+template <bool RC, int EPI>
+__global__ __launch_bounds__(256) void gemm_bf16_staged_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                         void* __restrict__ Cv, const bf16_t* __restrict__ R, int M,
                                                         int N, int K, int lda, int ldb, int ldc, int tiles_m,
                                                         int tiles_n) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int BM = 128, BN = 128, WM = 2, WN = 2;
   constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = BN * ROW_BYTES, BUF = A_BYTES + B_BYTES;
   constexpr int NTH = 64 * WM * WN;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // 32x32 MFMA tiles per wave in m and n
@@ -216,8 +127,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
   const int tile_m = first_m + in_grp % gsz, tile_n = in_grp / gsz;
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
-  typename StageSel<BM, NTH, A_RC>::type sa;
-  typename StageSel<BN, NTH, B_RC>::type sb;
+  typename StageSel<BM, NTH, RC>::type sa;
+  typename StageSel<BN, NTH, RC>::type sb;
 
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -308,11 +219,6 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
     sb.store(cur + A_BYTES, tid);
   }
 
-  if constexpr (BM == 256 && BN == 256 && TN == 4) {
-    __syncthreads();                                 // every wave is done with the operand tiles
-    epilogue_via_lds<EPI, TM, TN, WM * WN>(acc, smem, wave, lane, Cv, R, M, N, ldc, m0 + wm * (BM / WM), n0 + wn * (BN / WN));
-    return;
-  }
   // epilogue: lane owns m = .. + (lane & 31) and, per register group g, n = .. + 8 g + 4 (lane >> 5) + 0..3
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -352,8 +258,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16_t* _
 // 256 x 256 x 64 tiles, 2 x 2 waves (one per SIMD; each owns 128 x 128 of the output in 256 accumulator
 // registers).  The tiles never pass through registers: every wave issues 16 `buffer_load_dwordx4 ... lds` per
 // k-tile, each filling 1 KB of LDS (lane i writes 16 bytes at base + 16 i); which global address a lane loads
-// realises the LDS swizzle.  Requires K % 64 == 0 and operands below 4 GiB (checked on the host); rows or
-// columns past the operand read as zero through the buffer range check.
+// realises the LDS swizzle.  Requires operands below 4 GiB (checked on the host); rows, columns and k past the operand read
+// as zero through the buffer range check.
 //
 // What bounds them is power: the board holds its limit by lowering the clock, so time goes with the energy per flop.
 // v_mfma_f32_16x16x32_bf16 moves half the accumulator traffic per flop of v_mfma_f32_32x32x16_bf16 and runs 15 % faster in
@@ -601,8 +507,9 @@ __device__ constexpr int load_at(int t) {
 }
 
 // One output tile.  TNL = false: A(m, k) at A[m * lda + k], B(n, k) at B[n * ldb + k].  TNL = true: A[k * lda + m],
-// B[k * ldb + n]; there K may be anything (k-rows past it lie past the operand and read as zero), otherwise K % 64 == 0.
-template <bool TNL, int EPI>
+// B[k * ldb + n]; there K may be anything (k-rows past it lie past the operand and read as zero).  Otherwise K % 64 == 0 unless
+// RAGGED (then K % 8 == 0): the 16-byte chunks of the last k-tile that lie past K are fetched out of range.
+template <bool TNL, int EPI, bool RAGGED = false>
 __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                             void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N, int K, int lda,
                                             int ldb, int ldc, unsigned a_bytes, unsigned b_bytes, int tile_m, int tile_n,
@@ -669,6 +576,12 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     b_tile = b_slab ? 32768u : BK * 2;
   }
   const int nk = (K + BK - 1) / BK;
+  auto drop_tail = [&](bool is_b) __attribute__((always_inline)) {       // ahead of the loads of the last k-tile
+    const int c0 = (lane & 7) ^ (lane >> 3), valid = (K % BK) >> 3;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if ((c0 ^ j) >= valid) voff[2 * j + (is_b ? 1 : 0)] = 0xFFFFFF00u;
+  };
   // Descriptor of an operand: base and length both move with the k-tile, so that what lies past the operand's end reads as
   // zero whatever the range check makes of a scalar offset.  Past the last tile the length is zero (the load then moves
   // nothing from memory and zero-fills its slot, so the count of loads in flight is the same on every trip).
@@ -778,6 +691,9 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     // every fragment of this phase has landed (requested 16 MFMAs ago at the latest): said once, so that the compiler
     // does not put a wait ahead of each fragment's first use (lgkmcnt(0), the other counters left alone)
     if (t == 0) __builtin_amdgcn_s_waitcnt(0xC07F);
+    if (RAGGED && t == 0 && refill) {
+      if (kt + 1 + ph == nk - 1) drop_tail(ph == 0);
+    }
     if constexpr (n >= 0) {
       if (refill) issue_one(words(ph == 0 ? db : da), ph == 0, std::integral_constant<int, n>{});
     }
@@ -822,6 +738,7 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
   for (int u = 0; u < 5; ++u) {
     Desc& d = u & 1 ? db : da;
     if (u >= 2) { move_base(d, u & 1 ? b_tile : a_tile); move_end(d, u & 1 ? b_tile : a_tile, u >> 1, nk); }
+    if (RAGGED && (u >> 1) == nk - 1) drop_tail((u & 1) != 0);
     for_range<0, 8>([&](auto idx) __attribute__((always_inline)) {
       m0v = set_m0(lds_wave + u * OPB, idx);
       asm volatile("s_nop 0");
@@ -896,7 +813,7 @@ __device__ __forceinline__ void tile_coords(int id, int n, int tiles_m, int tile
   tile_n = in_grp / gsz;
 }
 
-template <bool TNL, int EPI>
+template <bool TNL, int EPI, bool RAGGED>
 __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                                void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N,
                                                                int K, int lda, int ldb, int ldc, int tiles_m, int tiles_n,
@@ -905,7 +822,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_direct_kernel(const bf16_t* __r
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int tile_m, tile_n;
   tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, order, tile_m, tile_n);
-  direct_tile<TNL, EPI>(smem, A, B, Cv, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, tile_m, tile_n, !TNL && b_slab != 0, ex);
+  direct_tile<TNL, EPI, RAGGED>(smem, A, B, Cv, R, M, N, K, lda, ldb, ldc, a_bytes, b_bytes, tile_m, tile_n, !TNL && b_slab != 0, ex);
 }
 
 // Several independent products with the same K in one launch (the weight-gradient GEMMs of a W op: four per
@@ -947,10 +864,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_direct_grouped_kernel(const Gro
 // miss the L2); the NT products are within 0.5 % either way and keep order 0.
 constexpr int tile_order(bool tnl) { return tnl ? 1 : 0; }
 
-template <bool TNL, int EPI>
+template <bool TNL, int EPI, bool RAGGED = false>
 hipError_t launch_direct(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
                          int ldc, hipStream_t s, bool b_slab = false, const GemmExtra& ex = GemmExtra()) {
-  auto kern = gemm_bf16_direct_kernel<TNL, EPI>;
+  auto kern = gemm_bf16_direct_kernel<TNL, EPI, RAGGED>;
   constexpr int smem = 163840;
   static LdsAttrOnce lds_attr;
   if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
@@ -964,12 +881,10 @@ hipError_t launch_direct(const void* A, const void* B, void* C, const void* R, i
   return hipGetLastError();
 }
 
-// the direct path needs whole 64-wide k-tiles and 32-bit byte offsets (NT: including the rows a partial edge
-// tile reaches past the operand)
+// the direct path needs 32-bit byte offsets (including what a partial edge tile reaches past the operand)
 bool direct_applies(bool tnl, int M, int N, int K, int lda, int ldb) {
-  if (K % 64) return false;
   const unsigned long long lim = 0xF0000000ull;
-  if (tnl) return ((unsigned long long)K * lda * 2 < lim) && ((unsigned long long)K * ldb * 2 < lim);
+  if (tnl) return ((unsigned long long)(K + 63) * lda * 2 < lim) && ((unsigned long long)(K + 63) * ldb * 2 < lim);
   return ((unsigned long long)(M + 256) * lda * 2 < lim) && ((unsigned long long)(N + 256) * ldb * 2 < lim);
 }
 template <bool TNL, int EPI>
@@ -999,33 +914,36 @@ hipError_t launch_direct_grouped(int n, const GemmProblem* pr, int K, hipStream_
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, bool A_RC, bool B_RC, int EPI>
-hipError_t launch_cfg(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
-                      int ldc, hipStream_t s) {
-  auto kern = gemm_bf16_kernel<BM, BN, WM, WN, A_RC, B_RC, EPI>;
-  constexpr int smem = 2 * (BM + BN) * ROW_BYTES;
+template <bool RC, int EPI>
+hipError_t launch_staged(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
+                         int ldc, hipStream_t s) {
+  auto kern = gemm_bf16_staged_kernel<RC, EPI>;
+  constexpr int smem = 2 * (128 + 128) * ROW_BYTES;
   static LdsAttrOnce lds_attr;
   if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(64 * WM * WN), smem, s, (const bf16_t*)A, (const bf16_t*)B, C,
+  const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
+  hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(256), smem, s, (const bf16_t*)A, (const bf16_t*)B, C,
                      (const bf16_t*)R, M, N, K, lda, ldb, ldc, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
+// The direct kernels from 128 tiles of 256 x 256 on, and below that where tiles of 128 would need a second round of workgroups
+// (one per compute unit; a k-tile of 128 x 128 takes half the time of one of 256 x 256, so two rounds cost what one of the
+// large tiles does, plus a second start and end: NT 1536 x 4096 x 1024 25.3 us on tiles of 128, 22.2 on 256; 2056 x 3080 x
+// 4096 76.7 / 67.5; TN 2048 x 2304 x 1000 30.7 / 29.2).  Everything smaller: tiles of 128 and 64.  The register-staged kernel
+// takes what is left: leading dimensions of 2^23 elements and more, whose rows within one tile span more than 32-bit
+// offsets reach.
 template <bool RC, int EPI>
 hipError_t launch_layout(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
                          int ldc, hipStream_t s) {
-  long big_tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (big_tiles >= 128) {
-    if (direct_applies(RC, M, N, K, lda, ldb)) return launch_direct<RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
-    // register-staged path: 8 waves (4 x 2) for the transposing TN loader, 4 waves (2 x 2) otherwise
-    if constexpr (RC) {
-      return launch_cfg<256, 256, 4, 2, RC, RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
-    } else {
-      return launch_cfg<256, 256, 2, 2, RC, RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
-    }
+  const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256), tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+  if ((tiles256 >= 128 || tiles128 > 256) && direct_applies(RC, M, N, K, lda, ldb)) {
+    if (!RC && K % BK) return launch_direct<RC, EPI, !RC>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
+    return launch_direct<RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
   }
-  return launch_cfg<128, 128, 2, 2, RC, RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
+  if (gemm_bf16_small_applies(M, N, K, lda, ldb))
+    return launch_gemm_bf16_small(RC ? GEMM_TN : GEMM_NT, EPI, GemmProblem{A, B, C, R, M, N, lda, ldb, ldc}, K, s);
+  return launch_staged<RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
 }
 
 }  // namespace
@@ -1093,13 +1011,14 @@ hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, v
 // n independent products sharing layout, epilogue and K in one launch: whether the set qualifies (every product
 // on the direct path, operands aligned as the kernels need, at least half a round of tiles in total)
 bool gemm_bf16_grouped_applies(int layout, int n, const GemmProblem* pr, int K) {
-  if (n <= 0 || n > MAX_GROUP || K <= 0 || (K % 64)) return false;
+  if (n <= 0 || n > MAX_GROUP || K <= 0) return false;
   long tiles = 0;
   for (int i = 0; i < n; ++i) {
     const GemmProblem& q = pr[i];
     if (q.M <= 0 || q.N <= 0) return false;
     if ((q.lda & 7) || (q.ldb & 7) || (q.ldc & 3) || (q.N & 3)) return false;
     if (layout == GEMM_TN && ((q.M & 7) || (q.N & 7))) return false;
+    if (layout == GEMM_NT && (K % 64)) return false;
     if (!direct_applies(layout == GEMM_TN, q.M, q.N, K, q.lda, q.ldb)) return false;
     tiles += (long)((q.M + 255) / 256) * ((q.N + 255) / 256);
   }

@@ -119,7 +119,7 @@ optstage_status optstage_op_gemm_grouped(uint32_t layout, uint32_t epilogue, uin
     REQ(q.ldc >= q.N, "gemm_grouped: ldc smaller than N");
     pr[i] = {q.A, q.B, q.C, q.R, (int)q.M, (int)q.N, (int)q.lda, (int)q.ldb, (int)q.ldc};
   }
-  REQ(gemm_bf16_grouped_applies((int)layout, (int)n, pr, (int)K), "gemm_grouped: the set does not qualify (K % 64, alignment, fewer than 128 tiles)");
+  REQ((K % 64) == 0 && gemm_bf16_grouped_applies((int)layout, (int)n, pr, (int)K), "gemm_grouped: the set does not qualify (K % 64, alignment, fewer than 128 tiles)");
   return wrap(launch_gemm_bf16_grouped((int)layout, (int)epilogue, (int)n, pr, (int)K, (hipStream_t)stream), "gemm_grouped");
 }
 

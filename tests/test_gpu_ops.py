@@ -72,6 +72,59 @@ def test_gemm_tn_accumulate(dtype, M, N, K):
     assert rel_err(host(C), ref) < (1e-5 if dtype == FP32 else 1e-4)    # fp32 accumulators: no bf16 rounding of C
 
 
+# Products below the 256 x 256 kernels and the edges between the kernels: one k-chunk, one k-tile, K with a tail that is no multiple
+# of 64 (NT: 16-byte chunks fetched out of range, TN: any K), tiles of 64 and 128 cut in both directions, 1 to 14 k-tiles
+# for the four waves that share a contraction, one tile more and less than a threshold, and the direct kernel with a K tail.
+# The absolute bound is the fp32 sum's plus, for bf16 results, one rounding (2^-9 of the value).
+@pytest.mark.parametrize("M,N,K", [(1, 4, 8), (63, 60, 64), (64, 64, 72), (65, 68, 200), (130, 516, 448), (127, 64, 896), (320, 1000, 264),
+                                   (1160, 2440, 136), (1160, 2304, 520), (2056, 2056, 72), (2824, 3080, 72), (4096, 2048, 8)])
+def test_gemm_tiles_of_every_size_nt(M, N, K):
+    a, w, r = (q(RNG.standard_normal(s), BF16) for s in ((M, K), (N, K), (M, N)))
+    A, W, R = dev(a, BF16), dev(w, BF16), dev(r, BF16)
+    ref, mag = a @ w.T, np.abs(a) @ np.abs(w).T
+    for epi, want, start in ((B.EPI_STORE, ref, None), (B.EPI_RESID, ref + r, None), (B.EPI_ACCUM, ref + 3.0, 3.0)):
+        C = torch.full((M + 1, N + 4), 7.0 if start is None else start, dtype=torch.bfloat16 if start is None else torch.float32, device="cuda")
+        keep = C.clone()
+        Rp = torch.full((M + 1, N + 4), 9.0, dtype=torch.bfloat16, device="cuda")
+        Rp[:M, :N] = R
+        ok(lib().optstage_op_gemm(BF16, B.GEMM_NT, epi, A.data_ptr(), W.data_ptr(), C.data_ptr(), Rp.data_ptr(), M, N, K, K, K, N + 4, stream()))
+        torch.cuda.synchronize()
+        bound = K * 2.0 ** -24 * (mag + 3.0) + (2.0 ** -8 * np.abs(want) if start is None else 0.0) + 1e-6
+        assert np.all(np.abs(host(C)[:M, :N] - want) <= bound), (epi, np.max(np.abs(host(C)[:M, :N] - want) / bound))
+        assert torch.equal(C[M:], keep[M:]) and torch.equal(C[:, N:], keep[:, N:])          # nothing past the edges
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 8, 1), (64, 64, 63), (72, 56, 65), (136, 520, 449), (264, 1000, 130), (1160, 3080, 67), (1800, 2048, 321),
+                                   (2056, 2056, 71), (2824, 3080, 129)])
+def test_gemm_tiles_of_every_size_tn(M, N, K):
+    dy, x = q(RNG.standard_normal((K, M)), BF16), q(RNG.standard_normal((K, N)), BF16)
+    DY, X = dev(dy, BF16), dev(x, BF16)
+    ref, mag = dy.T @ x, np.abs(dy).T @ np.abs(x)
+    for epi, want in ((B.EPI_ACCUM, ref + 3.0), (3, ref), (B.EPI_STORE, ref)):
+        C = torch.full((M + 1, N + 4), 3.0, dtype=torch.bfloat16 if epi == B.EPI_STORE else torch.float32, device="cuda")
+        ok(lib().optstage_op_gemm(BF16, B.GEMM_TN, epi, DY.data_ptr(), X.data_ptr(), C.data_ptr(), 0, M, N, K, M, N, N + 4, stream()))
+        torch.cuda.synchronize()
+        bound = K * 2.0 ** -24 * (mag + 3.0) + (2.0 ** -8 * np.abs(want) if epi == B.EPI_STORE else 0.0) + 1e-6
+        assert np.all(np.abs(host(C)[:M, :N] - want) <= bound), (epi, np.max(np.abs(host(C)[:M, :N] - want) / bound))
+        assert float((C[M:] - 3.0).abs().max()) == 0.0 and float((C[:, N:] - 3.0).abs().max()) == 0.0
+
+
+def test_gemm_with_rows_further_apart_than_a_tile_can_address():
+    """Leading dimensions of 2^23 elements: the kernel that stages its tiles through registers."""
+    ld, n, k = 1 << 23, 16, 72
+    a, w = q(RNG.standard_normal((n, k)), BF16), q(RNG.standard_normal((n, k)), BF16)
+    A = torch.zeros(n, ld, dtype=torch.bfloat16, device="cuda")
+    A[:, :k] = dev(a, BF16)
+    W, C = dev(w, BF16), torch.zeros(n, n, dtype=torch.bfloat16, device="cuda")
+    ok(lib().optstage_op_gemm(BF16, B.GEMM_NT, B.EPI_STORE, A.data_ptr(), W.data_ptr(), C.data_ptr(), 0, n, n, k, ld, k, n, stream()))
+    torch.cuda.synchronize()
+    assert rel_err(host(C), a @ w.T) < TOL[BF16] / 4
+    X, D = dev(w[:, :16].copy(), BF16), torch.zeros(k, 16, dtype=torch.float32, device="cuda")     # A as [16 tokens][ld], 72 columns used
+    ok(lib().optstage_op_gemm(BF16, B.GEMM_TN, 3, A.data_ptr(), X.data_ptr(), D.data_ptr(), 0, k, 16, n, ld, 16, 16, stream()))
+    torch.cuda.synchronize()
+    assert rel_err(host(D), a.T @ w[:, :16]) < 1e-5
+
+
 def test_gemm_grouped_equals_one_by_one_and_the_oracle():
     """The weight-gradient products of a W op in one launch (shapes of the Llama stage's four linears at a
     shorter token count, including a ragged 200-row edge tile): bitwise the same as launching each on its
