@@ -1,10 +1,175 @@
-// fp32 GEMM for the fp32 workload (tiny, launch-latency bound): C[M,N] = sum_k A(m,k) * B(n,k) with
-// the same layouts and epilogues as the bf16 kernel (Sec. 2.2: Y = X W^T, dX = dY W, dW += dY^T X).
-// Plain LDS-tiled FMA kernel: 64 x 64 tile, 256 threads, 4 x 4 outputs per thread, any M/N/K.
+// fp32 GEMM of the fp32 workload: C[M,N] = sum_k A(m,k) * B(n,k) with the same layouts and epilogues as the bf16 kernels
+// (Sec. 2.2: Y = X W^T, dX = dY W, dW += dY^T X), on the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (fp32 products and sums).
+//
+// What bounds it: an fp32 MFMA does 64 flop per cycle and SIMD, so operands are cheap to feed and what counts is how many compute
+// units have work.  A workgroup owns an R x R tile (R = 64, 32 or 16, see pick_tile), its four waves split the contraction in
+// steps of 16 k (wave w takes the steps w, w + 4, ...) and the four partial tiles are added through LDS in wave order.  No
+// operand is shared between waves, so nothing is staged through LDS: every lane loads its part of the fragments straight into
+// registers, 16 bytes at a time, several steps ahead (DEPTH), and the loop has no barrier.
+//  * NT (contiguous along k): lane = row (lane & 15), 4 consecutive k at 4 (lane >> 4); element e of the four goes to MFMA e of
+//    the step, the same k on both sides.  One load is 16 rows of 64 bytes.
+//  * TN (contiguous along the output index): a lane loads T = R / 16 consecutive rows (columns) T r .. of one k, r = lane & 15,
+//    and element i belongs to MFMA tile i: tile i holds the rows T r + i, which costs nothing but the index in the epilogue.
+//    One load is 4 k-rows of 4 R bytes.
+// Loads go through the buffer range check: rows past the operand and, by a lane offset out of range, k past K read as zero.
+// Measured (us, plain LDS-tiled FMA kernel -> this one): NT 128 x 256 x 1024 122 -> 6.3, 512 x 1024 x 4096
+// 592 -> 65.6, 2048 x 2048 x 2048 421 -> 149 (115 TFLOP/s); TN 1024 x 256 x 128 21.3 -> 4.6, 1024 x 4096 x 512 115 -> 50.1.
 #include "common.h"
 
 namespace {
 
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+constexpr unsigned OUT_OF_RANGE = 0xFFFFFF00u;
+constexpr int STEP = 16;                                     // k per step
+
+// One operand: R rows by 16 k per step, T = R / 16 MFMA tiles
+template <int R, bool TNL, bool VEC> struct Operand {
+  static constexpr int T = R / 16;
+  __amdgpu_buffer_rsrc_t rsrc;
+  unsigned off[T];             // NT: row 16 i + r of the tile at this lane's k; TN: off[0] = this lane's rows at k-row g
+  unsigned kstep;              // bytes per k
+  int k0;                      // first k of this lane within a step
+
+  __device__ __forceinline__ void init(const float* p, int ld, int first, int extent, int K, int lane) {
+    const int r = lane & 15, g = lane >> 4;
+    const float* base = TNL ? p + first : p + (size_t)first * ld;
+    const unsigned long long bytes = TNL ? ((unsigned long long)(K - 1) * ld + extent - first) * 4
+                                         : ((unsigned long long)(extent - 1 - first) * ld + K) * 4;
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(unsigned)(bytes > OUT_OF_RANGE ? OUT_OF_RANGE : bytes), 0x00020000);
+    if constexpr (TNL) {
+      k0 = g;                                                // rows g, g + 4, g + 8, g + 12 of a step
+      kstep = (unsigned)ld * 4u;
+      off[0] = first + r * T < extent ? (unsigned)(r * T) * 4u : OUT_OF_RANGE;
+    } else {
+      k0 = 4 * g;
+      kstep = 4u;
+#pragma unroll
+      for (int i = 0; i < T; ++i) off[i] = first + i * 16 + r < extent ? (unsigned)(i * 16 + r) * (unsigned)ld * 4u : OUT_OF_RANGE;
+    }
+  }
+  __device__ __forceinline__ float one(unsigned o) const {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, o, 0, 0));
+  }
+  // v[i][e] = operand of MFMA e (k-set e) of tile i for the step that starts at k
+  __device__ __forceinline__ void load(float (&v)[T][4], int k, int K, int rows_left) const {
+    if constexpr (TNL) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int kk = k + k0 + 4 * e;
+        const unsigned o = kk < K && off[0] != OUT_OF_RANGE ? off[0] + (unsigned)kk * kstep : OUT_OF_RANGE;
+        if constexpr (VEC && T == 4) {
+          const u32x4_t x = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i][e] = __uint_as_float(x[i]);
+        } else if constexpr (VEC && T == 2) {
+          typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+          const u32x2_t x = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, o, 0, 0));
+          v[0][e] = __uint_as_float(x[0]); v[1][e] = __uint_as_float(x[1]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < T; ++i) v[i][e] = one(o != OUT_OF_RANGE && i < rows_left ? o + i * 4u : OUT_OF_RANGE);
+        }
+      }
+    } else {
+      const int kk = k + k0;
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        if constexpr (VEC) {                                 // K % 4 == 0: the four k are inside or outside together
+          const unsigned o = kk < K && off[i] != OUT_OF_RANGE ? off[i] + (unsigned)kk * 4u : OUT_OF_RANGE;
+          const u32x4_t x = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][e] = __uint_as_float(x[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[i][e] = one(kk + e < K && off[i] != OUT_OF_RANGE ? off[i] + (unsigned)(kk + e) * 4u : OUT_OF_RANGE);
+        }
+      }
+    }
+  }
+};
+
+template <int R, bool TNL, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                                            const float* __restrict__ Res, int M, int N, int K, int lda, int ldb,
+                                                            int ldc, int tiles_m, int tiles_n, int epi) {
+  constexpr int T = R / 16, DEPTH = R == 64 ? 2 : R == 32 ? 4 : 8;
+  __shared__ __attribute__((aligned(16))) float part[4][R][R + 4];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // consecutive workgroup ids go to different XCDs: every XCD takes one contiguous eighth of the tiles, row by row
+  int id = blockIdx.x;
+  const int n_tiles = tiles_m * tiles_n;
+  if ((n_tiles & 7) == 0) id = (id & 7) * (n_tiles >> 3) + (id >> 3);
+  const int m0 = (id / tiles_n) * R, n0 = (id % tiles_n) * R;
+  Operand<R, TNL, VEC> a, b;
+  a.init(A, lda, m0, M, K, lane);
+  b.init(B, ldb, n0, N, K, lane);
+  const int a_left = TNL ? M - m0 - r * T : 0, b_left = TNL ? N - n0 - r * T : 0;   // rows of this lane inside the operand
+  f32x4_t acc[T][T];
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float av[DEPTH][T][4], bv[DEPTH][T][4];
+  const int steps = (K + STEP - 1) / STEP, count = (steps - wave + 3) >> 2;   // this wave's steps: wave + 4 s
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    a.load(av[d], (wave + 4 * d) * STEP, K, a_left);
+    b.load(bv[d], (wave + 4 * d) * STEP, K, b_left);
+  }
+  for (int s = 0; s < count; s += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {                        // steps past the last are zeros
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+          for (int j = 0; j < T; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[d][j][e], av[d][i][e], acc[i][j], 0, 0, 0);
+      a.load(av[d], (wave + 4 * (s + d + DEPTH)) * STEP, K, a_left);
+      b.load(bv[d], (wave + 4 * (s + d + DEPTH)) * STEP, K, b_left);
+    }
+  }
+  // partial tiles into LDS in the order of C: acc[i][j][v] is row r of tile i, column 4 g + v of tile j
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    const int row = TNL ? T * r + i : 16 * i + r;
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      if constexpr (TNL) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][row][T * (4 * g + v) + j] = acc[i][j][v];
+      } else {
+        *reinterpret_cast<f32x4_t*>(&part[wave][row][16 * j + 4 * g]) = acc[i][j];
+      }
+    }
+  }
+  __syncthreads();
+  // R * R / 4 pieces of four columns over 256 threads, partial tiles added in wave order
+  for (int q = tid; q < R * R / 4; q += 256) {
+    const int row = q / (R / 4), col = (q % (R / 4)) * 4, m = m0 + row, n = n0 + col;
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(&part[0][row][col]);
+#pragma unroll
+    for (int p = 1; p < 4; ++p) {
+      const f32x4_t o = *reinterpret_cast<const f32x4_t*>(&part[p][row][col]);
+      v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+    }
+    if (m >= M || n >= N) continue;
+    float* dst = C + (size_t)m * ldc + n;
+    const float* add = epi == EPI_RESID ? Res + (size_t)m * ldc + n : epi == EPI_ACCUM ? dst : nullptr;
+    if (n + 4 <= N && (ldc & 3) == 0) {
+      if (add) { const f32x4_t o = *reinterpret_cast<const f32x4_t*>(add); v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3]; }
+      *reinterpret_cast<f32x4_t*>(dst) = v;
+    } else {
+      for (int e = 0; e < 4 && n + e < N; ++e) dst[e] = add ? v[e] + add[e] : v[e];
+    }
+  }
+}
+
+// General path: 64 x 64 tile through LDS, 256 threads, 4 x 4 outputs per thread, any strides.  Takes what 32-bit offsets within
+// a tile do not reach.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                        float* __restrict__ C, const float* __restrict__ R, int M, int N,
@@ -61,22 +226,61 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+
+template <int R, bool TNL, bool VEC>
+hipError_t launch_mfma(int epi, const float* A, const float* B, float* C, const float* R_, int M, int N, int K, int lda, int ldb,
+                       int ldc, hipStream_t s) {
+  const int tiles_m = (M + R - 1) / R, tiles_n = (N + R - 1) / R;
+  hipLaunchKernelGGL((gemm_f32_mfma_kernel<R, TNL, VEC>), dim3((unsigned)tiles_m * (unsigned)tiles_n), dim3(256), 0, s, A, B, C, R_,
+                     M, N, K, lda, ldb, ldc, tiles_m, tiles_n, epi);
+  return hipGetLastError();
+}
+
+// The tile that needs the least time: rounds of 256 workgroups times the time of a round, measured for 1024 k as 21 us at R = 64,
+// 7.8 at 32, 3.8 at 16 (2.3 while no compute unit holds two, which share its load path).  E.g. 512 x 1024 x 1024 28.0 / 20.6 /
+// 34.4 us, 512 x 4096 x 1024 45.2 / 65.5 / 127, 128 x 256 x 1024 25.2 / 11.4 / 6.3.
+int pick_tile(int M, int N) {
+  auto cost = [&](int r, double per_round) {
+    const long long tiles = (long long)((M + r - 1) / r) * ((N + r - 1) / r);
+    return (double)((tiles + 255) / 256) * (r == 16 && tiles <= 256 ? 2.3 : per_round);
+  };
+  const double c64 = cost(64, 21.0), c32 = cost(32, 7.8), c16 = cost(16, 3.8);
+  return c64 <= c32 && c64 <= c16 ? 64 : c32 <= c16 ? 32 : 16;
+}
+
+template <bool TNL, bool VEC>
+hipError_t launch_sized(int epi, const float* A, const float* B, float* C, const float* R, int M, int N, int K, int lda, int ldb,
+                        int ldc, hipStream_t s) {
+  switch (pick_tile(M, N)) {
+    case 64: return launch_mfma<64, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
+    case 32: return launch_mfma<32, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
+    default: return launch_mfma<16, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                            int K, int lda, int ldb, int ldc, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-  long sam, sak, sbn, sbk;
-  if (layout == GEMM_NT) { sam = lda; sak = 1; sbn = ldb; sbk = 1; }
-  else if (layout == GEMM_TN) { sam = 1; sak = lda; sbn = 1; sbk = ldb; }
-  else return hipErrorInvalidValue;
-  dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
+  if ((layout != GEMM_NT && layout != GEMM_TN) || epi < EPI_STORE || epi > EPI_STOREF) return hipErrorInvalidValue;
+  const bool tn = layout == GEMM_TN;
   const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
   float* c = (float*)C;
-  if (epi == EPI_STORE || epi == EPI_STOREF) hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, grid, block, 0, s, a, b, c, r,
-      M, N, K, sam, sak, sbn, sbk, ldc);
-  else if (epi == EPI_RESID) hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, s, a, b, c, r, M, N, K, sam, sak, sbn, sbk, ldc);
+  // lane offsets: NT 64 rows of a tile, TN all k-rows of the operand's column strip
+  const unsigned long long reach = 0xF0000000ull / 4;
+  const unsigned long long span = (unsigned long long)(tn ? K + 64ull * 16 : 64ull) * (unsigned long long)(lda > ldb ? lda : ldb) + 64;
+  if (span < reach && (tn || (unsigned long long)K < reach / 2)) {
+    const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
+    if (tn) return vec ? launch_sized<true, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
+                       : launch_sized<true, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
+    return vec ? launch_sized<false, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
+               : launch_sized<false, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
+  }
+  const long sam = tn ? 1 : lda, sak = tn ? lda : 1, sbn = tn ? 1 : ldb, sbk = tn ? ldb : 1;
+  dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
+  if (epi == EPI_RESID) hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, s, a, b, c, r, M, N, K, sam, sak, sbn, sbk, ldc);
   else if (epi == EPI_ACCUM) hipLaunchKernelGGL(gemm_f32_kernel<EPI_ACCUM>, grid, block, 0, s, a, b, c, r, M, N, K, sam, sak, sbn, sbk, ldc);
-  else return hipErrorInvalidValue;
+  else hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, grid, block, 0, s, a, b, c, r, M, N, K, sam, sak, sbn, sbk, ldc);
   return hipGetLastError();
 }

@@ -109,6 +109,36 @@ def test_gemm_tiles_of_every_size_tn(M, N, K):
         assert float((C[M:] - 3.0).abs().max()) == 0.0 and float((C[:, N:] - 3.0).abs().max()) == 0.0
 
 
+# fp32 products on tiles of 16, 32 and 64, cut in both directions, with 16-byte loads (all extents multiples of 4) and without,
+# fewer steps of 16 k than waves and a ragged last step, and leading dimensions past 32-bit offsets (the plain kernel).
+# Bound: K + 1 roundings of 2^-24 on sums of magnitudes.
+@pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (16, 16, 4, 0), (17, 20, 15, 3), (130, 36, 68, 4), (200, 500, 200, 0), (201, 499, 77, 1),
+                                       (1000, 1100, 132, 0), (1001, 1023, 67, 2), (8, 8, 16, 1 << 24)])
+def test_gemm_fp32_tiles_of_every_size(M, N, K, pad):
+    nt = q(RNG.standard_normal((M, K)), FP32), q(RNG.standard_normal((N, K)), FP32)
+    r = q(RNG.standard_normal((M, N)), FP32)
+    ldc = N + min(pad, 5)
+    for layout in (B.GEMM_NT, B.GEMM_TN):
+        ops, lds = [], []
+        for x in nt:
+            x = x if layout == B.GEMM_NT else np.ascontiguousarray(x.T)
+            t = torch.full((x.shape[0], x.shape[1] + pad), float("nan"), dtype=torch.float32, device="cuda")   # what lies between rows is never used
+            t[:, :x.shape[1]] = dev(x, FP32)
+            ops.append(t)
+            lds.append(t.shape[1])
+        ref, mag = nt[0] @ nt[1].T, np.abs(nt[0]) @ np.abs(nt[1]).T
+        for epi, add in ((B.EPI_STORE, 0.0), (B.EPI_RESID, r), (B.EPI_ACCUM, 3.0), (3, 0.0)):
+            C = torch.full((M + 1, ldc), 3.0, dtype=torch.float32, device="cuda")
+            R = torch.full((M + 1, ldc), 9.0, dtype=torch.float32, device="cuda")
+            R[:M, :N] = dev(r, FP32)
+            ok(lib().optstage_op_gemm(FP32, layout, epi, ops[0].data_ptr(), ops[1].data_ptr(), C.data_ptr(), R.data_ptr(), M, N, K, lds[0], lds[1], ldc, stream()))
+            torch.cuda.synchronize()
+            bound = (K + 1) * 2.0 ** -24 * (mag + 3.0 + np.abs(r))
+            assert np.all(np.abs(host(C)[:M, :N] - (ref + add)) <= bound), (layout, epi)
+            assert float((C[M:] - 3.0).abs().max()) == 0.0 and (ldc == N or float((C[:, N:] - 3.0).abs().max()) == 0.0)
+        del ops
+
+
 def test_gemm_with_rows_further_apart_than_a_tile_can_address():
     """Leading dimensions of 2^23 elements: the kernel that stages its tiles through registers."""
     ld, n, k = 1 << 23, 16, 72
