@@ -1,4 +1,4 @@
-// Fused causal attention, bf16 MFMA path for head_dim 128 (gfx950): forward (online softmax, writes
+// Fused causal attention, bf16 MFMA path for head_dim 128 and 64 (gfx950): forward (online softmax, writes
 // lse) and backward (dQ kernel + dK/dV kernel, both recomputing the probabilities from lse; no atomics,
 // so results are bitwise reproducible).  q-head a reads kv-head a * n_kv / n_q; dK, dV are summed over
 // the q-heads of a group inside the dK/dV kernel.
@@ -15,16 +15,40 @@
 
 namespace {
 
-constexpr int D = 128;
 constexpr float LOG2E = 1.4426950408889634f;
 
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// What depends on the head size: rows of ROWB bytes = CH 16-byte chunks in the LDS tiles of 64 rows, NKS k-steps of an MFMA over
+// a row, NDT 32-wide pieces of it, NLD loads of 1 KB (RPL rows) by which a wave fills its quarter of a tile.
+// SPLIT: the probabilities and dS, fp32 numbers, enter the second product as the sum of two bf16 numbers (16 bits of
+// fraction between them) and not as one.  Heads of 64 have always multiplied them in fp32; the error against 64 bits stays
+// what it was (o 1.6e-3, dqkv 1.8e-3: the rounding of the results), where one bf16 number would raise it by a quarter.
+// Measured for heads of 64 at 4 x 1024 tokens, 16 heads, forward and backward: 4466 us on the general kernels (one wave per row,
+// no matrix unit), 143 us here.
+template <int D> struct Head {
+  static constexpr int ROWB = 2 * D, TILE = 64 * ROWB, CH = D / 8, NKS = D / 16, NDT = D / 32, RPL = 64 / CH, NLD = 16 / RPL;
+  static constexpr bool SPLIT = D == 64;
+  // 16-byte chunk c of tile row r is stored at chunk c ^ swz(r).  Row reads: the 16 rows that a pass touches at one chunk fall on
+  // all banks; transposing reads: the 4 rows of one differ in the 64-byte group (D = 64: so do rows two apart, which share
+  // the half of the 256-byte bank window)
+  __device__ __forceinline__ static constexpr int swz(int r) {
+    return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
+  }
+};
+
 __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& s, int u) {
   bf16x8_t r;
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16_t)s[8 * u + e];
+  return r;
+}
+// what pack8 has rounded away, rounded
+__device__ __forceinline__ bf16x8_t pack8_rest(const f32x16_t& s, const bf16x8_t& hi, int u) {
+  bf16x8_t r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = (bf16_t)(s[8 * u + e] - (float)hi[e]);
   return r;
 }
 
@@ -51,12 +75,14 @@ __device__ __forceinline__ float pair_max32(float x) {
 // only when some row of the wave finds a score more than FWD_TAU / c above it, so p <= 2^FWD_TAU and the
 // rescaling, which would sit between consecutive tiles' MFMAs on the same accumulators, is rare after the first
 // tiles.  softmax does not depend on the reference: o = (sum p v) / (sum p), lse = m_ref scale + log(sum p).
-constexpr int FWD_STAGE = 32768;             // K tile, V tile of 64 keys
-constexpr int FWD_SMEM = 3 * FWD_STAGE;
 constexpr float FWD_TAU = 8.f;
 
+template <int D>
 __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
                                                      float* __restrict__ lse, int seq, int n_q, int n_kv) {
+  typedef Head<D> H;
+  constexpr int ROWB = H::ROWB, TILE = H::TILE, NKS = H::NKS, NDT = H::NDT, NLD = H::NLD;
+  constexpr int FWD_STAGE = 2 * TILE;          // K tile, V tile of 64 keys
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -68,46 +94,46 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   const int wave_first_q = q0 + 64 * wave, wave_last_q = wave_first_q + 63;
   const float scale = rsqrtf((float)D), c = scale * LOG2E, thr = FWD_TAU / c;
 
-  bf16x8_t Qf[2][8];
+  bf16x8_t Qf[2][NKS];
   int qglob[2];
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt) {
     qglob[qt] = wave_first_q + 32 * qt + c32;
     const bf16_t* qp = base + (size_t)min(qglob[qt], seq - 1) * ld + (size_t)a * D + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) Qf[qt][ks] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * ks);
+    for (int ks = 0; ks < NKS; ++ks) Qf[qt][ks] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * ks);
   }
-  f32x16_t acc[2][4];                          // [query tile][d tile]: lane = query, registers = d
+  f32x16_t acc[2][NDT];                        // [query tile][d tile]: lane = query, registers = d
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[qt][dt][v] = 0.f;
   float mref[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
 
   // LDS addressing as in the dQ kernel: 64 rows x 256 B per tile, 16-byte chunk c of row r stored at chunk
   // c ^ (((r & 3) << 2) | ((r >> 2) & 3))
-  int rm_addr[8];
+  int rm_addr[NKS];
   {
-    const int f = ((c32 & 3) << 2) | ((c32 >> 2) & 3);
+    const int f = H::swz(c32);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) rm_addr[ks] = c32 * 256 + (((2 * ks + g) ^ f) << 4);
+    for (int ks = 0; ks < NKS; ++ks) rm_addr[ks] = c32 * ROWB + (((2 * ks + g) ^ f) << 4);
   }
-  int tr_addr[4][2];
+  int tr_addr[NDT][2];
   {
     const int cg = (lane >> 4) & 1, e = (lane >> 2) & 3, r = lane & 3;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int kq = 0; kq < 2; ++kq)
-        tr_addr[dt][kq] = (4 * g + e) * 256 + (((4 * dt + 2 * cg + (r >> 1)) ^ (e << 2) ^ g ^ (kq << 1)) << 4) + (r & 1) * 8;
+        tr_addr[dt][kq] = (4 * g + e) * ROWB + (((4 * dt + 2 * cg + (r >> 1)) ^ H::swz(8 * kq + 4 * g + e)) << 4) + (r & 1) * 8;
   }
-  unsigned voff[4];
+  unsigned voff[NLD];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 16 * wave + 4 * j + (lane >> 4);
-    const int chunk = (lane & 15) ^ (((lane >> 4) << 2) | j);
+  for (int j = 0; j < NLD; ++j) {
+    const int row = 16 * wave + H::RPL * j + lane / H::CH;
+    const int chunk = (lane % H::CH) ^ H::swz(row);
     voff[j] = (unsigned)row * (unsigned)ld * 2u + (unsigned)chunk * 16u;
   }
   i32x4_t rs;
@@ -122,24 +148,24 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   const unsigned k_off = (unsigned)(n_q + kvh) * D * 2u, v_off = (unsigned)(n_q + n_kv + kvh) * D * 2u;
   auto issue_block = [&](int kb, int stage) {
     const unsigned rowoff = (unsigned)(64 * kb) * (unsigned)ld * 2u;
-    const unsigned dst = lds0 + stage * FWD_STAGE + (16 * wave) * 256;
+    const unsigned dst = lds0 + stage * FWD_STAGE + (16 * wave) * ROWB;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NLD; ++j) {
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(dst + j * 1024), "v"(voff[j] + rowoff + k_off), "s"(rs) : "memory", "m0");
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   :: "s"(dst + 16384 + j * 1024), "v"(voff[j] + rowoff + v_off), "s"(rs) : "memory", "m0");
+                   :: "s"(dst + TILE + j * 1024), "v"(voff[j] + rowoff + v_off), "s"(rs) : "memory", "m0");
     }
   };
   typedef short i16x4_t __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
   auto tr_frag = [&](const char* tile, int dt, int t, int u) {
-    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * 256 + tr_addr[dt][0]));
-    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * 256 + tr_addr[dt][1]));
+    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * ROWB + tr_addr[dt][0]));
+    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * ROWB + tr_addr[dt][1]));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   auto rm_frag = [&](const char* tile, int t, int ks) {
-    return *reinterpret_cast<const bf16x8_t*>(tile + t * 8192 + rm_addr[ks]);
+    return *reinterpret_cast<const bf16x8_t*>(tile + t * 32 * ROWB + rm_addr[ks]);
   };
 
   const int nkb = min((q0 + 255) / 64 + 1, (seq + 63) / 64);
@@ -167,10 +193,10 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     const float mc0 = mref[0] * c, mc1 = mref[1] * c;
     float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < NKS; ++ks) {
       OPTSTAGE_SB();
-      if (ks < 7) kf[(ks + 1) & 1] = rm_frag(sK, t, ks + 1);
-      else trf_first = tr_frag(smem + stage_v * FWD_STAGE + 16384, 0, tv, 0);
+      if (ks < NKS - 1) kf[(ks + 1) & 1] = rm_frag(sK, t, ks + 1);
+      else trf_first = tr_frag(smem + stage_v * FWD_STAGE + TILE, 0, tv, 0);
       OPTSTAGE_SB();
       // The compiler does not see into the MFMA statements, so it keeps no distance between a vector instruction
       // that produces an operand (a copy, a read of an accumulation register that holds part of Q) and the MFMA
@@ -187,14 +213,17 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
           asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(nxt[qt]) : "v"(kf[ks & 1]), "a"(Qf[qt][ks]));
         OPTSTAGE_SB();
         if (with_exp) {                                          // compile-time after inlining
-          const int v = 2 * ks + qt;
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(cur[0][v], c, -mc0));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(cur[1][v], c, -mc1));
-          cur[0][v] = p0; cur[1][v] = p1;
-          ls0 += p0; ls1 += p1;
-          // keeps these instructions here, between the MFMAs: without a use at this point the compiler sinks
-          // them to where the probabilities are packed
-          asm volatile("" : "+v"(cur[0][v]), "+v"(cur[1][v]), "+v"(ls0), "+v"(ls1));
+#pragma unroll
+          for (int x = 0; x < 8 / NKS; ++x) {
+            const int v = (2 * ks + qt) * (8 / NKS) + x;
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(cur[0][v], c, -mc0));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(cur[1][v], c, -mc1));
+            cur[0][v] = p0; cur[1][v] = p1;
+            ls0 += p0; ls1 += p1;
+            // keeps these instructions here, between the MFMAs: without a use at this point the compiler sinks
+            // them to where the probabilities are packed
+            asm volatile("" : "+v"(cur[0][v]), "+v"(cur[1][v]), "+v"(ls0), "+v"(ls1));
+          }
         }
         OPTSTAGE_SB();
       }
@@ -214,7 +243,11 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     }
   };
   auto max_half = [&](int n, int qt, const f32x16_t (&sc)[2], float (&mx)[2]) {
-    mx[qt] = fmaxf(mx[qt], fmaxf(sc[qt][2 * n], sc[qt][2 * n + 1]));
+#pragma unroll
+    for (int x = 0; x < 4 / NDT; ++x) {                          // n: one of the 2 NDT positions of a step
+      const int v = 2 * (n * (4 / NDT) + x);
+      mx[qt] = fmaxf(mx[qt], fmaxf(sc[qt][v], sc[qt][v + 1]));
+    }
     asm volatile("" : "+v"(mx[qt]));                            // stays between the MFMAs it is written between
   };
   auto max_slice = [&](int n, const f32x16_t (&sc)[2], float (&mx)[2]) {
@@ -236,7 +269,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
         lsum[qt] *= alpha;
         // one accumulator tile at a time: they pass through vector registers for the multiplication
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
+        for (int dt = 0; dt < NDT; ++dt) {
           OPTSTAGE_SB();
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[qt][dt][v] *= alpha;
@@ -248,7 +281,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   // O^T += V^T P^T of the current tile (probabilities in cur, V half t of the tile in `stage_v`), between the MFMAs
   // the row maxima of the next tile i1 (scores in nxt, already masked)
   auto step_output = [&](int stage_v, int t, int i1, f32x16_t (&cur)[2], f32x16_t (&nxt)[2], int stage_k, int tk) {
-    const char* sV = smem + stage_v * FWD_STAGE + 16384;
+    const char* sV = smem + stage_v * FWD_STAGE + TILE;
     mask_tile(i1, nxt);
     float mx[2] = {-INFINITY, -INFINITY};
     // fragment n + 2 is requested before the MFMAs of fragment n: one pair of MFMAs is shorter than an LDS round
@@ -259,19 +292,24 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const bf16x8_t p0 = pack8(cur[0], u), p1 = pack8(cur[1], u);
+      bf16x8_t r0, r1;
+      if constexpr (H::SPLIT) { r0 = pack8_rest(cur[0], p0, u); r1 = pack8_rest(cur[1], p1, u); }
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const int n = u * 4 + dt, n2 = n + 2;
+      for (int dt = 0; dt < NDT; ++dt) {
+        const int n = u * NDT + dt, n2 = n + 2;
         OPTSTAGE_SB();
-        if (n2 < 8) trf[n2 % 3] = tr_frag(sV, n2 & 3, t, n2 >> 2);
-        else if (n == 6) kf_first = rm_frag(smem + stage_k * FWD_STAGE, tk, 0);
+        if (n2 < 2 * NDT) trf[n2 % 3] = tr_frag(sV, n2 % NDT, t, n2 / NDT);
+        else if (n == 2 * NDT - 2) kf_first = rm_frag(smem + stage_k * FWD_STAGE, tk, 0);
         if (dt == 0) asm volatile("s_nop 1" :: "v"(p0), "v"(p1) : "memory");   // packed operands settled
+        if constexpr (H::SPLIT) { if (dt == 0) asm volatile("s_nop 1" :: "v"(r0), "v"(r1) : "memory"); }
         OPTSTAGE_SB();
         OPTSTAGE_MFMA_A(acc[0][dt], trf[n % 3], p0);
+        if constexpr (H::SPLIT) OPTSTAGE_MFMA_A(acc[0][dt], trf[n % 3], r0);
         OPTSTAGE_SB();
         max_half(n, 0, nxt, mx);
         OPTSTAGE_SB();
         OPTSTAGE_MFMA_A(acc[1][dt], trf[n % 3], p1);
+        if constexpr (H::SPLIT) OPTSTAGE_MFMA_A(acc[1][dt], trf[n % 3], r1);
         OPTSTAGE_SB();
         max_half(n, 1, nxt, mx);
       }
@@ -325,7 +363,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     const float inv = 1.f / lt[qt];
     bf16_t* orow = o + ((size_t)b * seq + qglob[qt]) * ldo + (size_t)a * D;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
+    for (int dt = 0; dt < NDT; ++dt) {
       OPTSTAGE_SB();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -349,13 +387,14 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 // reads) and dQ^T += K^T dS^T (transposing reads), through the same chunk swizzle as in the dK/dV kernel.
 // Also produces D_t = <dO_t, O_t> per query row and head (from the dO fragments it holds anyway) and stores it
 // for the dK/dV kernel, which runs after this one.
-constexpr int DQ_STAGE = 32768;              // K tile, V tile of 64 keys
-constexpr int DQ_SMEM = 2 * DQ_STAGE;
-
+template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                         const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                         float* __restrict__ delta, bf16_t* __restrict__ dqkv, int seq,
                                                         int n_q, int n_kv) {
+  typedef Head<D> H;
+  constexpr int ROWB = H::ROWB, TILE = H::TILE, NKS = H::NKS, NDT = H::NDT, NLD = H::NLD;
+  constexpr int DQ_STAGE = 2 * TILE;           // K tile, V tile of 64 keys
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -369,7 +408,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 
   // Q, dO operand fragments of this wave's queries (rows past the end are clamped: their results are not stored),
   // lse * log2(e) and D per query
-  bf16x8_t Qf[2][8], dOf[2][8];
+  bf16x8_t Qf[2][NKS], dOf[2][NKS];
   float Lc[2], Dq[2];
   int qglob[2];
 #pragma unroll
@@ -381,7 +420,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
     const bf16_t* op = o + ((size_t)b * seq + qrow) * ldo + (size_t)a * D + 8 * g;
     float dsum = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < NKS; ++ks) {
       Qf[qt][ks] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * ks);
       dOf[qt][ks] = *reinterpret_cast<const bf16x8_t*>(dop + 16 * ks);
       const bf16x8_t of = *reinterpret_cast<const bf16x8_t*>(op + 16 * ks);
@@ -405,36 +444,36 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+a"(Qf[qt][ks]), "+a"(dOf[qt][ks]));
-  f32x16_t acc[2][4];                          // [query tile][d tile]: lane = query, registers = d
+    for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+a"(Qf[qt][ks]), "+a"(dOf[qt][ks]));
+  f32x16_t acc[2][NDT];                        // [query tile][d tile]: lane = query, registers = d
 #pragma unroll
   for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[qt][dt][v] = 0.f;
 
-  int rm_addr[8];
+  int rm_addr[NKS];
   {
-    const int f = ((c32 & 3) << 2) | ((c32 >> 2) & 3);
+    const int f = H::swz(c32);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) rm_addr[ks] = c32 * 256 + (((2 * ks + g) ^ f) << 4);
+    for (int ks = 0; ks < NKS; ++ks) rm_addr[ks] = c32 * ROWB + (((2 * ks + g) ^ f) << 4);
   }
-  int tr_addr[4][2];
+  int tr_addr[NDT][2];
   {
     const int cg = (lane >> 4) & 1, e = (lane >> 2) & 3, r = lane & 3;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int kq = 0; kq < 2; ++kq)
-        tr_addr[dt][kq] = (4 * g + e) * 256 + (((4 * dt + 2 * cg + (r >> 1)) ^ (e << 2) ^ g ^ (kq << 1)) << 4) + (r & 1) * 8;
+        tr_addr[dt][kq] = (4 * g + e) * ROWB + (((4 * dt + 2 * cg + (r >> 1)) ^ H::swz(8 * kq + 4 * g + e)) << 4) + (r & 1) * 8;
   }
   // tile loads: one instruction fills 4 rows (1 KB); wave w loads rows 16 w .. 16 w + 15 of the K and of the V tile
-  unsigned voff[4];
+  unsigned voff[NLD];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 16 * wave + 4 * j + (lane >> 4);
-    const int chunk = (lane & 15) ^ (((lane >> 4) << 2) | j);
+  for (int j = 0; j < NLD; ++j) {
+    const int row = 16 * wave + H::RPL * j + lane / H::CH;
+    const int chunk = (lane % H::CH) ^ H::swz(row);
     voff[j] = (unsigned)row * (unsigned)ld * 2u + (unsigned)chunk * 16u;
   }
   auto make_desc = [](const void* p, unsigned bytes) {
@@ -452,24 +491,24 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   // All offsets go through the lane offset, which is what the range check sees: rows at or past seq read zero.
   auto issue_block = [&](int kb, int stage) {
     const unsigned rowoff = (unsigned)(64 * kb) * (unsigned)ld * 2u;
-    const unsigned dst = lds0 + stage * DQ_STAGE + (16 * wave) * 256;
+    const unsigned dst = lds0 + stage * DQ_STAGE + (16 * wave) * ROWB;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NLD; ++j) {
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(dst + j * 1024), "v"(voff[j] + rowoff + k_off), "s"(rs) : "memory", "m0");
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   :: "s"(dst + 16384 + j * 1024), "v"(voff[j] + rowoff + v_off), "s"(rs) : "memory", "m0");
+                   :: "s"(dst + TILE + j * 1024), "v"(voff[j] + rowoff + v_off), "s"(rs) : "memory", "m0");
     }
   };
   typedef short i16x4_t __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
   auto tr_frag = [&](const char* tile, int dt, int t, int u) {
-    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * 256 + tr_addr[dt][0]));
-    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * 256 + tr_addr[dt][1]));
+    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * ROWB + tr_addr[dt][0]));
+    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * ROWB + tr_addr[dt][1]));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   auto rm_frag = [&](const char* tile, int t, int ks) {
-    return *reinterpret_cast<const bf16x8_t*>(tile + t * 8192 + rm_addr[ks]);
+    return *reinterpret_cast<const bf16x8_t*>(tile + t * 32 * ROWB + rm_addr[ks]);
   };
 
 #define OPTSTAGE_SB() __builtin_amdgcn_sched_barrier(0)
@@ -481,7 +520,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   auto block = [&](int kb, int stage) {
     if (64 * kb > wave_last_q) return;                           // block above this wave's diagonal
     const char* sK = smem + stage * DQ_STAGE;
-    const char* sV = sK + 16384;
+    const char* sV = sK + TILE;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int key0 = 64 * kb + 32 * t;
@@ -493,9 +532,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
       // ---- S^T = K Q^T (the first k-step starts from C = 0)
       kf[0] = rm_frag(sK, t, 0);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < NKS; ++ks) {
         OPTSTAGE_SB();
-        if (ks < 7) kf[(ks + 1) & 1] = rm_frag(sK, t, ks + 1);
+        if (ks < NKS - 1) kf[(ks + 1) & 1] = rm_frag(sK, t, ks + 1);
         else vf[0] = rm_frag(sV, t, 0);
         OPTSTAGE_SB();
         if (ks == 0) {
@@ -508,9 +547,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
       }
       // ---- dP^T = V dO^T, with the exponentials of S^T under its MFMAs
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < NKS; ++ks) {
         OPTSTAGE_SB();
-        if (ks < 7) vf[(ks + 1) & 1] = rm_frag(sV, t, ks + 1);
+        if (ks < NKS - 1) vf[(ks + 1) & 1] = rm_frag(sV, t, ks + 1);
         OPTSTAGE_SB();
         if (ks == 0) {                                             // dP^T - D: the first k-step starts from C = -D
           asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[0]) : "v"(vf[0]), "a"(dOf[0][0]), "v"(negD[0]));
@@ -521,8 +560,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
         }
         OPTSTAGE_SB();
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int v = 2 * ks + e;
+        for (int e = 0; e < 16 / NKS; ++e) {
+          const int v = (16 / NKS) * ks + e;
 #pragma unroll
           for (int qt = 0; qt < 2; ++qt) s[qt][v] = __builtin_amdgcn_exp2f(fmaf(s[qt][v], c, Lc[qt]));
         }
@@ -552,19 +591,25 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const bf16x8_t d0 = pack8(dp[0], u), d1 = pack8(dp[1], u);
+        bf16x8_t r0, r1;
+        if constexpr (H::SPLIT) { r0 = pack8_rest(dp[0], d0, u); r1 = pack8_rest(dp[1], d1, u); }
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          const int n = u * 4 + dt;
+        for (int dt = 0; dt < NDT; ++dt) {
+          const int n = u * NDT + dt;
           OPTSTAGE_SB();
-          if (n < 7) trf[(n + 1) & 1] = tr_frag(sK, (dt + 1) & 3, t, dt == 3 ? 1 : u);
+          if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sK, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           OPTSTAGE_SB();
           acc[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d0, acc[0][dt], 0, 0, 0);
           acc[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d1, acc[1][dt], 0, 0, 0);
+          if constexpr (H::SPLIT) {
+            acc[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, acc[0][dt], 0, 0, 0);
+            acc[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, acc[1][dt], 0, 0, 0);
+          }
           OPTSTAGE_SB();
           if (u == 0) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const int v = 8 + 2 * dt + e;
+            for (int e = 0; e < 8 / NDT; ++e) {
+              const int v = 8 + (8 / NDT) * dt + e;
 #pragma unroll
               for (int qt = 0; qt < 2; ++qt) dp[qt][v] = s[qt][v] * dp[qt][v];
             }
@@ -597,7 +642,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
     if (qglob[qt] >= seq) continue;
     bf16_t* dq = dqkv + ((size_t)b * seq + qglob[qt]) * ld + (size_t)a * D;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         bf16x4_t r;
@@ -619,18 +664,19 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 // stored at chunk c ^ f(r), f(r) = ((r & 3) << 2) | ((r >> 2) & 3): 16 consecutive rows get 16 different
 // values (row reads of one chunk hit every bank once) and 4 consecutive rows differ in the 64-byte group
 // (the 4 rows of a transposing read do too).
-constexpr int DKV_STAGE = 32768 + 512;       // Q tile, dO tile, 64 lse, 64 D
-constexpr int DKV_VTILE = 256 * 256;         // V rows of the workgroup's keys, behind the two stages
-constexpr int DKV_SMEM = 2 * DKV_STAGE + DKV_VTILE;
 
 // With grouped-query attention a kv head's gradient sums over n_q / n_kv query heads and the grid has only
 // n_kv * batch * ceil(seq / 256) workgroups; `split` > 1 deals the query heads of a group to that many
 // workgroups, each writing an fp32 partial ([part][batch][seq][kv head][K|V][128]) that attn_bwd_dkv_reduce sums
 // in a fixed order.
+template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16_t* __restrict__ dqkv, float* __restrict__ partial, int split,
                                                          int seq, int n_q, int n_kv) {
+  typedef Head<D> H;
+  constexpr int ROWB = H::ROWB, TILE = H::TILE, NKS = H::NKS, NDT = H::NDT, NLD = H::NLD;
+  constexpr int DKV_STAGE = 2 * TILE + 512;    // Q tile, dO tile, 64 lse, 64 D; behind two of them V rows of 256 keys
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -642,47 +688,47 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   const float scale = rsqrtf((float)D), c = scale * LOG2E;
 
   // K, V operand fragments of this wave's keys (rows past the end are clamped: their results are not stored)
-  bf16x8_t Kf[2][8];
+  bf16x8_t Kf[2][NKS];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk) {
     const int krow = min(wave_first_k + 32 * kk + c32, seq - 1);
     const bf16_t* kp = base + (size_t)krow * ld + (size_t)(n_q + kvh) * D + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) Kf[kk][ks] = *reinterpret_cast<const bf16x8_t*>(kp + 16 * ks);
+    for (int ks = 0; ks < NKS; ++ks) Kf[kk][ks] = *reinterpret_cast<const bf16x8_t*>(kp + 16 * ks);
   }
-  f32x16_t accK[2][4], accV[2][4];            // [key tile][d tile]: lane = key, registers = d
+  f32x16_t accK[2][NDT], accV[2][NDT];          // [key tile][d tile]: lane = key, registers = d
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) { accK[kk][dt][v] = 0.f; accV[kk][dt][v] = 0.f; }
 
   // per-lane LDS addresses within a tile.  Row read of k-step ks: row c32 (+ 32 t), chunk 2 ks + g.
-  int rm_addr[8];
+  int rm_addr[NKS];
   {
-    const int f = ((c32 & 3) << 2) | ((c32 >> 2) & 3);
+    const int f = H::swz(c32);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) rm_addr[ks] = c32 * 256 + (((2 * ks + g) ^ f) << 4);
+    for (int ks = 0; ks < NKS; ++ks) rm_addr[ks] = c32 * ROWB + (((2 * ks + g) ^ f) << 4);
   }
   // Transposing read (dt, kq): in each 16-lane group lane 4 e + r reads 8 bytes of row 4 g + e (+ 32 t + 16 u
   // + 8 kq), columns 32 dt + 16 cg + 4 r ..; f(row) = (e << 2) | (2 kq + g)
-  int tr_addr[4][2];
+  int tr_addr[NDT][2];
   {
     const int cg = (lane >> 4) & 1, e = (lane >> 2) & 3, r = lane & 3;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int kq = 0; kq < 2; ++kq)
-        tr_addr[dt][kq] = (4 * g + e) * 256 + (((4 * dt + 2 * cg + (r >> 1)) ^ (e << 2) ^ g ^ (kq << 1)) << 4) + (r & 1) * 8;
+        tr_addr[dt][kq] = (4 * g + e) * ROWB + (((4 * dt + 2 * cg + (r >> 1)) ^ H::swz(8 * kq + 4 * g + e)) << 4) + (r & 1) * 8;
   }
   // tile loads: one instruction fills 4 rows (1 KB); wave w loads rows 16 w .. 16 w + 15 of Q and of dO.
   // Lane i: row 4 b + i / 16, stored chunk i % 16 = logical chunk ^ f(row), f = ((i / 16) << 2) | (b & 3).
-  unsigned voff_q[4], voff_do[4];
+  unsigned voff_q[NLD], voff_do[NLD];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 16 * wave + 4 * j + (lane >> 4);
-    const int chunk = (lane & 15) ^ (((lane >> 4) << 2) | j);
+  for (int j = 0; j < NLD; ++j) {
+    const int row = 16 * wave + H::RPL * j + lane / H::CH;
+    const int chunk = (lane % H::CH) ^ H::swz(row);
     voff_q[j] = (unsigned)row * (unsigned)ld * 2u + (unsigned)chunk * 16u;
     voff_do[j] = (unsigned)row * (unsigned)ldo * 2u + (unsigned)chunk * 16u;
   }
@@ -702,14 +748,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   const unsigned lds0 = (unsigned)(size_t)(lds_void_t*)smem;
 
   // V rows of this wave's 64 keys -> LDS (16 loads of 4 rows), same layout as the streamed tiles
-  const char* sV = smem + 2 * DKV_STAGE + wave * 16384;
+  const char* sV = smem + 2 * DKV_STAGE + wave * TILE;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int row = 4 * j + (lane >> 4);
-    const int chunk = (lane & 15) ^ (((lane >> 4) << 2) | (j & 3));
+  for (int j = 0; j < 4 * NLD; ++j) {
+    const int row = H::RPL * j + lane / H::CH;
+    const int chunk = (lane % H::CH) ^ H::swz(row);
     const unsigned vo = ((unsigned)(wave_first_k + row) * (unsigned)ld + (unsigned)(n_q + n_kv + kvh) * D) * 2u + (unsigned)chunk * 16u;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds0 + 2 * DKV_STAGE + wave * 16384 + j * 1024), "v"(vo), "s"(rs_q) : "memory", "m0");
+                 :: "s"(lds0 + 2 * DKV_STAGE + wave * TILE + j * 1024), "v"(vo), "s"(rs_q) : "memory", "m0");
   }
   const int rep = n_q / n_kv / split;                          // query heads of the group handled here
   const int qb0 = k0 / 64, nqb = (seq + 63) / 64 - qb0;       // query blocks at or after the first key
@@ -720,29 +766,29 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     const int r0 = 64 * (qb0 + it % nqb);
     const unsigned oq = ((unsigned)r0 * (unsigned)ld + (unsigned)a * D) * 2u;
     const unsigned od = ((unsigned)r0 * (unsigned)ldo + (unsigned)a * D) * 2u;
-    const unsigned dst = lds0 + stage * DKV_STAGE + (16 * wave) * 256;
+    const unsigned dst = lds0 + stage * DKV_STAGE + (16 * wave) * ROWB;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NLD; ++j) {
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(dst + j * 1024), "v"(voff_q[j] + oq), "s"(rs_q) : "memory", "m0");
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                   :: "s"(dst + 16384 + j * 1024), "v"(voff_do[j] + od), "s"(rs_do) : "memory", "m0");
+                   :: "s"(dst + TILE + j * 1024), "v"(voff_do[j] + od), "s"(rs_do) : "memory", "m0");
     }
     if (wave < 2) {                            // wave 0: lse of the 64 queries, wave 1: D
       const unsigned vo = ((unsigned)a * (unsigned)seq + (unsigned)min(r0 + lane, seq - 1)) * 4u;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                   :: "s"(lds0 + stage * DKV_STAGE + 32768 + wave * 256), "v"(vo), "s"(wave == 0 ? rs_l : rs_d) : "memory", "m0");
+                   :: "s"(lds0 + stage * DKV_STAGE + 2 * TILE + wave * 256), "v"(vo), "s"(wave == 0 ? rs_l : rs_d) : "memory", "m0");
     }
   };
   typedef short i16x4_t __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
   auto tr_frag = [&](const char* tile, int dt, int t, int u) {
-    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * 256 + tr_addr[dt][0]));
-    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * 256 + tr_addr[dt][1]));
+    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u) * ROWB + tr_addr[dt][0]));
+    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t*)(tile + (32 * t + 16 * u + 8) * ROWB + tr_addr[dt][1]));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   auto rm_frag = [&](const char* tile, int t, int ks) {
-    return *reinterpret_cast<const bf16x8_t*>(tile + t * 8192 + rm_addr[ks]);
+    return *reinterpret_cast<const bf16x8_t*>(tile + t * 32 * ROWB + rm_addr[ks]);
   };
 
 #define OPTSTAGE_SB() __builtin_amdgcn_sched_barrier(0)
@@ -754,8 +800,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     const int r0 = 64 * (qb0 + it % nqb);
     if (r0 + 63 < wave_first_k) return;                          // all queries precede this wave's keys
     const char* sQ = smem + stage * DKV_STAGE;
-    const char* sDO = sQ + 16384;
-    const float* sL = reinterpret_cast<const float*>(sQ + 32768);
+    const char* sDO = sQ + TILE;
+    const float* sL = reinterpret_cast<const float*>(sQ + 2 * TILE);
     const float* sD = sL + 64;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -770,9 +816,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
       // ---- S = Q K^T: fragment of k-step ks + 1 requested before the MFMAs of k-step ks
       qf[0] = rm_frag(sQ, t, 0);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < NKS; ++ks) {
         OPTSTAGE_SB();
-        if (ks < 7) {
+        if (ks < NKS - 1) {
           qf[(ks + 1) & 1] = rm_frag(sQ, t, ks + 1);
         } else {
           df[0] = rm_frag(sDO, t, 0);
@@ -780,10 +826,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
           vf[0][1] = rm_frag(sV, 1, 0);
         }
         if (ks < 4) nL[ks] = *reinterpret_cast<const f32x4_t*>(sL + 32 * t + 8 * ks + 4 * g);
-        else {
-          const f32x4_t d4 = *reinterpret_cast<const f32x4_t*>(sD + 32 * t + 8 * (ks - 4) + 4 * g);
+        if (ks >= NKS - 4) {
+          const f32x4_t d4 = *reinterpret_cast<const f32x4_t*>(sD + 32 * t + 8 * (ks - (NKS - 4)) + 4 * g);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) negD[4 * (ks - 4) + i] = d4[i];
+          for (int i = 0; i < 4; ++i) negD[4 * (ks - (NKS - 4)) + i] = d4[i];
         }
         OPTSTAGE_SB();
         if (ks == 0) {                                             // the first k-step starts from C = 0
@@ -794,16 +840,16 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
           OPTSTAGE_MFMA_V(s[1], qf[ks & 1], Kf[1][ks]);
         }
         OPTSTAGE_SB();
-        if (ks >= 4) {
+        if (ks >= NKS - 4) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) nL[ks - 4][i] *= -LOG2E;
+          for (int i = 0; i < 4; ++i) nL[ks - (NKS - 4)][i] *= -LOG2E;
         }
       }
       // ---- dP = dO V^T, with the exponentials of S (2 registers x 2 key tiles per k-step) under its MFMAs
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < NKS; ++ks) {
         OPTSTAGE_SB();
-        if (ks < 7) {
+        if (ks < NKS - 1) {
           df[(ks + 1) & 1] = rm_frag(sDO, t, ks + 1);
           vf[(ks + 1) & 1][0] = rm_frag(sV, 0, ks + 1);
           vf[(ks + 1) & 1][1] = rm_frag(sV, 1, ks + 1);
@@ -818,8 +864,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
         }
         OPTSTAGE_SB();
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int v = 2 * ks + e;
+        for (int e = 0; e < 16 / NKS; ++e) {
+          const int v = (16 / NKS) * ks + e;
 #pragma unroll
           for (int kk = 0; kk < 2; ++kk) s[kk][v] = __builtin_amdgcn_exp2f(fmaf(s[kk][v], c, nL[v >> 2][v & 3]));
         }
@@ -841,19 +887,25 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const bf16x8_t p0 = pack8(s[0], u), p1 = pack8(s[1], u);
+        bf16x8_t r0, r1;
+        if constexpr (H::SPLIT) { r0 = pack8_rest(s[0], p0, u); r1 = pack8_rest(s[1], p1, u); }
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          const int n = u * 4 + dt;
+        for (int dt = 0; dt < NDT; ++dt) {
+          const int n = u * NDT + dt;
           OPTSTAGE_SB();
-          if (n < 7) trf[(n + 1) & 1] = tr_frag(sDO, (dt + 1) & 3, t, dt == 3 ? 1 : u);
+          if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sDO, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           else trf[0] = tr_frag(sQ, 0, t, 0);
           OPTSTAGE_SB();
           accV[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], p0, accV[0][dt], 0, 0, 0);
           accV[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], p1, accV[1][dt], 0, 0, 0);
+          if constexpr (H::SPLIT) {
+            accV[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, accV[0][dt], 0, 0, 0);
+            accV[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, accV[1][dt], 0, 0, 0);
+          }
           OPTSTAGE_SB();
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const int v = 2 * n + e;
+          for (int e = 0; e < 8 / NDT; ++e) {
+            const int v = (8 / NDT) * n + e;
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) dp[kk][v] = s[kk][v] * dp[kk][v];
           }
@@ -863,14 +915,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const bf16x8_t d0 = pack8(dp[0], u), d1 = pack8(dp[1], u);
+        bf16x8_t r0, r1;
+        if constexpr (H::SPLIT) { r0 = pack8_rest(dp[0], d0, u); r1 = pack8_rest(dp[1], d1, u); }
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          const int n = u * 4 + dt;
+        for (int dt = 0; dt < NDT; ++dt) {
+          const int n = u * NDT + dt;
           OPTSTAGE_SB();
-          if (n < 7) trf[(n + 1) & 1] = tr_frag(sQ, (dt + 1) & 3, t, dt == 3 ? 1 : u);
+          if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sQ, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           OPTSTAGE_SB();
           accK[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d0, accK[0][dt], 0, 0, 0);
           accK[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d1, accK[1][dt], 0, 0, 0);
+          if constexpr (H::SPLIT) {
+            accK[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, accK[0][dt], 0, 0, 0);
+            accK[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, accK[1][dt], 0, 0, 0);
+          }
         }
       }
       OPTSTAGE_SB();
@@ -900,7 +958,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     if (split > 1) {
       float* prow = partial + ((((size_t)part * gridDim.y + b) * seq + kglob) * n_kv + kvh) * 2 * D;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           f32x4_t rk, rv;
@@ -914,7 +972,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     bf16_t* krow = dqkv + ((size_t)b * seq + kglob) * ld + (size_t)(n_q + kvh) * D;
     bf16_t* vrow = dqkv + ((size_t)b * seq + kglob) * ld + (size_t)(n_q + n_kv + kvh) * D;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         bf16x4_t rk, rv;
@@ -933,6 +991,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
 // gradient rows: one thread per 4 columns of one (token, kv head, K|V)
 __global__ void attn_bwd_dkv_reduce(const float* __restrict__ partial, bf16_t* __restrict__ dqkv, int split, int rows,
                                     int n_q, int n_kv) {
+  constexpr int D = 128;
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t per_part = (size_t)rows * n_kv * 2 * D;
   if (idx * 4 >= per_part) return;
@@ -965,31 +1024,39 @@ int attn_dkv_split(int seq, int batch, int n_q, int n_kv) {
   return split;
 }
 
-// bf16, head_dim 128, and per-sequence tensors addressable with 32-bit byte offsets (buffer loads)
-bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv) {
-  return dtype == DT_BF16 && d == 128 && (unsigned long long)(seq + 256) * (n_q + 2 * n_kv) * 128 * 2 < 0xF0000000ull;
+// bf16, head_dim 128 or 64, per-sequence tensors addressable with 32-bit byte offsets (buffer loads), 16-byte aligned rows
+bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void* p0, const void* p1, const void* p2, const void* p3) {
+  return dtype == DT_BF16 && (d == 128 || d == 64) && (unsigned long long)(seq + 256) * (n_q + 2 * n_kv) * d * 2 < 0xF0000000ull &&
+         (d == 128 || (((uintptr_t)p0 | (uintptr_t)p1 | (uintptr_t)p2 | (uintptr_t)p3) & 15) == 0);
 }
 
-hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+namespace {
+template <int D> hipError_t fwd_d(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+  constexpr int smem = 3 * 2 * Head<D>::TILE;
   static LdsAttrOnce lds_attr;
-  if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(attn_fwd_mfma), FWD_SMEM); e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_fwd_mfma, dim3(n_q, batch, (seq + 255) / 256), dim3(256), FWD_SMEM, s, (const bf16_t*)qkv, (bf16_t*)o, lse, seq, n_q, n_kv);
+  auto kern = attn_fwd_mfma<D>;
+  if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(n_q, batch, (seq + 255) / 256), dim3(256), smem, s, (const bf16_t*)qkv, (bf16_t*)o, lse, seq, n_q, n_kv);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+template <int D> hipError_t bwd_d(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
+                                  int seq, int batch, int n_q, int n_kv, hipStream_t s) {
   hipError_t e;
+  constexpr int dq_smem = 2 * 2 * Head<D>::TILE, dkv_smem = 2 * (2 * Head<D>::TILE + 512) + 4 * Head<D>::TILE;
   static LdsAttrOnce dq_attr, dkv_attr;
-  if ((e = dq_attr.ensure(reinterpret_cast<const void*>(attn_bwd_dq_mfma), DQ_SMEM)) != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_bwd_dq_mfma, dim3(n_q, batch, (seq + 255) / 256), dim3(256), DQ_SMEM, s, (const bf16_t*)qkv,
+  auto dq = attn_bwd_dq_mfma<D>;
+  auto dkv = attn_bwd_dkv_mfma<D>;
+  if ((e = dq_attr.ensure(reinterpret_cast<const void*>(dq), dq_smem)) != hipSuccess) return e;
+  hipLaunchKernelGGL(dq, dim3(n_q, batch, (seq + 255) / 256), dim3(256), dq_smem, s, (const bf16_t*)qkv,
       (const bf16_t*)o, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, seq, n_q, n_kv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((e = dkv_attr.ensure(reinterpret_cast<const void*>(attn_bwd_dkv_mfma), DKV_SMEM)) != hipSuccess) return e;
-  const int split = attn_dkv_split(seq, batch, n_q, n_kv);
+  if ((e = dkv_attr.ensure(reinterpret_cast<const void*>(dkv), dkv_smem)) != hipSuccess) return e;
+  // partials of several workgroups per kv head need scratch that callers have for head size 128 only
+  const int split = D == 128 ? attn_dkv_split(seq, batch, n_q, n_kv) : 1;
   float* partial = ws + (size_t)batch * n_q * seq;            // behind the D array
-  hipLaunchKernelGGL(attn_bwd_dkv_mfma, dim3(n_kv * split, batch, (seq + 255) / 256), dim3(256), DKV_SMEM, s,
+  hipLaunchKernelGGL(dkv, dim3(n_kv * split, batch, (seq + 255) / 256), dim3(256), dkv_smem, s,
       (const bf16_t*)qkv, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, partial, split, seq, n_q, n_kv);
   if (split > 1) {
     e = hipGetLastError();
@@ -999,4 +1066,15 @@ hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout
         split, batch * seq, n_q, n_kv);
   }
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
+  return d == 128 ? fwd_d<128>(qkv, o, lse, seq, batch, n_q, n_kv, s) : fwd_d<64>(qkv, o, lse, seq, batch, n_q, n_kv, s);
+}
+
+hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
+                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
+  return d == 128 ? bwd_d<128>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s)
+                  : bwd_d<64>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
 }

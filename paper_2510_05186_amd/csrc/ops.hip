@@ -11,22 +11,23 @@ hipError_t launch_attn_fwd_simple(int dtype, const void* qkv, void* o, float* ls
 hipError_t launch_attn_bwd_simple(int dtype, const void* qkv, const void* o, const void* dout, const float* lse,
                                   void* dqkv, float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 
-bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv);
-hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s);
+bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void* p0, const void* p1, const void* p2, const void* p3);
+hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                int seq, int batch, int n_q, int n_kv, hipStream_t s);
+                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv,
                            int d, hipStream_t s) {
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
-  if (attn_mfma_applies(dtype, d, seq, n_q, n_kv)) return launch_attn_fwd_mfma(qkv, o, lse, seq, batch, n_q, n_kv, s);
+  if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, qkv, o)) return launch_attn_fwd_mfma(qkv, o, lse, seq, batch, n_q, n_kv, d, s);
   return launch_attn_fwd_simple(dtype, qkv, o, lse, seq, batch, n_q, n_kv, d, s);
 }
 
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv,
                            float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
-  if (attn_mfma_applies(dtype, d, seq, n_q, n_kv)) return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
+  if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, dout, dqkv))
+    return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
   return launch_attn_bwd_simple(dtype, qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
 }
 

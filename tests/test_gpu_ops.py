@@ -374,6 +374,48 @@ def test_attention_fwd_bwd(dtype, seq, batch, nq, nkv, d):
             assert rel_err(dq_g[sl, lo:hi], ref[:, lo:hi]) < TOL[dtype], (lo, hi)
 
 
+# Heads of 64: edges of the 32- and 64-wide tiles and of the 256 rows of a workgroup, one row, grouped heads, several sequences,
+# peaked and flat scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  The second
+# products multiply fp32 probabilities, so what is left is the rounding of the results: each is off by at most 2^-9 of its value,
+# which bounds the RMS-relative error; 5 % for everything in fp32.
+@pytest.mark.parametrize("seq,batch,nq,nkv,gain,shift", [(1, 2, 2, 1, 1.0, 0), (31, 1, 2, 2, 1.0, 0), (33, 1, 1, 1, 1.0, 0), (64, 2, 2, 1, 1.0, 0),
+                                                         (65, 1, 4, 1, 1.0, 0), (255, 1, 2, 2, 1.0, 0), (257, 2, 2, 1, 1.0, 0), (700, 1, 8, 2, 4.0, 0),
+                                                         (600, 1, 2, 2, 0.05, 0), (130, 1, 2, 1, 1.0, 1)])
+def test_attention_of_64_wide_heads_keeps_fp32_probabilities(seq, batch, nq, nkv, gain, shift):
+    d, rows, w = 64, seq * batch, (nq + 2 * nkv) * 64
+    qkv = RNG.standard_normal((rows, w))
+    qkv[:, : (nq + nkv) * d] *= gain
+    qkv, do = q(qkv, BF16), q(RNG.standard_normal((rows, nq * d)), BF16)
+
+    def place(a):
+        flat = torch.zeros(a.size + 8, dtype=torch.bfloat16, device="cuda")
+        flat[shift:shift + a.size] = dev(a, BF16).reshape(-1)
+        return flat[shift:shift + a.size].view(a.shape)
+    QKV, DO, Ot, DQKV = place(qkv), place(do), place(np.zeros((rows, nq * d))), place(np.zeros((rows, w)))
+    LSE = torch.empty(batch * nq * seq, dtype=torch.float32, device="cuda")
+    WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, batch, nq, nkv, d), dtype=torch.float32, device="cuda")
+    assert WS.numel() == batch * nq * seq
+    ok(lib().optstage_op_attn_fwd(BF16, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    ok(lib().optstage_op_attn_bwd(BF16, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    o_g, lse_g, dq_g = host(Ot), host(LSE).reshape(batch, nq, seq), host(DQKV)
+    refs = []
+    for b in range(batch):
+        sl = slice(b * seq, (b + 1) * seq)
+        qq, kk, vv = (x.reshape(seq, -1, d) for x in (qkv[sl, : nq * d], qkv[sl, nq * d: (nq + nkv) * d], qkv[sl, (nq + nkv) * d:]))
+        o, lse = O.attention_fwd(qq, kk, vv)
+        assert np.max(np.abs(lse_g[b] - lse) / np.maximum(1.0, np.abs(lse))) < 1e-5
+        dq, dk, dv = O.attention_bwd(qq, kk, vv, o_g[sl].reshape(seq, nq, d), do[sl].reshape(seq, nq, d))
+        refs.append((o.reshape(seq, -1), np.concatenate([x.reshape(seq, -1) for x in (dq, dk, dv)], axis=1)))
+    ref_o, ref_d = (np.concatenate(x) for x in zip(*refs))
+    assert rms_err(o_g, ref_o) < 1.05 * 2.0 ** -9
+    for lo, hi in ((0, nq * d), (nq * d, (nq + nkv) * d), ((nq + nkv) * d, w)):
+        scale = np.sqrt(np.mean(ref_d[:, lo:hi] ** 2))
+        # one row: its scores have no gradient, dQ and dK are the rounding of O in D = <dO, O> (both sides have it) and nothing else
+        assert scale < 1e-3 or rms_err(dq_g[:, lo:hi], ref_d[:, lo:hi]) < 1.05 * 2.0 ** -9 + 1e-6 / scale, (lo, hi)
+        assert np.isfinite(dq_g[:, lo:hi]).all()
+
+
 @pytest.mark.parametrize("gain", [6.0, 0.05])
 def test_attention_forward_with_peaked_and_flat_scores(gain):
     """Scores far larger than usual (the softmax reference has to be raised again and again, and most
