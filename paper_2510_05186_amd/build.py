@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liboptstage.so")
-SOURCES = ["gemm_bf16.hip", "gemm_bf16_small.hip", "gemm_f32.hip", "elementwise.hip", "attention_simple.hip", "attention_mfma.hip",
+SOURCES = ["gemm_bf16.hip", "gemm_bf16_small.hip", "gemm_f32.hip", "elementwise.hip", "attention_simple.hip", "attention_f32.hip", "attention_mfma.hip",
            "ops.hip", "stage.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

@@ -16,10 +16,16 @@ hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, i
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
                                 int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 
+bool attn_f32_applies(int dtype, int d, int seq, const void* p0, const void* p1, const void* p2, const void* p3);
+hipError_t launch_attn_fwd_f32(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
+hipError_t launch_attn_bwd_f32(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
+                               int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
+
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv,
                            int d, hipStream_t s) {
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
   if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, qkv, o)) return launch_attn_fwd_mfma(qkv, o, lse, seq, batch, n_q, n_kv, d, s);
+  if (attn_f32_applies(dtype, d, seq, qkv, o, qkv, o)) return launch_attn_fwd_f32(qkv, o, lse, seq, batch, n_q, n_kv, d, s);
   return launch_attn_fwd_simple(dtype, qkv, o, lse, seq, batch, n_q, n_kv, d, s);
 }
 
@@ -28,6 +34,8 @@ hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* o, const void
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
   if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, dout, dqkv))
     return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
+  if (attn_f32_applies(dtype, d, seq, qkv, o, dout, dqkv))
+    return launch_attn_bwd_f32(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
   return launch_attn_bwd_simple(dtype, qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
 }
 

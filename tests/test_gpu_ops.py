@@ -416,6 +416,40 @@ def test_attention_of_64_wide_heads_keeps_fp32_probabilities(seq, batch, nq, nkv
         assert np.isfinite(dq_g[:, lo:hi]).all()
 
 
+# fp32 attention on tiles of 16 rows shared by four waves: one row, a cut tile, more waves than tiles, both head sizes, grouped heads,
+# several sequences, peaked scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  Bound:
+# fp32 sums of up to a few hundred products, 2^-24 each, in softmax and both products; 1e-5 of the largest value.
+@pytest.mark.parametrize("seq,batch,nq,nkv,d,gain,shift", [(1, 1, 1, 1, 64, 1.0, 0), (15, 2, 2, 1, 128, 1.0, 0), (16, 1, 2, 2, 64, 1.0, 0),
+                                                           (17, 1, 4, 2, 64, 1.0, 0), (100, 2, 4, 1, 128, 1.0, 0), (257, 1, 2, 2, 64, 4.0, 0),
+                                                           (200, 1, 3, 3, 128, 0.05, 0), (65, 1, 2, 1, 64, 1.0, 1)])
+def test_attention_fp32(seq, batch, nq, nkv, d, gain, shift):
+    rows, w = seq * batch, (nq + 2 * nkv) * d
+    qkv = RNG.standard_normal((rows, w))
+    qkv[:, : (nq + nkv) * d] *= gain
+    qkv, do = q(qkv, FP32), q(RNG.standard_normal((rows, nq * d)), FP32)
+
+    def place(a):
+        flat = torch.zeros(a.size + 8, dtype=torch.float32, device="cuda")
+        flat[shift:shift + a.size] = dev(a, FP32).reshape(-1)
+        return flat[shift:shift + a.size].view(a.shape)
+    QKV, DO, Ot, DQKV = place(qkv), place(do), place(np.zeros((rows, nq * d))), place(np.zeros((rows, w)))
+    LSE = torch.empty(batch * nq * seq, dtype=torch.float32, device="cuda")
+    WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, batch, nq, nkv, d), dtype=torch.float32, device="cuda")
+    ok(lib().optstage_op_attn_fwd(FP32, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    ok(lib().optstage_op_attn_bwd(FP32, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    o_g, lse_g, dq_g = host(Ot), host(LSE).reshape(batch, nq, seq), host(DQKV)
+    for b in range(batch):
+        sl = slice(b * seq, (b + 1) * seq)
+        qq, kk, vv = (x.reshape(seq, -1, d) for x in (qkv[sl, : nq * d], qkv[sl, nq * d: (nq + nkv) * d], qkv[sl, (nq + nkv) * d:]))
+        o, lse = O.attention_fwd(qq, kk, vv)
+        assert np.max(np.abs(o_g[sl] - o.reshape(seq, -1))) < 1e-5 * np.max(np.abs(o))
+        assert np.max(np.abs(lse_g[b] - lse) / np.maximum(1.0, np.abs(lse))) < 1e-5
+        dq, dk, dv = O.attention_bwd(qq, kk, vv, o_g[sl].reshape(seq, nq, d), do[sl].reshape(seq, nq, d))
+        ref = np.concatenate([x.reshape(seq, -1) for x in (dq, dk, dv)], axis=1)
+        assert np.max(np.abs(dq_g[sl] - ref)) < 1e-5 * np.max(np.abs(ref)) * max(1.0, gain * gain)
+
+
 @pytest.mark.parametrize("gain", [6.0, 0.05])
 def test_attention_forward_with_peaked_and_flat_scores(gain):
     """Scores far larger than usual (the softmax reference has to be raised again and again, and most
