@@ -235,6 +235,24 @@ def test_weight_slabs_match_the_host_layout(N, K):
     assert lib().optstage_op_weight_slabs(S.data_ptr(), D.data_ptr(), N, K + 8, 0, stream()) == B.E_ARG
 
 
+@pytest.mark.parametrize("N,K,shift", [(256, 64, 0), (264, 128, 0), (256, 64, 1), (264, 128, 1)])
+def test_weight_slabs_with_and_without_16_byte_rows(N, K, shift):
+    """All three codes, from sources that start on 16 bytes and from ones that do not (shift, in elements)."""
+    w = q(RNG.standard_normal((N, K)), BF16)
+    n_pad = (N + 255) // 256 * 256
+    f = N // 2
+    rows = [qq * f + 128 * t + 64 * half + o for t in range(N // 256) for half in range(2) for qq in range(2) for o in range(64)]
+    cases = [(0, w, slabs_of(w)), (1, np.ascontiguousarray(w.T), slabs_of(w))] + ([(2, w, slabs_of(w[rows]))] if N % 256 == 0 else [])
+    for code, src, want in cases:
+        S = torch.zeros(src.size + 8, dtype=torch.bfloat16, device="cuda")
+        S[shift:shift + src.size] = dev(src, BF16).reshape(-1)
+        D = torch.full((n_pad * K + 8,), 3.0, dtype=torch.bfloat16, device="cuda")
+        ok(lib().optstage_op_weight_slabs(S[shift:].data_ptr(), D.data_ptr(), N, K, code, stream()))
+        torch.cuda.synchronize()
+        assert torch.equal(D[: n_pad * K].cpu(), torch.from_numpy(want.astype(np.float32)).bfloat16().reshape(-1)), code
+        assert float((D[n_pad * K:] - 3.0).abs().max()) == 0.0
+
+
 def test_gemm_rejects_bad_shapes():
     A = torch.zeros(64, 64, dtype=torch.bfloat16, device="cuda")
     f = lib().optstage_op_gemm
