@@ -93,6 +93,9 @@ hipError_t launch_gemm_bf16_small(int layout, int epi, const GemmProblem& proble
 bool gemm_bf16_fused_applies(int epi, int M, int N, int K, int lda, int head_dim);
 hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                            int K, int lda, int ldb, int ldc, hipStream_t s);
+// n (up to 16) independent fp32 TN products with the same K in one launch
+bool gemm_f32_grouped_applies(int n, const GemmProblem* problems, int K);
+hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* problems, int K, hipStream_t s);
 hipError_t launch_norm_fwd(int dtype, int family, const void* x, const void* gamma, const void* beta, void* out,
                            float* stats, int rows, int h, float eps, hipStream_t s);
 hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x, const float* stats,

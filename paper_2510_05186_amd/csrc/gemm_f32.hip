@@ -90,15 +90,14 @@ template <int R, bool TNL, bool VEC> struct Operand {
 };
 
 template <int R, bool TNL, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
-                                                            const float* __restrict__ Res, int M, int N, int K, int lda, int ldb,
-                                                            int ldc, int tiles_m, int tiles_n, int epi) {
+__device__ __forceinline__ void f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                         const float* __restrict__ Res, int M, int N, int K, int lda, int ldb, int ldc, int id,
+                                         int tiles_m, int tiles_n, int epi) {
   constexpr int T = R / 16, DEPTH = R == 64 ? 2 : R == 32 ? 4 : 8;
   __shared__ __attribute__((aligned(16))) float part[4][R][R + 4];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroup ids go to different XCDs: every XCD takes one contiguous eighth of the tiles, row by row
-  int id = blockIdx.x;
   const int n_tiles = tiles_m * tiles_n;
   if ((n_tiles & 7) == 0) id = (id & 7) * (n_tiles >> 3) + (id >> 3);
   const int m0 = (id / tiles_n) * R, n0 = (id % tiles_n) * R;
@@ -166,6 +165,27 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restr
       for (int e = 0; e < 4 && n + e < N; ++e) dst[e] = add ? v[e] + add[e] : v[e];
     }
   }
+}
+
+template <int R, bool TNL, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
+                                                            const float* __restrict__ Res, int M, int N, int K, int lda, int ldb,
+                                                            int ldc, int tiles_m, int tiles_n, int epi) {
+  f32_tile<R, TNL, VEC>(A, B, C, Res, M, N, K, lda, ldb, ldc, blockIdx.x, tiles_m, tiles_n, epi);
+}
+
+// The weight-gradient products of a W op in one launch: none depends on another, and at a few hundred tokens each is a launch
+// of 5 us that leaves most of the compute units idle (W of the two-layer hidden-256 stage: eight launches 44 us, one 15).
+constexpr int MAX_GROUP = 16;
+struct GroupedF32 { const float* A; const float* B; float* C; int M, N, lda, ldb, ldc, tiles_m, tiles_n, first; };
+struct GroupedF32Args { int n, K, epi; GroupedF32 p[MAX_GROUP]; };
+template <int R>
+__global__ __launch_bounds__(256) void gemm_f32_grouped_tn_kernel(const GroupedF32Args g) {
+  int q = 0;
+  for (int i = 1; i < g.n; ++i)
+    if ((int)blockIdx.x >= g.p[i].first) q = i;
+  const GroupedF32& p = g.p[q];
+  f32_tile<R, true, true>(p.A, p.B, p.C, p.C /* no residual; a null constant here crashes the compiler */, p.M, p.N, g.K, p.lda, p.ldb, p.ldc, blockIdx.x - p.first, p.tiles_m, p.tiles_n, g.epi);
 }
 
 // General path: 64 x 64 tile through LDS, 256 threads, 4 x 4 outputs per thread, any strides.  Takes what 32-bit offsets within
@@ -239,9 +259,10 @@ hipError_t launch_mfma(int epi, const float* A, const float* B, float* C, const 
 // The tile that needs the least time: rounds of 256 workgroups times the time of a round, measured for 1024 k as 21 us at R = 64,
 // 7.8 at 32, 3.8 at 16 (2.3 while no compute unit holds two, which share its load path).  E.g. 512 x 1024 x 1024 28.0 / 20.6 /
 // 34.4 us, 512 x 4096 x 1024 45.2 / 65.5 / 127, 128 x 256 x 1024 25.2 / 11.4 / 6.3.
-int pick_tile(int M, int N) {
+int pick_tile(int n, const GemmProblem* pr) {
   auto cost = [&](int r, double per_round) {
-    const long long tiles = (long long)((M + r - 1) / r) * ((N + r - 1) / r);
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (long long)((pr[i].M + r - 1) / r) * ((pr[i].N + r - 1) / r);
     return (double)((tiles + 255) / 256) * (r == 16 && tiles <= 256 ? 2.3 : per_round);
   };
   const double c64 = cost(64, 21.0), c32 = cost(32, 7.8), c16 = cost(16, 3.8);
@@ -251,7 +272,8 @@ int pick_tile(int M, int N) {
 template <bool TNL, bool VEC>
 hipError_t launch_sized(int epi, const float* A, const float* B, float* C, const float* R, int M, int N, int K, int lda, int ldb,
                         int ldc, hipStream_t s) {
-  switch (pick_tile(M, N)) {
+  const GemmProblem pr = {A, B, C, R, M, N, lda, ldb, ldc};
+  switch (pick_tile(1, &pr)) {
     case 64: return launch_mfma<64, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     case 32: return launch_mfma<32, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     default: return launch_mfma<16, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
@@ -260,6 +282,46 @@ hipError_t launch_sized(int epi, const float* A, const float* B, float* C, const
 
 }  // namespace
 
+namespace {
+// lane offsets of the matrix-instruction kernels: NT 64 rows of a tile, TN all k-rows of the operand's column strip
+bool mfma_reaches(bool tn, int K, int lda, int ldb) {
+  const unsigned long long reach = 0xF0000000ull / 4;
+  const unsigned long long span = (unsigned long long)(tn ? K + 64ull * 16 : 64ull) * (unsigned long long)(lda > ldb ? lda : ldb) + 64;
+  return span < reach && (tn || (unsigned long long)K < reach / 2);
+}
+
+template <int R>
+hipError_t launch_grouped(int epi, int n, const GemmProblem* pr, int K, hipStream_t s) {
+  GroupedF32Args g;
+  g.n = n; g.K = K; g.epi = epi;
+  int total = 0;
+  for (int i = 0; i < n; ++i) {
+    const int tm = (pr[i].M + R - 1) / R, tn = (pr[i].N + R - 1) / R;
+    g.p[i] = {(const float*)pr[i].A, (const float*)pr[i].B, (float*)pr[i].C, pr[i].M, pr[i].N, pr[i].lda, pr[i].ldb, pr[i].ldc, tm, tn, total};
+    total += tm * tn;
+  }
+  hipLaunchKernelGGL(gemm_f32_grouped_tn_kernel<R>, dim3(total), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+}  // namespace
+
+bool gemm_f32_grouped_applies(int n, const GemmProblem* pr, int K) {
+  if (n < 1 || n > MAX_GROUP || K <= 0) return false;
+  for (int i = 0; i < n; ++i)
+    if (pr[i].M <= 0 || pr[i].N <= 0 || ((pr[i].lda | pr[i].ldb | pr[i].M | pr[i].N) & 3) || !mfma_reaches(true, K, pr[i].lda, pr[i].ldb)) return false;
+  return true;
+}
+
+// n independent TN products with the same K: C (fp32) += product (EPI_ACCUM) or = product
+hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* pr, int K, hipStream_t s) {
+  if (!gemm_f32_grouped_applies(n, pr, K) || (epi != EPI_ACCUM && epi != EPI_STOREF)) return hipErrorInvalidValue;
+  switch (pick_tile(n, pr)) {
+    case 64: return launch_grouped<64>(epi, n, pr, K, s);
+    case 32: return launch_grouped<32>(epi, n, pr, K, s);
+    default: return launch_grouped<16>(epi, n, pr, K, s);
+  }
+}
+
 hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                            int K, int lda, int ldb, int ldc, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
@@ -267,10 +329,7 @@ hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, vo
   const bool tn = layout == GEMM_TN;
   const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
   float* c = (float*)C;
-  // lane offsets: NT 64 rows of a tile, TN all k-rows of the operand's column strip
-  const unsigned long long reach = 0xF0000000ull / 4;
-  const unsigned long long span = (unsigned long long)(tn ? K + 64ull * 16 : 64ull) * (unsigned long long)(lda > ldb ? lda : ldb) + 64;
-  if (span < reach && (tn || (unsigned long long)K < reach / 2)) {
+  if (mfma_reaches(tn, K, lda, ldb)) {
     const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
     if (tn) return vec ? launch_sized<true, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
                        : launch_sized<true, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);

@@ -477,7 +477,8 @@ optstage_status k_gemm_fused(optstage* st, int layout, int epi, const void* A, c
 optstage_status k_gemm_grouped(optstage* st, int layout, int epi, int n, const GemmProblem* pr, int K) {
   double flops = 0;
   for (int i = 0; i < n; ++i) flops += 2.0 * pr[i].M * pr[i].N * K;
-  KT(OPTSTAGE_KC_GEMM_TN_ACCUM, flops, launch_gemm_bf16_grouped(layout, epi, n, pr, K, st->cs));
+  KT(OPTSTAGE_KC_GEMM_TN_ACCUM, flops, st->sh.dtype == OPTSTAGE_BF16 ? launch_gemm_bf16_grouped(layout, epi, n, pr, K, st->cs)
+                                                                     : launch_gemm_f32_grouped(epi, n, pr, K, st->cs));
   return OPTSTAGE_OK;
 }
 optstage_status k_norm_fwd(optstage* st, const void* x, const void* g, const void* b, void* out, float* stats) {
@@ -642,8 +643,8 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   const int T = s.tokens;
   auto P = [&](int l, int k) { return (void*)(st->arena() + ob.dev[(size_t)l * NK + k]); };
   // dW += dY^T X for the four linears of every layer (fp32 accumulators).  None of these products depends on
-  // another: bf16 stages hand them to one grouped launch per 16, so that only the last launch leaves a partly
-  // filled round of workgroups; anything the grouped path does not take runs product by product.
+  // another: they go to one grouped launch per 16, so that only the last launch leaves a partly filled round of
+  // workgroups; anything the grouped path does not take runs product by product.
   std::vector<GemmProblem> pr;
   for (int l = c * s.Lc; l < (c + 1) * s.Lc; ++l) {
     pr.push_back({P(l, OPTSTAGE_K_DY), P(l, OPTSTAGE_K_A), GW(st, l, OPTSTAGE_W_D), nullptr, s.h, s.f, s.h, s.f, s.f});
@@ -656,7 +657,7 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   const int epi = st->overwrite && j == 0 ? EPI_STOREF : EPI_ACCUM;
   for (size_t i0 = 0; i0 < pr.size(); i0 += 16) {
     const int n = (int)std::min<size_t>(16, pr.size() - i0);
-    const bool grouped = s.dtype == OPTSTAGE_BF16 && gemm_bf16_grouped_applies(GEMM_TN, n, &pr[i0], T);
+    const bool grouped = s.dtype == OPTSTAGE_BF16 ? gemm_bf16_grouped_applies(GEMM_TN, n, &pr[i0], T) : gemm_f32_grouped_applies(n, &pr[i0], T);
     if (grouped) TRY(k_gemm_grouped(st, GEMM_TN, epi, n, &pr[i0], T));
     if (!grouped)
       for (int i = 0; i < n; ++i) {
