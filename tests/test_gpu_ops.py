@@ -394,8 +394,10 @@ def test_attention_fwd_bwd(dtype, seq, batch, nq, nkv, d):
 
 # Heads of 64: edges of the 32- and 64-wide tiles and of the 256 rows of a workgroup, one row, grouped heads, several sequences,
 # peaked and flat scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  The second
-# products multiply fp32 probabilities, so what is left is the rounding of the results: each is off by at most 2^-9 of its value,
-# which bounds the RMS-relative error; 5 % for everything in fp32.
+# products multiply fp32 probabilities (16 bits of fraction at least), so what is left is the rounding of the results to 8
+# bits: an error spread evenly over +- 2^-8 of the power of two below a value, at most 2^-8 / sqrt(3) RMS-relative, and all but
+# the values within about 2^-16 of a tie, 2^-7 of them and a few more where a sum cancels, equal the correctly rounded
+# ones (below 6 %; probabilities of 8 bits miss a third).
 @pytest.mark.parametrize("seq,batch,nq,nkv,gain,shift", [(1, 2, 2, 1, 1.0, 0), (31, 1, 2, 2, 1.0, 0), (33, 1, 1, 1, 1.0, 0), (64, 2, 2, 1, 1.0, 0),
                                                          (65, 1, 4, 1, 1.0, 0), (255, 1, 2, 2, 1.0, 0), (257, 2, 2, 1, 1.0, 0), (700, 1, 8, 2, 4.0, 0),
                                                          (600, 1, 2, 2, 0.05, 0), (130, 1, 2, 1, 1.0, 1)])
@@ -426,12 +428,14 @@ def test_attention_of_64_wide_heads_keeps_fp32_probabilities(seq, batch, nq, nkv
         dq, dk, dv = O.attention_bwd(qq, kk, vv, o_g[sl].reshape(seq, nq, d), do[sl].reshape(seq, nq, d))
         refs.append((o.reshape(seq, -1), np.concatenate([x.reshape(seq, -1) for x in (dq, dk, dv)], axis=1)))
     ref_o, ref_d = (np.concatenate(x) for x in zip(*refs))
-    assert rms_err(o_g, ref_o) < 1.05 * 2.0 ** -9
-    for lo, hi in ((0, nq * d), (nq * d, (nq + nkv) * d), ((nq + nkv) * d, w)):
-        scale = np.sqrt(np.mean(ref_d[:, lo:hi] ** 2))
-        # one row: its scores have no gradient, dQ and dK are the rounding of O in D = <dO, O> (both sides have it) and nothing else
-        assert scale < 1e-3 or rms_err(dq_g[:, lo:hi], ref_d[:, lo:hi]) < 1.05 * 2.0 ** -9 + 1e-6 / scale, (lo, hi)
-        assert np.isfinite(dq_g[:, lo:hi]).all()
+    for got, ref in ((o_g, ref_o), *((dq_g[:, lo:hi], ref_d[:, lo:hi]) for lo, hi in ((0, nq * d), (nq * d, (nq + nkv) * d), ((nq + nkv) * d, w)))):
+        assert np.isfinite(got).all()
+        if np.sqrt(np.mean(ref ** 2)) < 1e-3:      # a single row: its scores have no gradient, dQ and dK are what the rounding of O leaves
+            continue
+        assert rms_err(got, ref) < 1.05 * 2.0 ** -8 / np.sqrt(3.0)
+        # scores of order one only: at gain 4 they reach +- 60, whose fp32 rounding is 2^-18 of a probability, and dP - D cancels
+        # to the rounding of dP in most elements
+        assert gain > 1.0 or np.mean(got != q(ref, BF16)) < 0.06
 
 
 # fp32 attention on tiles of 16 rows shared by four waves: one row, a cut tile, more waves than tiles, both head sizes, grouped heads,
