@@ -26,7 +26,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // fraction between them) and not as one.  Heads of 64 have always multiplied them in fp32; the error against 64 bits stays
 // what it was (o 1.6e-3, dqkv 1.8e-3: the rounding of the results), where one bf16 number would raise it by a quarter.
 // Measured for heads of 64 at 4 x 1024 tokens, 16 heads, forward and backward: 4466 us on the general kernels (one wave per row,
-// no matrix unit), 143 us here.
+// no matrix unit), 97 us here.
 template <int D> struct Head {
   static constexpr int ROWB = 2 * D, TILE = 64 * ROWB, CH = D / 8, NKS = D / 16, NDT = D / 32, RPL = 64 / CH, NLD = 16 / RPL;
   static constexpr bool SPLIT = D == 64;
@@ -60,8 +60,8 @@ __device__ __forceinline__ float pair_max32(float x) {
   return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
-// ---- forward: grid (n_q, batch, ceil(seq / 256)); 4 waves (one per SIMD) ---------------------------------
-// Same frame as the dQ kernel below: wave w owns queries q0 + 64 w .. + 63 as two 32-query tiles, Q operand
+// ---- forward: grid (n_q, batch, ceil(seq / (128 QT))); 4 waves (one per SIMD); text and figures for QT = 2 ---------------------------------
+// Same frame as the dQ kernel below: wave w owns 32 QT queries from q0 + 32 QT w on as QT 32-query tiles, Q operand
 // fragments in registers, O^T ([d 128][64 queries]) in accumulator registers, key blocks of 64 (K and V rows)
 // streaming through an LDS ring filled straight from global memory (three stages: the scores of the next
 // block's first tile are issued before the current block's last tile is finished).  Per 32-key tile:
@@ -77,7 +77,7 @@ __device__ __forceinline__ float pair_max32(float x) {
 // tiles.  softmax does not depend on the reference: o = (sum p v) / (sum p), lse = m_ref scale + log(sum p).
 constexpr float FWD_TAU = 8.f;
 
-template <int D>
+template <int D, int QT>
 __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o,
                                                      float* __restrict__ lse, int seq, int n_q, int n_kv) {
   typedef Head<D> H;
@@ -86,31 +86,34 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nqb = (seq + 255) / 256;
-  const int q0 = (nqb - 1 - (int)blockIdx.z) * 256;          // longest rows are dispatched first, for every head
+  constexpr int WQ = 32 * QT, GQ = 4 * WQ;     // queries of a wave, of the workgroup
+  const int nqb = (seq + GQ - 1) / GQ;
+  const int q0 = (nqb - 1 - (int)blockIdx.z) * GQ;          // longest rows are dispatched first, for every head
   const int a = blockIdx.x, b = blockIdx.y, kvh = a * n_kv / n_q;
   const int ld = (n_q + 2 * n_kv) * D, ldo = n_q * D;
   const bf16_t* base = qkv + (size_t)b * seq * ld;
-  const int wave_first_q = q0 + 64 * wave, wave_last_q = wave_first_q + 63;
+  const int wave_first_q = q0 + WQ * wave;
   const float scale = rsqrtf((float)D), c = scale * LOG2E, thr = FWD_TAU / c;
 
-  bf16x8_t Qf[2][NKS];
-  int qglob[2];
+  bf16x8_t Qf[QT][NKS];
+  int qglob[QT];
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     qglob[qt] = wave_first_q + 32 * qt + c32;
     const bf16_t* qp = base + (size_t)min(qglob[qt], seq - 1) * ld + (size_t)a * D + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) Qf[qt][ks] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * ks);
   }
-  f32x16_t acc[2][NDT];                        // [query tile][d tile]: lane = query, registers = d
+  f32x16_t acc[QT][NDT];                        // [query tile][d tile]: lane = query, registers = d
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[qt][dt][v] = 0.f;
-  float mref[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
+  float mref[QT], lsum[QT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) { mref[qt] = -INFINITY; lsum[qt] = 0.f; }
 
   // LDS addressing as in the dQ kernel: 64 rows x 256 B per tile, 16-byte chunk c of row r stored at chunk
   // c ^ (((r & 3) << 2) | ((r >> 2) & 3))
@@ -168,7 +171,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     return *reinterpret_cast<const bf16x8_t*>(tile + t * 32 * ROWB + rm_addr[ks]);
   };
 
-  const int nkb = min((q0 + 255) / 64 + 1, (seq + 63) / 64);
+  const int nkb = min((q0 + GQ - 1) / 64 + 1, (seq + 63) / 64);
 
 #define OPTSTAGE_SB() __builtin_amdgcn_sched_barrier(0)
 #define OPTSTAGE_MFMA_V(acc, a, b) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b))
@@ -186,12 +189,13 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   // The first operand fragment of every step is read during the step before it (kf_first, trf_first), so that no
   // step starts with the matrix unit idle for an LDS round trip.
   bf16x8_t kf_first, trf_first;
-  auto step_scores = [&](bool with_exp, int stage_k, int t, f32x16_t (&cur)[2], f32x16_t (&nxt)[2], int stage_v, int tv) {
+  auto step_scores = [&](bool with_exp, int stage_k, int t, f32x16_t (&cur)[QT], f32x16_t (&nxt)[QT], int stage_v, int tv) {
     const char* sK = smem + stage_k * FWD_STAGE;
     bf16x8_t kf[2];
     kf[0] = kf_first;
-    const float mc0 = mref[0] * c, mc1 = mref[1] * c;
-    float ls0 = 0.f, ls1 = 0.f;
+    float mc[QT], ls[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) { mc[qt] = mref[qt] * c; ls[qt] = 0.f; }
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       OPTSTAGE_SB();
@@ -206,43 +210,47 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
       // reaches an MFMA while the unit is busy waits there and issues nothing else, so two MFMAs back to back
       // followed by all of the vector work run one after the other instead of side by side.
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
+      for (int qt = 0; qt < QT; ++qt) {
         if (ks == 0)                                             // the first k-step starts from C = 0
           asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(nxt[qt]) : "v"(kf[0]), "a"(Qf[qt][0]));
         else
           asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(nxt[qt]) : "v"(kf[ks & 1]), "a"(Qf[qt][ks]));
         OPTSTAGE_SB();
         if (with_exp) {                                          // compile-time after inlining
+          constexpr int PV = 16 / (NKS * QT);                    // registers of every query tile per MFMA
 #pragma unroll
-          for (int x = 0; x < 8 / NKS; ++x) {
-            const int v = (2 * ks + qt) * (8 / NKS) + x;
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(cur[0][v], c, -mc0));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(cur[1][v], c, -mc1));
-            cur[0][v] = p0; cur[1][v] = p1;
-            ls0 += p0; ls1 += p1;
+          for (int x = 0; x < PV; ++x) {
+            const int v = (QT * ks + qt) * PV + x;
+#pragma unroll
+            for (int y = 0; y < QT; ++y) cur[y][v] = __builtin_amdgcn_exp2f(fmaf(cur[y][v], c, -mc[y]));
+#pragma unroll
+            for (int y = 0; y < QT; ++y) ls[y] += cur[y][v];
             // keeps these instructions here, between the MFMAs: without a use at this point the compiler sinks
             // them to where the probabilities are packed
-            asm volatile("" : "+v"(cur[0][v]), "+v"(cur[1][v]), "+v"(ls0), "+v"(ls1));
+#pragma unroll
+            for (int y = 0; y < QT; ++y) asm volatile("" : "+v"(cur[y][v]), "+v"(ls[y]));
           }
         }
         OPTSTAGE_SB();
       }
     }
     OPTSTAGE_SB();
-    lsum[0] += ls0; lsum[1] += ls1;
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) lsum[qt] += ls[qt];
   };
   // scores above the diagonal (and keys past the sequence, which lie above every stored query) leave the softmax
-  auto mask_tile = [&](int i, f32x16_t (&sc)[2]) {
+  auto mask_tile = [&](int i, f32x16_t (&sc)[QT]) {
     if (32 * i + 31 <= wave_first_q) return;                     // wave-uniform: the tile lies below the diagonal
+    if (QT == 1) asm volatile("s_nop 7" ::: "memory");           // the scores' last MFMA has written its results
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int key = 32 * i + 8 * (v >> 2) + 4 * g + (v & 3);
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt)
+      for (int qt = 0; qt < QT; ++qt)
         if (key > qglob[qt]) sc[qt][v] = -INFINITY;
     }
   };
-  auto max_half = [&](int n, int qt, const f32x16_t (&sc)[2], float (&mx)[2]) {
+  auto max_half = [&](int n, int qt, const f32x16_t (&sc)[QT], float (&mx)[QT]) {
 #pragma unroll
     for (int x = 0; x < 4 / NDT; ++x) {                          // n: one of the 2 NDT positions of a step
       const int v = 2 * (n * (4 / NDT) + x);
@@ -250,19 +258,25 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     }
     asm volatile("" : "+v"(mx[qt]));                            // stays between the MFMAs it is written between
   };
-  auto max_slice = [&](int n, const f32x16_t (&sc)[2], float (&mx)[2]) {
-    mx[0] = fmaxf(mx[0], fmaxf(sc[0][2 * n], sc[0][2 * n + 1]));
-    mx[1] = fmaxf(mx[1], fmaxf(sc[1][2 * n], sc[1][2 * n + 1]));
-    asm volatile("" : "+v"(mx[0]), "+v"(mx[1]));               // stays between the MFMAs it is written between
+  auto max_slice = [&](int n, const f32x16_t (&sc)[QT], float (&mx)[QT]) {
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      mx[qt] = fmaxf(mx[qt], fmaxf(sc[qt][2 * n], sc[qt][2 * n + 1]));
+      asm volatile("" : "+v"(mx[qt]));                          // stays between the MFMAs it is written between
+    }
   };
   // the rare raise of m_ref, with O^T and the row sums rescaled
-  auto raise_reference = [&](float (&mx)[2]) {
-    mx[0] = pair_max32(mx[0]);                                  // the two lanes of a row hold 16 keys each
-    mx[1] = pair_max32(mx[1]);
-    if (__any((mx[0] > mref[0] + thr) | (mx[1] > mref[1] + thr))) {
+  auto raise_reference = [&](float (&mx)[QT]) {
+    bool above = false;
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      mx[qt] = pair_max32(mx[qt]);                              // the two lanes of a row hold 16 keys each
+      above |= mx[qt] > mref[qt] + thr;
+    }
+    if (__any(above)) {
       asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");         // the last O^T MFMAs have left the matrix unit
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt) {
+      for (int qt = 0; qt < QT; ++qt) {
         const float mn = fmaxf(mref[qt], mx[qt]);
         const float alpha = mn == mref[qt] ? 1.f : __builtin_amdgcn_exp2f((mref[qt] - mn) * c);
         mref[qt] = mn;
@@ -280,10 +294,12 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   };
   // O^T += V^T P^T of the current tile (probabilities in cur, V half t of the tile in `stage_v`), between the MFMAs
   // the row maxima of the next tile i1 (scores in nxt, already masked)
-  auto step_output = [&](int stage_v, int t, int i1, f32x16_t (&cur)[2], f32x16_t (&nxt)[2], int stage_k, int tk) {
+  auto step_output = [&](int stage_v, int t, int i1, f32x16_t (&cur)[QT], f32x16_t (&nxt)[QT], int stage_k, int tk) {
     const char* sV = smem + stage_v * FWD_STAGE + TILE;
     mask_tile(i1, nxt);
-    float mx[2] = {-INFINITY, -INFINITY};
+    float mx[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) mx[qt] = -INFINITY;
     // fragment n + 2 is requested before the MFMAs of fragment n: one pair of MFMAs is shorter than an LDS round
     // trip
     bf16x8_t trf[3];
@@ -291,27 +307,29 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     trf[1] = tr_frag(sV, 1, t, 0);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const bf16x8_t p0 = pack8(cur[0], u), p1 = pack8(cur[1], u);
-      bf16x8_t r0, r1;
-      if constexpr (H::SPLIT) { r0 = pack8_rest(cur[0], p0, u); r1 = pack8_rest(cur[1], p1, u); }
+      bf16x8_t p[QT], rest[QT];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) p[qt] = pack8(cur[qt], u);
+      if constexpr (H::SPLIT) {
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) rest[qt] = pack8_rest(cur[qt], p[qt], u);
+      }
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         const int n = u * NDT + dt, n2 = n + 2;
         OPTSTAGE_SB();
         if (n2 < 2 * NDT) trf[n2 % 3] = tr_frag(sV, n2 % NDT, t, n2 / NDT);
         else if (n == 2 * NDT - 2) kf_first = rm_frag(smem + stage_k * FWD_STAGE, tk, 0);
-        if (dt == 0) asm volatile("s_nop 1" :: "v"(p0), "v"(p1) : "memory");   // packed operands settled
-        if constexpr (H::SPLIT) { if (dt == 0) asm volatile("s_nop 1" :: "v"(r0), "v"(r1) : "memory"); }
-        OPTSTAGE_SB();
-        OPTSTAGE_MFMA_A(acc[0][dt], trf[n % 3], p0);
-        if constexpr (H::SPLIT) OPTSTAGE_MFMA_A(acc[0][dt], trf[n % 3], r0);
-        OPTSTAGE_SB();
-        max_half(n, 0, nxt, mx);
-        OPTSTAGE_SB();
-        OPTSTAGE_MFMA_A(acc[1][dt], trf[n % 3], p1);
-        if constexpr (H::SPLIT) OPTSTAGE_MFMA_A(acc[1][dt], trf[n % 3], r1);
-        OPTSTAGE_SB();
-        max_half(n, 1, nxt, mx);
+        if (dt == 0) asm volatile("s_nop 1" :: "v"(p[0]), "v"(p[QT - 1]) : "memory");   // packed operands settled
+        if constexpr (H::SPLIT) { if (dt == 0) asm volatile("s_nop 1" :: "v"(rest[0]), "v"(rest[QT - 1]) : "memory"); }
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+          OPTSTAGE_SB();
+          OPTSTAGE_MFMA_A(acc[qt][dt], trf[n % 3], p[qt]);
+          if constexpr (H::SPLIT) OPTSTAGE_MFMA_A(acc[qt][dt], trf[n % 3], rest[qt]);
+          OPTSTAGE_SB();
+          max_half(n, qt, nxt, mx);
+        }
       }
     }
     OPTSTAGE_SB();
@@ -319,7 +337,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   };
 #define OPTSTAGE_BLOCK_SYNC() asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory")
 
-  f32x16_t sA[2], sB[2];
+  f32x16_t sA[QT], sB[QT];
   issue_block(0, 0);
   OPTSTAGE_BLOCK_SYNC();
   if (nkb > 1) issue_block(1, 1);
@@ -330,7 +348,9 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
     // after the last pass
     asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
     mask_tile(0, sA);
-    float mx[2] = {-INFINITY, -INFINITY};
+    float mx[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) mx[qt] = -INFINITY;
 #pragma unroll
     for (int n = 0; n < 8; ++n) max_slice(n, sA, mx);
     raise_reference(mx);
@@ -354,11 +374,11 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 #undef OPTSTAGE_MFMA_A
   asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
 
-  float lt[2];
+  float lt[QT];
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) lt[qt] = lsum[qt] + __shfl_xor(lsum[qt], 32, 64);
+  for (int qt = 0; qt < QT; ++qt) lt[qt] = lsum[qt] + __shfl_xor(lsum[qt], 32, 64);
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     if (qglob[qt] >= seq) continue;
     const float inv = 1.f / lt[qt];
     bf16_t* orow = o + ((size_t)b * seq + qglob[qt]) * ldo + (size_t)a * D;
@@ -379,7 +399,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 }
 
 
-// ---- backward, dQ: grid (n_q, batch, ceil(seq / 256)); 4 waves (one per SIMD) -----------------------------
+// ---- backward, dQ: grid (n_q, batch, ceil(seq / (128 QT))); 4 waves (one per SIMD); text for QT = 2 -----------------------------
 // Mirror image of the dK/dV kernel below.  Wave w owns queries q0 + 64 w .. + 63 as two 32-query tiles: their Q
 // and dO operand fragments stay in registers (128) and dQ^T ([d 128][64 queries]) in accumulator registers, so
 // every K / V fragment read from LDS feeds two MFMAs.  Key blocks of 64 (K and V rows) stream through a
@@ -387,7 +407,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 // reads) and dQ^T += K^T dS^T (transposing reads), through the same chunk swizzle as in the dK/dV kernel.
 // Also produces D_t = <dO_t, O_t> per query row and head (from the dO fragments it holds anyway) and stores it
 // for the dK/dV kernel, which runs after this one.
-template <int D>
+template <int D, int QT>
 __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                         const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                         float* __restrict__ delta, bf16_t* __restrict__ dqkv, int seq,
@@ -398,21 +418,22 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nqb = (seq + 255) / 256;
-  const int q0 = (nqb - 1 - (int)blockIdx.z) * 256;          // longest rows are dispatched first, for every head
+  constexpr int WQ = 32 * QT, GQ = 4 * WQ;     // queries of a wave, of the workgroup
+  const int nqb = (seq + GQ - 1) / GQ;
+  const int q0 = (nqb - 1 - (int)blockIdx.z) * GQ;          // longest rows are dispatched first, for every head
   const int a = blockIdx.x, b = blockIdx.y, kvh = a * n_kv / n_q;
   const int ld = (n_q + 2 * n_kv) * D, ldo = n_q * D;
   const bf16_t* base = qkv + (size_t)b * seq * ld;
-  const int wave_first_q = q0 + 64 * wave, wave_last_q = wave_first_q + 63;
+  const int wave_first_q = q0 + WQ * wave, wave_last_q = wave_first_q + WQ - 1;
   const float scale = rsqrtf((float)D), c = scale * LOG2E;
 
   // Q, dO operand fragments of this wave's queries (rows past the end are clamped: their results are not stored),
   // lse * log2(e) and D per query
-  bf16x8_t Qf[2][NKS], dOf[2][NKS];
-  float Lc[2], Dq[2];
-  int qglob[2];
+  bf16x8_t Qf[QT][NKS], dOf[QT][NKS];
+  float Lc[QT], Dq[QT];
+  int qglob[QT];
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     qglob[qt] = wave_first_q + 32 * qt + c32;
     const int qrow = min(qglob[qt], seq - 1);
     const bf16_t* qp = base + (size_t)qrow * ld + (size_t)a * D + 8 * g;
@@ -434,20 +455,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   }
   // -D of this lane's two queries in every register of an accumulator-shaped tuple: the initial value of the dP^T
   // MFMAs, which then deliver dP^T - D
-  f32x16_t negD[2];
+  f32x16_t negD[QT];
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) negD[qt][v] = -Dq[qt];
   // from here on the fragments are operands of MFMAs only: they move to the accumulation half of the register file
   // for good (the empty statements are where the move happens)
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+a"(Qf[qt][ks]), "+a"(dOf[qt][ks]));
-  f32x16_t acc[2][NDT];                        // [query tile][d tile]: lane = query, registers = d
+  f32x16_t acc[QT][NDT];                        // [query tile][d tile]: lane = query, registers = d
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -527,7 +548,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
       if (key0 > wave_last_q) continue;                          // wave-uniform
       const bool edge = key0 + 31 > wave_first_q;                // touches the diagonal (keys past seq are masked by it)
       // lane = query, registers = keys key0 + 8 (v / 4) + 4 g + v % 4
-      f32x16_t s[2], dp[2];
+      f32x16_t s[QT], dp[QT];
       bf16x8_t kf[2], vf[2];
       // ---- S^T = K Q^T (the first k-step starts from C = 0)
       kf[0] = rm_frag(sK, t, 0);
@@ -538,11 +559,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
         else vf[0] = rm_frag(sV, t, 0);
         OPTSTAGE_SB();
         if (ks == 0) {
-          OPTSTAGE_MFMA_0(s[0], kf[0], Qf[0][0]);
-          OPTSTAGE_MFMA_0(s[1], kf[0], Qf[1][0]);
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) OPTSTAGE_MFMA_0(s[qt], kf[0], Qf[qt][0]);
         } else {
-          OPTSTAGE_MFMA_V(s[0], kf[ks & 1], Qf[0][ks]);
-          OPTSTAGE_MFMA_V(s[1], kf[ks & 1], Qf[1][ks]);
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) OPTSTAGE_MFMA_V(s[qt], kf[ks & 1], Qf[qt][ks]);
         }
       }
       // ---- dP^T = V dO^T, with the exponentials of S^T under its MFMAs
@@ -552,18 +573,21 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
         if (ks < NKS - 1) vf[(ks + 1) & 1] = rm_frag(sV, t, ks + 1);
         OPTSTAGE_SB();
         if (ks == 0) {                                             // dP^T - D: the first k-step starts from C = -D
-          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[0]) : "v"(vf[0]), "a"(dOf[0][0]), "v"(negD[0]));
-          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[1]) : "v"(vf[0]), "a"(dOf[1][0]), "v"(negD[1]));
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt)
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[qt]) : "v"(vf[0]), "a"(dOf[qt][0]), "v"(negD[qt]));
+          // the exponentials read S^T a few cycles after the matrix unit has written it: a second query tile's MFMA is that long
+          if (QT == 1) asm volatile("s_nop 7" ::: "memory");
         } else {
-          OPTSTAGE_MFMA_V(dp[0], vf[ks & 1], dOf[0][ks]);
-          OPTSTAGE_MFMA_V(dp[1], vf[ks & 1], dOf[1][ks]);
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) OPTSTAGE_MFMA_V(dp[qt], vf[ks & 1], dOf[qt][ks]);
         }
         OPTSTAGE_SB();
 #pragma unroll
         for (int e = 0; e < 16 / NKS; ++e) {
           const int v = (16 / NKS) * ks + e;
 #pragma unroll
-          for (int qt = 0; qt < 2; ++qt) s[qt][v] = __builtin_amdgcn_exp2f(fmaf(s[qt][v], c, Lc[qt]));
+          for (int qt = 0; qt < QT; ++qt) s[qt][v] = __builtin_amdgcn_exp2f(fmaf(s[qt][v], c, Lc[qt]));
         }
       }
       OPTSTAGE_SB();
@@ -573,7 +597,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
         for (int v = 0; v < 16; ++v) {
           const int key = key0 + 8 * (v >> 2) + 4 * g + (v & 3);
 #pragma unroll
-          for (int qt = 0; qt < 2; ++qt)
+          for (int qt = 0; qt < QT; ++qt)
             if (key > qglob[qt]) s[qt][v] = 0.f;
         }
       }
@@ -587,23 +611,27 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 #pragma unroll
       for (int v = 0; v < 8; ++v)
 #pragma unroll
-        for (int qt = 0; qt < 2; ++qt) dp[qt][v] = s[qt][v] * dp[qt][v];
+        for (int qt = 0; qt < QT; ++qt) dp[qt][v] = s[qt][v] * dp[qt][v];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const bf16x8_t d0 = pack8(dp[0], u), d1 = pack8(dp[1], u);
-        bf16x8_t r0, r1;
-        if constexpr (H::SPLIT) { r0 = pack8_rest(dp[0], d0, u); r1 = pack8_rest(dp[1], d1, u); }
+        bf16x8_t d[QT], rest[QT];
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) d[qt] = pack8(dp[qt], u);
+        if constexpr (H::SPLIT) {
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) rest[qt] = pack8_rest(dp[qt], d[qt], u);
+        }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
           const int n = u * NDT + dt;
           OPTSTAGE_SB();
           if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sK, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           OPTSTAGE_SB();
-          acc[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d0, acc[0][dt], 0, 0, 0);
-          acc[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d1, acc[1][dt], 0, 0, 0);
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) acc[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d[qt], acc[qt][dt], 0, 0, 0);
           if constexpr (H::SPLIT) {
-            acc[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, acc[0][dt], 0, 0, 0);
-            acc[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, acc[1][dt], 0, 0, 0);
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) acc[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], rest[qt], acc[qt][dt], 0, 0, 0);
           }
           OPTSTAGE_SB();
           if (u == 0) {
@@ -611,7 +639,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
             for (int e = 0; e < 8 / NDT; ++e) {
               const int v = 8 + (8 / NDT) * dt + e;
 #pragma unroll
-              for (int qt = 0; qt < 2; ++qt) dp[qt][v] = s[qt][v] * dp[qt][v];
+              for (int qt = 0; qt < QT; ++qt) dp[qt][v] = s[qt][v] * dp[qt][v];
             }
           }
         }
@@ -623,7 +651,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 #undef OPTSTAGE_MFMA_0
 #undef OPTSTAGE_SB
 
-  const int nkb = min((q0 + 255) / 64 + 1, (seq + 63) / 64);
+  const int nkb = min((q0 + GQ - 1) / 64 + 1, (seq + 63) / 64);
   issue_block(0, 0);
   for (int kb = 0; kb < nkb; kb += 2) {
     // block kb has landed (this wave's part; the barrier covers the rest) and nobody still reads stage 1
@@ -638,7 +666,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   }
 
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     if (qglob[qt] >= seq) continue;
     bf16_t* dq = dqkv + ((size_t)b * seq + qglob[qt]) * ld + (size_t)a * D;
 #pragma unroll
@@ -653,7 +681,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
   }
 }
 
-// ---- backward, dK / dV: grid (n_kv, batch, ceil(seq / 256)); 4 waves (one per SIMD) ----------------------
+// ---- backward, dK / dV: grid (n_kv, batch, ceil(seq / (128 KT))); 4 waves (one per SIMD); text for KT = 2 ----------------------
 // Wave w owns keys k0 + 64 w .. + 63 as two 32-key tiles: their K operand fragments stay in registers for the
 // whole kernel (the V rows of the workgroup's 256 keys stay in LDS: both operand sets do not fit beside the
 // accumulators) and dK^T, dV^T ([d 128][64 keys] each) in the 256 accumulator registers, so every Q / dO
@@ -669,7 +697,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 // n_kv * batch * ceil(seq / 256) workgroups; `split` > 1 deals the query heads of a group to that many
 // workgroups, each writing an fp32 partial ([part][batch][seq][kv head][K|V][128]) that attn_bwd_dkv_reduce sums
 // in a fixed order.
-template <int D>
+template <int D, int KT>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16_t* __restrict__ dqkv, float* __restrict__ partial, int split,
@@ -680,25 +708,26 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int k0 = blockIdx.z * 256;               // first key blocks (most queries) are dispatched first, for every head
+  constexpr int WK = 32 * KT, GK = 4 * WK;       // keys of a wave, of the workgroup
+  const int k0 = blockIdx.z * GK;               // first key blocks (most queries) are dispatched first, for every head
   const int kvh = blockIdx.x / split, part = blockIdx.x % split, b = blockIdx.y;
   const int ld = (n_q + 2 * n_kv) * D, ldo = n_q * D;
   const bf16_t* base = qkv + (size_t)b * seq * ld;
-  const int wave_first_k = k0 + 64 * wave;
+  const int wave_first_k = k0 + WK * wave;
   const float scale = rsqrtf((float)D), c = scale * LOG2E;
 
   // K, V operand fragments of this wave's keys (rows past the end are clamped: their results are not stored)
-  bf16x8_t Kf[2][NKS];
+  bf16x8_t Kf[KT][NKS];
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
+  for (int kk = 0; kk < KT; ++kk) {
     const int krow = min(wave_first_k + 32 * kk + c32, seq - 1);
     const bf16_t* kp = base + (size_t)krow * ld + (size_t)(n_q + kvh) * D + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) Kf[kk][ks] = *reinterpret_cast<const bf16x8_t*>(kp + 16 * ks);
   }
-  f32x16_t accK[2][NDT], accV[2][NDT];          // [key tile][d tile]: lane = key, registers = d
+  f32x16_t accK[KT][NDT], accV[KT][NDT];          // [key tile][d tile]: lane = key, registers = d
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk)
+  for (int kk = 0; kk < KT; ++kk)
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -748,14 +777,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   const unsigned lds0 = (unsigned)(size_t)(lds_void_t*)smem;
 
   // V rows of this wave's 64 keys -> LDS (16 loads of 4 rows), same layout as the streamed tiles
-  const char* sV = smem + 2 * DKV_STAGE + wave * TILE;
+  const char* sV = smem + 2 * DKV_STAGE + wave * WK * ROWB;
 #pragma unroll
-  for (int j = 0; j < 4 * NLD; ++j) {
+  for (int j = 0; j < 2 * KT * NLD; ++j) {
     const int row = H::RPL * j + lane / H::CH;
     const int chunk = (lane % H::CH) ^ H::swz(row);
     const unsigned vo = ((unsigned)(wave_first_k + row) * (unsigned)ld + (unsigned)(n_q + n_kv + kvh) * D) * 2u + (unsigned)chunk * 16u;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds0 + 2 * DKV_STAGE + wave * TILE + j * 1024), "v"(vo), "s"(rs_q) : "memory", "m0");
+                 :: "s"(lds0 + 2 * DKV_STAGE + wave * WK * ROWB + j * 1024), "v"(vo), "s"(rs_q) : "memory", "m0");
   }
   const int rep = n_q / n_kv / split;                          // query heads of the group handled here
   const int qb0 = k0 / 64, nqb = (seq + 63) / 64 - qb0;       // query blocks at or after the first key
@@ -807,12 +836,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     for (int t = 0; t < 2; ++t) {
       const int q0 = r0 + 32 * t;
       if (q0 + 31 < wave_first_k) continue;                      // wave-uniform
-      const bool edge = q0 < wave_first_k + 63 || q0 + 32 > seq;   // touches the diagonal or the ragged tail
+      const bool edge = q0 < wave_first_k + WK - 1 || q0 + 32 > seq;   // touches the diagonal or the ragged tail
       // lane = key, registers = queries q0 + 8 (v / 4) + 4 g + v % 4
-      f32x16_t s[2], dp[2];
+      f32x16_t s[KT], dp[KT];
       f32x4_t nL[4];                                               // -lse * log2(e) of this lane's queries
       f32x16_t negD;                                               // -D of this lane's queries, in accumulator order
-      bf16x8_t qf[2], df[2], vf[2][2];
+      bf16x8_t qf[2], df[2], vf[2][KT];
       // ---- S = Q K^T: fragment of k-step ks + 1 requested before the MFMAs of k-step ks
       qf[0] = rm_frag(sQ, t, 0);
 #pragma unroll
@@ -822,8 +851,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
           qf[(ks + 1) & 1] = rm_frag(sQ, t, ks + 1);
         } else {
           df[0] = rm_frag(sDO, t, 0);
-          vf[0][0] = rm_frag(sV, 0, 0);
-          vf[0][1] = rm_frag(sV, 1, 0);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) vf[0][kk] = rm_frag(sV, kk, 0);
         }
         if (ks < 4) nL[ks] = *reinterpret_cast<const f32x4_t*>(sL + 32 * t + 8 * ks + 4 * g);
         if (ks >= NKS - 4) {
@@ -833,11 +862,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
         }
         OPTSTAGE_SB();
         if (ks == 0) {                                             // the first k-step starts from C = 0
-          OPTSTAGE_MFMA_0(s[0], qf[0], Kf[0][0]);
-          OPTSTAGE_MFMA_0(s[1], qf[0], Kf[1][0]);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) OPTSTAGE_MFMA_0(s[kk], qf[0], Kf[kk][0]);
         } else {
-          OPTSTAGE_MFMA_V(s[0], qf[ks & 1], Kf[0][ks]);
-          OPTSTAGE_MFMA_V(s[1], qf[ks & 1], Kf[1][ks]);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) OPTSTAGE_MFMA_V(s[kk], qf[ks & 1], Kf[kk][ks]);
         }
         OPTSTAGE_SB();
         if (ks >= NKS - 4) {
@@ -851,23 +880,26 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
         OPTSTAGE_SB();
         if (ks < NKS - 1) {
           df[(ks + 1) & 1] = rm_frag(sDO, t, ks + 1);
-          vf[(ks + 1) & 1][0] = rm_frag(sV, 0, ks + 1);
-          vf[(ks + 1) & 1][1] = rm_frag(sV, 1, ks + 1);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) vf[(ks + 1) & 1][kk] = rm_frag(sV, kk, ks + 1);
         }
         OPTSTAGE_SB();
         if (ks == 0) {                                             // dP - D: the first k-step starts from C = -D
-          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[0]) : "v"(df[0]), "v"(vf[0][0]), "v"(negD));
-          asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[1]) : "v"(df[0]), "v"(vf[0][1]), "v"(negD));
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk)
+            asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp[kk]) : "v"(df[0]), "v"(vf[0][kk]), "v"(negD));
+          // the exponentials read S a few cycles after the matrix unit has written it: a second key tile's MFMA is that long
+          if (KT == 1) asm volatile("s_nop 7" ::: "memory");
         } else {
-          OPTSTAGE_MFMA_V(dp[0], df[ks & 1], vf[ks & 1][0]);
-          OPTSTAGE_MFMA_V(dp[1], df[ks & 1], vf[ks & 1][1]);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) OPTSTAGE_MFMA_V(dp[kk], df[ks & 1], vf[ks & 1][kk]);
         }
         OPTSTAGE_SB();
 #pragma unroll
         for (int e = 0; e < 16 / NKS; ++e) {
           const int v = (16 / NKS) * ks + e;
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk) s[kk][v] = __builtin_amdgcn_exp2f(fmaf(s[kk][v], c, nL[v >> 2][v & 3]));
+          for (int kk = 0; kk < KT; ++kk) s[kk][v] = __builtin_amdgcn_exp2f(fmaf(s[kk][v], c, nL[v >> 2][v & 3]));
         }
       }
       OPTSTAGE_SB();
@@ -876,7 +908,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
         for (int v = 0; v < 16; ++v) {
           const int qg = q0 + 8 * (v >> 2) + 4 * g + (v & 3);
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk)
+          for (int kk = 0; kk < KT; ++kk)
             if (qg < wave_first_k + 32 * kk + c32 || qg >= seq) s[kk][v] = 0.f;
         }
       }
@@ -886,9 +918,13 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
       trf[0] = tr_frag(sDO, 0, t, 0);
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const bf16x8_t p0 = pack8(s[0], u), p1 = pack8(s[1], u);
-        bf16x8_t r0, r1;
-        if constexpr (H::SPLIT) { r0 = pack8_rest(s[0], p0, u); r1 = pack8_rest(s[1], p1, u); }
+        bf16x8_t p[KT], rest[KT];
+#pragma unroll
+        for (int kk = 0; kk < KT; ++kk) p[kk] = pack8(s[kk], u);
+        if constexpr (H::SPLIT) {
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) rest[kk] = pack8_rest(s[kk], p[kk], u);
+        }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
           const int n = u * NDT + dt;
@@ -896,38 +932,43 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
           if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sDO, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           else trf[0] = tr_frag(sQ, 0, t, 0);
           OPTSTAGE_SB();
-          accV[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], p0, accV[0][dt], 0, 0, 0);
-          accV[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], p1, accV[1][dt], 0, 0, 0);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) accV[kk][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], p[kk], accV[kk][dt], 0, 0, 0);
           if constexpr (H::SPLIT) {
-            accV[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, accV[0][dt], 0, 0, 0);
-            accV[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, accV[1][dt], 0, 0, 0);
+#pragma unroll
+            for (int kk = 0; kk < KT; ++kk) accV[kk][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], rest[kk], accV[kk][dt], 0, 0, 0);
           }
           OPTSTAGE_SB();
+          if (KT == 1 && n == 0) asm volatile("s_nop 7" ::: "memory");   // dP has left the matrix unit
 #pragma unroll
           for (int e = 0; e < 8 / NDT; ++e) {
             const int v = (8 / NDT) * n + e;
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk) dp[kk][v] = s[kk][v] * dp[kk][v];
+            for (int kk = 0; kk < KT; ++kk) dp[kk][v] = s[kk][v] * dp[kk][v];
           }
         }
       }
       // ---- dK^T += Q^T dS
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const bf16x8_t d0 = pack8(dp[0], u), d1 = pack8(dp[1], u);
-        bf16x8_t r0, r1;
-        if constexpr (H::SPLIT) { r0 = pack8_rest(dp[0], d0, u); r1 = pack8_rest(dp[1], d1, u); }
+        bf16x8_t d[KT], rest[KT];
+#pragma unroll
+        for (int kk = 0; kk < KT; ++kk) d[kk] = pack8(dp[kk], u);
+        if constexpr (H::SPLIT) {
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) rest[kk] = pack8_rest(dp[kk], d[kk], u);
+        }
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
           const int n = u * NDT + dt;
           OPTSTAGE_SB();
           if (n < 2 * NDT - 1) trf[(n + 1) & 1] = tr_frag(sQ, (dt + 1) % NDT, t, dt == NDT - 1 ? 1 : u);
           OPTSTAGE_SB();
-          accK[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d0, accK[0][dt], 0, 0, 0);
-          accK[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d1, accK[1][dt], 0, 0, 0);
+#pragma unroll
+          for (int kk = 0; kk < KT; ++kk) accK[kk][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], d[kk], accK[kk][dt], 0, 0, 0);
           if constexpr (H::SPLIT) {
-            accK[0][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r0, accK[0][dt], 0, 0, 0);
-            accK[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], r1, accK[1][dt], 0, 0, 0);
+#pragma unroll
+            for (int kk = 0; kk < KT; ++kk) accK[kk][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(trf[n & 1], rest[kk], accK[kk][dt], 0, 0, 0);
           }
         }
       }
@@ -952,7 +993,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   }
 
 #pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
+  for (int kk = 0; kk < KT; ++kk) {
     const int kglob = wave_first_k + 32 * kk + c32;
     if (kglob >= seq) continue;
     if (split > 1) {
@@ -1031,24 +1072,25 @@ bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void*
 }
 
 namespace {
-template <int D> hipError_t fwd_d(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+template <int D, int QT> hipError_t fwd_d(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s) {
   constexpr int smem = 3 * 2 * Head<D>::TILE;
   static LdsAttrOnce lds_attr;
-  auto kern = attn_fwd_mfma<D>;
+  auto kern = attn_fwd_mfma<D, QT>;
   if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(n_q, batch, (seq + 255) / 256), dim3(256), smem, s, (const bf16_t*)qkv, (bf16_t*)o, lse, seq, n_q, n_kv);
+  hipLaunchKernelGGL(kern, dim3(n_q, batch, (seq + 128 * QT - 1) / (128 * QT)), dim3(256), smem, s, (const bf16_t*)qkv, (bf16_t*)o, lse, seq, n_q, n_kv);
   return hipGetLastError();
 }
 
-template <int D> hipError_t bwd_d(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                  int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
+                                         int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+  constexpr int G = 128 * T;                                  // rows of a workgroup
   hipError_t e;
-  constexpr int dq_smem = 2 * 2 * Head<D>::TILE, dkv_smem = 2 * (2 * Head<D>::TILE + 512) + 4 * Head<D>::TILE;
+  constexpr int dq_smem = 2 * 2 * Head<D>::TILE, dkv_smem = 2 * (2 * Head<D>::TILE + 512) + 2 * T * Head<D>::TILE;
   static LdsAttrOnce dq_attr, dkv_attr;
-  auto dq = attn_bwd_dq_mfma<D>;
-  auto dkv = attn_bwd_dkv_mfma<D>;
+  auto dq = attn_bwd_dq_mfma<D, T>;
+  auto dkv = attn_bwd_dkv_mfma<D, T>;
   if ((e = dq_attr.ensure(reinterpret_cast<const void*>(dq), dq_smem)) != hipSuccess) return e;
-  hipLaunchKernelGGL(dq, dim3(n_q, batch, (seq + 255) / 256), dim3(256), dq_smem, s, (const bf16_t*)qkv,
+  hipLaunchKernelGGL(dq, dim3(n_q, batch, (seq + G - 1) / G), dim3(256), dq_smem, s, (const bf16_t*)qkv,
       (const bf16_t*)o, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, seq, n_q, n_kv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1056,7 +1098,7 @@ template <int D> hipError_t bwd_d(const void* qkv, const void* o, const void* do
   // partials of several workgroups per kv head need scratch that callers have for head size 128 only
   const int split = D == 128 ? attn_dkv_split(seq, batch, n_q, n_kv) : 1;
   float* partial = ws + (size_t)batch * n_q * seq;            // behind the D array
-  hipLaunchKernelGGL(dkv, dim3(n_kv * split, batch, (seq + 255) / 256), dim3(256), dkv_smem, s,
+  hipLaunchKernelGGL(dkv, dim3(n_kv * split, batch, (seq + G - 1) / G), dim3(256), dkv_smem, s,
       (const bf16_t*)qkv, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, partial, split, seq, n_q, n_kv);
   if (split > 1) {
     e = hipGetLastError();
@@ -1067,14 +1109,25 @@ template <int D> hipError_t bwd_d(const void* qkv, const void* o, const void* do
   }
   return hipGetLastError();
 }
+// One 32-row tile per wave (128 rows per workgroup) or two (256).  Two feed every fragment read from LDS to two MFMAs, which is
+// what a full chip wants; with at most one such workgroup per compute unit the longest row of the causal triangle sets the time,
+// and halving the workgroups halves its share.  Forward / backward us, two -> one tile: 1237 tokens x 3, 16 / 4 heads (240
+// workgroups) 46.6 / 146 -> 38.8 / 115, 8192 tokens, 8 / 1 heads (256) 233 / 681 -> 177 / 516, 320 tokens, 8 / 2 heads (16) 17.3 /
+// 51 -> 10.7 / 31; 2000 tokens, 40 heads (320) 67.5 / 198 -> 73.4 / 185, 1024 tokens x 8 (512) 62.8 / 204 -> 76.9 / 216.
+// Heads of 64, which leave registers for two waves per SIMD, always take one: 4096 tokens, 32 heads (512) 156 / 407 -> 133 / 376.
+constexpr long FWD_WGS = 256, BWD_WGS = 320;
+long wide_workgroups(int seq, int batch, int n_q) { return (long)n_q * batch * ((seq + 255) / 256); }
 }  // namespace
 
 hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
-  return d == 128 ? fwd_d<128>(qkv, o, lse, seq, batch, n_q, n_kv, s) : fwd_d<64>(qkv, o, lse, seq, batch, n_q, n_kv, s);
+  if (d == 64) return fwd_d<64, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s);
+  return wide_workgroups(seq, batch, n_q) <= FWD_WGS ? fwd_d<128, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s)
+                                                     : fwd_d<128, 2>(qkv, o, lse, seq, batch, n_q, n_kv, s);
 }
 
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
                                 int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
-  return d == 128 ? bwd_d<128>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s)
-                  : bwd_d<64>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
+  if (d == 64) return bwd_d<64, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
+  return wide_workgroups(seq, batch, n_q) <= BWD_WGS ? bwd_d<128, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s)
+                                                     : bwd_d<128, 2>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
 }

@@ -392,6 +392,35 @@ def test_attention_fwd_bwd(dtype, seq, batch, nq, nkv, d):
             assert rel_err(dq_g[sl, lo:hi], ref[:, lo:hi]) < TOL[dtype], (lo, hi)
 
 
+# Both tile counts of the kernels for heads of 128: one 32-row tile per wave while there is at most a workgroup of 256 rows per
+# compute unit, two above; ragged ends, grouped heads (partials of several workgroups per kv head), several sequences.
+@pytest.mark.parametrize("seq,batch,nq,nkv", [(127, 1, 2, 2), (129, 2, 4, 1), (257, 1, 256, 256), (257, 1, 64, 8), (33, 5, 64, 64), (257, 3, 128, 128)])
+def test_attention_with_one_and_two_tiles_per_wave(seq, batch, nq, nkv):
+    d, rows, w = 128, seq * batch, (nq + 2 * nkv) * 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    QKV = torch.randn((rows, w), generator=g, device="cuda").bfloat16()
+    DO = torch.randn((rows, nq * d), generator=g, device="cuda").bfloat16()
+    Ot, DQKV = torch.empty_like(DO), torch.full_like(QKV, float("nan"))
+    LSE = torch.empty(batch * nq * seq, dtype=torch.float32, device="cuda")
+    WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, batch, nq, nkv, d), dtype=torch.float32, device="cuda")
+    ok(lib().optstage_op_attn_fwd(BF16, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    ok(lib().optstage_op_attn_bwd(BF16, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(DQKV).all()) and bool(torch.isfinite(Ot).all())
+    qkv, o_g, do, dq_g = host(QKV), host(Ot), host(DO), host(DQKV)
+    rep = nq // nkv
+    for b, kvh in ((0, 0), (batch - 1, nkv - 1)):          # a whole group of the first and of the last sequence
+        sl, hs = slice(b * seq, (b + 1) * seq), slice(kvh * rep * d, (kvh + 1) * rep * d)
+        ks, vs = (slice((nq + x * nkv + kvh) * d, (nq + x * nkv + kvh + 1) * d) for x in (0, 1))
+        qq, kk, vv = qkv[sl, hs].reshape(seq, rep, d), qkv[sl, ks].reshape(seq, 1, d), qkv[sl, vs].reshape(seq, 1, d)
+        o, _ = O.attention_fwd(qq, kk, vv)
+        assert rms_err(o_g[sl, hs], o.reshape(seq, -1)) < TOL[BF16] / 4
+        dq, dk, dv = O.attention_bwd(qq, kk, vv, o_g[sl, hs].reshape(seq, rep, d), do[sl, hs].reshape(seq, rep, d))
+        for got, ref in ((dq_g[sl, hs], dq), (dq_g[sl, ks], dk), (dq_g[sl, vs], dv)):
+            assert rms_err(got, ref.reshape(seq, -1)) < TOL[BF16] / 4
+
+
 # Heads of 64: edges of the 32- and 64-wide tiles and of the 256 rows of a workgroup, one row, grouped heads, several sequences,
 # peaked and flat scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  The second
 # products multiply fp32 probabilities (16 bits of fraction at least), so what is left is the rounding of the results to 8
