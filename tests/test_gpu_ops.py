@@ -185,6 +185,33 @@ def test_gemm_grouped_equals_one_by_one_and_the_oracle():
     assert lib().optstage_op_gemm_grouped(B.GEMM_TN, B.EPI_ACCUM, len(shapes), C.cast(probs, C.c_void_p), 72, stream()) == B.E_ARG
 
 
+@pytest.mark.parametrize("shapes,K", [([(4096, 4200)], 64), ([(4096, 4096), (1024, 1032)], 128), ([(2048, 8192), (512, 1000), (8192, 264)], 64)])
+def test_gemm_grouped_with_a_short_last_round(shapes, K):
+    """Sets of one round of 256 tiles and a few more, whose last columns go to the small kernels: bitwise each product
+    on its own, for every epilogue, ragged last column included."""
+    import ctypes as C
+    for epi, dt in ((B.EPI_ACCUM, torch.float32), (3, torch.float32), (B.EPI_STORE, torch.bfloat16)):
+        probs, keep = (B.GemmProblem * len(shapes))(), []
+        for i, (M, N) in enumerate(shapes):
+            g = torch.Generator(device="cuda")
+            g.manual_seed(17 * i + K)
+            DY, X = (torch.randn((K, x), generator=g, device="cuda").bfloat16() for x in (M, N))
+            grouped = torch.full((M, N + 8), 2.0, dtype=dt, device="cuda")
+            single = grouped.clone()
+            ok(lib().optstage_op_gemm(BF16, B.GEMM_TN, epi, DY.data_ptr(), X.data_ptr(), single.data_ptr(), 0, M, N, K, M, N, N + 8, stream()))
+            probs[i].A, probs[i].B, probs[i].C, probs[i].R = DY.data_ptr(), X.data_ptr(), grouped.data_ptr(), 0
+            probs[i].M, probs[i].N, probs[i].lda, probs[i].ldb, probs[i].ldc = M, N, M, N, N + 8
+            keep.append((DY, X, grouped, single))
+        ok(lib().optstage_op_gemm_grouped(B.GEMM_TN, epi, len(shapes), C.cast(probs, C.c_void_p), K, stream()))
+        torch.cuda.synchronize()
+        for DY, X, grouped, single in keep:
+            assert torch.equal(grouped, single), epi
+            rows = [0, 255, grouped.shape[0] - 1]
+            ref = host(DY)[:, rows].T @ host(X) + (2.0 if epi == B.EPI_ACCUM else 0.0)
+            assert rel_err(host(grouped)[rows, : X.shape[1]], ref) < (TOL[BF16] / 4 if epi == B.EPI_STORE else 1e-5)
+            assert float((grouped[:, X.shape[1]:].float() - 2.0).abs().max()) == 0.0
+
+
 def slabs_of(w):
     """[N, K] -> the slab layout of layout code 2: slab (n // 256, k // 64) holds rows 256 x columns 64, row-major,
     slabs ordered by (n // 256, k // 64); rows padded to a multiple of 256."""
