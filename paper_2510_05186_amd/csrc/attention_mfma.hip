@@ -227,8 +227,9 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
             for (int y = 0; y < QT; ++y) ls[y] += cur[y][v];
             // keeps these instructions here, between the MFMAs: without a use at this point the compiler sinks
             // them to where the probabilities are packed
-#pragma unroll
-            for (int y = 0; y < QT; ++y) asm volatile("" : "+v"(cur[y][v]), "+v"(ls[y]));
+            // (one statement for both tiles: between two, the hardware wants a wait for the exponential)
+            if constexpr (QT == 2) asm volatile("" : "+v"(cur[0][v]), "+v"(cur[QT - 1][v]), "+v"(ls[0]), "+v"(ls[QT - 1]));
+            else asm volatile("" : "+v"(cur[0][v]), "+v"(ls[0]));
           }
         }
         OPTSTAGE_SB();
