@@ -15,9 +15,12 @@
 //           output tile 4 h + i, whose row r is column 64 h + 4 r + i.  Rows 4 g + e are where the probabilities of MFMA e sit: a lane
 //           holds D[4 g + e][r], which is B[k g][column r] for the contraction over 4 g + e.
 //  Result   tile 4 h + i, register v: column 64 h + 4 (4 g + v) + i of row r, i.e. 4 consecutive columns over i.
+// A tile on the diagonal multiplies keys above it by a probability of zero, and rows past the end repeat the last one: with finite
+// operands that adds nothing, with others it makes NaN of rows that do not depend on them.  Where a result is not finite the
+// workgroup therefore redoes its rows one by one (attention_rows.h): one barrier more, nothing else, for finite ones.
 // Measured (us, general kernels -> these): 512 tokens, 16 heads of 64: forward 188 -> 17.8, dQ 275 -> 19.5, dK / dV 286 -> 29.5;
 // 128 tokens, 4 heads: 35.1 -> 7.0, 21.2 -> 7.4, 22.0 -> 9.0.
-#include "common.h"
+#include "attention_rows.h"
 
 namespace {
 
@@ -77,6 +80,10 @@ template <int D> struct F32 {
   }
 };
 
+__device__ __forceinline__ bool all_finite(const f32x4_t& v) {
+  const float z = (v[0] * 0.f + v[1] * 0.f) + (v[2] * 0.f + v[3] * 0.f);   // 0 times infinity or NaN is NaN
+  return z == 0.f;
+}
 // sum or maximum over the four lanes that hold a column's rows
 __device__ __forceinline__ float sum_g(float x) { x += __shfl_xor(x, 16, 64); return x + __shfl_xor(x, 32, 64); }
 __device__ __forceinline__ float max_g(float x) { x = fmaxf(x, __shfl_xor(x, 16, 64)); return fmaxf(x, __shfl_xor(x, 32, 64)); }
@@ -88,6 +95,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const float* __restrict__ qk
   typedef F32<D> F;
   __shared__ __attribute__((aligned(16))) float part[4][ROWS][D + 4];
   __shared__ float pm[4][ROWS], pl[4][ROWS];
+  __shared__ int redo;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   const int tile = gridDim.z - 1 - blockIdx.z, a = blockIdx.x, b = blockIdx.y, kvh = a * n_kv / n_q;
   const int q0 = tile * ROWS, last = seq - 1;
@@ -126,9 +134,13 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const float* __restrict__ qk
   l = sum_g(l);
   F::put(part[wave], acc, g, r);
   if (g == 0) { pm[wave][r] = m; pl[wave][r] = l; }
+  if (threadIdx.x == 0) redo = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < ROWS * D / 4; i += 256) {
-    const int row = i / (D / 4), c = (i % (D / 4)) * 4, t = q0 + row;
+  f32x4_t out[F::H];
+  float ls[F::H];
+#pragma unroll
+  for (int h = 0; h < F::H; ++h) {
+    const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4;
     const float M = fmaxf(fmaxf(pm[0][row], pm[1][row]), fmaxf(pm[2][row], pm[3][row]));
     float L = 0.f;
     f32x4_t v = {0.f, 0.f, 0.f, 0.f};
@@ -140,11 +152,24 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const float* __restrict__ qk
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += x[e] * f;
     }
-    if (t >= seq) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] /= L;
-    *reinterpret_cast<f32x4_t*>(o + ((size_t)b * seq + t) * ((size_t)n_q * D) + (size_t)a * D + c) = v;
-    if (c == 0) lse[((size_t)b * n_q + a) * seq + t] = M + logf(L);
+    out[h] = v;
+    ls[h] = M + logf(L);
+    if (q0 + row < seq && !(all_finite(v) && fabsf(ls[h]) < INFINITY)) redo = 1;
+  }
+  __syncthreads();
+  if (redo) {
+    for (int row = wave; row < ROWS && q0 + row < seq; row += 4)
+      attn_fwd_row<float, F::H>(qkv, o, lse, seq, n_q, n_kv, q0 + row, a, b, &part[wave][0][0]);
+    return;
+  }
+#pragma unroll
+  for (int h = 0; h < F::H; ++h) {
+    const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4, t = q0 + row;
+    if (t >= seq) continue;
+    *reinterpret_cast<f32x4_t*>(o + ((size_t)b * seq + t) * ((size_t)n_q * D) + (size_t)a * D + c) = out[h];
+    if (c == 0) lse[((size_t)b * n_q + a) * seq + t] = ls[h];
   }
 }
 
@@ -155,6 +180,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__
                                                        float* __restrict__ dqkv, float* __restrict__ Dws, int seq, int n_q, int n_kv) {
   typedef F32<D> F;
   __shared__ __attribute__((aligned(16))) float part[4][ROWS][D + 4];
+  __shared__ int redo;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   const int tile = gridDim.z - 1 - blockIdx.z, a = blockIdx.x, b = blockIdx.y, kvh = a * n_kv / n_q;
   const int q0 = tile * ROWS, last = seq - 1, row_q = min(q0 + r, last);
@@ -189,15 +215,27 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__
     F::accumulate(acc, kc, ds);
   }
   F::put(part[wave], acc, g, r);
+  if (threadIdx.x == 0) redo = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < ROWS * D / 4; i += 256) {
-    const int row = i / (D / 4), c = (i % (D / 4)) * 4, t = q0 + row;
-    if (t >= seq) continue;
-    f32x4_t v;
+  f32x4_t out[F::H];
+#pragma unroll
+  for (int h = 0; h < F::H; ++h) {
+    const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      v[e] = (((part[0][row][c + e] + part[1][row][c + e]) + part[2][row][c + e]) + part[3][row][c + e]) * scale;
-    *reinterpret_cast<f32x4_t*>(dqkv + ((size_t)b * seq + t) * ld + (size_t)a * D + c) = v;
+      out[h][e] = (((part[0][row][c + e] + part[1][row][c + e]) + part[2][row][c + e]) + part[3][row][c + e]) * scale;
+    if (q0 + row < seq && !all_finite(out[h])) redo = 1;
+  }
+  __syncthreads();
+  if (redo) {
+    for (int row = wave; row < ROWS && q0 + row < seq; row += 4)
+      attn_bwd_dq_row<float, F::H>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, q0 + row, a, b, &part[wave][0][0], &part[wave][2][0]);
+    return;
+  }
+#pragma unroll
+  for (int h = 0; h < F::H; ++h) {
+    const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4, t = q0 + row;
+    if (t < seq) *reinterpret_cast<f32x4_t*>(dqkv + ((size_t)b * seq + t) * ld + (size_t)a * D + c) = out[h];
   }
 }
 
@@ -208,6 +246,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict_
                                                         float* __restrict__ dqkv, int seq, int n_q, int n_kv) {
   typedef F32<D> F;
   __shared__ __attribute__((aligned(16))) float part[4][ROWS][D + 4];
+  __shared__ int redo;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
   const int tile = blockIdx.z, kvh = blockIdx.x, b = blockIdx.y, k0 = tile * ROWS, last = seq - 1;
   const size_t ld = (size_t)(n_q + 2 * n_kv) * D, ldo = (size_t)n_q * D;
@@ -240,23 +279,37 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict_
     F::columns(c, Qp, ld, 16 * t, last, g, r);
     F::accumulate(ak, c, ds);
   }
+  if (threadIdx.x == 0) redo = 0;
+  f32x4_t out[2][F::H];
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     if (which) __syncthreads();
     F::put(part[wave], which ? av : ak, g, r);
     __syncthreads();
-    for (int i = threadIdx.x; i < ROWS * D / 4; i += 256) {
-      const int row = i / (D / 4), c = (i % (D / 4)) * 4, t = k0 + row;
-      if (t >= seq) continue;
-      f32x4_t x;
+#pragma unroll
+    for (int h = 0; h < F::H; ++h) {
+      const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        x[e] = ((part[0][row][c + e] + part[1][row][c + e]) + part[2][row][c + e]) + part[3][row][c + e];
-        if (!which) x[e] *= scale;
+        const float x = ((part[0][row][c + e] + part[1][row][c + e]) + part[2][row][c + e]) + part[3][row][c + e];
+        out[which][h][e] = which ? x : x * scale;
       }
-      *reinterpret_cast<f32x4_t*>(dqkv + ((size_t)b * seq + t) * ld + (size_t)(n_q + which * n_kv + kvh) * D + c) = x;
+      if (k0 + row < seq && !all_finite(out[which][h])) redo = 1;
     }
   }
+  __syncthreads();
+  if (redo) {
+    for (int row = wave; row < ROWS && k0 + row < seq; row += 4)
+      attn_bwd_dkv_row<float, F::H, false>(qkv, dout, lse, Dws, dqkv, seq, n_q, n_kv, k0 + row, kvh, b, &part[wave][0][0], &part[wave][2][0]);
+    return;
+  }
+#pragma unroll
+  for (int which = 0; which < 2; ++which)
+#pragma unroll
+    for (int h = 0; h < F::H; ++h) {
+      const int i = threadIdx.x + 256 * h, row = i / (D / 4), c = (i % (D / 4)) * 4, t = k0 + row;
+      if (t < seq) *reinterpret_cast<f32x4_t*>(dqkv + ((size_t)b * seq + t) * ld + (size_t)(n_q + which * n_kv + kvh) * D + c) = out[which][h];
+    }
 }
 
 }  // namespace

@@ -11,7 +11,12 @@
 // Tiles go from global memory straight into LDS, row-major; operands that are contracted over their row
 // index (V^T, K^T, dO^T, Q^T) come out of the same tile through transposing LDS reads.  All LDS tiles are
 // XOR-swizzled so that both kinds of operand reads are bank-conflict free.
-#include "common.h"
+//
+// Tiles are multiplied whole: what causality leaves out enters as zero times a row, which is NaN where that row is not finite, and an
+// infinity that does belong to a row meets both parts of a split probability.  Heads of 64 keep such values to the rows that
+// depend on them: a wave that finds a result that is not finite redoes its rows one by one (attention_rows.h).  Heads of 128 do
+// not: there one such value makes NaN of up to 256 rows around it.
+#include "attention_rows.h"
 
 namespace {
 
@@ -30,6 +35,10 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 template <int D> struct Head {
   static constexpr int ROWB = 2 * D, TILE = 64 * ROWB, CH = D / 8, NKS = D / 16, NDT = D / 32, RPL = 64 / CH, NLD = 16 / RPL;
   static constexpr bool SPLIT = D == 64;
+  // rows with a result that is not finite are redone one by one (needs all of a key's queries in one workgroup: split == 1);
+  // ROW_LDS: bytes of LDS that they need behind the tiles, two rows of fp32 per wave
+  static constexpr bool ROW_EXACT = D == 64;
+  static constexpr int ROW_LDS = ROW_EXACT ? 4 * 2 * D * 4 : 0;
   // 16-byte chunk c of tile row r is stored at chunk c ^ swz(r).  Row reads: the 16 rows that a pass touches at one chunk fall on
   // all banks; transposing reads: the 4 rows of one differ in the 64-byte group (D = 64: so do rows two apart, which share
   // the half of the 256-byte bank window)
@@ -50,6 +59,13 @@ __device__ __forceinline__ bf16x8_t pack8_rest(const f32x16_t& s, const bf16x8_t
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = (bf16_t)(s[8 * u + e] - (float)hi[e]);
   return r;
+}
+
+// NaN where any of the values is not finite, 0 otherwise
+__device__ __forceinline__ float not_finite(const f32x16_t& s, float z = 0.f) {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) z = fmaf(s[v], 0.f, z);
+  return z;
 }
 
 // max over the two lanes 32 apart (the two halves of a score row), in both of them: v_permlane32_swap exchanges
@@ -380,8 +396,18 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   for (int qt = 0; qt < QT; ++qt) lt[qt] = lsum[qt] + __shfl_xor(lsum[qt], 32, 64);
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
+    const float inv = 1.f / lt[qt], row_lse = mref[qt] * scale + logf(lt[qt]);
+    if constexpr (H::ROW_EXACT) {
+      float z = fmaf(row_lse, 0.f, inv * 0.f);
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) z = not_finite(acc[qt][dt], z);
+      if (__any(qglob[qt] < seq && z != 0.f)) {
+        for (int t = wave_first_q + 32 * qt; t < min(wave_first_q + 32 * qt + 32, seq); ++t)
+          attn_fwd_row<bf16_t, D / 64>(qkv, o, lse, seq, n_q, n_kv, t, a, b, reinterpret_cast<float*>(smem + 3 * FWD_STAGE) + wave * D);
+        continue;
+      }
+    }
     if (qglob[qt] >= seq) continue;
-    const float inv = 1.f / lt[qt];
     bf16_t* orow = o + ((size_t)b * seq + qglob[qt]) * ldo + (size_t)a * D;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt) {
@@ -394,7 +420,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
         *reinterpret_cast<bf16x4_t*>(orow + 32 * dt + 8 * j + 4 * g) = r;
       }
     }
-    if (g == 0) lse[((size_t)b * n_q + a) * seq + qglob[qt]] = mref[qt] * scale + logf(lt[qt]);
+    if (g == 0) lse[((size_t)b * n_q + a) * seq + qglob[qt]] = row_lse;
   }
 #undef OPTSTAGE_SB
 }
@@ -668,6 +694,17 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
+    if constexpr (H::ROW_EXACT) {
+      float z = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) z = not_finite(acc[qt][dt], z);
+      if (__any(qglob[qt] < seq && z != 0.f)) {
+        float* own = reinterpret_cast<float*>(smem + 2 * DQ_STAGE) + wave * 2 * D;
+        for (int t = wave_first_q + 32 * qt; t < min(wave_first_q + 32 * qt + 32, seq); ++t)
+          attn_bwd_dq_row<bf16_t, D / 64>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, t, a, b, own, own + D);
+        continue;
+      }
+    }
     if (qglob[qt] >= seq) continue;
     bf16_t* dq = dqkv + ((size_t)b * seq + qglob[qt]) * ld + (size_t)a * D;
 #pragma unroll
@@ -996,6 +1033,17 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
 #pragma unroll
   for (int kk = 0; kk < KT; ++kk) {
     const int kglob = wave_first_k + 32 * kk + c32;
+    if constexpr (H::ROW_EXACT) {
+      float z = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) z = not_finite(accV[kk][dt], not_finite(accK[kk][dt], z));
+      if (__any(kglob < seq && z != 0.f)) {
+        float* own = reinterpret_cast<float*>(smem + 2 * DKV_STAGE + 4 * WK * ROWB) + wave * 2 * D;
+        for (int t = wave_first_k + 32 * kk; t < min(wave_first_k + 32 * kk + 32, seq); ++t)
+          attn_bwd_dkv_row<bf16_t, D / 64, true>(qkv, dout, lse, delta, dqkv, seq, n_q, n_kv, t, kvh, b, own, own + D);
+        continue;
+      }
+    }
     if (kglob >= seq) continue;
     if (split > 1) {
       float* prow = partial + ((((size_t)part * gridDim.y + b) * seq + kglob) * n_kv + kvh) * 2 * D;
@@ -1074,7 +1122,7 @@ bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void*
 
 namespace {
 template <int D, int QT> hipError_t fwd_d(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, hipStream_t s) {
-  constexpr int smem = 3 * 2 * Head<D>::TILE;
+  constexpr int smem = 3 * 2 * Head<D>::TILE + Head<D>::ROW_LDS;
   static LdsAttrOnce lds_attr;
   auto kern = attn_fwd_mfma<D, QT>;
   if (hipError_t e = lds_attr.ensure(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
@@ -1086,7 +1134,8 @@ template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const v
                                          int seq, int batch, int n_q, int n_kv, hipStream_t s) {
   constexpr int G = 128 * T;                                  // rows of a workgroup
   hipError_t e;
-  constexpr int dq_smem = 2 * 2 * Head<D>::TILE, dkv_smem = 2 * (2 * Head<D>::TILE + 512) + 2 * T * Head<D>::TILE;
+  constexpr int dq_smem = 2 * 2 * Head<D>::TILE + Head<D>::ROW_LDS;
+  constexpr int dkv_smem = 2 * (2 * Head<D>::TILE + 512) + 2 * T * Head<D>::TILE + Head<D>::ROW_LDS;
   static LdsAttrOnce dq_attr, dkv_attr;
   auto dq = attn_bwd_dq_mfma<D, T>;
   auto dkv = attn_bwd_dkv_mfma<D, T>;

@@ -528,6 +528,58 @@ def test_attention_fp32(seq, batch, nq, nkv, d, gain, shift):
         assert np.max(np.abs(dq_g[sl] - ref)) < 1e-5 * np.max(np.abs(ref)) * max(1.0, gain * gain)
 
 
+def attention_by_rows(qkv, do, seq, nq, nkv, d):
+    """fp64 attention of one sequence in which a row multiplies the keys up to its own and nothing else, so that a value that is
+    not finite reaches exactly the rows that depend on it: o, lse, dqkv, and dqkv from the o that is passed."""
+    qkv, do = torch.from_numpy(qkv), torch.from_numpy(do)
+    head = lambda i: qkv[:, i * d:(i + 1) * d]  # noqa: E731
+    o, lse, dqkv = torch.zeros(seq, nq * d, dtype=torch.float64), torch.zeros(nq, seq, dtype=torch.float64), torch.zeros_like(qkv)
+    for a in range(nq):
+        g = a * nkv // nq
+        Q, K, V, dO = head(a), head(nq + g), head(nq + nkv + g), do[:, a * d:(a + 1) * d]
+        dk, dv = (dqkv[:, (nq + x * nkv + g) * d:(nq + x * nkv + g + 1) * d] for x in (0, 1))
+        for t in range(seq):
+            s = (K[:t + 1] * Q[t]).sum(1) / np.sqrt(d)
+            m = s[~s.isnan()].max() if bool((~s.isnan()).any()) else s.max()
+            e = torch.exp(s - m)
+            p = e / e.sum()
+            row = (p[:, None] * V[:t + 1]).sum(0)
+            o[t, a * d:(a + 1) * d], lse[a, t] = row, m + torch.log(e.sum())
+            ds = p * ((V[:t + 1] * dO[t]).sum(1) - (row * dO[t]).sum()) / np.sqrt(d)
+            dqkv[t, a * d:(a + 1) * d] = (ds[:, None] * K[:t + 1]).sum(0)
+            dk[:t + 1] += ds[:, None] * Q[t]
+            dv[:t + 1] += p[:, None] * dO[t]
+    return o.numpy(), lse.numpy(), dqkv.numpy()
+
+
+# A value that is not finite stays with the rows that depend on it: a later token's with the later rows (forward, dQ), an earlier
+# one's with the earlier keys (dK, dV).  The poisoned token sits inside a tile of 16 and of 32 rows, and at the end of a cut
+# one, whose last row stands in for the rows past it.  Infinity and NaN themselves only have to be where the reference has either.
+@pytest.mark.parametrize("dtype,d", [(BF16, 64), (FP32, 64), (FP32, 128)])
+@pytest.mark.parametrize("what", ["q", "k", "v", "do"])
+def test_attention_keeps_what_is_not_finite_to_the_rows_that_depend_on_it(dtype, d, what):
+    seq, nq, nkv = 75, 2, 1
+    w, tol = (nq + 2 * nkv) * d, {BF16: 2.0 ** -7, FP32: 1e-5}[dtype]
+    clean, do0 = q(RNG.standard_normal((seq, w)), dtype), q(RNG.standard_normal((seq, nq * d)), dtype)
+    for row, value in ((36, np.inf), (36, np.nan), (seq - 1, np.inf)):
+        qkv, do = clean.copy(), do0.copy()
+        if what == "do":
+            do[row, 5] = value
+        else:
+            qkv[row, {"q": 0, "k": nq * d, "v": (nq + nkv) * d}[what] + 5] = value
+        QKV, DO = dev(qkv, dtype), dev(do, dtype)
+        Ot, DQKV = torch.zeros_like(DO), torch.zeros_like(QKV)
+        LSE = torch.zeros(nq * seq, dtype=torch.float32, device="cuda")
+        WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, 1, nq, nkv, d), dtype=torch.float32, device="cuda")
+        ok(lib().optstage_op_attn_fwd(dtype, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, 1, nq, nkv, d, stream()))
+        ok(lib().optstage_op_attn_bwd(dtype, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, 1, nq, nkv, d, stream()))
+        torch.cuda.synchronize()
+        for got, want in zip((host(Ot), host(LSE).reshape(nq, seq), host(DQKV)), attention_by_rows(qkv, do, seq, nq, nkv, d)):
+            fine = np.isfinite(want)
+            assert np.array_equal(np.isfinite(got), fine), (what, row, value)
+            assert np.max(np.abs(got[fine] - want[fine])) <= tol * np.max(np.abs(want[fine])), (what, row, value)
+
+
 @pytest.mark.parametrize("gain", [6.0, 0.05])
 def test_attention_forward_with_peaked_and_flat_scores(gain):
     """Scores far larger than usual (the softmax reference has to be raised again and again, and most
