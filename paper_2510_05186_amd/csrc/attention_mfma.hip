@@ -396,7 +396,18 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
   for (int qt = 0; qt < QT; ++qt) lt[qt] = lsum[qt] + __shfl_xor(lsum[qt], 32, 64);
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
-    const float inv = 1.f / lt[qt], row_lse = mref[qt] * scale + logf(lt[qt]);
+    const float inv = 1.f / lt[qt];
+    float row_lse = mref[qt] * scale + logf(lt[qt]);
+    if constexpr (H::SPLIT) {
+      // One fp32 rounding of lse and little more: the exponents were formed as c s - (c m_ref rounded), and what that rounding
+      // left out scaled every p of the row alike (o does not see it); log(sum p) is larger than lse where m_ref is not the
+      // maximum, so its integer part is added in fp64.  RMS-relative error at 1024 tokens 2.3e-8, 4.9e-8 as the plain sum
+      // above, 4.3e-8 in the general kernels; 3.4e-8 is the most that rounding the exact value gives.
+      const float mc = mref[qt] * c;
+      int k;
+      const float f = frexpf(lt[qt], &k);
+      row_lse = (float)((double)mref[qt] * scale + k * 0.6931471805599453 + (double)(logf(f) - fmaf(mref[qt], c, -mc) * 0.6931471805599453f));
+    }
     if constexpr (H::ROW_EXACT) {
       float z = fmaf(row_lse, 0.f, inv * 0.f);
 #pragma unroll

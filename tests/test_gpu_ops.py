@@ -528,6 +528,24 @@ def test_attention_fp32(seq, batch, nq, nkv, d, gain, shift):
         assert np.max(np.abs(dq_g[sl] - ref)) < 1e-5 * np.max(np.abs(ref)) * max(1.0, gain * gain)
 
 
+# lse of 64-wide heads is held to its own rounding: at most 2^-24 / sqrt(3) of the value, RMS, and a third of 2^-24 for the
+# exponentials, their sum and its logarithm (scores of order one, whose own rounding does not show).
+@pytest.mark.parametrize("seq,batch,nq,nkv", [(700, 2, 4, 2), (1024, 1, 8, 8)])
+def test_lse_of_64_wide_heads_is_rounded_once(seq, batch, nq, nkv):
+    d, rows = 64, seq * batch
+    qkv = q(RNG.standard_normal((rows, (nq + 2 * nkv) * d)), BF16)
+    QKV = dev(qkv, BF16)
+    Ot = torch.empty(rows, nq * d, dtype=torch.bfloat16, device="cuda")
+    LSE = torch.empty(batch * nq * seq, dtype=torch.float32, device="cuda")
+    ok(lib().optstage_op_attn_fwd(BF16, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    want = []
+    for b in range(batch):
+        x = qkv[b * seq:(b + 1) * seq]
+        want.append(O.attention_fwd(*(v.reshape(seq, -1, d) for v in (x[:, : nq * d], x[:, nq * d: (nq + nkv) * d], x[:, (nq + nkv) * d:])))[1])
+    assert rms_err(host(LSE).reshape(batch, nq, seq), np.stack(want)) < 2.0 ** -24 * np.sqrt(1 / 3 + 1 / 9)
+
+
 def attention_by_rows(qkv, do, seq, nq, nkv, d):
     """fp64 attention of one sequence in which a row multiplies the keys up to its own and nothing else, so that a value that is
     not finite reaches exactly the rows that depend on it: o, lse, dqkv, and dqkv from the o that is passed."""
