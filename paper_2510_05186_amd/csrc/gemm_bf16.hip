@@ -297,7 +297,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_staged_kernel(const bf16_t* __r
 //    slots) and the address adds are pinned between MFMAs too, at the positions that carry no read: gathered at the top of
 //    the trip, as the compiler leaves them, they cost 4 %.
 //  * A tile index past the end is fetched through a zero-length descriptor, which zero-fills its slot, so the
-//    number of loads in flight is the same on every trip and the waits need no second code path.
+//    number of loads in flight is the same on every trip and the waits need no second code path.  The trip of the last tile
+//    loads nothing, so that all loads have landed well before the epilogue takes LDS over.
 //  * The tile loads are written in assembly: issued through the compiler builtin, every later transposing
 //    read is ordered after them with a full vmcnt(0) wait, which serialises the loop.  The one wait + barrier
 //    per tile orders them instead.
@@ -743,14 +744,20 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     else read_nt(0, RQ[q]);
   }
   trip(P64, P128, false, true);
-  for (kt = 1; kt < nk; ++kt) {
+  for (kt = 1; kt < nk - 1; ++kt) {
     OPTSTAGE_TILE_SYNC(8);
     trip(P0, P128, true, true);
   }
+  if (nk > 1) {                                      // the last tile: nothing is left to load
+    OPTSTAGE_TILE_SYNC(8);
+    trip(P0, P128, false, true);
+  }
   const int mw = m0 + wm * (BM / WM), nw = n0 + wn * (BN / WN);
+  // No tile load is in flight from here on: the last ones went out a trip ago, so this waits for nothing, and what the epilogue
+  // requests below can neither be mistaken for a tile load nor has to be counted, wherever the compiler puts it.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   // What the epilogue adds is requested ahead of the last 64 MFMAs, which read and load nothing any more: the residual, or
-  // the old values of the first 64 rows.  Every lane issues every load (rows and columns past the end read a value that is
-  // not used), so that their number is known: the sync below then waits for what is older, the tile loads, and not for them.
+  // the old values of the first 64 rows (rows and columns past the end read a value that is not used).
   // (4096 x 8192 x 8192 with residual 1467 -> 1513 TFLOP/s, grouped TN set of a hidden-8192 layer 1352 -> 1366.)
   f32x4_t old[EPI == EPI_ACCUM ? 32 : 1];
   bf16x4_t res[EPI == EPI_RESID ? 64 : 1];
@@ -766,10 +773,8 @@ __device__ __forceinline__ void direct_tile(char* smem, const bf16_t* __restrict
     }
   }
   trip(P0, P64, false, false);
-  // every wave is done with the operand tiles, no tile load in flight
-  if constexpr (EPI == EPI_ACCUM) OPTSTAGE_TILE_SYNC(32);
-  else if constexpr (EPI == EPI_RESID) OPTSTAGE_TILE_SYNC(63);
-  else OPTSTAGE_TILE_SYNC(0);
+  // every wave is done with the operand tiles, and none of them has a tile load in flight: LDS is the epilogue's
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #undef OPTSTAGE_TILE_SYNC
   if constexpr (EPI == EPI_ACCUM || EPI == EPI_STOREF) {
     epilogue_f32_rows<EPI>(acc, old, smem, wave, lane, reinterpret_cast<float*>(Cv), M, N, ldc, mw, nw);
