@@ -366,16 +366,18 @@ __device__ __forceinline__ void epilogue_bf16_rows(acc_tile_t& acc, const bf16x4
   }
 }
 
-// old value p2 (0..63, two rows each) of C += product for this lane: row 2 p2 + lane / 32, columns 4 (lane % 32) ..
+// old value p2 (0..63, two rows each) of C += product for this lane: row 2 p2 + lane / 32, columns 4 (lane % 32) ..  An ordinary load:
+// non-temporal ones are the slower the fewer tiles there are (TN, 128 tiles, 64 / 512 / 2048 tokens: 16.8 / 25.6 / 47.3 us
+// non-temporal, 15.9 / 22.7 / 44.4 so; 256 tiles, 512: 34.4 / 33.5; sets of 3088 and 13056 tiles the same).
 __device__ __forceinline__ f32x4_t old_value(const float* C, int p2, int lane, int M, int N, int ldc, int mw, int nw) {
   const int m = min(mw + 2 * p2 + (lane >> 5), M - 1), n = min(nw + (lane & 31) * 4, N - 4);
-  return __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(C + (size_t)m * ldc + n));
+  return *reinterpret_cast<const f32x4_t*>(C + (size_t)m * ldc + n);
 }
 
 // Epilogue of the direct kernels for fp32 outputs (C = product or C += product): 64 rows at a time go through the wave's
 // 32 KB of LDS ([64 rows][512 B], 16-byte chunks XOR-swizzled by the row) so that global memory sees whole 512-byte row
 // segments.  The old values of the first 64 rows come in `old`; each is replaced by one of the second 64 when it has been
-// used, so that those arrive under the stores.  Rows are touched once: non-temporal.
+// used, so that those arrive under the stores.  Stores are non-temporal: nothing reads a row again in this launch.
 template <int EPI>
 __device__ __forceinline__ void epilogue_f32_rows(acc_tile_t& acc, f32x4_t (&old)[EPI == EPI_ACCUM ? 32 : 1], char* smem, int wave, int lane,
                                                   float* C, int M, int N, int ldc, int mw, int nw) {
