@@ -6,7 +6,8 @@
 // Design (CDNA4): three kernels by size (launch_layout).  Large products take the direct kernels below: one workgroup of
 // 4 waves per tile, the K loop advances 64 elements at a time, operand tiles go straight from global memory into a ring of
 // five LDS slots, one barrier per step.  Smaller products run on tiles of 128 or 64 (gemm_bf16_small.hip).  What neither can
-// address (rows of one tile spread over more than 32-bit offsets) goes through the register-staged kernel: 128 x 128 tiles, global
+// address (rows of one tile spread over more than 32-bit offsets), and some products between their sizes (direct_on_few_tiles),
+// go through the register-staged kernel: 128 x 128 tiles, global
 // -> registers -> LDS, two buffers, operands that are contiguous along their output index (TN) transposed in registers on the
 // way into LDS.  Everywhere the LDS tiles' 16-byte chunk index is XOR-swizzled by the row so that operand reads and tile writes
 // are free of bank conflicts, and the MFMA is issued with the B fragment as its first operand: each lane then owns
@@ -943,21 +944,37 @@ hipError_t launch_staged(const void* A, const void* B, void* C, const void* R, i
   return hipGetLastError();
 }
 
-// The direct kernels from 128 tiles of 256 x 256 on, and below that where tiles of 128 would need a second round of workgroups
-// (one per compute unit; a k-tile of 128 x 128 takes half the time of one of 256 x 256, so two rounds cost what one of the
-// large tiles does, plus a second start and end: NT 1536 x 4096 x 1024 25.3 us on tiles of 128, 22.2 on 256; 2056 x 3080 x
-// 4096 76.7 / 67.5; TN 2048 x 2304 x 1000 30.7 / 29.2).  Everything smaller: tiles of 128 and 64.  The register-staged kernel
-// takes what is left: leading dimensions of 2^23 elements and more, whose rows within one tile span more than 32-bit
-// offsets reach.
+// Products of more than 256 tiles of 128 x 128 but fewer than 128 of 256 x 256: the direct kernel leaves half the chip idle and more, but
+// its loop is 5 (NT) to 15 % (TN) cheaper than that of the register-staged kernel, two of whose workgroups share a compute
+// unit.  Both give the same bits.  Time of the direct kernel over the staged one:
+//  * rows that do not start on 128 bytes (NT): every 128-byte piece of a tile is two cache lines.  K 1624: 1.03 to 1.18.
+//  * residual: loads and stores of a whole tile by one compute unit.  K 64 / 512 / 1024 / 2048: 1.15 - 1.33 / 1.00 - 1.08 /
+//    .98 - 1.04 / .97 - 1.00.
+//  * no more work than one full tile of 128 per compute unit, in many cut ones (1053 x 3664, 300 x 12000): store, NT, K 64 / 1024 /
+//    2048: 1.09 - 1.23 / .97 - 1.05 / .96 - .99; accumulate, TN, K 64 / 512 / 768: .95 - 1.25 / .86 - 1.02 / .86 - .99.
+//  * otherwise, whole tiles along N: .77 - 1.02 at every K; cut ones: accumulate .84 - 1.02; store, NT, K 64 / 768 / 1024:
+//    1.00 - 1.04 / .92 - 1.04 / .92 - 1.01; store, TN, K 64 / 128 / 256: .98 - 1.14 / .95 - 1.05 / .95 - .98.
+bool direct_on_few_tiles(bool tnl, int epi, int M, int N, int K, int lda, int ldb) {
+  const bool spare = (long long)M * N <= 256ll * 128 * 128;
+  if (!tnl && ((K | lda | ldb) & 63)) return false;
+  if (epi == EPI_RESID) return !spare && K >= 2048;
+  const int from = spare ? (tnl ? 768 : 2048) : N % 256 == 0 || epi == EPI_ACCUM ? 0 : tnl ? 256 : 1024;
+  return K >= from;
+}
+
+// The direct kernels from 128 tiles of 256 x 256 on.  Up to 256 tiles of 128 x 128 (one per compute unit) the small kernels, on tiles
+// of 128 and 64; between the two the rule above.  The register-staged kernel also takes leading dimensions of 2^23
+// elements and more, whose rows within one tile span more than 32-bit offsets reach.
 template <bool RC, int EPI>
 hipError_t launch_layout(const void* A, const void* B, void* C, const void* R, int M, int N, int K, int lda, int ldb,
                          int ldc, hipStream_t s) {
   const long tiles256 = (long)((M + 255) / 256) * ((N + 255) / 256), tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-  if ((tiles256 >= 128 || tiles128 > 256) && direct_applies(RC, M, N, K, lda, ldb)) {
+  const bool between = tiles256 < 128 && tiles128 > 256;
+  if ((tiles256 >= 128 || (between && direct_on_few_tiles(RC, EPI, M, N, K, lda, ldb))) && direct_applies(RC, M, N, K, lda, ldb)) {
     if (!RC && K % BK) return launch_direct<RC, EPI, !RC>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
     return launch_direct<RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
   }
-  if (gemm_bf16_small_applies(M, N, K, lda, ldb))
+  if (!between && gemm_bf16_small_applies(M, N, K, lda, ldb))
     return launch_gemm_bf16_small(RC ? GEMM_TN : GEMM_NT, EPI, GemmProblem{A, B, C, R, M, N, lda, ldb, ldc}, K, s);
   return launch_staged<RC, EPI>(A, B, C, R, M, N, K, lda, ldb, ldc, s);
 }
