@@ -13,7 +13,7 @@
 //          k-tile costs a barrier, so the 64 k of a tile take 640 cycles at 64 x 64 and 1050 at 128 x 128 (LDS reads and
 //          their latency) against 128 and 512 cycles of matrix work, however deep the prefetch.  The sums run over k in the
 //          order of the 256 x 256 kernels, bit for bit.
-//  split   the waves split the contraction instead: wave w computes the whole 64 x 64 tile over the k-tiles w, w + 4, ... and
+//  split   (NT, few tiles) the waves split the contraction instead: wave w computes the whole 64 x 64 tile over the k-tiles w, w + 4, ... and
 //          the four partial tiles are added through LDS at the end.  No wave reads what another has loaded: no barrier in the
 //          loop, half the LDS reads, 250 cycles per 64 k.
 // Measured (us, register-staged 128 x 128 kernel -> this file): NT 320 x 1024 x 3584 44.3 -> 11.0 (split; shared 64 18.8,
@@ -342,20 +342,23 @@ hipError_t launch(Kernel kern, LdsAttrOnce& lds_attr, const GemmProblem& pr, int
   return hipGetLastError();
 }
 
-// The larger tile wins once it gives most of the compute units one: NT 768 x 2048 x 2048 (96 tiles of 128) split 15.9 us, shared 128
-// 20.2; 1024 x 2048 x 2048 (128) 16.4 / 20.3; 1536 x 2048 x 2048 (192) 24.3 / 20.8; 2048 x 2048 x 2048 (256) 31.6 / 21.7.
-// TN, whose tiles also read and write fp32 sums: 3072 x 1024 x 1000 (192) shared 64 16.7, shared 128 18.2; 3584 x 1024 x 320 (224)
-// 11.8 / 11.7; 2048 x 2048 x 1024 (256) 20.2 / 17.7.
-constexpr long NT_128_TILES = 160, TN_128_TILES = 224;
-
+// Which kernel, by the number of 64 x 64 tiles.  Two workgroups of the shared kernel with tiles of 64 fit a compute unit, one of the others.
+// Times over those of the register-staged 128 x 128 kernel:
+//  * up to 256 (a tile per compute unit), NT: split from K = 768 on (K 904 / 1536 / 4800 .44 / .32 / .24, shared .48 / .42 /
+//    .38), shared below (K 64 / 256 / 704 .53 - .98 / .47 - .64 / .44; split .71 - 1.11 / .59 - .78 / .46).  TN: shared.
+//  * up to 512 the shared kernel with tiles of 64, one round for the chip: NT .53 - .77 (tiles of 128 .65 - .95, split, now two rounds, .57 -
+//    1.63), TN .51 - .95 (tiles of 128 .50 - .97).  NT towards the end of that range, where it is fully loaded, tiles of 128
+//    with a long contraction (490 tiles, K 1472 .73 / .83; 468, K 1352 .77 / .77; 452, K 5536 .70 / .59).
+//  * beyond, where tiles of 64 take a second round, tiles of 128: NT 550 to 986 tiles .73 - .95 (64: .83 - 1.29; K 24, 40: .93 /
+//    .83, .95 / .92), TN 540 to 950 .55 - .93 (64: .79 - 1.16).
 template <bool TNL, int EPI>
 hipError_t launch_sized(const GemmProblem& pr, int K, hipStream_t s) {
-  const long tiles128 = (long)((pr.M + 127) / 128) * ((pr.N + 127) / 128);
-  static LdsAttrOnce big, small;
-  if (tiles128 >= (TNL ? TN_128_TILES : NT_128_TILES))
-    return launch<128, 5 * 32768>(gemm_bf16_shared_kernel<128, TNL, EPI>, big, pr, K, s);
-  if constexpr (TNL) return launch<64, 5 * 16384>(gemm_bf16_shared_kernel<64, TNL, EPI>, small, pr, K, s);
-  else return launch<64, 4 * 32768>(gemm_bf16_split_kernel<EPI>, small, pr, K, s);
+  const long tiles64 = (long)((pr.M + 63) / 64) * ((pr.N + 63) / 64);
+  static LdsAttrOnce big, small, split;
+  if constexpr (!TNL)
+    if (tiles64 <= 256 && K >= 768) return launch<64, 4 * 32768>(gemm_bf16_split_kernel<EPI>, split, pr, K, s);
+  if (tiles64 > (!TNL && K >= 1024 ? 480 : 512)) return launch<128, 5 * 32768>(gemm_bf16_shared_kernel<128, TNL, EPI>, big, pr, K, s);
+  return launch<64, 5 * 16384>(gemm_bf16_shared_kernel<64, TNL, EPI>, small, pr, K, s);
 }
 
 }  // namespace

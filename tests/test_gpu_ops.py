@@ -79,7 +79,10 @@ def test_gemm_tn_accumulate(dtype, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(1, 4, 8), (63, 60, 64), (64, 64, 72), (65, 68, 200), (130, 516, 448), (127, 64, 896), (320, 1000, 264),
                                    (1160, 2440, 136), (1160, 2304, 520), (2056, 2056, 72), (2824, 3080, 72), (4096, 2048, 8),
                                    # between 256 tiles of 128 and 128 of 256: little work in many cut tiles, whole and cut columns, rows off 128 bytes
-                                   (1053, 3664, 128), (2048, 2304, 64), (2056, 2056, 1024), (2056, 2056, 1016), (2056, 2056, 2048)])
+                                   (1053, 3664, 128), (2048, 2304, 64), (2056, 2056, 1024), (2056, 2056, 1016), (2056, 2056, 2048),
+                                   # 256 and 257 tiles of 64 and the contraction that four waves share from K = 768 on, 480 and 486, 512 and 513
+                                   (1024, 1024, 760), (1024, 1024, 768), (64, 16448, 768), (960, 2048, 1024), (1152, 1728, 1024), (1152, 1728, 64),
+                                   (2048, 1024, 200), (1216, 1728, 200)])
 def test_gemm_tiles_of_every_size_nt(M, N, K):
     a, w, r = (q(RNG.standard_normal(s), BF16) for s in ((M, K), (N, K), (M, N)))
     A, W, R = dev(a, BF16), dev(w, BF16), dev(r, BF16)
@@ -97,7 +100,8 @@ def test_gemm_tiles_of_every_size_nt(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(8, 8, 1), (64, 64, 63), (72, 56, 65), (136, 520, 449), (264, 1000, 130), (1160, 3080, 67), (1800, 2048, 321),
-                                   (2056, 2056, 71), (2824, 3080, 129), (1048, 3664, 128), (2048, 2304, 65), (2056, 2056, 255), (2056, 2056, 256)])
+                                   (2056, 2056, 71), (2824, 3080, 129), (1048, 3664, 128), (2048, 2304, 65), (2056, 2056, 255), (2056, 2056, 256), (2048, 1024, 40),
+                                   (1216, 1728, 40)])
 def test_gemm_tiles_of_every_size_tn(M, N, K):
     dy, x = q(RNG.standard_normal((K, M)), BF16), q(RNG.standard_normal((K, N)), BF16)
     DY, X = dev(dy, BF16), dev(x, BF16)
