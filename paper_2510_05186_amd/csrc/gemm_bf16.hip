@@ -1059,15 +1059,18 @@ bool gemm_bf16_grouped_applies(int layout, int n, const GemmProblem* pr, int K) 
 }
 
 // A set that leaves a few tiles for a last round of workgroups (one per compute unit) pays a whole round for them.  Up to 64 such
-// tiles are cut off as columns of one product and go to the small kernels, whose sums run over k in the same order.  The four
-// products of a hidden-4096 layer (3088 tiles = 12 rounds and 16 tiles) at 4096 tokens: 1308 -> 1278 us.
-constexpr long ROUND = 256, TAIL_TILES = 64;
+// tiles are cut off as columns of one product and go to the small kernels, whose sums run over k in the same order; more than 32
+// only from K = 1024 on, since a short round costs little (256 tiles and `left` more, store fp32, uncut / cut us: left 16, K 64
+// 22.7 / 19.7, K 512 36.2 / 29.7, K 4096 156 / 118; left 32 22.8 / 21.7, 36.3 / 32.5, 156 / 127; left 64 22.7 / 25.8, 36.7 /
+// 38.7, K 1024 53.6 / 54.0, K 2048 87.4 / 84.5, K 4096 155 / 148; accumulating and bf16 sets gain more).  The four products of a
+// hidden-4096 layer (3088 tiles = 12 rounds and 16 tiles) at 4096 tokens: 1308 -> 1278 us.
+constexpr long ROUND = 256, TAIL_TILES = 64, TAIL_TILES_SHORT = 32, TAIL_LONG_K = 1024;
 static bool cut_tail(int n, GemmProblem* pr, int epi, int K, GemmProblem* tail) {
   auto up = [](int x) { return (long)(x + 255) / 256; };
   long total = 0, best = TAIL_TILES + 1;
   for (int i = 0; i < n; ++i) total += up(pr[i].M) * up(pr[i].N);
   const long left = total % ROUND;
-  if (total < ROUND || !left || left > TAIL_TILES) return false;
+  if (total < ROUND || !left || left > (K < TAIL_LONG_K ? TAIL_TILES_SHORT : TAIL_TILES)) return false;
   int at = -1;
   long cols = 0;
   for (int i = 0; i < n; ++i) {

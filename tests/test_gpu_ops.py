@@ -191,11 +191,19 @@ def test_gemm_grouped_equals_one_by_one_and_the_oracle():
     assert lib().optstage_op_gemm_grouped(B.GEMM_TN, B.EPI_ACCUM, len(shapes), C.cast(probs, C.c_void_p), 72, stream()) == B.E_ARG
 
 
-@pytest.mark.parametrize("shapes,K", [([(4096, 4200)], 64), ([(4096, 4096), (1024, 1032)], 128), ([(2048, 8192), (512, 1000), (8192, 264)], 64)])
-def test_gemm_grouped_with_a_short_last_round(shapes, K):
+@pytest.mark.parametrize("shapes,K,left", [([(4096, 4200)], 64, 16), ([(4096, 4096), (1024, 1032)], 128, 20),
+                                           ([(2048, 8192), (512, 1000), (8192, 264)], 64, 72),     # too many to cut
+                                           ([(4096, 3840), (512, 4872)], 64, 24),                  # the cheapest cut is in the second product
+                                           ([(4096, 4096), (2048, 1032)], 1024, 40),               # a tail of 656 tiles of 64: on tiles of 128
+                                           ([(4096, 4096), (4096, 1024)], 1024, 64),               # the most that is cut
+                                           ([(4096, 4096), (1280, 3320)], 1024, 65),               # one more: uncut
+                                           ([(4096, 4096), (2048, 1024)], 960, 32),    # the most with a short contraction
+                                           ([(4096, 4096), (256, 8400)], 960, 33)])                # one more: uncut
+def test_gemm_grouped_with_a_short_last_round(shapes, K, left):
     """Sets of one round of 256 tiles and a few more, whose last columns go to the small kernels: bitwise each product
     on its own, for every epilogue, ragged last column included."""
     import ctypes as C
+    assert sum(-(-M // 256) * -(-N // 256) for M, N in shapes) % 256 == left
     for epi, dt in ((B.EPI_ACCUM, torch.float32), (3, torch.float32), (B.EPI_STORE, torch.bfloat16)):
         probs, keep = (B.GemmProblem * len(shapes))(), []
         for i, (M, N) in enumerate(shapes):
