@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void gemm_f32_grouped_tn_kernel(const GroupedF
 }
 
 // General path: 64 x 64 tile through LDS, 256 threads, 4 x 4 outputs per thread, any strides.  Takes what 32-bit offsets within
-// a tile do not reach.
+// a tile do not reach, and short contractions of many tiles (plain_is_faster).
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                        float* __restrict__ C, const float* __restrict__ R, int M, int N,
@@ -280,6 +280,26 @@ hipError_t launch_sized(int epi, const float* A, const float* B, float* C, const
   }
 }
 
+// With a contraction of a few steps of 16 the four waves have little to share, and adding their partial tiles through LDS costs more than
+// the products: what is left is the writing of C, which the plain kernel does at once.  Operands that do not load, or a C that
+// does not store, 16 bytes at a time (vec = false) move that point up.  Time of the matrix-instruction kernel over the plain one, NT / TN:
+//  vec   1024 tiles of 64 (2048 x 2048), K 8 / 32 / 40 1.08 / 1.13 / .99, 1.09 / 1.11 / 1.02; 2048 tiles, K 32 / 64 / 96 1.35 / 1.09 /
+//        .84, 1.30 / 1.10 / .84; 8192 tiles 1.53 / 1.21 / .97, 1.45 / 1.21 / .94; 384 tiles, K 8 .85, .72; TN without old values, 26
+//        tiles, K 2 / 12 1.17 / 1.07
+//  else  560 tiles (1760 x 1262), K 6 / 41 / 64 / 130 1.69 / 1.34 / 1.02 / 1.03, 1.85 / 1.42 / 1.24 / 1.03; 256 tiles, K 6 / 17 / 32 1.36 /
+//        1.07 / .98, 1.53 / 1.16 / 1.11; 40 tiles, K 6 / 12 / 17 .92 / .84 / .73, 1.18 / 1.14 / .87 (accumulating .86 / .84 / .70)
+bool plain_is_faster(bool tn, bool vec, int epi, long tiles64, int K) {
+  if (tn && epi != EPI_ACCUM && K <= (vec ? 12 : 16)) return true;
+  if (vec) return K <= 32 ? tiles64 >= 1024 : K < 80 && tiles64 >= 2048;
+  if (tiles64 >= 512) return K <= (tn ? 130 : 60);
+  return tiles64 > 128 && K <= (tn ? 32 : 20);
+}
+long tiles64_of(int n, const GemmProblem* pr) {
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += (long)((pr[i].M + 63) / 64) * ((pr[i].N + 63) / 64);
+  return tiles;
+}
+
 }  // namespace
 
 namespace {
@@ -309,7 +329,7 @@ bool gemm_f32_grouped_applies(int n, const GemmProblem* pr, int K) {
   if (n < 1 || n > MAX_GROUP || K <= 0) return false;
   for (int i = 0; i < n; ++i)
     if (pr[i].M <= 0 || pr[i].N <= 0 || ((pr[i].lda | pr[i].ldb | pr[i].M | pr[i].N) & 3) || !mfma_reaches(true, K, pr[i].lda, pr[i].ldb)) return false;
-  return true;
+  return !plain_is_faster(true, true, EPI_ACCUM, tiles64_of(n, pr), K);
 }
 
 // n independent TN products with the same K: C (fp32) += product (EPI_ACCUM) or = product
@@ -329,8 +349,10 @@ hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, vo
   const bool tn = layout == GEMM_TN;
   const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
   float* c = (float*)C;
-  if (mfma_reaches(tn, K, lda, ldb)) {
-    const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
+  const GemmProblem pr = {A, B, C, R, M, N, lda, ldb, ldc};
+  const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
+  const bool plain = plain_is_faster(tn, vec && (ldc & 3) == 0, epi, tiles64_of(1, &pr), K) && (M + 63) / 64 < 65536;   // the second dimension of its grid
+  if (!plain && mfma_reaches(tn, K, lda, ldb)) {
     if (tn) return vec ? launch_sized<true, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
                        : launch_sized<true, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
     return vec ? launch_sized<false, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)

@@ -119,7 +119,11 @@ def test_gemm_tiles_of_every_size_tn(M, N, K):
 # fewer steps of 16 k than waves and a ragged last step, and leading dimensions past 32-bit offsets (the plain kernel).
 # Bound: K + 1 roundings of 2^-24 on sums of magnitudes.
 @pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (16, 16, 4, 0), (17, 20, 15, 3), (130, 36, 68, 4), (200, 500, 200, 0), (201, 499, 77, 1),
-                                       (1000, 1100, 132, 0), (1001, 1023, 67, 2), (8, 8, 16, 1 << 24)])
+                                       (1000, 1100, 132, 0), (1001, 1023, 67, 2), (8, 8, 16, 1 << 24),
+                                       # short contractions of many tiles (the plain kernel) and the first past each limit, 16-byte rows and others
+                                       (2048, 2040, 32, 0), (2048, 2040, 36, 0), (4052, 2048, 76, 0), (4052, 2048, 80, 0), (1760, 1262, 60, 0),
+                                       (1760, 1262, 61, 0), (1760, 1262, 64, 0), (1760, 1262, 130, 0), (1760, 1262, 131, 0), (1001, 1023, 20, 0), (1001, 1023, 33, 0),
+                                       (301, 499, 16, 0), (301, 499, 17, 0)])
 def test_gemm_fp32_tiles_of_every_size(M, N, K, pad):
     nt = q(RNG.standard_normal((M, K)), FP32), q(RNG.standard_normal((N, K)), FP32)
     r = q(RNG.standard_normal((M, N)), FP32)
