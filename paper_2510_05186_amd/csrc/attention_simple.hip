@@ -1,6 +1,6 @@
 // Causal attention forward / backward, general path (any storage type, head_dim 64 or 128): one wave
 // per query row (forward, dQ) or per key row (dK, dV), fp32 arithmetic, online softmax.  The fallback
-// where the MFMA kernels do not apply (operands that are not 16-byte aligned, sequences past 32-bit offsets).  q-head a reads kv-head
+// where the MFMA kernels do not apply (operands that are not 16-byte aligned, sequences past 32-bit offsets) or gain nothing (a few tokens).  q-head a reads kv-head
 // a * n_kv / n_q; dK and dV are summed over the q-heads of a group.  Packed qkv rows:
 // [q heads | k heads | v heads].  lse is [batch][n_q][seq], natural log.
 #include "attention_rows.h"

@@ -21,9 +21,28 @@ hipError_t launch_attn_fwd_f32(const void* qkv, void* o, float* lse, int seq, in
 hipError_t launch_attn_bwd_f32(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 
+// Sequences of a few tokens, for fp32 and for heads of 64: a tile of 16 (fp32) or 32 rows is nearly empty, and the general kernels, a wave
+// per row, have four rows to a workgroup.  Time of the tile kernels over the general ones:
+//  forward   heads of 64, 64 / 128 sequences of 16 / 32 heads: 4 tokens 2.0 / 2.7, 8 tokens 1.35, 9 tokens .96 / .79 (few sequences,
+//            8 tokens 1.03); fp32 4 tokens 1.1 - 1.2, 5 tokens .6 - .8, few sequences, 8 / 9 tokens 1.07 / .9
+//  backward  heads of 64: 4 tokens 1.6 / 2.1, 6 tokens 1.09, 8 tokens 1.03 / .96, 9 tokens .74 / .70, few sequences .9 - 1.05; fp32 4 tokens 1.1 - 1.5, 5
+//            tokens .6 - .8, few sequences, 4 / 8 / 12 tokens 1.13 / 1.16 / 1.1.  With grouped heads a row of dK / dV takes all of a
+//            group's queries: heads of 64, 8 / 2 heads x 4 .8 at 4 tokens, 32 / 8 x 64 1.54; fp32 .6 - .9.
+static bool attn_short(int dtype, int d, int seq, int batch, int n_q) {
+  if (seq > 8 || (dtype == DT_BF16 && d != 64)) return false;
+  return dtype == DT_BF16 || seq <= 4 || (long long)batch * n_q * 2 <= 256;      // two workgroups per head, one per compute unit
+}
+static bool attn_short_bwd(int dtype, int d, int seq, int batch, int n_q, int n_kv) {
+  if (seq > 12 || (dtype == DT_BF16 && d != 64)) return false;
+  const long long wgs = (long long)batch * n_q * ((seq + 3) / 4);
+  if (n_q != n_kv) return dtype == DT_BF16 && seq <= 4 && wgs >= 256;
+  return seq <= (dtype == DT_BF16 ? 8 : wgs <= 256 ? 12 : 4);
+}
+
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv,
                            int d, hipStream_t s) {
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
+  if (attn_short(dtype, d, seq, batch, n_q)) return launch_attn_fwd_simple(dtype, qkv, o, lse, seq, batch, n_q, n_kv, d, s);
   if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, qkv, o)) return launch_attn_fwd_mfma(qkv, o, lse, seq, batch, n_q, n_kv, d, s);
   if (attn_f32_applies(dtype, d, seq, qkv, o, qkv, o)) return launch_attn_fwd_f32(qkv, o, lse, seq, batch, n_q, n_kv, d, s);
   return launch_attn_fwd_simple(dtype, qkv, o, lse, seq, batch, n_q, n_kv, d, s);
@@ -32,6 +51,7 @@ hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int 
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv,
                            float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
+  if (attn_short_bwd(dtype, d, seq, batch, n_q, n_kv)) return launch_attn_bwd_simple(dtype, qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
   if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, dout, dqkv))
     return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
   if (attn_f32_applies(dtype, d, seq, qkv, o, dout, dqkv))

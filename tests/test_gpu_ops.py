@@ -406,6 +406,9 @@ def test_rotary(dtype, seq, batch, nq, nkv, d):
     (FP32, 128, 1, 4, 4, 64), (FP32, 67, 2, 4, 2, 64), (BF16, 200, 1, 4, 2, 128), (BF16, 130, 1, 2, 2, 64),
     (BF16, 512, 1, 8, 2, 128), (BF16, 1, 1, 2, 1, 128), (BF16, 384, 2, 2, 2, 128), (BF16, 1000, 1, 4, 1, 128),
     (BF16, 65, 1, 1, 1, 128), (BF16, 129, 3, 2, 2, 128),
+    # heads of 64, short sequences (the general kernels): both sides of each limit
+    (BF16, 4, 3, 4, 2, 64), (BF16, 4, 64, 4, 2, 64), (BF16, 5, 64, 4, 2, 64), (BF16, 8, 2, 2, 2, 64), (BF16, 9, 2, 2, 2, 64),
+    (BF16, 8, 1, 2, 1, 64), (BF16, 9, 1, 2, 1, 64),
 ])
 def test_attention_fwd_bwd(dtype, seq, batch, nq, nkv, d):
     rows = seq * batch
@@ -517,7 +520,10 @@ def test_attention_of_64_wide_heads_keeps_fp32_probabilities(seq, batch, nq, nkv
 # fp32 sums of up to a few hundred products, 2^-24 each, in softmax and both products; 1e-5 of the largest value.
 @pytest.mark.parametrize("seq,batch,nq,nkv,d,gain,shift", [(1, 1, 1, 1, 64, 1.0, 0), (15, 2, 2, 1, 128, 1.0, 0), (16, 1, 2, 2, 64, 1.0, 0),
                                                            (17, 1, 4, 2, 64, 1.0, 0), (100, 2, 4, 1, 128, 1.0, 0), (257, 1, 2, 2, 64, 4.0, 0),
-                                                           (200, 1, 3, 3, 128, 0.05, 0), (65, 1, 2, 1, 64, 1.0, 1)])
+                                                           (200, 1, 3, 3, 128, 0.05, 0), (65, 1, 2, 1, 64, 1.0, 1),
+                                                           # short sequences (the general kernels): both sides of each limit
+                                                           (4, 65, 2, 2, 64, 1.0, 0), (5, 65, 2, 2, 64, 1.0, 0), (8, 1, 2, 1, 128, 1.0, 0),
+                                                           (9, 1, 2, 2, 128, 1.0, 0), (12, 2, 2, 2, 64, 1.0, 0), (13, 2, 2, 2, 64, 1.0, 0)])
 def test_attention_fp32(seq, batch, nq, nkv, d, gain, shift):
     rows, w = seq * batch, (nq + 2 * nkv) * d
     qkv = RNG.standard_normal((rows, w))
