@@ -622,6 +622,31 @@ def test_attention_keeps_what_is_not_finite_to_the_rows_that_depend_on_it(dtype,
             assert np.max(np.abs(got[fine] - want[fine])) <= tol * np.max(np.abs(want[fine])), (what, row, value)
 
 
+@pytest.mark.parametrize("which", ["qkv", "o", "do", "dqkv"])
+def test_attention_of_128_wide_heads_off_16_bytes(which):
+    """An operand that does not start on 16 bytes takes the general kernels: 16-byte accesses would not be aligned."""
+    seq, nq, nkv, d = 130, 2, 1, 128
+    w = (nq + 2 * nkv) * d
+    qkv, do = q(RNG.standard_normal((seq, w)), BF16), q(RNG.standard_normal((seq, nq * d)), BF16)
+
+    def place(a, name):
+        flat = torch.zeros(a.size + 8, dtype=torch.bfloat16, device="cuda")
+        at = 1 if name == which else 0
+        flat[at:at + a.size] = dev(a, BF16).reshape(-1)
+        return flat[at:at + a.size].view(a.shape)
+    QKV, DO, Ot, DQKV = place(qkv, "qkv"), place(do, "do"), place(0 * do, "o"), place(0 * qkv, "dqkv")
+    LSE = torch.empty(nq * seq, dtype=torch.float32, device="cuda")
+    WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, 1, nq, nkv, d), dtype=torch.float32, device="cuda")
+    ok(lib().optstage_op_attn_fwd(BF16, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, 1, nq, nkv, d, stream()))
+    ok(lib().optstage_op_attn_bwd(BF16, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, 1, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    qq, kk, vv = (x.reshape(seq, -1, d) for x in (qkv[:, : nq * d], qkv[:, nq * d: (nq + nkv) * d], qkv[:, (nq + nkv) * d:]))
+    o, lse = O.attention_fwd(qq, kk, vv)
+    assert rms_err(host(Ot), o.reshape(seq, -1)) < TOL[BF16] / 4 and np.max(np.abs(host(LSE).reshape(nq, seq) - lse)) < 1e-4
+    ref = O.attention_bwd(qq, kk, vv, host(Ot).reshape(seq, nq, d), do.reshape(seq, nq, d))
+    assert rms_err(host(DQKV), np.concatenate([x.reshape(seq, -1) for x in ref], axis=1)) < TOL[BF16] / 4
+
+
 @pytest.mark.parametrize("gain", [6.0, 0.05])
 def test_attention_forward_with_peaked_and_flat_scores(gain):
     """Scores far larger than usual (the softmax reference has to be raised again and again, and most
