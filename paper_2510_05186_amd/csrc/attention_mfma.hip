@@ -1125,9 +1125,10 @@ int attn_dkv_split(int seq, int batch, int n_q, int n_kv) {
   return split;
 }
 
-// bf16, head_dim 128 or 64, per-sequence tensors addressable with 32-bit byte offsets (buffer loads), 16-byte aligned rows
+// bf16, head_dim 128 or 64, per-sequence tensors addressable with 32-bit byte offsets (buffer loads), 16-byte aligned rows, row blocks
+// that fit the grid's third dimension (a few narrow heads reach it before the offsets do)
 bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void* p0, const void* p1, const void* p2, const void* p3) {
-  return dtype == DT_BF16 && (d == 128 || d == 64) && (unsigned long long)(seq + 256) * (n_q + 2 * n_kv) * d * 2 < 0xF0000000ull &&
+  return dtype == DT_BF16 && (d == 128 || d == 64) && (seq + 127) / 128 < 65536 && (unsigned long long)(seq + 256) * (n_q + 2 * n_kv) * d * 2 < 0xF0000000ull &&
          (((uintptr_t)p0 | (uintptr_t)p1 | (uintptr_t)p2 | (uintptr_t)p3) & 15) == 0;
 }
 

@@ -34,6 +34,17 @@ def test_library_exports_every_declared_symbol():
     assert names == set(B.EXPORTS)
 
 
+def test_matrix_unit_attention_takes_what_its_grid_and_offsets_reach():
+    """attn_mfma_applies(dtype, d, seq, n_q, n_kv, four pointers): row blocks of 128 are the grid's third dimension, at most 65535
+    of them; one query and one kv head of 64 columns stay within 32-bit offsets up to 10.4 million rows."""
+    f = ctypes.CDLL(B.LIB_PATH)["_Z17attn_mfma_appliesiiiiiPKvS0_S0_S0_"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int] * 5 + [ctypes.c_void_p] * 4
+    takes = lambda d, seq, nq, nkv, at=4096: f(1, d, seq, nq, nkv, at, 4096, 4096, 4096)  # noqa: E731
+    assert takes(64, 65535 * 128, 1, 1) and not takes(64, 65535 * 128 + 1, 1, 1)
+    assert takes(128, 5_000_000, 1, 1) and not takes(128, 5_500_000, 1, 1)
+    assert takes(128, 4096, 32, 8) and not takes(128, 4096, 32, 8, 4098) and not takes(64, 4096, 32, 8, 4104) and not takes(96, 4096, 32, 8)
+
+
 def oracle_table(cfg):
     return S.memory_table(cfg.family, cfg.hidden, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.ffn,
                           cfg.seq * cfg.micro_batch, cfg.elem_size)
