@@ -471,14 +471,14 @@ def test_attention_with_one_and_two_tiles_per_wave(seq, batch, nq, nkv):
 
 # Heads of 64: edges of the 32- and 64-wide tiles and of the 256 rows of a workgroup, one row, grouped heads, several sequences,
 # peaked and flat scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  The second
-# products multiply fp32 probabilities (16 bits of fraction at least), so what is left is the rounding of the results to 8
-# bits: an error spread evenly over +- 2^-8 of the power of two below a value, at most 2^-8 / sqrt(3) RMS-relative, and all but
+# products multiply probabilities of 16 significant bits (two bf16 numbers; the general kernels 24), so what is left is the
+# rounding of the results to 8 bits: an error spread evenly over +- 2^-8 of the power of two below a value, at most 2^-8 / sqrt(3) RMS-relative, and all but
 # the values within about 2^-16 of a tie, 2^-7 of them and a few more where a sum cancels, equal the correctly rounded
 # ones (below 6 %; probabilities of 8 bits miss a third).
 @pytest.mark.parametrize("seq,batch,nq,nkv,gain,shift", [(1, 2, 2, 1, 1.0, 0), (31, 1, 2, 2, 1.0, 0), (33, 1, 1, 1, 1.0, 0), (64, 2, 2, 1, 1.0, 0),
                                                          (65, 1, 4, 1, 1.0, 0), (255, 1, 2, 2, 1.0, 0), (257, 2, 2, 1, 1.0, 0), (700, 1, 8, 2, 4.0, 0),
                                                          (600, 1, 2, 2, 0.05, 0), (130, 1, 2, 1, 1.0, 1)])
-def test_attention_of_64_wide_heads_keeps_fp32_probabilities(seq, batch, nq, nkv, gain, shift):
+def test_attention_of_64_wide_heads_rounds_only_its_results(seq, batch, nq, nkv, gain, shift):
     d, rows, w = 64, seq * batch, (nq + 2 * nkv) * 64
     qkv = RNG.standard_normal((rows, w))
     qkv[:, : (nq + nkv) * d] *= gain

@@ -721,6 +721,56 @@ def test_grad_overwrite_mode_needs_no_cleared_accumulators():
         ref.close()
 
 
+def _grouped(base, name, hidden, n_q, n_kv, ffn, seq, n_layers):
+    return CFG.shrunken(base, hidden=hidden, n_q=n_q, n_kv=n_kv, ffn=ffn, seq=seq, n_layers=n_layers, n_microbatches=2, name=name)
+
+
+# Weight-gradient products of a W op in grouped launches of up to 16.  bf16: token counts that are no multiple of 64, 136 tiles of 256
+# (one layer) and 272, whose last round of 16 is cut off.  fp32: the tile that a set picks (estimated time: rounds of 256
+# workgroups times 2.3 / 3.8, 7.8 and 21 for tiles of 16 (up to 256 / more), 32 and 64), edges that are no multiple of it next to the
+# next product's first tile, 20 products in two launches.
+@pytest.mark.parametrize("cfg,tiles", [(_grouped(CFG.CFG4, "one_token", 1024, 8, 2, 2048, 1, 1), [256]), (_grouped(CFG.CFG4, "tokens_63", 1024, 8, 2, 2048, 63, 1), [256]),
+                                       (_grouped(CFG.CFG4, "tokens_65_cut", 1024, 8, 2, 2048, 65, 2), [256]),
+                                       (_grouped(CFG.CFG4, "tokens_200_cut", 1024, 8, 2, 2048, 200, 2), [256]),
+                                       (_grouped(CFG.CFG1, "fp32_16", 64, 1, 1, 100, 38, 1), [16]),
+                                       (_grouped(CFG.CFG1, "fp32_32_and_16", 64, 1, 1, 132, 38, 5), [32, 16]),
+                                       (_grouped(CFG.CFG1, "fp32_32", 132, 2, 1, 260, 45, 1), [32]),
+                                       (_grouped(CFG.CFG1, "fp32_64", 260, 4, 2, 1028, 51, 2), [64])], ids=lambda c: getattr(c, "name", ""))
+def test_grouped_weight_gradients(cfg, tiles):
+    ws = T.stage_weights(cfg)
+    h, f, q = cfg.hidden, cfg.ffn, cfg.n_q_heads * cfg.head_dim
+    up = 2 * f if cfg.family == O.LLAMA else f
+    products = [(h, f), (up, h), (h, q), (q + 2 * cfg.n_kv_heads * cfg.head_dim, h)] * cfg.n_layers
+    count = lambda group, r: sum(-(-a // r) * -(-b // r) for a, b in group)  # noqa: E731
+    groups = [products[i:i + 16] for i in range(0, len(products), 16)]
+    if cfg.dtype == CFG.BF16:
+        assert len(groups) == 1 and count(products, 256) == 136 * cfg.n_layers and cfg.seq % 64
+    else:
+        cost = lambda group, r: -(-count(group, r) // 256) * {64: 21.0, 32: 7.8, 16: 2.3 if count(group, 16) <= 256 else 3.8}[r]  # noqa: E731
+        assert [min((64, 32, 16), key=lambda r, g=g: cost(g, r)) for g in groups] == tiles
+    events = [("F", 0), ("F", 1), ("B", 0), ("W", 0), ("B", 1), ("W", 1)]
+    ref, runs = oracle_run(cfg, ws), []
+    for overwrite in (False, True):
+        st = Stage(cfg, grad_overwrite=overwrite)
+        st.set_weights(ws)
+        for j in range(cfg.n_microbatches):
+            st.bind(j, T.stage_input(cfg, j), T.output_grad(cfg, j))
+        if overwrite:
+            for g in st.grads:
+                for v in g.values():
+                    v.fill_(float("nan"))
+        B.check(B.lib().optstage_set_kernel_timing(st.h, 1))
+        st.run(events)
+        st.synchronize()
+        compare(cfg, st, ref)
+        launches = dict(zip(B.KERNEL_CLASSES, st.stats().kernel_launches))
+        assert launches["gemm_tn_accum"] == cfg.n_microbatches * len(groups)
+        runs.append([{n: v.clone() for n, v in g.items()} for g in st.grads])
+        st.close()
+    for a, b in zip(*runs):
+        assert all(torch.equal(a[n], b[n]) for n in a)
+
+
 def test_stats_report_the_trace_the_live_levels_and_the_stalls():
     cfg = SMALL2
     ws = T.stage_weights(cfg)
