@@ -27,9 +27,11 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 
 // What depends on the head size: rows of ROWB bytes = CH 16-byte chunks in the LDS tiles of 64 rows, NKS k-steps of an MFMA over
 // a row, NDT 32-wide pieces of it, NLD loads of 1 KB (RPL rows) by which a wave fills its quarter of a tile.
-// SPLIT: the probabilities and dS, fp32 numbers, enter the second product as the sum of two bf16 numbers (16 bits of
-// fraction between them) and not as one.  Heads of 64 have always multiplied them in fp32; the error against 64 bits stays
-// what it was (o 1.6e-3, dqkv 1.8e-3: the rounding of the results), where one bf16 number would raise it by a quarter.
+// SPLIT: the probabilities and dS, fp32 numbers, enter the second product as the sum of two bf16 numbers (16 significant bits
+// between them, a rounding of 2^-17 at most) and not as one.  The general kernels multiply them in fp32; the error against 64
+// bits is no larger here (o 1.6e-3, dqkv 1.8e-3: the rounding of the results), where one bf16 number would raise it by a quarter.
+// The exponentials themselves are v_exp_f32 (1 ulp) of x = c s - c m rounded once, |x| 2^-24: p is off by at most 2^-23 +
+// 0.7 |x| 2^-24 of itself, as expf of a rounded difference is.
 // Measured for heads of 64 at 4 x 1024 tokens, 16 heads, forward and backward: 4466 us on the general kernels (one wave per row,
 // no matrix unit), 97 us here.
 template <int D> struct Head {
@@ -131,8 +133,7 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) { mref[qt] = -INFINITY; lsum[qt] = 0.f; }
 
-  // LDS addressing as in the dQ kernel: 64 rows x 256 B per tile, 16-byte chunk c of row r stored at chunk
-  // c ^ (((r & 3) << 2) | ((r >> 2) & 3))
+  // LDS addressing as in the dQ kernel: 64 rows of ROWB bytes per tile, 16-byte chunk c of row r stored at chunk c ^ swz(r)
   int rm_addr[NKS];
   {
     const int f = H::swz(c32);
@@ -1115,8 +1116,10 @@ __global__ void attn_bwd_dkv_reduce(const float* __restrict__ partial, bf16_t* _
 
 }  // namespace
 
-// how many workgroups share the query heads of one kv head in the dK/dV kernel: enough to give every compute
-// unit about two workgroups, a divisor of n_q / n_kv
+// how many workgroups share the query heads of one kv head in the dK/dV kernel, a divisor of n_q / n_kv: enough to give every compute
+// unit about two workgroups of 256 keys.  Callers size their scratch by it, so it does not look at the tile count that the launch picks:
+// with one tile per wave the same split makes twice as many workgroups of half the size (8192 tokens, 8 / 1 heads: 512 of 128
+// keys; dK / dV 382 -> 278 us).
 int attn_dkv_split(int seq, int batch, int n_q, int n_kv) {
   const int rep = n_q / n_kv;
   const long wgs = (long)n_kv * batch * ((seq + 255) / 256);
@@ -1175,7 +1178,10 @@ template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const v
 // what a full chip wants; with at most one such workgroup per compute unit the longest row of the causal triangle sets the time,
 // and halving the workgroups halves its share.  Forward / backward us, two -> one tile: 1237 tokens x 3, 16 / 4 heads (240
 // workgroups) 46.6 / 146 -> 38.8 / 115, 8192 tokens, 8 / 1 heads (256) 233 / 681 -> 177 / 516, 320 tokens, 8 / 2 heads (16) 17.3 /
-// 51 -> 10.7 / 31; 2000 tokens, 40 heads (320) 67.5 / 198 -> 73.4 / 185, 1024 tokens x 8 (512) 62.8 / 204 -> 76.9 / 216.
+// 51 -> 10.7 / 31; 2000 tokens, 40 heads (320) 67.5 / 198 -> 73.4 / 185, 1024 tokens x 8 (512) 62.8 / 204 -> 76.9 / 216.  The two
+// backward kernels apart, one tile over two, dQ / dK dV: 256 workgroups (4096 tokens, 16 heads) .76 / .81, 288 (2048, 36) .77 / .99,
+// 320 (4096, 20) .80 / 1.02, with grouped heads (20 / 4) .81 / .64, 384 (2048, 48) .90 / 1.12, 512 (4096, 32) .99 / 1.18: one
+// line for both, where their sum turns.
 // Heads of 64, which leave registers for two waves per SIMD, always take one: 4096 tokens, 32 heads (512) 156 / 407 -> 133 / 376.
 constexpr long FWD_WGS = 256, BWD_WGS = 320;
 long wide_workgroups(int seq, int batch, int n_q) { return (long)n_q * batch * ((seq + 255) / 256); }

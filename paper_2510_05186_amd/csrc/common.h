@@ -87,7 +87,8 @@ bool gemm_bf16_grouped_applies(int layout, int n, const GemmProblem* problems, i
 hipError_t launch_gemm_bf16_grouped(int layout, int epi, int n, const GemmProblem* problems, int K, hipStream_t s);
 hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                             int K, int lda, int ldb, int ldc, hipStream_t s, const GemmExtra* extra = nullptr);
-// products below 128 tiles of 256 x 256 (tiles of 128 or 64); bf16 alignment rules as for launch_gemm_bf16
+// tiles of 128 or 64, for products of up to 256 tiles of 128 x 128 and for what is cut off a grouped TN set; bf16 alignment rules as
+// for launch_gemm_bf16
 bool gemm_bf16_small_applies(int M, int N, int K, int lda, int ldb);
 hipError_t launch_gemm_bf16_small(int layout, int epi, const GemmProblem& problem, int K, hipStream_t s);
 bool gemm_bf16_fused_applies(int epi, int M, int N, int K, int lda, int head_dim);

@@ -443,6 +443,25 @@ __global__ void rope_kernel(const T* src, T* dst, const float2* __restrict__ tab
 // TRANSPOSED = false: B[n][k] = src[n * K + k]; true: B[n][k] = src[k * N + n] (the transposed weight)
 // pair_f > 0 (not TRANSPOSED): the source is a [gate | up] weight with pair_f rows each; the 64 slab rows of this
 // workgroup (tile t = n0 / 256, wave half w, q = 0 gate / 1 up) come from source rows q pair_f + 128 t + 64 w + 0..63
+template <bool TRANSPOSED>
+__global__ void slab_kernel(const unsigned short* __restrict__ src, unsigned short* __restrict__ dst, int N, int K, int pair_f) {
+  __shared__ unsigned short tile[64][65];
+  const int n0 = blockIdx.y * 64, k0 = blockIdx.x * 64;
+  const int s0 = pair_f > 0 ? ((n0 >> 6) & 1) * pair_f + (n0 >> 8) * 128 + ((n0 >> 7) & 1) * 64 : n0;   // first source row
+  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
+    const int hi = e / 64, lo = e % 64;               // lo runs along the source's contiguous direction
+    const int nn = TRANSPOSED ? lo : hi, kk = TRANSPOSED ? hi : lo;
+    unsigned short v = 0;
+    if (n0 + nn < N) v = TRANSPOSED ? src[(size_t)(k0 + kk) * N + n0 + nn] : src[(size_t)(s0 + nn) * K + k0 + kk];
+    tile[nn][kk] = v;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
+    const int nn = e / 64, kk = e % 64, n = n0 + nn;
+    dst[((size_t)(n / 256) * (K / 64) + k0 / 64) * 16384 + (size_t)(n % 256) * 64 + kk] = tile[nn][kk];
+  }
+}
+
 // The same with 16-byte accesses, for sources whose rows start on 16 bytes (a 64 x 64 piece is 8 KB of consecutive memory in the
 // slab layout).  Bound by HBM: the four weights of a hidden-4096 layer, both copies of each (1.2 GB), 679 -> 309 us; one
 // thread per element moves 128 bytes per wave and instruction where this moves 1 KB.  A transposed piece passes through LDS in rows
@@ -484,25 +503,6 @@ __global__ __launch_bounds__(256) void slab_vec_kernel(const unsigned short* __r
         v[e] = (unsigned)t16[(c * 8 + 2 * e) * 66 + n] | ((unsigned)t16[(c * 8 + 2 * e + 1) * 66 + n] << 16);
       out[q] = v;
     }
-  }
-}
-
-template <bool TRANSPOSED>
-__global__ void slab_kernel(const unsigned short* __restrict__ src, unsigned short* __restrict__ dst, int N, int K, int pair_f) {
-  __shared__ unsigned short tile[64][65];
-  const int n0 = blockIdx.y * 64, k0 = blockIdx.x * 64;
-  const int s0 = pair_f > 0 ? ((n0 >> 6) & 1) * pair_f + (n0 >> 8) * 128 + ((n0 >> 7) & 1) * 64 : n0;   // first source row
-  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-    const int hi = e / 64, lo = e % 64;               // lo runs along the source's contiguous direction
-    const int nn = TRANSPOSED ? lo : hi, kk = TRANSPOSED ? hi : lo;
-    unsigned short v = 0;
-    if (n0 + nn < N) v = TRANSPOSED ? src[(size_t)(k0 + kk) * N + n0 + nn] : src[(size_t)(s0 + nn) * K + k0 + kk];
-    tile[nn][kk] = v;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-    const int nn = e / 64, kk = e % 64, n = n0 + nn;
-    dst[((size_t)(n / 256) * (K / 64) + k0 / 64) * 16384 + (size_t)(n % 256) * 64 + kk] = tile[nn][kk];
   }
 }
 

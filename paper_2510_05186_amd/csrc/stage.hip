@@ -643,8 +643,8 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   const int T = s.tokens;
   auto P = [&](int l, int k) { return (void*)(st->arena() + ob.dev[(size_t)l * NK + k]); };
   // dW += dY^T X for the four linears of every layer (fp32 accumulators).  None of these products depends on
-  // another: they go to one grouped launch per 16, so that only the last launch leaves a partly filled round of
-  // workgroups; anything the grouped path does not take runs product by product.
+  // another: they go to one grouped call per 16, so that only its last round of workgroups is partly filled (and goes to
+  // the small kernels where it is short); anything the grouped path does not take runs product by product.
   std::vector<GemmProblem> pr;
   for (int l = c * s.Lc; l < (c + 1) * s.Lc; ++l) {
     pr.push_back({P(l, OPTSTAGE_K_DY), P(l, OPTSTAGE_K_A), GW(st, l, OPTSTAGE_W_D), nullptr, s.h, s.f, s.h, s.f, s.f});
