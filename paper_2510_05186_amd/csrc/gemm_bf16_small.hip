@@ -132,6 +132,9 @@ template <int EPI> __device__ __forceinline__ void finish(const GemmProblem& pr,
   if (EPI == EPI_STOREF || EPI == EPI_ACCUM) {
     f32x4_t* c = reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(pr.C) + off);
     if (EPI == EPI_ACCUM) { const f32x4_t o = *c; v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3]; }
+    // stored straight from the accumulation registers, the accumulators push the fragments of the loop into those, and every MFMA
+    // waits for copies
+    else asm volatile("" : "+v"(v));
     *c = v;
   } else {
     if (EPI == EPI_RESID) {
@@ -347,17 +350,19 @@ hipError_t launch(Kernel kern, LdsAttrOnce& lds_attr, const GemmProblem& pr, int
 //  * up to 256 (a tile per compute unit), NT: split from K = 768 on (K 904 / 1536 / 4800 .44 / .32 / .24, shared .48 / .42 /
 //    .38), shared below (K 64 / 256 / 704 .53 - .98 / .47 - .64 / .44; split .71 - 1.11 / .59 - .78 / .46).  TN: shared.
 //  * up to 512 the shared kernel with tiles of 64, one round for the chip: NT .53 - .77 (tiles of 128 .65 - .95, split, now two rounds, .57 -
-//    1.63), TN .51 - .95 (tiles of 128 .50 - .97).  NT towards the end of that range, where it is fully loaded, tiles of 128
+//    1.63), TN .40 - .95 (tiles of 128 .52 - .97).  NT towards the end of that range, where it is fully loaded, tiles of 128
 //    with a long contraction (490 tiles, K 1472 .73 / .83; 468, K 1352 .77 / .77; 452, K 5536 .70 / .59).
 //  * beyond, where tiles of 64 take a second round, tiles of 128: NT 550 to 986 tiles .73 - .95 (64: .83 - 1.29; K 24, 40: .93 /
-//    .83, .95 / .92), TN 540 to 950 .55 - .93 (64: .79 - 1.16).
+//    .83, .95 / .92), TN 528 to 890 .52 - .90 (64: .66 - 1.17; accumulating, K 102 / 279, .88 / .82, .79 / .77: with short contractions
+//    the line is 700).
 template <bool TNL, int EPI>
 hipError_t launch_sized(const GemmProblem& pr, int K, hipStream_t s) {
   const long tiles64 = (long)((pr.M + 63) / 64) * ((pr.N + 63) / 64);
   static LdsAttrOnce big, small, split;
   if constexpr (!TNL)
     if (tiles64 <= 256 && K >= 768) return launch<64, 4 * 32768>(gemm_bf16_split_kernel<EPI>, split, pr, K, s);
-  if (tiles64 > (!TNL && K >= 1024 ? 480 : 512)) return launch<128, 5 * 32768>(gemm_bf16_shared_kernel<128, TNL, EPI>, big, pr, K, s);
+  const long round64 = TNL ? (K <= 160 ? 700 : 512) : K >= 1024 ? 480 : 512;
+  if (tiles64 > round64) return launch<128, 5 * 32768>(gemm_bf16_shared_kernel<128, TNL, EPI>, big, pr, K, s);
   return launch<64, 5 * 16384>(gemm_bf16_shared_kernel<64, TNL, EPI>, small, pr, K, s);
 }
 

@@ -100,8 +100,8 @@ def test_gemm_tiles_of_every_size_nt(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(8, 8, 1), (64, 64, 63), (72, 56, 65), (136, 520, 449), (264, 1000, 130), (1160, 3080, 67), (1800, 2048, 321),
-                                   (2056, 2056, 71), (2824, 3080, 129), (1048, 3664, 128), (2048, 2304, 65), (2056, 2056, 255), (2056, 2056, 256), (2048, 1024, 40),
-                                   (1216, 1728, 40)])
+                                   (2056, 2056, 71), (2824, 3080, 129), (1048, 3664, 128), (2048, 2304, 65), (2056, 2056, 255), (2056, 2056, 256), (2048, 1024, 161),
+                                   (1216, 1728, 161), (1600, 1792, 160), (1600, 1800, 160)])
 def test_gemm_tiles_of_every_size_tn(M, N, K):
     dy, x = q(RNG.standard_normal((K, M)), BF16), q(RNG.standard_normal((K, N)), BF16)
     DY, X = dev(dy, BF16), dev(x, BF16)
