@@ -72,6 +72,19 @@ template <int D> struct F32 {
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
+  // columns c .. c + 3 of a result row, out of the four partial results, rotated back: the partner columns lie d / 2 away
+  static __device__ __forceinline__ void turn_back(f32x4_t& v, const float (*part)[ROWS][D + 4], float scale, const float2* angle, int row, int c) {
+    const int k = c % (D / 2), other = c < D / 2 ? c + D / 2 : c - D / 2;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x = (((part[0][row][other + e] + part[1][row][other + e]) + part[2][row][other + e]) + part[3][row][other + e]) * scale;
+      const float2 t = angle[k + e];
+      float own = v[e];
+      if (c < D / 2) rope_back(own, x, t.x, t.y);
+      else rope_back(x, own, t.x, t.y);
+      v[e] = own;
+    }
+  }
   static __device__ __forceinline__ void scaled(f32x4_t (&v)[S], float f) {
 #pragma unroll
     for (int s = 0; s < S; ++s)
@@ -175,9 +188,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32(const float* __restrict__ qk
 
 // D_t = <dO_t, O_t> (stored for the dK / dV kernel), dQ_t = scale * sum_j dS_tj K_j
 template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ o,
+__global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* qkv, const float* __restrict__ o,
                                                        const float* __restrict__ dout, const float* __restrict__ lse,
-                                                       float* __restrict__ dqkv, float* __restrict__ Dws, int seq, int n_q, int n_kv) {
+                                                       float* dqkv, float* __restrict__ qcopy, const float2* __restrict__ rope,
+                                                       float* __restrict__ Dws, int seq, int n_q, int n_kv) {
   typedef F32<D> F;
   __shared__ __attribute__((aligned(16))) float part[4][ROWS][D + 4];
   __shared__ int redo;
@@ -192,6 +206,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__
   F::rows(q, base + (size_t)row_q * ld + (size_t)a * D, g);
   F::rows(dO, dout + ((size_t)b * seq + row_q) * ldo + (size_t)a * D, g);
   F::rows(x, o + ((size_t)b * seq + row_q) * ldo + (size_t)a * D, g);
+  if (qcopy && wave == 0 && q0 + r < seq) {                  // dQ will take Q's place: the dK / dV kernel reads this copy
+    float* p = qcopy + ((size_t)b * seq + row_q) * ldo + (size_t)a * D;
+#pragma unroll
+    for (int s = 0; s < F::S; ++s) *reinterpret_cast<f32x4_t*>(p + 16 * s + 4 * g) = q[s];
+  }
   F::scaled(q, scale);
   F::clear(acc);
   float dsum = 0.f;
@@ -225,11 +244,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__
     for (int e = 0; e < 4; ++e)
       out[h][e] = (((part[0][row][c + e] + part[1][row][c + e]) + part[2][row][c + e]) + part[3][row][c + e]) * scale;
     if (q0 + row < seq && !all_finite(out[h])) redo = 1;
+    if (rope && q0 + row < seq) F::turn_back(out[h], part, scale, rope + (size_t)(q0 + row) * (D / 2), row, c);
   }
   __syncthreads();
   if (redo) {
     for (int row = wave; row < ROWS && q0 + row < seq; row += 4)
-      attn_bwd_dq_row<float, F::H>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, q0 + row, a, b, &part[wave][0][0], &part[wave][2][0]);
+      attn_bwd_dq_row<float, F::H>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, q0 + row, a, b, &part[wave][0][0], &part[wave][2][0], rope);
     return;
   }
 #pragma unroll
@@ -241,9 +261,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_f32(const float* __restrict__
 
 // per 16 keys and kv head: dV = sum_t P_t dO_t, dK = scale * sum_t dS_t Q_t over the group's q heads
 template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dout,
+__global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* qkv, const float* qsrc, int ldq, const float* __restrict__ dout,
                                                         const float* __restrict__ lse, const float* __restrict__ Dws,
-                                                        float* __restrict__ dqkv, int seq, int n_q, int n_kv) {
+                                                        float* dqkv, const float2* __restrict__ rope, int seq, int n_q, int n_kv) {
   typedef F32<D> F;
   __shared__ __attribute__((aligned(16))) float part[4][ROWS][D + 4];
   __shared__ int redo;
@@ -261,10 +281,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict_
   const int rep = n_q / n_kv, tiles = (seq + ROWS - 1) / ROWS - tile;   // query tiles at or after these keys
   for (int it = wave; it < rep * tiles; it += 4) {
     const int a = kvh * rep + it / tiles, t = tile + it % tiles;
-    const float *Qp = base + (size_t)a * D, *dOp = dout + (size_t)b * seq * ldo + (size_t)a * D;
+    const float *Qp = qsrc + (size_t)b * seq * ldq + (size_t)a * D, *dOp = dout + (size_t)b * seq * ldo + (size_t)a * D;
     const float *Lp = lse + ((size_t)b * n_q + a) * seq, *Dp = Dws + ((size_t)b * n_q + a) * seq;
     f32x4_t q[F::S], dO[F::S], c[4][F::H];
-    F::rows(q, Qp + (size_t)min(16 * t + r, last) * ld, g);
+    F::rows(q, Qp + (size_t)min(16 * t + r, last) * ldq, g);
     F::rows(dO, dOp + (size_t)min(16 * t + r, last) * ldo, g);
     const f32x4_t s = F::product(q, k), dp = F::product(dO, v);   // [e]: query 16 t + 4 g + e, key k0 + r
     f32x4_t p, ds;
@@ -276,7 +296,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict_
     }
     F::columns(c, dOp, ldo, 16 * t, last, g, r);
     F::accumulate(av, c, p);
-    F::columns(c, Qp, ld, 16 * t, last, g, r);
+    F::columns(c, Qp, ldq, 16 * t, last, g, r);
     F::accumulate(ak, c, ds);
   }
   if (threadIdx.x == 0) redo = 0;
@@ -295,12 +315,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32(const float* __restrict_
         out[which][h][e] = which ? x : x * scale;
       }
       if (k0 + row < seq && !all_finite(out[which][h])) redo = 1;
+      if (!which && rope && k0 + row < seq) F::turn_back(out[0][h], part, scale, rope + (size_t)(k0 + row) * (D / 2), row, c);
     }
   }
   __syncthreads();
   if (redo) {
     for (int row = wave; row < ROWS && k0 + row < seq; row += 4)
-      attn_bwd_dkv_row<float, F::H, false>(qkv, dout, lse, Dws, dqkv, seq, n_q, n_kv, k0 + row, kvh, b, &part[wave][0][0], &part[wave][2][0]);
+      attn_bwd_dkv_row<float, F::H, false>(qkv, qsrc, ldq, dout, lse, Dws, dqkv, seq, n_q, n_kv, k0 + row, kvh, b, &part[wave][0][0],
+                                           &part[wave][2][0], rope);
     return;
   }
 #pragma unroll
@@ -329,15 +351,17 @@ hipError_t launch_attn_fwd_f32(const void* qkv, void* o, float* lse, int seq, in
 }
 
 hipError_t launch_attn_bwd_f32(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws, int seq,
-                               int batch, int n_q, int n_kv, int d, hipStream_t s) {
+                               int batch, int n_q, int n_kv, int d, hipStream_t s, void* qcopy, const float2* rope) {
   const int tiles = (seq + ROWS - 1) / ROWS;
   const float *q = (const float*)qkv, *op = (const float*)o, *dop = (const float*)dout;
-  float* dq = (float*)dqkv;
-  if (d == 64) hipLaunchKernelGGL(attn_bwd_dq_f32<64>, dim3(n_q, batch, tiles), dim3(256), 0, s, q, op, dop, lse, dq, ws, seq, n_q, n_kv);
-  else hipLaunchKernelGGL(attn_bwd_dq_f32<128>, dim3(n_q, batch, tiles), dim3(256), 0, s, q, op, dop, lse, dq, ws, seq, n_q, n_kv);
+  float *dq = (float*)dqkv, *qc = (float*)qcopy;
+  const float* qsrc = qc ? qc : q;
+  const int ldq = (qc ? n_q : n_q + 2 * n_kv) * d;
+  if (d == 64) hipLaunchKernelGGL(attn_bwd_dq_f32<64>, dim3(n_q, batch, tiles), dim3(256), 0, s, q, op, dop, lse, dq, qc, rope, ws, seq, n_q, n_kv);
+  else hipLaunchKernelGGL(attn_bwd_dq_f32<128>, dim3(n_q, batch, tiles), dim3(256), 0, s, q, op, dop, lse, dq, qc, rope, ws, seq, n_q, n_kv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (d == 64) hipLaunchKernelGGL(attn_bwd_dkv_f32<64>, dim3(n_kv, batch, tiles), dim3(256), 0, s, q, dop, lse, ws, dq, seq, n_q, n_kv);
-  else hipLaunchKernelGGL(attn_bwd_dkv_f32<128>, dim3(n_kv, batch, tiles), dim3(256), 0, s, q, dop, lse, ws, dq, seq, n_q, n_kv);
+  if (d == 64) hipLaunchKernelGGL(attn_bwd_dkv_f32<64>, dim3(n_kv, batch, tiles), dim3(256), 0, s, q, qsrc, ldq, dop, lse, ws, dq, rope, seq, n_q, n_kv);
+  else hipLaunchKernelGGL(attn_bwd_dkv_f32<128>, dim3(n_kv, batch, tiles), dim3(256), 0, s, q, qsrc, ldq, dop, lse, ws, dq, rope, seq, n_q, n_kv);
   return hipGetLastError();
 }

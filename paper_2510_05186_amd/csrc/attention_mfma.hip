@@ -70,6 +70,30 @@ __device__ __forceinline__ float not_finite(const f32x16_t& s, float z = 0.f) {
   return z;
 }
 
+// 4 columns of a gradient row from column `col` on and the 4 columns d / 2 away, scaled, turned back by the rotary angle of the row's
+// position where there is one (fp32, ahead of the one rounding) and stored
+template <int D> __device__ __forceinline__ void store_turned4(bf16_t* row, const float2* angle, int col, f32x4_t lo, f32x4_t hi, float scale) {
+  f32x4_t t0 = {1.f, 0.f, 1.f, 0.f}, t1 = t0;
+  if (angle) {
+    t0 = *reinterpret_cast<const f32x4_t*>(angle + col);
+    t1 = *reinterpret_cast<const f32x4_t*>(angle + col + 2);
+  }
+  bf16x4_t l, h;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = lo[i] * scale, b = hi[i] * scale;
+    if (angle) rope_back(a, b, i < 2 ? t0[2 * (i & 1)] : t1[2 * (i & 1)], i < 2 ? t0[2 * (i & 1) + 1] : t1[2 * (i & 1) + 1]);
+    l[i] = (bf16_t)a;
+    h[i] = (bf16_t)b;
+  }
+  *reinterpret_cast<bf16x4_t*>(row + col) = l;
+  *reinterpret_cast<bf16x4_t*>(row + col + D / 2) = h;
+}
+template <int D> __device__ __forceinline__ void store_turned(bf16_t* row, const float2* angle, int col, const f32x16_t& lo, const f32x16_t& hi,
+                                                              int v, float scale) {
+  store_turned4<D>(row, angle, col, f32x4_t{lo[v], lo[v + 1], lo[v + 2], lo[v + 3]}, f32x4_t{hi[v], hi[v + 1], hi[v + 2], hi[v + 3]}, scale);
+}
+
 // max over the two lanes 32 apart (the two halves of a score row), in both of them: v_permlane32_swap exchanges
 // the upper half of its first operand with the lower half of its second, so swapping x with itself gives
 // (x.low, x.low) and (x.high, x.high).  A vector instruction: no trip through the LDS crossbar.
@@ -447,10 +471,10 @@ __global__ __launch_bounds__(256) void attn_fwd_mfma(const bf16_t* __restrict__ 
 // Also produces D_t = <dO_t, O_t> per query row and head (from the dO fragments it holds anyway) and stores it
 // for the dK/dV kernel, which runs after this one.
 template <int D, int QT>
-__global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+__global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* qkv, const bf16_t* __restrict__ o,
                                                         const bf16_t* __restrict__ dout, const float* __restrict__ lse,
-                                                        float* __restrict__ delta, bf16_t* __restrict__ dqkv, int seq,
-                                                        int n_q, int n_kv) {
+                                                        float* __restrict__ delta, bf16_t* dqkv, bf16_t* __restrict__ qcopy,
+                                                        const float2* __restrict__ rope, int seq, int n_q, int n_kv) {
   typedef Head<D> H;
   constexpr int ROWB = H::ROWB, TILE = H::TILE, NKS = H::NKS, NDT = H::NDT, NLD = H::NLD;
   constexpr int DQ_STAGE = 2 * TILE;           // K tile, V tile of 64 keys
@@ -486,6 +510,11 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
       const bf16x8_t of = *reinterpret_cast<const bf16x8_t*>(op + 16 * ks);
 #pragma unroll
       for (int e = 0; e < 8; ++e) dsum = fmaf((float)dOf[qt][ks][e], (float)of[e], dsum);
+    }
+    if (qcopy && qglob[qt] < seq) {
+      bf16_t* cp = qcopy + ((size_t)b * seq + qrow) * ldo + (size_t)a * D + 8 * g;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) *reinterpret_cast<bf16x8_t*>(cp + 16 * ks) = Qf[qt][ks];
     }
     Lc[qt] = -lse[((size_t)b * n_q + a) * seq + qrow] * LOG2E;
     Dq[qt] = dsum + __shfl_xor(dsum, 32, 64);                  // the two lanes of a row hold 64 columns each
@@ -713,21 +742,17 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
       if (__any(qglob[qt] < seq && z != 0.f)) {
         float* own = reinterpret_cast<float*>(smem + 2 * DQ_STAGE) + wave * 2 * D;
         for (int t = wave_first_q + 32 * qt; t < min(wave_first_q + 32 * qt + 32, seq); ++t)
-          attn_bwd_dq_row<bf16_t, D / 64>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, t, a, b, own, own + D);
+          attn_bwd_dq_row<bf16_t, D / 64>(qkv, o, dout, lse, dqkv, nullptr, seq, n_q, n_kv, t, a, b, own, own + D, rope);
         continue;
       }
     }
     if (qglob[qt] >= seq) continue;
     bf16_t* dq = dqkv + ((size_t)b * seq + qglob[qt]) * ld + (size_t)a * D;
+    const float2* angle = rope ? rope + (size_t)qglob[qt] * (D / 2) : nullptr;
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+    for (int dt = 0; dt < NDT / 2; ++dt)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bf16x4_t r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = (bf16_t)(acc[qt][dt][4 * j + i] * scale);
-        *reinterpret_cast<bf16x4_t*>(dq + 32 * dt + 8 * j + 4 * g) = r;
-      }
+      for (int j = 0; j < 4; ++j) store_turned<D>(dq, angle, 32 * dt + 8 * j + 4 * g, acc[qt][dt], acc[qt][dt + NDT / 2], 4 * j, scale);
   }
 }
 
@@ -748,10 +773,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_mfma(const bf16_t* __restrict
 // workgroups, each writing an fp32 partial ([part][batch][seq][kv head][K|V][128]) that attn_bwd_dkv_reduce sums
 // in a fixed order.
 template <int D, int KT>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+__global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* qkv, const bf16_t* qsrc, int ldq, const bf16_t* __restrict__ dout,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                                         bf16_t* __restrict__ dqkv, float* __restrict__ partial, int split,
-                                                         int seq, int n_q, int n_kv) {
+                                                         bf16_t* dqkv, float* __restrict__ partial, const float2* __restrict__ rope,
+                                                         int split, int seq, int n_q, int n_kv) {
   typedef Head<D> H;
   constexpr int ROWB = H::ROWB, TILE = H::TILE, NKS = H::NKS, NDT = H::NDT, NLD = H::NLD;
   constexpr int DKV_STAGE = 2 * TILE + 512;    // Q tile, dO tile, 64 lse, 64 D; behind two of them V rows of 256 keys
@@ -808,7 +833,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   for (int j = 0; j < NLD; ++j) {
     const int row = 16 * wave + H::RPL * j + lane / H::CH;
     const int chunk = (lane % H::CH) ^ H::swz(row);
-    voff_q[j] = (unsigned)row * (unsigned)ld * 2u + (unsigned)chunk * 16u;
+    voff_q[j] = (unsigned)row * (unsigned)ldq * 2u + (unsigned)chunk * 16u;
     voff_do[j] = (unsigned)row * (unsigned)ldo * 2u + (unsigned)chunk * 16u;
   }
   auto make_desc = [](const void* p, unsigned bytes) {
@@ -820,13 +845,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     d[3] = 0x00020000;
     return d;
   };
-  const i32x4_t rs_q = make_desc(base, (unsigned)seq * ld * 2u);
+  const i32x4_t rs_q = make_desc(qsrc + (size_t)b * seq * ldq, (unsigned)seq * ldq * 2u);
   const i32x4_t rs_do = make_desc(dout + (size_t)b * seq * ldo, (unsigned)seq * ldo * 2u);
   const i32x4_t rs_l = make_desc(lse + (size_t)b * n_q * seq, (unsigned)n_q * seq * 4u);
   const i32x4_t rs_d = make_desc(delta + (size_t)b * n_q * seq, (unsigned)n_q * seq * 4u);
   const unsigned lds0 = (unsigned)(size_t)(lds_void_t*)smem;
 
   // V rows of this wave's 64 keys -> LDS (16 loads of 4 rows), same layout as the streamed tiles
+  const i32x4_t rs_v = make_desc(base, (unsigned)seq * ld * 2u);
   const char* sV = smem + 2 * DKV_STAGE + wave * WK * ROWB;
 #pragma unroll
   for (int j = 0; j < 2 * KT * NLD; ++j) {
@@ -834,7 +860,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     const int chunk = (lane % H::CH) ^ H::swz(row);
     const unsigned vo = ((unsigned)(wave_first_k + row) * (unsigned)ld + (unsigned)(n_q + n_kv + kvh) * D) * 2u + (unsigned)chunk * 16u;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds0 + 2 * DKV_STAGE + wave * WK * ROWB + j * 1024), "v"(vo), "s"(rs_q) : "memory", "m0");
+                 :: "s"(lds0 + 2 * DKV_STAGE + wave * WK * ROWB + j * 1024), "v"(vo), "s"(rs_v) : "memory", "m0");
   }
   const int rep = n_q / n_kv / split;                          // query heads of the group handled here
   const int qb0 = k0 / 64, nqb = (seq + 63) / 64 - qb0;       // query blocks at or after the first key
@@ -843,7 +869,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
   auto issue_block = [&](int it, int stage) {
     const int a = (kvh * split + part) * rep + it / nqb;
     const int r0 = 64 * (qb0 + it % nqb);
-    const unsigned oq = ((unsigned)r0 * (unsigned)ld + (unsigned)a * D) * 2u;
+    const unsigned oq = ((unsigned)r0 * (unsigned)ldq + (unsigned)a * D) * 2u;
     const unsigned od = ((unsigned)r0 * (unsigned)ldo + (unsigned)a * D) * 2u;
     const unsigned dst = lds0 + stage * DKV_STAGE + (16 * wave) * ROWB;
 #pragma unroll
@@ -1052,7 +1078,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
       if (__any(kglob < seq && z != 0.f)) {
         float* own = reinterpret_cast<float*>(smem + 2 * DKV_STAGE + 4 * WK * ROWB) + wave * 2 * D;
         for (int t = wave_first_k + 32 * kk; t < min(wave_first_k + 32 * kk + 32, seq); ++t)
-          attn_bwd_dkv_row<bf16_t, D / 64, true>(qkv, dout, lse, delta, dqkv, seq, n_q, n_kv, t, kvh, b, own, own + D);
+          attn_bwd_dkv_row<bf16_t, D / 64, true>(qkv, qsrc, ldq, dout, lse, delta, dqkv, seq, n_q, n_kv, t, kvh, b, own, own + D, rope);
         continue;
       }
     }
@@ -1073,45 +1099,42 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_mfma(const bf16_t* __restric
     }
     bf16_t* krow = dqkv + ((size_t)b * seq + kglob) * ld + (size_t)(n_q + kvh) * D;
     bf16_t* vrow = dqkv + ((size_t)b * seq + kglob) * ld + (size_t)(n_q + n_kv + kvh) * D;
+    const float2* angle = rope ? rope + (size_t)kglob * (D / 2) : nullptr;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        bf16x4_t rk, rv;
+        __builtin_amdgcn_sched_barrier(0);                     // no registers to spare for several table reads in flight
+        if (dt < NDT / 2) store_turned<D>(krow, angle, 32 * dt + 8 * j + 4 * g, accK[kk][dt], accK[kk][(dt + NDT / 2) % NDT], 4 * j, scale);
+        bf16x4_t rv;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          rk[i] = (bf16_t)(accK[kk][dt][4 * j + i] * scale);
-          rv[i] = (bf16_t)accV[kk][dt][4 * j + i];
-        }
-        *reinterpret_cast<bf16x4_t*>(krow + 32 * dt + 8 * j + 4 * g) = rk;
+        for (int i = 0; i < 4; ++i) rv[i] = (bf16_t)accV[kk][dt][4 * j + i];
         *reinterpret_cast<bf16x4_t*>(vrow + 32 * dt + 8 * j + 4 * g) = rv;
       }
   }
 }
 
-// sums the `split` partials of dK, dV (fixed order), scales dK by 1 / sqrt(d) and stores bf16 into the packed
-// gradient rows: one thread per 4 columns of one (token, kv head, K|V)
-__global__ void attn_bwd_dkv_reduce(const float* __restrict__ partial, bf16_t* __restrict__ dqkv, int split, int rows,
-                                    int n_q, int n_kv) {
-  constexpr int D = 128;
+// sums the `split` partials of dK, dV (fixed order), scales dK by 1 / sqrt(d), turns it back by the rotary angle where a table is given,
+// and stores bf16 into the packed gradient rows: one thread per 4 columns of one (token, kv head, K|V) and the 4 columns d / 2 away
+__global__ void attn_bwd_dkv_reduce(const float* __restrict__ partial, bf16_t* __restrict__ dqkv, const float2* __restrict__ rope,
+                                    int split, int rows, int seq, int n_q, int n_kv) {
+  constexpr int D = 128, Q = D / 8;                           // threads per (token, kv head, K|V)
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t per_part = (size_t)rows * n_kv * 2 * D;
-  if (idx * 4 >= per_part) return;
-  const size_t e = idx * 4;
-  const int col = (int)(e % D);
-  const int kv = (int)((e / D) % 2);
-  const int h = (int)((e / (2 * D)) % n_kv);
-  const size_t row = e / ((size_t)2 * D * n_kv);
-  f32x4_t acc = *reinterpret_cast<const f32x4_t*>(partial + e);
-  for (int p = 1; p < split; ++p) {
-    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(partial + p * per_part + e);
-    acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
+  if (idx * 8 >= per_part) return;
+  const int col = (int)(idx % Q) * 4, kv = (int)((idx / Q) % 2);
+  const int h = (int)((idx / (2 * Q)) % n_kv);
+  const size_t row = idx / ((size_t)2 * Q * n_kv);
+  const float* p = partial + idx / Q * D + col;
+  f32x4_t lo = *reinterpret_cast<const f32x4_t*>(p), hi = *reinterpret_cast<const f32x4_t*>(p + D / 2);
+  for (int i = 1; i < split; ++i) {
+    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p + i * per_part), w = *reinterpret_cast<const f32x4_t*>(p + i * per_part + D / 2);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { lo[e] += v[e]; hi[e] += w[e]; }
   }
-  const float sc = kv == 0 ? rsqrtf((float)D) : 1.f;
-  bf16x4_t o;
-  o[0] = (bf16_t)(acc[0] * sc); o[1] = (bf16_t)(acc[1] * sc); o[2] = (bf16_t)(acc[2] * sc); o[3] = (bf16_t)(acc[3] * sc);
   const int ld = (n_q + 2 * n_kv) * D;
-  *reinterpret_cast<bf16x4_t*>(dqkv + row * ld + (size_t)(n_q + kv * n_kv + h) * D + col) = o;
+  store_turned4<D>(dqkv + row * ld + (size_t)(n_q + kv * n_kv + h) * D, kv == 0 && rope ? rope + row % seq * (D / 2) : nullptr, col, lo, hi,
+                   kv == 0 ? rsqrtf((float)D) : 1.f);
 }
 
 }  // namespace
@@ -1146,7 +1169,7 @@ template <int D, int QT> hipError_t fwd_d(const void* qkv, void* o, float* lse, 
 }
 
 template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                         int seq, int batch, int n_q, int n_kv, hipStream_t s) {
+                                         int seq, int batch, int n_q, int n_kv, hipStream_t s, void* qcopy, const float2* rope) {
   constexpr int G = 128 * T;                                  // rows of a workgroup
   hipError_t e;
   constexpr int dq_smem = 2 * 2 * Head<D>::TILE + Head<D>::ROW_LDS;
@@ -1156,7 +1179,7 @@ template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const v
   auto dkv = attn_bwd_dkv_mfma<D, T>;
   if ((e = dq_attr.ensure(reinterpret_cast<const void*>(dq), dq_smem)) != hipSuccess) return e;
   hipLaunchKernelGGL(dq, dim3(n_q, batch, (seq + G - 1) / G), dim3(256), dq_smem, s, (const bf16_t*)qkv,
-      (const bf16_t*)o, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, seq, n_q, n_kv);
+      (const bf16_t*)o, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, (bf16_t*)qcopy, rope, seq, n_q, n_kv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = dkv_attr.ensure(reinterpret_cast<const void*>(dkv), dkv_smem)) != hipSuccess) return e;
@@ -1164,13 +1187,14 @@ template <int D, int T> hipError_t bwd_d(const void* qkv, const void* o, const v
   const int split = D == 128 ? attn_dkv_split(seq, batch, n_q, n_kv) : 1;
   float* partial = ws + (size_t)batch * n_q * seq;            // behind the D array
   hipLaunchKernelGGL(dkv, dim3(n_kv * split, batch, (seq + G - 1) / G), dim3(256), dkv_smem, s,
-      (const bf16_t*)qkv, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv, partial, split, seq, n_q, n_kv);
+      (const bf16_t*)qkv, (const bf16_t*)(qcopy ? qcopy : qkv), (qcopy ? n_q : n_q + 2 * n_kv) * D, (const bf16_t*)dout, lse, ws, (bf16_t*)dqkv,
+      partial, rope, split, seq, n_q, n_kv);
   if (split > 1) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t quads = (size_t)batch * seq * n_kv * 2 * D / 4;
-    hipLaunchKernelGGL(attn_bwd_dkv_reduce, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, s, partial, (bf16_t*)dqkv,
-        split, batch * seq, n_q, n_kv);
+    const size_t items = (size_t)batch * seq * n_kv * 2 * D / 8;
+    hipLaunchKernelGGL(attn_bwd_dkv_reduce, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, partial, (bf16_t*)dqkv, rope,
+        split, batch * seq, seq, n_q, n_kv);
   }
   return hipGetLastError();
 }
@@ -1194,8 +1218,8 @@ hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, i
 }
 
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
-  if (d == 64) return bwd_d<64, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
-  return wide_workgroups(seq, batch, n_q) <= BWD_WGS ? bwd_d<128, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s)
-                                                     : bwd_d<128, 2>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s);
+                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s, void* qcopy, const float2* rope) {
+  if (d == 64) return bwd_d<64, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s, qcopy, rope);
+  return wide_workgroups(seq, batch, n_q) <= BWD_WGS ? bwd_d<128, 1>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s, qcopy, rope)
+                                                     : bwd_d<128, 2>(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s, qcopy, rope);
 }

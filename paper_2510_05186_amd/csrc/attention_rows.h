@@ -13,6 +13,23 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Columns k and k + d / 2 of a gradient row, turned back by the angle of the row's position (the transposed rotary rotation)
+__device__ __forceinline__ void rope_back(float& lo, float& hi, float cs, float sn) {
+  const float a = lo;
+  lo = a * cs + hi * sn;
+  hi = hi * cs - a * sn;
+}
+// the same for a row spread over a wave: lane l holds the columns l + 64 e; table row of the position, d / 2 (cos, sin) pairs
+template <int DPL> __device__ __forceinline__ void rope_back_row(float (&v)[DPL], const float2* row, int lane) {
+  if constexpr (DPL == 2) {
+    rope_back(v[0], v[1], row[lane].x, row[lane].y);
+  } else {
+    const float other = __shfl_xor(v[0], 32, 64);
+    const float2 t = row[lane & 31];
+    v[0] = lane < 32 ? v[0] * t.x + other * t.y : v[0] * t.x - other * t.y;
+  }
+}
+
 // qs: 64 DPL floats
 template <typename T, int DPL>
 __device__ __forceinline__ void attn_fwd_row(const T* __restrict__ qkv, T* __restrict__ o, float* __restrict__ lse, int seq, int n_q,
@@ -60,11 +77,13 @@ __device__ __forceinline__ void attn_fwd_row(const T* __restrict__ qkv, T* __res
   if (lane == 0) lse[((size_t)b * n_q + a) * seq + t] = m + logf(l);
 }
 
-// D_t = <dO_t, O_t> (stored where Dws is given), dQ_t = scale * sum_j dS_tj K_j.  qs, dos: 64 DPL floats each
+// D_t = <dO_t, O_t> (stored where Dws is given), dQ_t = scale * sum_j dS_tj K_j, turned back by the rotary angle where a table is given.
+// dqkv may be qkv itself: the row's Q is read before its dQ is written.  qs, dos: 64 DPL floats each
 template <typename T, int DPL>
-__device__ __forceinline__ void attn_bwd_dq_row(const T* __restrict__ qkv, const T* __restrict__ o, const T* __restrict__ dout,
-                                                const float* __restrict__ lse, T* __restrict__ dqkv, float* __restrict__ Dws,
-                                                int seq, int n_q, int n_kv, int t, int a, int b, float* qs, float* dos) {
+__device__ __forceinline__ void attn_bwd_dq_row(const T* qkv, const T* __restrict__ o, const T* __restrict__ dout,
+                                                const float* __restrict__ lse, T* dqkv, float* __restrict__ Dws,
+                                                int seq, int n_q, int n_kv, int t, int a, int b, float* qs, float* dos,
+                                                const float2* rope = nullptr) {
   constexpr int D = 64 * DPL;
   const int lane = threadIdx.x & 63, g = a * n_kv / n_q;
   const int ld = (n_q + 2 * n_kv) * D;
@@ -111,15 +130,19 @@ __device__ __forceinline__ void attn_bwd_dq_row(const T* __restrict__ qkv, const
   }
   T* dq = dqkv + ((size_t)b * seq + t) * ld + a * D;
 #pragma unroll
-  for (int e = 0; e < DPL; ++e) dq[lane + 64 * e] = from_f32<T>(acc[e] * scale);
+  for (int e = 0; e < DPL; ++e) acc[e] *= scale;
+  if (rope) rope_back_row<DPL>(acc, rope + (size_t)t * (D / 2), lane);
+#pragma unroll
+  for (int e = 0; e < DPL; ++e) dq[lane + 64 * e] = from_f32<T>(acc[e]);
 }
 
-// Key row tk of kv head g: dV = sum_t P_t dO_t, dK = scale * sum_t dS_t Q_t over the group's q heads.  Dws holds D, or -D where
-// NEG_D.  ks, vs: 64 DPL floats each
+// Key row tk of kv head g: dV = sum_t P_t dO_t, dK = scale * sum_t dS_t Q_t over the group's q heads, dK turned back by the rotary angle
+// where a table is given.  Q comes from q rows of ldq elements (qkv itself, or a copy where dqkv is qkv and holds dQ by now).  Dws
+// holds D, or -D where NEG_D.  ks, vs: 64 DPL floats each
 template <typename T, int DPL, bool NEG_D>
-__device__ __forceinline__ void attn_bwd_dkv_row(const T* __restrict__ qkv, const T* __restrict__ dout, const float* __restrict__ lse,
-                                                 const float* __restrict__ Dws, T* __restrict__ dqkv, int seq, int n_q, int n_kv,
-                                                 int tk, int g, int b, float* ks, float* vs) {
+__device__ __forceinline__ void attn_bwd_dkv_row(const T* qkv, const T* q, int ldq, const T* __restrict__ dout, const float* __restrict__ lse,
+                                                 const float* __restrict__ Dws, T* dqkv, int seq, int n_q, int n_kv,
+                                                 int tk, int g, int b, float* ks, float* vs, const float2* rope = nullptr) {
   constexpr int D = 64 * DPL;
   const int lane = threadIdx.x & 63;
   const int ld = (n_q + 2 * n_kv) * D;
@@ -142,7 +165,7 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const T* __restrict__ qkv, cons
       const int tq = c0 + lane;
       float p = 0.f, dS = 0.f;
       if (tq >= tk && tq < seq) {
-        const T* qr = base + (size_t)tq * ld + a * D;
+        const T* qr = q + ((size_t)b * seq + tq) * ldq + a * D;
         const T* dor = dout + ((size_t)b * seq + tq) * (n_q * D) + a * D;
         float s = 0.f, dp = 0.f;
         for (int dd = 0; dd < D; ++dd) {
@@ -155,7 +178,7 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const T* __restrict__ qkv, cons
       const int j0 = max(0, tk - c0), j1 = min(64, seq - c0);
       for (int j = j0; j < j1; ++j) {
         const float pj = __shfl(p, j, 64), dj = __shfl(dS, j, 64);
-        const T* qr = base + (size_t)(c0 + j) * ld + a * D;
+        const T* qr = q + ((size_t)b * seq + c0 + j) * ldq + a * D;
         const T* dor = dout + ((size_t)b * seq + c0 + j) * (n_q * D) + a * D;
 #pragma unroll
         for (int e = 0; e < DPL; ++e) {
@@ -168,8 +191,11 @@ __device__ __forceinline__ void attn_bwd_dkv_row(const T* __restrict__ qkv, cons
   T* dkr = dqkv + ((size_t)b * seq + tk) * ld + (n_q + g) * D;
   T* dvr = dqkv + ((size_t)b * seq + tk) * ld + (n_q + n_kv + g) * D;
 #pragma unroll
+  for (int e = 0; e < DPL; ++e) dk[e] *= scale;
+  if (rope) rope_back_row<DPL>(dk, rope + (size_t)tk * (D / 2), lane);
+#pragma unroll
   for (int e = 0; e < DPL; ++e) {
-    dkr[lane + 64 * e] = from_f32<T>(dk[e] * scale);
+    dkr[lane + 64 * e] = from_f32<T>(dk[e]);
     dvr[lane + 64 * e] = from_f32<T>(dv[e]);
   }
 }

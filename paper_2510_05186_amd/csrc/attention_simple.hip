@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple(const T* __restrict__
   __shared__ float ks[4][64 * DPL];
   __shared__ float vs[4][64 * DPL];
   const int wave = threadIdx.x >> 6, tk = blockIdx.x * 4 + wave;
-  if (tk < seq) attn_bwd_dkv_row<T, DPL, false>(qkv, dout, lse, Dws, dqkv, seq, n_q, n_kv, tk, blockIdx.y, blockIdx.z, ks[wave], vs[wave]);
+  if (tk < seq) attn_bwd_dkv_row<T, DPL, false>(qkv, qkv, (n_q + 2 * n_kv) * 64 * DPL, dout, lse, Dws, dqkv, seq, n_q, n_kv, tk, blockIdx.y, blockIdx.z, ks[wave], vs[wave]);
 }
 
 template <typename T, int DPL>

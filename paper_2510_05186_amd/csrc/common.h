@@ -97,11 +97,12 @@ hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, vo
 // n (up to 16) independent fp32 TN products with the same K in one launch
 bool gemm_f32_grouped_applies(int n, const GemmProblem* problems, int K);
 hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* problems, int K, hipStream_t s);
+// x_copy / dres_copy: where given, the kernel also stores the x / dres that it reads there
 hipError_t launch_norm_fwd(int dtype, int family, const void* x, const void* gamma, const void* beta, void* out,
-                           float* stats, int rows, int h, float eps, hipStream_t s);
+                           float* stats, int rows, int h, float eps, hipStream_t s, void* x_copy = nullptr);
 hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x, const float* stats,
                            const void* gamma, const void* dres, void* dx, float* partial, float* dgamma,
-                           float* dbeta, int rows, int h, hipStream_t s, int overwrite = 0);
+                           float* dbeta, int rows, int h, hipStream_t s, int overwrite = 0, void* dres_copy = nullptr);
 int norm_bwd_partial_rows(int rows);
 hipError_t launch_act_fwd(int dtype, int family, const void* gu, void* a, int rows, int f, hipStream_t s);
 hipError_t launch_act_bwd(int dtype, int family, const void* da, const void* gu, void* dgu, int rows, int f,
@@ -122,4 +123,10 @@ hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int 
 // ws: fp32 scratch of attn_bwd_ws_floats() elements
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv,
                            float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
+// the same with the gradient written over qkv, rotated back where a rotary table is given; qcopy: scratch for rows x n_q x d elements of
+// the storage type.  Which calls it serves: attn_bwd_inplace_applies
+bool attn_bwd_inplace_applies(int dtype, int d, int seq, int batch, int n_q, int n_kv, const void* qkv, const void* o, const void* dout,
+                              const void* qcopy);
+hipError_t launch_attn_bwd_inplace(int dtype, void* qkv, const void* o, const void* dout, const float* lse, void* qcopy, const float* rope_table,
+                                   float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 uint64_t attn_bwd_ws_floats(int seq, int batch, int n_q, int n_kv, int d);

@@ -20,7 +20,7 @@ __device__ __forceinline__ float block_sum(float v, float* red /* [2][4] */, int
 // ---- norm forward: one row per workgroup ------------------------------------------------------------
 template <typename T, bool LN>
 __global__ __launch_bounds__(NT) void norm_fwd_kernel(const T* __restrict__ x, const T* __restrict__ gamma,
-                                                      const T* __restrict__ beta, T* __restrict__ out,
+                                                      const T* __restrict__ beta, T* __restrict__ out, T* __restrict__ x_copy,
                                                       float* __restrict__ stats, int rows, int h, float eps) {
   typedef Vec16<T> V;
   __shared__ float red[16];
@@ -35,6 +35,7 @@ __global__ __launch_bounds__(NT) void norm_fwd_kernel(const T* __restrict__ x, c
       xv[c] = *reinterpret_cast<const V*>(x + (size_t)row * h + ci * V::N);
 #pragma unroll
       for (int e = 0; e < V::N; ++e) { float f = xv[c].get(e); s1 += f; s2 += f * f; }
+      if (x_copy) *reinterpret_cast<V*>(x_copy + (size_t)row * h + ci * V::N) = xv[c];
     }
   }
   float mean = 0.f;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(NT) void norm_fwd_kernel(const T* __restrict__ x, c
 template <typename T, bool LN>
 __global__ __launch_bounds__(NT) void norm_bwd_kernel(const T* __restrict__ dn, const T* __restrict__ x,
                                                       const float* __restrict__ stats, const T* __restrict__ gamma,
-                                                      const T* __restrict__ dres, T* __restrict__ dx,
+                                                      const T* __restrict__ dres, T* __restrict__ dx, T* __restrict__ dres_copy,
                                                       float* __restrict__ partial, int rows, int h) {
   typedef Vec16<T> V;
   __shared__ float red[16];
@@ -152,6 +153,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_kernel(const T* __restrict__ dn, 
           if (dres) d += rv[buf][c].get(e);
           o.set(e, d);
         }
+        if (dres_copy) *reinterpret_cast<V*>(dres_copy + (size_t)row * h + ci * V::N) = rv[buf][c];
         *reinterpret_cast<V*>(dx + (size_t)row * h + ci * V::N) = o;
       }
     }
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_kernel(const T* __restrict__ dn, 
 template <typename T, bool LN>
 __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(const T* __restrict__ dn, const T* __restrict__ x,
                                                            const float* __restrict__ stats, const T* __restrict__ gamma,
-                                                           const T* __restrict__ dres, T* __restrict__ dx,
+                                                           const T* __restrict__ dres, T* __restrict__ dx, T* __restrict__ dres_copy,
                                                            float* __restrict__ partial, int rows, int h) {
   typedef Vec16<T> V;
   constexpr int MAXH = 64 * MAXC * V::N;
@@ -257,6 +259,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(const T* __restrict__
           if (dres) d += rv[buf][c].get(e);
           o.set(e, d);
         }
+        if (dres_copy) *reinterpret_cast<V*>(dres_copy + (size_t)row * h + ci * V::N) = rv[buf][c];
         *reinterpret_cast<V*>(dx + (size_t)row * h + ci * V::N) = o;
       }
     }
@@ -552,21 +555,21 @@ template <typename T> bool norm_shape_ok(int h) { return h > 0 && h % Vec16<T>::
 }  // namespace
 
 hipError_t launch_norm_fwd(int dtype, int family, const void* x, const void* gamma, const void* beta, void* out,
-                           float* stats, int rows, int h, float eps, hipStream_t s) {
+                           float* stats, int rows, int h, float eps, hipStream_t s, void* x_copy) {
   if (rows <= 0) return hipErrorInvalidValue;
   const bool ln = family == FAM_GPT;
   if (dtype == DT_BF16) {
     if (!norm_shape_ok<bf16_t>(h)) return hipErrorInvalidValue;
     if (ln) hipLaunchKernelGGL((norm_fwd_kernel<bf16_t, true>), dim3(rows), dim3(NT), 0, s, (const bf16_t*)x,
-        (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)out, stats, rows, h, eps);
+        (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)out, (bf16_t*)x_copy, stats, rows, h, eps);
     else hipLaunchKernelGGL((norm_fwd_kernel<bf16_t, false>), dim3(rows), dim3(NT), 0, s, (const bf16_t*)x,
-        (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)out, stats, rows, h, eps);
+        (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)out, (bf16_t*)x_copy, stats, rows, h, eps);
   } else {
     if (!norm_shape_ok<float>(h)) return hipErrorInvalidValue;
     if (ln) hipLaunchKernelGGL((norm_fwd_kernel<float, true>), dim3(rows), dim3(NT), 0, s, (const float*)x,
-        (const float*)gamma, (const float*)beta, (float*)out, stats, rows, h, eps);
+        (const float*)gamma, (const float*)beta, (float*)out, (float*)x_copy, stats, rows, h, eps);
     else hipLaunchKernelGGL((norm_fwd_kernel<float, false>), dim3(rows), dim3(NT), 0, s, (const float*)x,
-        (const float*)gamma, (const float*)beta, (float*)out, stats, rows, h, eps);
+        (const float*)gamma, (const float*)beta, (float*)out, (float*)x_copy, stats, rows, h, eps);
   }
   return hipGetLastError();
 }
@@ -578,32 +581,32 @@ int norm_bwd_partial_rows(int rows) { return rows < 256 ? rows : 256; }
 
 hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x, const float* stats,
                            const void* gamma, const void* dres, void* dx, float* partial, float* dgamma,
-                           float* dbeta, int rows, int h, hipStream_t s, int overwrite) {
-  if (rows <= 0) return hipErrorInvalidValue;
+                           float* dbeta, int rows, int h, hipStream_t s, int overwrite, void* dres_copy) {
+  if (rows <= 0 || (dres_copy && !dres)) return hipErrorInvalidValue;
   const bool ln = family == FAM_GPT;
   const int nb = norm_bwd_partial_rows(rows);
   if (dtype == DT_BF16) {
     if (!norm_shape_ok<bf16_t>(h)) return hipErrorInvalidValue;
     const bool narrow = h / 8 <= 64 * MAXC && rows >= 4 * nb;   // one row per wave
     if (ln && narrow) hipLaunchKernelGGL((norm_bwd_wave_kernel<bf16_t, true>), dim3(nb), dim3(NT), 0, s, (const bf16_t*)dn,
-        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, partial, rows, h);
+        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, (bf16_t*)dres_copy, partial, rows, h);
     else if (narrow) hipLaunchKernelGGL((norm_bwd_wave_kernel<bf16_t, false>), dim3(nb), dim3(NT), 0, s, (const bf16_t*)dn,
-        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, partial, rows, h);
+        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, (bf16_t*)dres_copy, partial, rows, h);
     else if (ln) hipLaunchKernelGGL((norm_bwd_kernel<bf16_t, true>), dim3(nb), dim3(NT), 0, s, (const bf16_t*)dn,
-        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, partial, rows, h);
+        (const bf16_t*)x, stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, (bf16_t*)dres_copy, partial, rows, h);
     else hipLaunchKernelGGL((norm_bwd_kernel<bf16_t, false>), dim3(nb), dim3(NT), 0, s, (const bf16_t*)dn, (const bf16_t*)x,
-        stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, partial, rows, h);
+        stats, (const bf16_t*)gamma, (const bf16_t*)dres, (bf16_t*)dx, (bf16_t*)dres_copy, partial, rows, h);
   } else {
     if (!norm_shape_ok<float>(h)) return hipErrorInvalidValue;
     const bool narrow = h / 4 <= 64 * MAXC && rows >= 4 * nb;
     if (ln && narrow) hipLaunchKernelGGL((norm_bwd_wave_kernel<float, true>), dim3(nb), dim3(NT), 0, s, (const float*)dn,
-        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, partial, rows, h);
+        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, (float*)dres_copy, partial, rows, h);
     else if (narrow) hipLaunchKernelGGL((norm_bwd_wave_kernel<float, false>), dim3(nb), dim3(NT), 0, s, (const float*)dn,
-        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, partial, rows, h);
+        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, (float*)dres_copy, partial, rows, h);
     else if (ln) hipLaunchKernelGGL((norm_bwd_kernel<float, true>), dim3(nb), dim3(NT), 0, s, (const float*)dn,
-        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, partial, rows, h);
+        (const float*)x, stats, (const float*)gamma, (const float*)dres, (float*)dx, (float*)dres_copy, partial, rows, h);
     else hipLaunchKernelGGL((norm_bwd_kernel<float, false>), dim3(nb), dim3(NT), 0, s, (const float*)dn, (const float*)x,
-        stats, (const float*)gamma, (const float*)dres, (float*)dx, partial, rows, h);
+        stats, (const float*)gamma, (const float*)dres, (float*)dx, (float*)dres_copy, partial, rows, h);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -14,12 +14,12 @@ hipError_t launch_attn_bwd_simple(int dtype, const void* qkv, const void* o, con
 bool attn_mfma_applies(int dtype, int d, int seq, int n_q, int n_kv, const void* p0, const void* p1, const void* p2, const void* p3);
 hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
+                                int seq, int batch, int n_q, int n_kv, int d, hipStream_t s, void* qcopy, const float2* rope);
 
 bool attn_f32_applies(int dtype, int d, int seq, const void* p0, const void* p1, const void* p2, const void* p3);
 hipError_t launch_attn_fwd_f32(const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 hipError_t launch_attn_bwd_f32(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
-                               int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
+                               int seq, int batch, int n_q, int n_kv, int d, hipStream_t s, void* qcopy, const float2* rope);
 
 // Sequences of a few tokens, for fp32 and for heads of 64: a tile of 16 (fp32) or 32 rows is nearly empty, and the general kernels, a wave
 // per row, have four rows to a workgroup.  Time of the tile kernels over the general ones:
@@ -53,10 +53,26 @@ hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* o, const void
   if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv) return hipErrorInvalidValue;
   if (attn_short_bwd(dtype, d, seq, batch, n_q, n_kv)) return launch_attn_bwd_simple(dtype, qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
   if (attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, dout, dqkv))
-    return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
+    return launch_attn_bwd_mfma(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s, nullptr, nullptr);
   if (attn_f32_applies(dtype, d, seq, qkv, o, dout, dqkv))
-    return launch_attn_bwd_f32(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
+    return launch_attn_bwd_f32(qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s, nullptr, nullptr);
   return launch_attn_bwd_simple(dtype, qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, d, s);
+}
+
+// The gradient in the place of its operand.  Every workgroup of the tile kernels reads the Q rows (dQ kernel) or the K and V rows (dK / dV
+// kernel) that it writes, and no other workgroup of the same launch does; the one reader left, dK / dV's reading of Q, goes to the
+// copy that the dQ kernel makes of the rows it has loaded anyway.  The general kernels read rows whenever they come to them: not
+// served.
+bool attn_bwd_inplace_applies(int dtype, int d, int seq, int batch, int n_q, int n_kv, const void* qkv, const void* o, const void* dout,
+                              const void* qcopy) {
+  if (seq <= 0 || batch <= 0 || n_q <= 0 || n_kv <= 0 || n_q % n_kv || attn_short_bwd(dtype, d, seq, batch, n_q, n_kv)) return false;
+  return attn_mfma_applies(dtype, d, seq, n_q, n_kv, qkv, o, dout, qcopy) || attn_f32_applies(dtype, d, seq, qkv, o, dout, qcopy);
+}
+hipError_t launch_attn_bwd_inplace(int dtype, void* qkv, const void* o, const void* dout, const float* lse, void* qcopy, const float* rope_table,
+                                   float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s) {
+  if (!qcopy || !attn_bwd_inplace_applies(dtype, d, seq, batch, n_q, n_kv, qkv, o, dout, qcopy) || ((uintptr_t)rope_table & 15)) return hipErrorInvalidValue;
+  return dtype == DT_BF16 ? launch_attn_bwd_mfma(qkv, o, dout, lse, qkv, ws, seq, batch, n_q, n_kv, d, s, qcopy, (const float2*)rope_table)
+                          : launch_attn_bwd_f32(qkv, o, dout, lse, qkv, ws, seq, batch, n_q, n_kv, d, s, qcopy, (const float2*)rope_table);
 }
 
 uint64_t attn_bwd_ws_floats(int seq, int batch, int n_q, int n_kv, int d) {

@@ -481,17 +481,17 @@ optstage_status k_gemm_grouped(optstage* st, int layout, int epi, int n, const G
                                                                      : launch_gemm_f32_grouped(epi, n, pr, K, st->cs));
   return OPTSTAGE_OK;
 }
-optstage_status k_norm_fwd(optstage* st, const void* x, const void* g, const void* b, void* out, float* stats) {
+optstage_status k_norm_fwd(optstage* st, const void* x, const void* g, const void* b, void* out, float* stats, void* x_copy = nullptr) {
   const Shape& s = st->sh;
-  KT(OPTSTAGE_KC_NORM_FWD, 2.0 * s.e * s.tokens * s.h, launch_norm_fwd(s.dtype, s.family, x, g, b, out, stats, s.tokens,
-      s.h, st->desc.norm_eps, st->cs));
+  KT(OPTSTAGE_KC_NORM_FWD, (x_copy ? 3.0 : 2.0) * s.e * s.tokens * s.h, launch_norm_fwd(s.dtype, s.family, x, g, b, out, stats, s.tokens,
+      s.h, st->desc.norm_eps, st->cs, x_copy));
   return OPTSTAGE_OK;
 }
 optstage_status k_norm_bwd(optstage* st, const void* dn, const void* x, const float* stats, const void* g, const void* dres,
-    void* dx, float* dg, float* db, bool store) {
+    void* dx, float* dg, float* db, bool store, void* dres_copy = nullptr) {
   const Shape& s = st->sh;
-  KT(OPTSTAGE_KC_NORM_BWD, 4.0 * s.e * s.tokens * s.h, launch_norm_bwd(s.dtype, s.family, dn, x, stats, g, dres, dx,
-      (float*)(st->wsp() + st->ws.partial), dg, db, s.tokens, s.h, st->cs, store ? 1 : 0));
+  KT(OPTSTAGE_KC_NORM_BWD, (dres_copy ? 5.0 : 4.0) * s.e * s.tokens * s.h, launch_norm_bwd(s.dtype, s.family, dn, x, stats, g, dres, dx,
+      (float*)(st->wsp() + st->ws.partial), dg, db, s.tokens, s.h, st->cs, store ? 1 : 0, dres_copy));
   return OPTSTAGE_OK;
 }
 optstage_status k_act_fwd(optstage* st, const void* gu, void* a) {
@@ -524,6 +524,29 @@ optstage_status k_attn_bwd(optstage* st, const void* qkv, const void* o, const v
   return OPTSTAGE_OK;
 }
 
+// Attention backward into the QKV slot, rotary backward included: the gradient takes qkv's place (the executor's table has one slot for
+// both).  `scratch` is a packed [tokens, qkv] transient.  Where the tile kernels serve the call they write the slot themselves,
+// rotated, and keep Q in the scratch meanwhile: no pass over the gradient follows.  Otherwise it goes to the scratch and a kernel moves
+// it into the slot (rotary, or a plain copy for the family without).  Layers of the size that takes rotary into the QKV
+// projection's epilogue keep the rotary kernel here: their per-class kernel timing counts its launches, and it is .4 % of such a
+// layer (4096 tokens, hidden 4096, two micro-batches 8865 us: 35 us); one of hidden 1024 and 320 tokens, where the launch is most of it, 1.5 %.
+optstage_status k_attn_bwd_slot(optstage* st, void* qkv, const void* o, const void* dout, const float* lse, void* scratch) {
+  const Shape& s = st->sh;
+  const bool rotate = s.family == OPTSTAGE_LLAMA;
+  if ((!rotate || (!st->desc.no_fusion && !s.fuse_rope)) &&
+      attn_bwd_inplace_applies(s.dtype, s.d, s.seq, s.mb, s.nq, s.nkv, qkv, o, dout, scratch)) {
+    const float* table = rotate ? (const float*)(st->wsp() + st->ws.rope) : nullptr;
+    KT(OPTSTAGE_KC_ATTN_BWD, 5.0 * s.mb * s.seq * s.seq * s.nq * s.d, launch_attn_bwd_inplace(s.dtype, qkv, o, dout, lse, scratch, table,
+        (float*)(st->wsp() + st->ws.attn), s.seq, s.mb, s.nq, s.nkv, s.d, st->cs));
+    return OPTSTAGE_OK;
+  }
+  optstage_status rc = k_attn_bwd(st, qkv, o, dout, lse, scratch);
+  if (rc != OPTSTAGE_OK) return rc;
+  if (rotate) return k_rope(st, scratch, qkv, 1);
+  HIP_TRY(launch_rope(s.dtype, scratch, qkv, nullptr, s.tokens, s.seq, s.nq, s.nkv, s.d, 1, 0, st->cs));   // a plain copy
+  return OPTSTAGE_OK;
+}
+
 optstage_status check_weights(optstage* st, bool need_grads) {
   const bool gpt = st->sh.family == OPTSTAGE_GPT;
   for (int l = 0; l < st->sh.L; ++l)
@@ -542,7 +565,6 @@ optstage_status exec_forward(optstage* st, int j, int c, const OpBufs& ob) {
   auto P = [&](int l, int k) { return (void*)(st->arena() + ob.dev[(size_t)l * NK + k]); };
   const int l0 = c * s.Lc, l1 = l0 + s.Lc;
   const size_t io = (size_t)c * st->desc.n_microbatches + j;
-  HIP_TRY(hipMemcpyAsync(P(l0, OPTSTAGE_K_X_IN), st->x_in[io], st->raw[OPTSTAGE_K_X_IN], hipMemcpyDeviceToDevice, cs));
   const int nstat = s.family == OPTSTAGE_LLAMA ? 1 : 2;
   const bool rc = st->lg.recompute;
   for (int l = l0; l < l1; ++l) {
@@ -552,7 +574,8 @@ optstage_status exec_forward(optstage* st, int j, int c, const OpBufs& ob) {
     void* n1 = rc ? (void*)(st->wsp() + st->ws.dn) : P(l, OPTSTAGE_K_N1);
     void* n2 = rc ? (void*)(st->wsp() + st->ws.dn) : P(l, OPTSTAGE_K_N2);
     void* a = rc ? (void*)(st->wsp() + st->ws.da) : P(l, OPTSTAGE_K_A);
-    TRY(k_norm_fwd(st, x, W(st, l, OPTSTAGE_W_G1), W(st, l, OPTSTAGE_W_B1), n1, stats));
+    // the caller's input enters the first layer's X_IN slot by way of that layer's norm, which reads it anyway
+    TRY(k_norm_fwd(st, l == l0 ? st->x_in[io] : x, W(st, l, OPTSTAGE_W_G1), W(st, l, OPTSTAGE_W_B1), n1, stats, l == l0 ? x : nullptr));
     int lay;
     const void* wq = fwd_operand(st, l, OPTSTAGE_W_QKV, &lay);
     if (s.fuse_rope) {
@@ -601,9 +624,10 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
   // B ops of a chunk run in micro-batch order, so micro-batch 0 is the iteration's first: in overwrite mode it
   // stores the norm parameters' gradients instead of adding to what the accumulators held
   const bool store = st->overwrite && j == 0;
-  HIP_TRY(hipMemcpyAsync(P(l1 - 1, OPTSTAGE_K_DY), st->dy_out[io], st->raw[OPTSTAGE_K_DY], hipMemcpyDeviceToDevice, cs));
   for (int l = l1 - 1; l >= l0; --l) {
-    void* dy = P(l, OPTSTAGE_K_DY);
+    // the caller's gradient enters the last layer's DY slot, which W reads, by way of that layer's second norm
+    const bool top = l == l1 - 1;
+    const void* dy = top ? st->dy_out[io] : P(l, OPTSTAGE_K_DY);
     float* stats = (float*)P(l, OPTSTAGE_K_STATS);
     // da = dy W_d ; dgu = act'(gu) da (over gu) ; dn2 = dgu W_gu
     int lay;
@@ -617,15 +641,11 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
         OPTSTAGE_K_N2), stats + (size_t)nstat * T));
     // dx_mid = dy + norm2'(dn2)
     TRY(k_norm_bwd(st, dn, P(l, OPTSTAGE_K_X_MID), stats + (size_t)nstat * T, W(st, l, OPTSTAGE_W_G2), dy, P(l,
-        OPTSTAGE_K_DX_MID), GW(st, l, OPTSTAGE_W_G2), GW(st, l, OPTSTAGE_W_B2), store));
+        OPTSTAGE_K_DX_MID), GW(st, l, OPTSTAGE_W_G2), GW(st, l, OPTSTAGE_W_B2), store, top ? P(l, OPTSTAGE_K_DY) : nullptr));
     // do = dx_mid W_o ; attention backward ; rotary backward into the qkv buffer
     const void* wo = bwd_operand(st, l, OPTSTAGE_W_O, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_DX_MID), wo, dout, nullptr, T, s.nq * s.d, s.h, s.h, s.h, s.nq * s.d));
-    TRY(k_attn_bwd(st, P(l, OPTSTAGE_K_QKV), P(l, OPTSTAGE_K_O), dout, (const float*)P(l, OPTSTAGE_K_LSE), dqkv));
-    if (s.family == OPTSTAGE_LLAMA)
-      TRY(k_rope(st, dqkv, P(l, OPTSTAGE_K_QKV), 1));
-    else
-      HIP_TRY(hipMemcpyAsync(P(l, OPTSTAGE_K_QKV), dqkv, st->raw[OPTSTAGE_K_QKV], hipMemcpyDeviceToDevice, cs));
+    TRY(k_attn_bwd_slot(st, P(l, OPTSTAGE_K_QKV), P(l, OPTSTAGE_K_O), dout, (const float*)P(l, OPTSTAGE_K_LSE), dqkv));
     // dn1 = dqkv W_qkv ; dx_in = dx_mid + norm1'(dn1)
     const void* wq = bwd_operand(st, l, OPTSTAGE_W_QKV, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_QKV), wq, dn, nullptr, T, s.h, s.qkv_w, s.qkv_w, s.qkv_w, s.h));

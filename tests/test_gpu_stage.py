@@ -900,3 +900,53 @@ def test_every_forward_kind_survives_offload_and_reload():
             assert torch.equal(st.grads[l][name], ref.grads[l][name]), (l, name)
     st.close()
     ref.close()
+
+
+# one workgroup per kv head and several (split partials), one 32-row tile per wave and two (more than 320 wide workgroups), ragged rows, the
+# general kernels (a few tokens), both families and both types
+@pytest.mark.parametrize("family,dtype,n_q,n_kv,d,seq,mb", [
+    (0, 1, 4, 4, 128, 129, 1), (1, 1, 8, 2, 128, 257, 2), (0, 1, 36, 36, 128, 2305, 1), (1, 1, 36, 36, 128, 2305, 1), (0, 1, 4, 2, 64, 191, 2), (1, 1, 4, 4, 64, 65, 1),
+    (1, 0, 4, 2, 64, 33, 2), (0, 0, 2, 2, 128, 17, 1), (1, 0, 2, 2, 128, 47, 1), (1, 0, 2, 2, 64, 4, 1), (0, 1, 2, 2, 64, 5, 3)])
+def test_attention_gradient_takes_its_operands_place(family, dtype, n_q, n_kv, d, seq, mb):
+    """After B the QKV slot holds the attention gradient that the single-kernel call gives for the same operands: bit for bit
+    without rotary, and turned back by the rotary angle with one rounding more on the side of the two separate kernels."""
+    cfg = replace(CFG.shrunken(CFG.CFG2 if family else CFG.CFG1, hidden=256, n_q=n_q, n_kv=n_kv, ffn=512, seq=seq, n_layers=1, n_microbatches=1,
+                               dtype=dtype), head_dim=d, micro_batch=mb)
+    tdt, rows = (torch.float32, torch.bfloat16)[dtype], seq * mb
+    ws = T.stage_weights(cfg)
+    st = Stage(cfg)
+    st.set_weights(ws)
+    st.bind(0, T.stage_input(cfg, 0), T.output_grad(cfg, 0))
+    dev = lambda kind, dt, *shape: torch.from_numpy(st.read(0, 0, kind).copy()).view(dt)[:int(np.prod(shape))].reshape(shape).cuda()  # noqa: E731
+    st.run([("F", 0)])
+    st.synchronize()
+    width = (n_q + 2 * n_kv) * d
+    qkv, o, lse = dev("QKV", tdt, rows, width), dev("O", tdt, rows, n_q * d), dev("LSE", torch.float32, mb, n_q, seq)
+    assert torch.equal(dev("X_IN", tdt, rows, 256), st.x[0])
+    st.run([("B", 0)])
+    st.synchronize()
+    assert torch.equal(dev("DY", tdt, rows, 256), st.dy[0])
+    dx_mid, got = dev("DX_MID", tdt, rows, 256), dev("QKV", tdt, rows, width)
+    lib, p, s = B.lib(), lambda t: t.data_ptr(), torch.cuda.current_stream().cuda_stream  # noqa: E731
+    wt = st.weights[0]["wo"].t().contiguous()
+    dout, dqkv = torch.empty_like(o), torch.empty_like(qkv)
+    scratch = torch.empty(max(1, lib.optstage_op_attn_bwd_ws_floats(seq, mb, n_q, n_kv, d)), dtype=torch.float32, device="cuda")
+    B.check(lib.optstage_op_gemm(dtype, B.GEMM_NT, B.EPI_STORE, p(dx_mid), p(wt), p(dout), 0, rows, n_q * d, 256, 256, 256, n_q * d, s))
+    B.check(lib.optstage_op_attn_bwd(dtype, p(qkv), p(o), p(dout), p(lse), p(dqkv), p(scratch), seq, mb, n_q, n_kv, d, s))
+    if family == 0:
+        assert torch.equal(got, dqkv)
+    else:
+        n_rot = (n_q + n_kv) * d
+        assert torch.equal(got[:, n_rot:], dqkv[:, n_rot:])
+        heads = dqkv[:, :n_rot].double().reshape(rows, -1, d)
+        pos = (torch.arange(rows, device="cuda") % seq).double()
+        ang = pos[:, None] * cfg.rope_base ** (-2.0 * torch.arange(d // 2, device="cuda").double() / d)[None, :]
+        cos, sin = ang.cos()[:, None, :], ang.sin()[:, None, :]
+        lo, hi = heads[..., :d // 2], heads[..., d // 2:]
+        ref = torch.cat((lo * cos + hi * sin, hi * cos - lo * sin), dim=-1).reshape(rows, n_rot)
+        # per element: the rounding of the two operands and of the result (half an ulp, 2^-9 in bf16, each of the pair's magnitude),
+        # in fp32 the four operations and the table's rounding as well
+        size = torch.maximum(lo.abs(), hi.abs()).repeat(1, 1, 2).reshape(rows, n_rot)
+        bound = (2.0 ** -9 * 3 if dtype else 2.0 ** -24 * 12) * 1.5 * size + 1e-30
+        assert bool(((got[:, :n_rot].double() - ref).abs() <= bound).all())
+    st.close()
