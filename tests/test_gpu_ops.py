@@ -469,6 +469,51 @@ def test_attention_with_one_and_two_tiles_per_wave(seq, batch, nq, nkv):
             assert rms_err(got, ref.reshape(seq, -1)) < TOL[BF16] / 4
 
 
+# Every division of the rows among workgroups and waves (two, four or eight waves, one or two groups that share a block of keys or queries) on
+# both sides of the lines between them, ragged ends and grouped heads, and scores whose largest key lies in either half of a block,
+# so that each group's softmax reference is the higher one for some rows.  Bounds: rounding of the results and of the probabilities
+# (heads of 128) to 8 bits, as in the tests above.
+@pytest.mark.parametrize("seq,batch,nq,nkv,d", [
+    (91, 1, 3, 1, 128), (129, 1, 2, 1, 128), (193, 1, 2, 2, 128), (449, 1, 8, 2, 128), (321, 3, 32, 16, 128), (705, 3, 16, 16, 128),
+    (1601, 1, 36, 36, 128), (1601, 1, 36, 12, 128), (2561, 1, 16, 8, 128), (577, 1, 104, 52, 128), (257, 4, 64, 64, 128), (385, 1, 256, 128, 128),
+    (63, 1, 2, 2, 64), (129, 1, 4, 1, 64), (391, 2, 8, 8, 64), (705, 3, 16, 16, 64), (300, 1, 128, 32, 64), (129, 2, 256, 256, 64)])
+def test_attention_divisions_of_the_rows(seq, batch, nq, nkv, d):
+    rows, w, rep = seq * batch, (nq + 2 * nkv) * d, nq // nkv
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    QKV = torch.randn((rows, w), generator=g, device="cuda")
+    QKV[:, nq * d:(nq + nkv) * d] *= 1.0 + 2.0 * ((torch.arange(rows, device="cuda") // 37) % 3 == 1).float()[:, None]   # keys of unequal weight
+    QKV = QKV.bfloat16()
+    DO = torch.randn((rows, nq * d), generator=g, device="cuda").bfloat16()
+    Ot, DQKV = torch.full_like(DO, float("nan")), torch.full_like(QKV, float("nan"))
+    LSE = torch.full((batch, nq, seq), float("nan"), dtype=torch.float32, device="cuda")
+    WS = torch.empty(lib().optstage_op_attn_bwd_ws_floats(seq, batch, nq, nkv, d), dtype=torch.float32, device="cuda")
+    ok(lib().optstage_op_attn_fwd(BF16, QKV.data_ptr(), Ot.data_ptr(), LSE.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    ok(lib().optstage_op_attn_bwd(BF16, QKV.data_ptr(), Ot.data_ptr(), DO.data_ptr(), LSE.data_ptr(), DQKV.data_ptr(), WS.data_ptr(), seq, batch, nq, nkv, d, stream()))
+    torch.cuda.synchronize()
+    assert all(bool(torch.isfinite(t).all()) for t in (DQKV, Ot, LSE))
+    mask = torch.ones((seq, seq), dtype=torch.bool, device="cuda").triu(1)
+    rms = lambda got, ref: ((got.double() - ref).norm() / ref.norm()).item()  # noqa: E731
+    for b, kvh in ((0, 0), (batch - 1, nkv - 1)):
+        sl = slice(b * seq, (b + 1) * seq)
+        k, v = (QKV[sl, (nq + x * nkv + kvh) * d:(nq + x * nkv + kvh + 1) * d].double() for x in (0, 1))
+        dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+        for a in range(kvh * rep, (kvh + 1) * rep):
+            cols = slice(a * d, (a + 1) * d)
+            q_, do = QKV[sl, cols].double(), DO[sl, cols].double()
+            s = ((q_ @ k.t()) / d ** 0.5).masked_fill(mask, float("-inf"))
+            p = torch.softmax(s, -1)
+            assert (LSE[b, a].double() - torch.logsumexp(s, -1)).abs().max().item() < 2e-5 * max(1.0, s.abs()[~mask].max().item())
+            assert rms(Ot[sl, cols], p @ v) < TOL[BF16] / 4
+            dp = do @ v.t()
+            ds = p * (dp - (do * Ot[sl, cols].double()).sum(-1, keepdim=True)) / d ** 0.5      # the kernels' row term: the stored o
+            assert rms(DQKV[sl, cols], ds @ k) < TOL[BF16] / 4
+            dk += ds.t() @ q_
+            dv += p.t() @ do
+        for x, ref in ((0, dk), (1, dv)):
+            assert rms(DQKV[sl, (nq + x * nkv + kvh) * d:(nq + x * nkv + kvh + 1) * d], ref) < TOL[BF16] / 4
+
+
 # Heads of 64: edges of the 32- and 64-wide tiles and of the 256 rows of a workgroup, one row, grouped heads, several sequences,
 # peaked and flat scores, and operands that are not 16-byte aligned (shift, in elements: the general kernels).  The second
 # products multiply probabilities of 16 significant bits (two bf16 numbers; the general kernels 24), so what is left is the
