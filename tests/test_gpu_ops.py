@@ -115,6 +115,27 @@ def test_gemm_tiles_of_every_size_tn(M, N, K):
         assert float((C[M:] - 3.0).abs().max()) == 0.0 and float((C[:, N:] - 3.0).abs().max()) == 0.0
 
 
+# fp32 products on every tile shape that the least estimated time picks (64 x 64, 64 x 32, 32 x 32, 16 x 32, 16 x 16), both layouts, cut tiles, contractions
+# that are no multiple of a step of 16, of four steps, or of the steps a wave keeps in flight, and fewer steps than waves.  Bound: partial
+# sums of K rounded products, each rounding 2^-24 of a sum that grows as a random walk: sqrt(K) 2^-24 RMS-relative is never reached.
+@pytest.mark.parametrize("M,N,K", [(1000, 1004, 1000), (1023, 1021, 999), (508, 1020, 1040), (510, 1023, 1043), (1020, 252, 132), (1021, 251, 133),
+                                   (124, 764, 260), (123, 763, 261), (60, 44, 1028), (61, 43, 1029), (20, 36, 12), (33, 17, 67), (256, 512, 320), (512, 512, 52),
+                                   # either side of the plain kernel's limits
+                                   (1004, 1024, 16), (1004, 1024, 20), (4100, 4096, 32), (4100, 4096, 36), (1761, 1262, 12), (1761, 1262, 13), (1761, 1262, 24), (1761, 1262, 25)])
+def test_gemm_fp32_tile_shapes_and_remainders(M, N, K):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    A, Bt = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
+    ref = A.double() @ Bt.double().t()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    ok(lib().optstage_op_gemm(FP32, B.GEMM_NT, B.EPI_STORE, A.data_ptr(), Bt.data_ptr(), C.data_ptr(), 0, M, N, K, K, K, N, stream()))
+    At, Btt, C2 = A.t().contiguous(), Bt.t().contiguous(), torch.full((M, N), 2.0, device="cuda")
+    ok(lib().optstage_op_gemm(FP32, B.GEMM_TN, B.EPI_ACCUM, At.data_ptr(), Btt.data_ptr(), C2.data_ptr(), 0, M, N, K, M, N, N, stream()))
+    torch.cuda.synchronize()
+    for got in (C.double(), C2.double() - 2.0):
+        assert ((got - ref).norm() / ref.norm()).item() < K ** 0.5 * 2.0 ** -24 + 2.0 ** -24
+
+
 # fp32 products on tiles of 16, 32 and 64, cut in both directions, with 16-byte loads (all extents multiples of 4) and without,
 # fewer steps of 16 k than waves and a ragged last step, and leading dimensions past 32-bit offsets (the plain kernel).
 # Bound: K + 1 roundings of 2^-24 on sums of magnitudes.
