@@ -111,8 +111,8 @@ typedef struct {
                                                  single serial transfer channel of the paper's model (Eq. 8-11).  A
                                                  stream of its own lets reloads run while offloads are in flight (the
                                                  host link is full duplex); ordering of an item's R after its O, of R
-                                                 after the compute ops listed before it and of B after its reloads is
-                                                 kept by events either way */
+                                                 after the compute ops listed before it and of what B reads after its
+                                                 reload is kept by events either way */
 } optstage_desc;
 
 typedef struct {
@@ -153,8 +153,8 @@ typedef struct {
   uint64_t min_live_bytes;
   double avg_live_bytes;
   /* time the compute stream spent waiting for transfers (valid after synchronize): [0] at OWAIT events, for an
-   * offload to end before the bytes it frees are reused (Eq. 12); [1] ahead of B ops, for the reloads of their
-   * micro-batch to end */
+   * offload to end before the bytes it frees are reused (Eq. 12); [1] in B ops, ahead of the first kernel of a layer
+   * that reads what its reload brings (not part of ms_ops) */
   double stall_ms[2];
   uint64_t n_trace;                             /* entries optstage_get_trace() holds */
 } optstage_stats;
@@ -162,7 +162,8 @@ typedef struct {
 /* One executed event: what was enqueued, the live activation bytes after it (list-order accounting), and, once
  * optstage_synchronize() has returned, its device times in ms since the first event after the last reset: F, B, W
  * on the compute stream, O and R on their transfer stream; -1 for OWAIT, which takes no time of its own.
- * stall_ms: how long the compute stream waited at this event (OWAIT: for the offload; B: for the reloads). */
+ * stall_ms: how long the compute stream waited at this event (OWAIT: for the offload; B: for the reloads, within its
+ * start and end). */
 typedef struct {
   uint32_t op, microbatch, layer, kind_mask;    /* as in optstage_event */
   uint64_t live_bytes;

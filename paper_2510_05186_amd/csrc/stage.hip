@@ -196,9 +196,18 @@ struct OpBufs {   // device offsets an op touches, captured before its releases;
 };
 
 // op >= 0: schedule op; op < 0: kernel class -(op + 1); op == SPAN_STALL: the compute stream waiting for transfers.
-// trace >= 0: the entry of the executed trace that receives the span's times
+// trace >= 0: the entry of the executed trace that receives the span's times.  A stall runs from a (what the compute stream
+// had ahead of the wait) to b (the end of the transfer), where that is later; c: an earlier wait's b with nothing in between
 constexpr int SPAN_STALL = 100;
-struct TimedSpan { int op; hipEvent_t a, b; int trace; };
+struct TimedSpan { int op; hipEvent_t a, b; int trace; hipEvent_t c; };
+
+// The transfers of one layer of one micro-batch that may still be in flight (null: none since the last synchronize).
+struct Pending {
+  hipEvent_t f = nullptr;    // that layer's forward kernels have ended
+  hipEvent_t o = nullptr;    // its latest offload has ended
+  hipEvent_t r = nullptr;    // its latest reload has ended
+  uint32_t r_mask = 0;       // kinds reloaded by it and the ones before it
+};
 
 }  // namespace
 
@@ -213,8 +222,13 @@ struct optstage {
   std::vector<float*> gw;              // [layer][which]
   std::vector<const void*> x_in, dy_out;
   std::vector<void*> y_out, dx_in;
-  std::vector<hipEvent_t> ev_f, ev_o, ev_r, ev_pos;   // [mb], [mb][layer] x3
-  std::vector<hipEvent_t> ev_fl;                      // [mb][layer]: that layer's forward kernels of F mb have ended
+  // Every event record is a packet of its own on its stream (3-4 us between the kernels around it), so one event
+  // serves all that ask for the same point: the end of an op is the next one's start, what a reload waits for and,
+  // in F, the end of the last layer; a transfer's end is what OWAIT and B wait for.
+  std::vector<Pending> pending;   // [mb][layer]
+  hipEvent_t cs_tail = nullptr;   // recorded last on the compute stream, with no kernel behind it
+  hipEvent_t cs_waited = nullptr; // ... but a wait for this transfer
+  hipEvent_t rs_tail = nullptr, rs_pos = nullptr;   // recorded / waited for last on the reload stream
   hipEvent_t last_r = nullptr;   // event of the most recent reload (separate reload stream only)
   std::vector<hipEvent_t> tpool;
   size_t tnext = 0;
@@ -226,7 +240,6 @@ struct optstage {
   hipEvent_t origin = nullptr;   // recorded on the compute stream when the first event after a reset is enqueued
   bool origin_set = false;
   std::vector<optstage_trace_entry> trace;   // executed events since the last reset
-  std::vector<uint8_t> reloaded;             // [chunk][mb]: a reload of this micro-batch was enqueued this iteration
   uint64_t in_flight = 0, min_live = UINT64_MAX;
   double sum_live = 0.0;
   char* arena() const { return (char*)desc.arena; }
@@ -404,19 +417,24 @@ hipEvent_t timing_event(optstage* st) {
   return st->tpool[st->tnext++];
 }
 
-optstage_status span_begin(optstage* st, int op, hipStream_t s, TimedSpan* sp, int trace = -1) {
-  sp->op = op;
-  sp->trace = trace;
-  sp->a = timing_event(st);
-  sp->b = timing_event(st);
-  if (!sp->a || !sp->b) return fail(OPTSTAGE_E_HIP, "hipEventCreate failed");
-  HIP_TRY(hipEventRecord(sp->a, s));
+optstage_status record(optstage* st, hipStream_t s, hipEvent_t* out) {
+  *out = timing_event(st);
+  if (!*out) return fail(OPTSTAGE_E_HIP, "hipEventCreate failed");
+  HIP_TRY(hipEventRecord(*out, s));
   return OPTSTAGE_OK;
 }
-optstage_status span_end(optstage* st, hipStream_t s, const TimedSpan& sp) {
-  HIP_TRY(hipEventRecord(sp.b, s));
-  st->spans.push_back(sp);
-  return OPTSTAGE_OK;
+// begin: an event that already marks this point of the stream, or null to record one
+optstage_status span_begin(optstage* st, int op, hipStream_t s, TimedSpan* sp, int trace = -1, hipEvent_t begin = nullptr) {
+  sp->op = op;
+  sp->trace = trace;
+  sp->a = begin;
+  sp->c = nullptr;
+  return begin ? OPTSTAGE_OK : record(st, s, &sp->a);
+}
+optstage_status span_end(optstage* st, hipStream_t s, TimedSpan& sp) {
+  optstage_status rc = record(st, s, &sp.b);
+  if (rc == OPTSTAGE_OK) st->spans.push_back(sp);
+  return rc;
 }
 
 // optional per-kernel timing: brackets one launch with events and books its algorithmic work
@@ -604,15 +622,29 @@ optstage_status exec_forward(optstage* st, int j, int c, const OpBufs& ob) {
     const void* wd = fwd_operand(st, l, OPTSTAGE_W_D, &lay);
     TRY(k_gemm(st, lay, EPI_RESID, a, wd, y, P(l, OPTSTAGE_K_X_MID), T, s.h, s.f, s.f, s.f, s.h));
     // everything this layer keeps is final from here on: an offload of its activations may start while the layers
-    // after it still run
-    HIP_TRY(hipEventRecord(st->ev_fl[(size_t)j * s.L + l], cs));
+    // after it still run (the last layer ends with F itself; without a host pool nothing is ever offloaded)
+    if (st->desc.host_pool && l + 1 < l1) TRY(record(st, cs, &st->pending[(size_t)j * s.L + l].f));
   }
   return OPTSTAGE_OK;
 }
 
-optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob) {
+// B's wait for the reload of one layer, ahead of the first kernel that reads one of the reloaded kinds: `need` has the
+// kinds that the kernels from here on read.  All kinds of a layer come with one event, so one wait serves them.
+optstage_status wait_reload(optstage* st, int j, int l, uint32_t need, int trace) {
+  Pending& p = st->pending[(size_t)j * st->sh.L + l];
+  if (!p.r || !(p.r_mask & need)) return OPTSTAGE_OK;
+  TimedSpan sp;
+  TRY(span_begin(st, SPAN_STALL, st->cs, &sp, trace));
+  HIP_TRY(hipStreamWaitEvent(st->cs, p.r, 0));
+  sp.b = p.r;
+  st->spans.push_back(sp);
+  p.r = nullptr;
+  p.r_mask = 0;
+  return OPTSTAGE_OK;
+}
+
+optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob, int trace) {
   const Shape& s = st->sh;
-  hipStream_t cs = st->cs;
   const int T = s.tokens;
   auto P = [&](int l, int k) { return (void*)(st->arena() + ob.dev[(size_t)l * NK + k]); };
   char* ws = st->wsp();
@@ -624,7 +656,9 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
   // B ops of a chunk run in micro-batch order, so micro-batch 0 is the iteration's first: in overwrite mode it
   // stores the norm parameters' gradients instead of adding to what the accumulators held
   const bool store = st->overwrite && j == 0;
+  auto bit = [](int k) { return 1u << k; };
   for (int l = l1 - 1; l >= l0; --l) {
+    TRY(wait_reload(st, j, l, bit(OPTSTAGE_K_GU), trace));
     // the caller's gradient enters the last layer's DY slot, which W reads, by way of that layer's second norm
     const bool top = l == l1 - 1;
     const void* dy = top ? st->dy_out[io] : P(l, OPTSTAGE_K_DY);
@@ -637,6 +671,7 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
     TRY(k_act_bwd(st, da, P(l, OPTSTAGE_K_GU), P(l, OPTSTAGE_K_GU)));
     const void* wgu = bwd_operand(st, l, OPTSTAGE_W_GU, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_GU), wgu, dn, nullptr, T, s.h, s.up_w, s.up_w, s.up_w, s.h));
+    TRY(wait_reload(st, j, l, bit(OPTSTAGE_K_X_MID) | bit(OPTSTAGE_K_STATS), trace));
     if (rc) TRY(k_norm_fwd(st, P(l, OPTSTAGE_K_X_MID), W(st, l, OPTSTAGE_W_G2), W(st, l, OPTSTAGE_W_B2), P(l,
         OPTSTAGE_K_N2), stats + (size_t)nstat * T));
     // dx_mid = dy + norm2'(dn2)
@@ -645,6 +680,8 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
     // do = dx_mid W_o ; attention backward ; rotary backward into the qkv buffer
     const void* wo = bwd_operand(st, l, OPTSTAGE_W_O, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_DX_MID), wo, dout, nullptr, T, s.nq * s.d, s.h, s.h, s.h, s.nq * s.d));
+    // what is left is read from here on, in the rest of this layer or by W, which waits for nothing itself
+    TRY(wait_reload(st, j, l, ~0u, trace));
     TRY(k_attn_bwd_slot(st, P(l, OPTSTAGE_K_QKV), P(l, OPTSTAGE_K_O), dout, (const float*)P(l, OPTSTAGE_K_LSE), dqkv));
     // dn1 = dqkv W_qkv ; dx_in = dx_mid + norm1'(dn1)
     const void* wq = bwd_operand(st, l, OPTSTAGE_W_QKV, &lay);
@@ -688,49 +725,31 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   return OPTSTAGE_OK;
 }
 
-// enqueues the compute-stream wait for `n` events bracketed by a stall span
-optstage_status timed_wait(optstage* st, const hipEvent_t* evs, int n, int trace) {
-  TimedSpan sp;
-  optstage_status rc = span_begin(st, SPAN_STALL, st->cs, &sp, trace);
-  if (rc != OPTSTAGE_OK) return rc;
-  for (int i = 0; i < n; ++i) HIP_TRY(hipStreamWaitEvent(st->cs, evs[i], 0));
-  return span_end(st, st->cs, sp);
-}
-
 optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs& ob, int ti) {
   const int j = ev.microbatch, L = st->sh.L, m = st->desc.n_microbatches;
   // F / B / W carry their chunk in the layer field; a transfer belongs to the chunk that holds its layer
   const int c = ev.op <= OPTSTAGE_W ? (int)ev.layer : (int)ev.layer / st->sh.Lc;
-  hipEvent_t ev_f = st->ev_f[(size_t)c * m + j];
   TimedSpan sp;
   optstage_status rc;
   switch (ev.op) {
     case OPTSTAGE_F:
-      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti)) != OPTSTAGE_OK) return rc;
-      if ((rc = exec_forward(st, j, c, ob)) != OPTSTAGE_OK) return rc;
-      if ((rc = span_end(st, st->cs, sp)) != OPTSTAGE_OK) return rc;
-      HIP_TRY(hipEventRecord(ev_f, st->cs));
-      break;
     case OPTSTAGE_B:
-      // every reload of this micro-batch must have completed (the reload ends before its consumer starts); an
-      // event that was not recorded in this iteration holds an older, completed record
-      if (st->reloaded[(size_t)c * m + j]) {
-        if ((rc = timed_wait(st, &st->ev_r[(size_t)j * L + c * st->sh.Lc], st->sh.Lc, ti)) != OPTSTAGE_OK) return rc;
-      }
-      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti)) != OPTSTAGE_OK) return rc;
-      if ((rc = exec_backward_input(st, j, c, ob)) != OPTSTAGE_OK) return rc;
-      if ((rc = span_end(st, st->cs, sp)) != OPTSTAGE_OK) return rc;
-      break;
     case OPTSTAGE_W:
-      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti)) != OPTSTAGE_OK) return rc;
-      if ((rc = exec_backward_weight(st, j, c, ob)) != OPTSTAGE_OK) return rc;
+      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti, st->cs_waited ? nullptr : st->cs_tail)) != OPTSTAGE_OK) return rc;
+      // B starts at once; every reload of its micro-batch has completed before the first kernel that reads what it brought
+      rc = ev.op == OPTSTAGE_F ? exec_forward(st, j, c, ob) : ev.op == OPTSTAGE_B ? exec_backward_input(st, j, c, ob, ti)
+                                                                                   : exec_backward_weight(st, j, c, ob);
+      if (rc != OPTSTAGE_OK) return rc;
       if ((rc = span_end(st, st->cs, sp)) != OPTSTAGE_OK) return rc;
+      st->cs_tail = sp.b;
+      st->cs_waited = nullptr;
+      if (ev.op == OPTSTAGE_F) st->pending[(size_t)j * L + (c + 1) * st->sh.Lc - 1].f = sp.b;
       break;
     case OPTSTAGE_O: {
+      Pending& p = st->pending[(size_t)j * L + ev.layer];
       // the offload starts once the layer that produced the data has ended (the F it belongs to may still be running
-      // its later layers; the list has the O after that F, so the layer's event has been recorded)
-      (void)ev_f;
-      HIP_TRY(hipStreamWaitEvent(st->xs, st->ev_fl[(size_t)j * L + ev.layer], 0));
+      // its later layers)
+      if (p.f) HIP_TRY(hipStreamWaitEvent(st->xs, p.f, 0));
       // a pinned slot released by a reload listed earlier may be handed to this offload: with a reload stream
       // of its own that reload must have drained first (on a shared channel stream order already says so)
       if (st->rs != st->xs && st->last_r) HIP_TRY(hipStreamWaitEvent(st->xs, st->last_r, 0));
@@ -742,21 +761,39 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
           st->stats.bytes_offloaded += st->raw[k];
         }
       if ((rc = span_end(st, st->xs, sp)) != OPTSTAGE_OK) return rc;
-      HIP_TRY(hipEventRecord(st->ev_o[(size_t)j * L + ev.layer], st->xs));
+      p.o = sp.b;
+      if (st->rs == st->xs) st->rs_tail = nullptr;
       break;
     }
-    case OPTSTAGE_OWAIT:
+    case OPTSTAGE_OWAIT: {
       // compute ops listed from here on may reuse the freed bytes: they start after the offload ended
-      if ((rc = timed_wait(st, &st->ev_o[(size_t)j * L + ev.layer], 1, ti)) != OPTSTAGE_OK) return rc;
+      const hipEvent_t o = st->pending[(size_t)j * L + ev.layer].o;
+      if (!o || o == st->cs_waited) break;
+      if (!st->cs_tail && (rc = record(st, st->cs, &st->cs_tail)) != OPTSTAGE_OK) return rc;
+      HIP_TRY(hipStreamWaitEvent(st->cs, o, 0));
+      st->spans.push_back({SPAN_STALL, st->cs_tail, o, ti, st->cs_waited});
+      st->cs_waited = o;
       break;
+    }
     case OPTSTAGE_R: {
-      // the reload starts after the compute ops listed before it have ended
-      hipEvent_t pos = st->ev_pos[(size_t)j * L + ev.layer];
-      HIP_TRY(hipEventRecord(pos, st->cs));
-      HIP_TRY(hipStreamWaitEvent(st->rs, pos, 0));
+      Pending& p = st->pending[(size_t)j * L + ev.layer];
+      // the reload starts after the compute ops listed before it have ended; on a stream of its own also after the
+      // offloads whose bytes it may take, which the compute stream has waited for (on a shared channel they are ahead of it)
+      if (!st->cs_tail || (st->cs_waited && st->rs != st->xs)) {
+        if ((rc = record(st, st->cs, &st->cs_tail)) != OPTSTAGE_OK) return rc;
+        st->cs_waited = nullptr;
+      }
+      if (st->rs_pos != st->cs_tail) {
+        HIP_TRY(hipStreamWaitEvent(st->rs, st->cs_tail, 0));
+        st->rs_pos = st->cs_tail;
+        st->rs_tail = nullptr;
+      }
       // ... and after the offload that filled the host slot (implied by stream order on a shared channel)
-      if (st->rs != st->xs) HIP_TRY(hipStreamWaitEvent(st->rs, st->ev_o[(size_t)j * L + ev.layer], 0));
-      if ((rc = span_begin(st, ev.op, st->rs, &sp, ti)) != OPTSTAGE_OK) return rc;
+      if (st->rs != st->xs && p.o) {
+        HIP_TRY(hipStreamWaitEvent(st->rs, p.o, 0));
+        st->rs_tail = nullptr;
+      }
+      if ((rc = span_begin(st, ev.op, st->rs, &sp, ti, st->rs_tail)) != OPTSTAGE_OK) return rc;
       for (int k = 0; k < NFK; ++k)
         if (ev.kind_mask & (1u << k)) {
           size_t i = (size_t)ev.layer * NK + k;
@@ -764,9 +801,8 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
           st->stats.bytes_reloaded += st->raw[k];
         }
       if ((rc = span_end(st, st->rs, sp)) != OPTSTAGE_OK) return rc;
-      HIP_TRY(hipEventRecord(st->ev_r[(size_t)j * L + ev.layer], st->rs));
-      st->last_r = st->ev_r[(size_t)j * L + ev.layer];
-      st->reloaded[(size_t)c * m + j] = 1;
+      st->rs_tail = st->last_r = p.r = sp.b;
+      p.r_mask |= ev.kind_mask;
       break;
     }
   }
@@ -814,9 +850,11 @@ optstage_status run_list(optstage* st, const optstage_event* events, size_t n) {
     HIP_TRY(hipEventRecord(st->origin, st->cs));
     st->origin_set = true;
   }
-  OpBufs ob;
-  for (size_t i = 0; i < n; ++i) {
-    if ((rc = apply_event(st->lg, events[i], &ob)) != OPTSTAGE_OK) return rc;   // cannot fail: same steps as the trial
+  // what the caller has queued on the streams since the last call is not ours
+  st->cs_tail = st->cs_waited = st->rs_tail = st->rs_pos = nullptr;
+  auto commit = [&](size_t i, OpBufs* ob) -> optstage_status {
+    optstage_status r = apply_event(st->lg, events[i], ob);   // cannot fail: same steps as the trial
+    if (r != OPTSTAGE_OK) return r;
     if (events[i].op == OPTSTAGE_F) st->in_flight++;
     if (events[i].op == OPTSTAGE_W) st->in_flight--;
     st->sum_live += (double)st->lg.live;
@@ -827,12 +865,34 @@ optstage_status run_list(optstage* st, const optstage_event* events, size_t n) {
     te.live_bytes = st->lg.live;
     te.start_ms = te.end_ms = -1.0;
     st->trace.push_back(te);
-    if ((rc = exec_event(st, events[i], ob, (int)st->trace.size() - 1)) != OPTSTAGE_OK) {
-      // the accounting is ahead of what was enqueued and an op graph may be half launched: nothing more runs on
-      // this handle until optstage_reset
-      st->failed = true;
-      return rc;
+    return OPTSTAGE_OK;
+  };
+  // the accounting is ahead of what was enqueued and an op graph may be half launched: after a failure nothing more runs
+  // on this handle until optstage_reset
+  auto enqueue = [&](size_t i, const OpBufs& ob, int ti) -> optstage_status {
+    optstage_status r = exec_event(st, events[i], ob, ti);
+    st->failed |= r != OPTSTAGE_OK;
+    return r;
+  };
+  std::vector<OpBufs> obs(1);
+  std::vector<size_t> order;
+  for (size_t i = 0; i < n;) {
+    // Reloads of one micro-batch with nothing between them are accounted in list order and go to the channel in the order
+    // B needs them: last layer first.  (They end at the same time in any order; B starts when the first has.)
+    size_t e = i + 1;
+    if (events[i].op == OPTSTAGE_R)
+      while (e < n && events[e].op == OPTSTAGE_R && events[e].microbatch == events[i].microbatch) ++e;
+    const int ti = (int)st->trace.size();
+    if (obs.size() < e - i) obs.resize(e - i);
+    order.clear();
+    for (size_t k = i; k < e; ++k) {
+      if ((rc = commit(k, &obs[k - i])) != OPTSTAGE_OK) return rc;
+      order.push_back(k);
     }
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return events[a].layer > events[b].layer; });
+    for (size_t k : order)
+      if ((rc = enqueue(k, obs[k - i], ti + (int)(k - i))) != OPTSTAGE_OK) return rc;
+    i = e;
   }
   return OPTSTAGE_OK;
 }
@@ -915,23 +975,12 @@ optstage_status optstage_create(const optstage_desc* desc, optstage_t** out) {
   st->x_in.assign(nio, nullptr); st->dy_out.assign(nio, nullptr); st->y_out.assign(nio, nullptr); st->dx_in.assign(nio, nullptr);
   memset(&st->stats, 0, sizeof st->stats);
   reset_logical(st);
-  auto mk = [&](std::vector<hipEvent_t>& v, size_t n) -> bool {
-    v.assign(n, nullptr);
-    for (size_t i = 0; i < n; ++i)
-      if (hipEventCreateWithFlags(&v[i], hipEventDisableTiming) != hipSuccess) return false;
-    return true;
-  };
-  st->reloaded.assign(nio, 0);
+  st->pending.assign(m * L, Pending());
   if (hipError_t e = hipEventCreate(&st->origin); e != hipSuccess) {
     st->origin = nullptr;
     optstage_destroy(st);
     return fail(OPTSTAGE_E_HIP, "hipEventCreate: %s", hipGetErrorString(e));
   }
-  if (!mk(st->ev_f, nio) || !mk(st->ev_o, m * L) || !mk(st->ev_r, m * L) || !mk(st->ev_pos, m * L) || !mk(st->ev_fl, m * L)) {
-    optstage_destroy(st);
-    return fail(OPTSTAGE_E_HIP, "hipEventCreateWithFlags failed");
-  }
-  // an event that was never recorded counts as complete, so B may wait on every ev_r unconditionally
   if (s.family == OPTSTAGE_LLAMA) {
     hipError_t e = launch_rope_table((float*)(st->wsp() + ws.rope), s.seq, s.d, desc->rope_base, st->cs);
     if (e != hipSuccess) { optstage_destroy(st); return fail(OPTSTAGE_E_HIP, "rope table: %s", hipGetErrorString(e)); }
@@ -942,8 +991,7 @@ optstage_status optstage_create(const optstage_desc* desc, optstage_t** out) {
 
 void optstage_destroy(optstage_t* st) {
   if (!st) return;
-  for (auto* v : {&st->ev_f, &st->ev_o, &st->ev_r, &st->ev_pos, &st->ev_fl, &st->tpool})
-    for (hipEvent_t e : *v) if (e) (void)hipEventDestroy(e);
+  for (hipEvent_t e : st->tpool) if (e) (void)hipEventDestroy(e);
   if (st->origin) (void)hipEventDestroy(st->origin);
   delete st;
 }
@@ -1057,8 +1105,15 @@ optstage_status optstage_synchronize(optstage_t* st) {
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, sp.a, sp.b));
     if (sp.op == SPAN_STALL) {
+      if (sp.c) {
+        float since = 0.f;
+        HIP_TRY(hipEventElapsedTime(&since, sp.c, sp.b));
+        ms = std::min(ms, since);
+      }
+      ms = std::max(ms, 0.f);
       const bool reload = sp.trace >= 0 && st->trace[sp.trace].op == OPTSTAGE_B;
       st->stats.stall_ms[reload ? 1 : 0] += ms;
+      if (reload) st->stats.ms_ops[OPTSTAGE_B] -= ms;        // B's span has its waits within
       if (sp.trace >= 0) st->trace[sp.trace].stall_ms += ms;
     } else if (sp.op >= 0) {
       st->stats.ms_ops[sp.op] += ms;
@@ -1074,6 +1129,9 @@ optstage_status optstage_synchronize(optstage_t* st) {
   }
   st->spans.clear();
   st->tnext = 0;
+  // nothing is in flight any more, and the events are free to be recorded again
+  std::fill(st->pending.begin(), st->pending.end(), Pending());
+  st->last_r = nullptr;
   return OPTSTAGE_OK;
 }
 
@@ -1085,8 +1143,8 @@ optstage_status optstage_reset(optstage_t* st) {
   st->last_r = nullptr;
   st->failed = false;
   st->origin_set = false;
+  std::fill(st->pending.begin(), st->pending.end(), Pending());
   st->trace.clear();
-  std::fill(st->reloaded.begin(), st->reloaded.end(), 0);
   st->in_flight = 0;
   st->min_live = UINT64_MAX;
   st->sum_live = 0.0;

@@ -147,10 +147,9 @@ class Stage:
     def _order_after_torch(self):
         """The library's streams know nothing of torch's: work torch has queued on its current stream (tensor
         creation, copies, fills) must finish before the library reads those tensors."""
-        cur = torch.cuda.current_stream()
-        self.compute_stream.wait_stream(cur)
-        self.copy_stream.wait_stream(cur)
-        self.reload_stream.wait_stream(cur)
+        here = torch.cuda.current_stream().record_event()
+        for stream in (self.compute_stream, self.copy_stream, self.reload_stream):
+            stream.wait_event(here)
 
     # ---- execution
     def validate(self, events):
