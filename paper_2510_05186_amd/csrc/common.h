@@ -117,6 +117,15 @@ hipError_t launch_transpose(int dtype, const void* src, void* dst, int rows, int
 // (f % 128 == 0)
 hipError_t launch_slabs(const void* src, void* dst, int N, int K, int transposed, hipStream_t s);
 bool gemm_bf16_slab_applies(int M, int N, int K, int lda);
+// up to MAX copies of 16-byte units in one launch, between memory that the device can address
+struct CopyList {
+  static constexpr int MAX = 10;
+  const void* src[MAX];
+  void* dst[MAX];
+  unsigned long long units[MAX];
+  int n;
+};
+hipError_t launch_copy_list(const CopyList& list, hipStream_t s);
 hipError_t launch_checksum(const void* buf, uint64_t bytes, uint64_t* out_dev, hipStream_t s);
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* o, float* lse, int seq, int batch, int n_q, int n_kv,
                            int d, hipStream_t s);

@@ -525,6 +525,29 @@ __global__ void transpose_kernel(const T* __restrict__ src, T* __restrict__ dst,
   }
 }
 
+// ---- the tensors of one transfer, device to pinned host memory or back --------------------------------------------------
+// Bound by the host link.  A copy call per tensor leaves the link idle for some 14 us between two of them; here all go in
+// one launch.  A workgroup moves pieces of 32 KB, eight 16-byte loads of a thread in flight ahead of its stores; few
+// workgroups are enough to fill the link and leave the compute units to the kernels of the other stream.
+constexpr int COPY_PIECE = 256 * 8;                          // 16-byte units
+__global__ __launch_bounds__(256) void copy_list_kernel(const CopyList list, unsigned pieces) {
+  for (unsigned p = blockIdx.x; p < pieces; p += gridDim.x) {
+    int e = 0;
+    unsigned first = 0;
+    for (unsigned n; p - first >= (n = (unsigned)((list.units[e] + COPY_PIECE - 1) / COPY_PIECE)); ++e) first += n;
+    const f32x4_t* src = (const f32x4_t*)list.src[e];
+    f32x4_t* dst = (f32x4_t*)list.dst[e];
+    const size_t n = list.units[e], at = (size_t)(p - first) * COPY_PIECE + threadIdx.x;
+    f32x4_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (at + i * 256 < n) v[i] = src[at + i * 256];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (at + i * 256 < n) dst[at + i * 256] = v[i];
+  }
+}
+
 // ---- checksum: out[0] = sum of 64-bit words (mod 2^64), out[1] = xor of 64-bit words ---------------------
 __global__ void checksum_zero_kernel(unsigned long long* out) { out[0] = 0ull; out[1] = 0ull; }
 __global__ void checksum_kernel(const unsigned long long* __restrict__ w, size_t n, unsigned long long* out) {
@@ -699,6 +722,19 @@ hipError_t launch_transpose(int dtype, const void* src, void* dst, int rows, int
   if (dtype == DT_BF16) hipLaunchKernelGGL(transpose_kernel<unsigned short>, grid, dim3(256), 0, s,
       (const unsigned short*)src, (unsigned short*)dst, rows, cols);
   else hipLaunchKernelGGL(transpose_kernel<float>, grid, dim3(256), 0, s, (const float*)src, (float*)dst, rows, cols);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_list(const CopyList& list, hipStream_t s) {
+  size_t pieces = 0;
+  if (list.n < 1 || list.n > CopyList::MAX) return hipErrorInvalidValue;
+  for (int i = 0; i < list.n; ++i) {
+    if (!list.units[i] || (((uintptr_t)list.src[i] | (uintptr_t)list.dst[i]) & 15)) return hipErrorInvalidValue;
+    pieces += (list.units[i] + COPY_PIECE - 1) / COPY_PIECE;
+  }
+  if (pieces > 0x7fffffffu) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)(pieces < 8 ? pieces : 8);
+  hipLaunchKernelGGL(copy_list_kernel, dim3(grid), dim3(256), 0, s, list, (unsigned)pieces);
   return hipGetLastError();
 }
 

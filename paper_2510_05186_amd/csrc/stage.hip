@@ -217,6 +217,7 @@ struct optstage {
   WorkspaceLayout ws;
   uint64_t raw[NK];
   Logical lg;
+  char* pool_dev = nullptr; // the host pool as kernels address it; null where they cannot
   hipStream_t cs, xs, rs;   // compute, copy (offloads), reloads (= xs unless the caller gave a stream of its own)
   std::vector<const void*> w;          // [layer][which]
   std::vector<float*> gw;              // [layer][which]
@@ -725,6 +726,39 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   return OPTSTAGE_OK;
 }
 
+// Transfer of an event's kinds between the arena and the pinned pool: small ones in one kernel, large ones in a copy call per kind.
+// A call costs 14 us beside its bytes' time on the link; the kernel holds compute units that the compute stream's products
+// then wait for.  Two layers, five micro-batches, three kinds of every item moved, one event's MB and us per iteration, calls /
+// kernel: .3 1869 / 1595, .6 2181 / 2004, 1.0 2360 / 2291, 1.3 2448 / 2467, 2.8 3115 / 3298, 109 56230 / 68431.
+constexpr uint64_t COPY_KERNEL_MAX = 1 << 20;
+optstage_status transfer(optstage* st, const optstage_event& ev, const OpBufs& ob, hipStream_t s) {
+  const bool out = ev.op == OPTSTAGE_O;
+  uint64_t total = 0;
+  CopyList list;
+  list.n = 0;
+  for (int k = 0; k < NFK; ++k)
+    if (ev.kind_mask & (1u << k)) {
+      const size_t i = (size_t)ev.layer * NK + k;
+      char *dev = st->arena() + ob.dev[i], *host = st->pool_dev + ob.host[i];
+      list.src[list.n] = out ? dev : host;
+      list.dst[list.n] = out ? host : dev;
+      list.units[list.n++] = (st->raw[k] + 15) / 16;         // either side has its slot to the next multiple of 256
+      total += st->raw[k];
+    }
+  (out ? st->stats.bytes_offloaded : st->stats.bytes_reloaded) += total;
+  if (st->pool_dev && total <= COPY_KERNEL_MAX) {
+    HIP_TRY(launch_copy_list(list, s));
+    return OPTSTAGE_OK;
+  }
+  for (int k = 0; k < NFK; ++k)
+    if (ev.kind_mask & (1u << k)) {
+      const size_t i = (size_t)ev.layer * NK + k;
+      char *dev = st->arena() + ob.dev[i], *host = (char*)st->desc.host_pool + ob.host[i];
+      HIP_TRY(hipMemcpyAsync(out ? host : dev, out ? dev : host, st->raw[k], out ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice, s));
+    }
+  return OPTSTAGE_OK;
+}
+
 optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs& ob, int ti) {
   const int j = ev.microbatch, L = st->sh.L, m = st->desc.n_microbatches;
   // F / B / W carry their chunk in the layer field; a transfer belongs to the chunk that holds its layer
@@ -754,12 +788,7 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
       // of its own that reload must have drained first (on a shared channel stream order already says so)
       if (st->rs != st->xs && st->last_r) HIP_TRY(hipStreamWaitEvent(st->xs, st->last_r, 0));
       if ((rc = span_begin(st, ev.op, st->xs, &sp, ti)) != OPTSTAGE_OK) return rc;
-      for (int k = 0; k < NFK; ++k)
-        if (ev.kind_mask & (1u << k)) {
-          size_t i = (size_t)ev.layer * NK + k;
-          HIP_TRY(hipMemcpyAsync((char*)st->desc.host_pool + ob.host[i], st->arena() + ob.dev[i], st->raw[k], hipMemcpyDeviceToHost, st->xs));
-          st->stats.bytes_offloaded += st->raw[k];
-        }
+      if ((rc = transfer(st, ev, ob, st->xs)) != OPTSTAGE_OK) return rc;
       if ((rc = span_end(st, st->xs, sp)) != OPTSTAGE_OK) return rc;
       p.o = sp.b;
       if (st->rs == st->xs) st->rs_tail = nullptr;
@@ -794,12 +823,7 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
         st->rs_tail = nullptr;
       }
       if ((rc = span_begin(st, ev.op, st->rs, &sp, ti, st->rs_tail)) != OPTSTAGE_OK) return rc;
-      for (int k = 0; k < NFK; ++k)
-        if (ev.kind_mask & (1u << k)) {
-          size_t i = (size_t)ev.layer * NK + k;
-          HIP_TRY(hipMemcpyAsync(st->arena() + ob.dev[i], (char*)st->desc.host_pool + ob.host[i], st->raw[k], hipMemcpyHostToDevice, st->rs));
-          st->stats.bytes_reloaded += st->raw[k];
-        }
+      if ((rc = transfer(st, ev, ob, st->rs)) != OPTSTAGE_OK) return rc;
       if ((rc = span_end(st, st->rs, sp)) != OPTSTAGE_OK) return rc;
       st->rs_tail = st->last_r = p.r = sp.b;
       p.r_mask |= ev.kind_mask;
@@ -960,6 +984,14 @@ optstage_status optstage_create(const optstage_desc* desc, optstage_t** out) {
   st->desc = *desc;
   st->sh = s;
   st->ws = ws;
+  if (desc->host_pool && desc->host_pool_bytes) {
+    hipPointerAttribute_t lo, hi;
+    if (hipPointerGetAttributes(&lo, desc->host_pool) == hipSuccess && lo.type == hipMemoryTypeHost && lo.devicePointer &&
+        hipPointerGetAttributes(&hi, (char*)desc->host_pool + desc->host_pool_bytes - 1) == hipSuccess && hi.type == hipMemoryTypeHost &&
+        (char*)hi.devicePointer == (char*)lo.devicePointer + desc->host_pool_bytes - 1)
+      st->pool_dev = (char*)lo.devicePointer;
+    (void)hipGetLastError();
+  }
   kind_raw_bytes(s, st->raw);
   for (int k = 0; k < NK; ++k) {
     st->lg.bytes[k] = round_up(st->raw[k]);

@@ -950,3 +950,43 @@ def test_attention_gradient_takes_its_operands_place(family, dtype, n_q, n_kv, d
         bound = (2.0 ** -9 * 3 if dtype else 2.0 ** -24 * 12) * 1.5 * size + 1e-30
         assert bool(((got[:, :n_rot].double() - ref).abs() <= bound).all())
     st.close()
+
+
+# transfers below and above the size up to which one kernel moves all kinds of an item; an odd number of tokens, whose statistics are no
+# multiple of 16 bytes; the reloads on the offloads' channel and on one of their own
+@pytest.mark.parametrize("duplex", [False, True])
+@pytest.mark.parametrize("seq,hidden", [(101, 256), (640, 512)])
+def test_reloads_arrive_before_the_kernels_that_read_them(duplex, seq, hidden):
+    """The whole list enqueued at once, reloads right before their B in ascending layer order (the channel takes them from the last
+    layer down), each layer's kinds such that B's wait comes at another kernel: results bitwise those without transfers."""
+    cfg = replace(SMALL2, name="cfg2_small_waits", hidden=hidden, ffn=2 * hidden, seq=seq, n_layers=4, n_microbatches=3)
+    ws, t = T.stage_weights(cfg), oracle_table(cfg)
+    first = {0: [("GU", "A")], 1: [("STATS", "X_MID", "N2")], 2: [("QKV",), ("X_IN", "LSE")], 3: [("N1", "N2"), tuple(k for k in S.F_KINDS if k not in ("N1", "N2"))]}
+    comp, events = [], []
+    for j in range(3):
+        moves = [(j, l, kinds) for l in first for kinds in first[l]]
+        events += [("F", j)] + [("O", *m) for m in moves] + [("OWAIT", *m) for m in moves]
+        comp.append(("F", j))
+    for j in range(3):
+        events += [("R", j, l, kinds) for l in first for kinds in first[l]] + [("B", j), ("W", j)]
+        comp += [("B", j), ("W", j)]
+    S.check_order(events, 3, cfg.n_layers)
+    ref = gpu_run(cfg, ws, comp)
+    pool = sum(t[k] for l in first for kinds in first[l] for k in kinds) * 3
+    st = Stage(cfg, host_pool_bytes=pool, duplex=duplex, grad_overwrite=True)
+    st.set_weights(ws)
+    for j in range(3):
+        st.bind(j, T.stage_input(cfg, j), T.output_grad(cfg, j))
+    for _ in range(3):
+        st.run(events)
+        st.synchronize()
+        s = st.stats()
+        assert s.live_bytes == 0 and s.ms_ops[B.OP_CODE["B"]] > 0 and s.bytes_offloaded == s.bytes_reloaded
+        for j in range(3):
+            assert torch.equal(st.y[j], ref.y[j]) and torch.equal(st.dx[j], ref.dx[j])
+        for l in range(cfg.n_layers):
+            for name in st.grads[l]:
+                assert torch.equal(st.grads[l][name], ref.grads[l][name]), (l, name)
+        st.reset()
+    st.close()
+    ref.close()
