@@ -39,7 +39,9 @@ enum { GEMM_NT = 0, GEMM_TN = 1, GEMM_NT_SLAB = 2 };
 // EPI_ROPE: store C with the q and k head columns rotated by position (rotary embedding fused into the QKV projection);
 // EPI_SWIGLU: B holds the gate / up weight in paired slabs (GEMM_NT_SLAB with rows paired, see launch_slabs): stores the
 // product in the plain [gate | up] layout AND a = silu(gate) * up (the MLP activation fused into the gate / up projection)
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_ACCUM = 2, EPI_STOREF = 3, EPI_ROPE = 4, EPI_SWIGLU = 5 };
+// EPI_GELU: store C and gelu(C as stored) to R, rows like C's; EPI_DGELU, EPI_DSWIGLU: the product is the gradient of the MLP
+// activation's output; C holds the activation's input ([gate | up] for SwiGLU, up at column N + n) and receives its gradient
+enum { EPI_STORE = 0, EPI_RESID = 1, EPI_ACCUM = 2, EPI_STOREF = 3, EPI_ROPE = 4, EPI_SWIGLU = 5, EPI_GELU = 6, EPI_DGELU = 7, EPI_DSWIGLU = 8 };
 // what the two fused epilogues need beyond C: the rotary table [seq][64] (cos, sin), the sequence length (position =
 // row % seq) and the number of leading columns that are q / k heads; the activation output [M, f] and f
 struct GemmExtra {
@@ -53,6 +55,21 @@ template <> __device__ __forceinline__ float to_f32<bf16_t>(bf16_t v) { return (
 template <typename T> __device__ __forceinline__ T from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return (bf16_t)v; }
+
+// MLP activations: GELU (Phi, the normal distribution) and SwiGLU = silu(gate) * up.  The sums of products are written out, so that
+// every kernel rounds alike.
+__device__ __forceinline__ float sigmoidf_(float x) { return 1.f / (1.f + expf(-x)); }
+__device__ __forceinline__ float gelu(float x) { return 0.5f * x * (1.f + erff(x * 0.70710678118654752f)); }
+__device__ __forceinline__ float dgelu(float x, float d) {
+  const float Phi = 0.5f * (1.f + erff(x * 0.70710678118654752f));
+  const float phi = 0.39894228040143268f * expf(-0.5f * x * x);
+  return d * fmaf(x, phi, Phi);
+}
+__device__ __forceinline__ void dswiglu(float gate, float up, float d, float& dgate, float& dup) {
+  const float s = sigmoidf_(gate);
+  dgate = d * up * s * fmaf(gate, 1.f - s, 1.f);
+  dup = d * gate * s;
+}
 
 // 16-byte vector of T (4 floats or 8 bf16) with element access in fp32
 template <typename T> struct Vec16;
@@ -87,6 +104,9 @@ bool gemm_bf16_grouped_applies(int layout, int n, const GemmProblem* problems, i
 hipError_t launch_gemm_bf16_grouped(int layout, int epi, int n, const GemmProblem* problems, int K, hipStream_t s);
 hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                             int K, int lda, int ldb, int ldc, hipStream_t s, const GemmExtra* extra = nullptr);
+// whether a product y = x W^T (dense operands) is served with the activation in its epilogue (EPI_GELU, EPI_DGELU, EPI_DSWIGLU)
+bool gemm_bf16_act_applies(int epi, int M, int N, int K);
+bool gemm_f32_act_applies(int M, int N, int K);
 // tiles of 128 or 64, for products of up to 256 tiles of 128 x 128 and for what is cut off a grouped TN set; bf16 alignment rules as
 // for launch_gemm_bf16
 bool gemm_bf16_small_applies(int M, int N, int K, int lda, int ldb);
@@ -102,7 +122,16 @@ hipError_t launch_norm_fwd(int dtype, int family, const void* x, const void* gam
                            float* stats, int rows, int h, float eps, hipStream_t s, void* x_copy = nullptr);
 hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x, const float* stats,
                            const void* gamma, const void* dres, void* dx, float* partial, float* dgamma,
-                           float* dbeta, int rows, int h, hipStream_t s, int overwrite = 0, void* dres_copy = nullptr);
+                           float* dbeta, int rows, int h, hipStream_t s, int overwrite = 0, void* dres_copy = nullptr, bool reduce = true);
+// the sums that launch_norm_bwd(reduce = false) left in `partial` of up to MAX norms of the same rows and h, in one launch
+struct NormReduce {
+  static constexpr int MAX = 8;
+  const float* partial[MAX];
+  float* dgamma[MAX];
+  float* dbeta[MAX];
+  int n;
+};
+hipError_t launch_norm_reduce(int family, const NormReduce& list, int rows, int h, int overwrite, hipStream_t s);
 int norm_bwd_partial_rows(int rows);
 hipError_t launch_act_fwd(int dtype, int family, const void* gu, void* a, int rows, int f, hipStream_t s);
 hipError_t launch_act_bwd(int dtype, int family, const void* da, const void* gu, void* dgu, int rows, int f,

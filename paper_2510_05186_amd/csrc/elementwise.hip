@@ -293,13 +293,14 @@ __global__ __launch_bounds__(NT) void norm_bwd_wave_kernel(const T* __restrict__
 }
 
 // sums the per-workgroup partials column-wise and adds them into the caller's fp32 accumulators (overwrite: stores
-// them instead): workgroup = 32 columns x 8 row groups, fixed summation order (deterministic)
-__global__ __launch_bounds__(256) void norm_bwd_reduce_kernel(const float* __restrict__ partial, float* __restrict__ dgamma,
-                                                              float* __restrict__ dbeta, int nb, int h, int overwrite) {
+// them instead): workgroup = 32 columns x 8 row groups, fixed summation order (deterministic).  Nothing waits for these sums, and
+// a launch of them takes 4 us at any width, so that a backward pass leaves them to the end, those of all its norms in one launch
+// (two layers of hidden 256, 128 tokens, GPT: B 101 -> 86 us).
+__global__ __launch_bounds__(256) void norm_bwd_reduce_kernel(const NormReduce list, int nb, int h, int overwrite) {
   __shared__ float red[8][33];
   const int cx = threadIdx.x & 31, rg = threadIdx.x >> 5;
   const int col = blockIdx.x * 32 + cx;
-  const float* p = partial + (size_t)blockIdx.y * nb * h;
+  const float* p = list.partial[blockIdx.z] + (size_t)blockIdx.y * nb * h;
   // four independent partial sums keep four loads in flight per lane; fixed combination order
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   if (col < h) {
@@ -318,14 +319,12 @@ __global__ __launch_bounds__(256) void norm_bwd_reduce_kernel(const float* __res
     float t = 0.f;
 #pragma unroll
     for (int r = 0; r < 8; ++r) t += red[r][cx];
-    float* dst = blockIdx.y == 0 ? dgamma : dbeta;
+    float* dst = blockIdx.y == 0 ? list.dgamma[blockIdx.z] : list.dbeta[blockIdx.z];
     dst[col] = overwrite ? t : dst[col] + t;
   }
 }
 
 // ---- MLP activations --------------------------------------------------------------------------------
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.f / (1.f + expf(-x)); }
-
 template <typename T, bool SWIGLU>
 __global__ void act_fwd_kernel(const T* __restrict__ gu, T* __restrict__ a, int rows, int f) {
   typedef Vec16<T> V;
@@ -340,7 +339,7 @@ __global__ void act_fwd_kernel(const T* __restrict__ gu, T* __restrict__ a, int 
     for (int e = 0; e < V::N; ++e) {
       float x = g.get(e);
       if (SWIGLU) o.set(e, x * sigmoidf_(x) * u.get(e));
-      else o.set(e, 0.5f * x * (1.f + erff(x * 0.70710678118654752f)));
+      else o.set(e, gelu(x));
     }
     *reinterpret_cast<V*>(a + (size_t)row * f + c * V::N) = o;
   }
@@ -362,13 +361,12 @@ __global__ void act_bwd_kernel(const T* __restrict__ da, const T* gu, T* dgu, in
     for (int e = 0; e < V::N; ++e) {
       float x = g.get(e), dd = d.get(e);
       if (SWIGLU) {
-        float s = sigmoidf_(x);
-        og.set(e, dd * u.get(e) * s * (1.f + x * (1.f - s)));
-        ou.set(e, dd * x * s);
+        float dg, du;
+        dswiglu(x, u.get(e), dd, dg, du);
+        og.set(e, dg);
+        ou.set(e, du);
       } else {
-        float Phi = 0.5f * (1.f + erff(x * 0.70710678118654752f));
-        float phi = 0.39894228040143268f * expf(-0.5f * x * x);
-        og.set(e, dd * (Phi + x * phi));
+        og.set(e, dgelu(x, dd));
       }
     }
     *reinterpret_cast<V*>(dgu + (size_t)row * ldg + c * V::N) = og;
@@ -604,7 +602,7 @@ int norm_bwd_partial_rows(int rows) { return rows < 256 ? rows : 256; }
 
 hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x, const float* stats,
                            const void* gamma, const void* dres, void* dx, float* partial, float* dgamma,
-                           float* dbeta, int rows, int h, hipStream_t s, int overwrite, void* dres_copy) {
+                           float* dbeta, int rows, int h, hipStream_t s, int overwrite, void* dres_copy, bool reduce) {
   if (rows <= 0 || (dres_copy && !dres)) return hipErrorInvalidValue;
   const bool ln = family == FAM_GPT;
   const int nb = norm_bwd_partial_rows(rows);
@@ -632,8 +630,14 @@ hipError_t launch_norm_bwd(int dtype, int family, const void* dn, const void* x,
         stats, (const float*)gamma, (const float*)dres, (float*)dx, (float*)dres_copy, partial, rows, h);
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(norm_bwd_reduce_kernel, dim3((h + 31) / 32, ln ? 2 : 1), dim3(256), 0, s, partial, dgamma, dbeta, nb, h, overwrite);
+  if (e != hipSuccess || !reduce) return e;
+  return launch_norm_reduce(family, NormReduce{{partial}, {dgamma}, {dbeta}, 1}, rows, h, overwrite, s);
+}
+
+hipError_t launch_norm_reduce(int family, const NormReduce& list, int rows, int h, int overwrite, hipStream_t s) {
+  if (list.n < 1 || list.n > NormReduce::MAX || rows <= 0 || h <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(norm_bwd_reduce_kernel, dim3((h + 31) / 32, family == FAM_GPT ? 2 : 1, list.n), dim3(256), 0, s, list,
+                     norm_bwd_partial_rows(rows), h, overwrite);
   return hipGetLastError();
 }
 

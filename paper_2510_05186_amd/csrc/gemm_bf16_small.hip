@@ -136,6 +136,27 @@ template <int EPI> __device__ __forceinline__ void finish(const GemmProblem& pr,
     // waits for copies
     else asm volatile("" : "+v"(v));
     *c = v;
+  } else if (EPI == EPI_DGELU || EPI == EPI_DSWIGLU) {       // of the gradient rounded as a product of its own would store it
+    bf16x4_t* c = reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16_t*>(pr.C) + off);
+    const bf16x4_t x = *c;
+    bf16x4_t o;
+    if (EPI == EPI_DGELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)dgelu((float)x[e], (float)(bf16_t)v[e]);
+    } else {
+      bf16x4_t* cu = reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16_t*>(pr.C) + off + pr.N);
+      const bf16x4_t u = *cu;
+      bf16x4_t ou;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float dg, du;
+        dswiglu((float)x[e], (float)u[e], (float)(bf16_t)v[e], dg, du);
+        o[e] = (bf16_t)dg;
+        ou[e] = (bf16_t)du;
+      }
+      *cu = ou;
+    }
+    *c = o;
   } else {
     if (EPI == EPI_RESID) {
       const bf16x4_t r = *reinterpret_cast<const bf16x4_t*>(reinterpret_cast<const bf16_t*>(pr.R) + off);
@@ -144,6 +165,11 @@ template <int EPI> __device__ __forceinline__ void finish(const GemmProblem& pr,
     bf16x4_t o;
     o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
     *reinterpret_cast<bf16x4_t*>(reinterpret_cast<bf16_t*>(pr.C) + off) = o;
+    if (EPI == EPI_GELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (bf16_t)gelu((float)o[e]);
+      *reinterpret_cast<bf16x4_t*>(const_cast<bf16_t*>(reinterpret_cast<const bf16_t*>(pr.R)) + off) = o;
+    }
   }
 }
 
@@ -378,6 +404,9 @@ hipError_t launch_gemm_bf16_small(int layout, int epi, const GemmProblem& pr, in
     if (epi == EPI_STORE) return launch_sized<false, EPI_STORE>(pr, K, s);
     if (epi == EPI_RESID) return launch_sized<false, EPI_RESID>(pr, K, s);
     if (epi == EPI_ACCUM) return launch_sized<false, EPI_ACCUM>(pr, K, s);
+    if (epi == EPI_GELU) return launch_sized<false, EPI_GELU>(pr, K, s);
+    if (epi == EPI_DGELU) return launch_sized<false, EPI_DGELU>(pr, K, s);
+    if (epi == EPI_DSWIGLU) return launch_sized<false, EPI_DSWIGLU>(pr, K, s);
   } else if (layout == GEMM_TN) {
     if (epi == EPI_STORE) return launch_sized<true, EPI_STORE>(pr, K, s);
     if (epi == EPI_ACCUM) return launch_sized<true, EPI_ACCUM>(pr, K, s);

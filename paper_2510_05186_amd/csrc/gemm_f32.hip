@@ -185,6 +185,34 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
     }
     if (m >= M || n >= N) continue;
     float* dst = C + (size_t)m * ldc + n;
+    if (epi >= EPI_GELU) {                                   // N and ldc are multiples of four
+      f32x4_t o;
+      if (epi == EPI_GELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = gelu(v[e]);
+        *reinterpret_cast<f32x4_t*>(dst) = v;
+        *reinterpret_cast<f32x4_t*>(const_cast<float*>(Res) + (size_t)m * ldc + n) = o;
+        continue;
+      }
+      const f32x4_t x = *reinterpret_cast<const f32x4_t*>(dst);
+      if (epi == EPI_DGELU) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = dgelu(x[e], v[e]);
+      } else {
+        const f32x4_t u = *reinterpret_cast<const f32x4_t*>(dst + N);
+        f32x4_t du;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float dg, d1;
+          dswiglu(x[e], u[e], v[e], dg, d1);
+          o[e] = dg;
+          du[e] = d1;
+        }
+        *reinterpret_cast<f32x4_t*>(dst + N) = du;
+      }
+      *reinterpret_cast<f32x4_t*>(dst) = o;
+      continue;
+    }
     const float* add = epi == EPI_RESID ? Res + (size_t)m * ldc + n : epi == EPI_ACCUM ? dst : nullptr;
     if (n + 4 <= N && (ldc & 3) == 0) {
       if (add) { const f32x4_t o = *reinterpret_cast<const f32x4_t*>(add); v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3]; }
@@ -379,16 +407,26 @@ hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* pr, int K,
   }
 }
 
+// The activation's epilogues are in the matrix-instruction kernels only
+bool gemm_f32_act_applies(int M, int N, int K) {
+  if (M <= 0 || N <= 0 || K <= 0 || (N & 3) || !mfma_reaches(false, K, K, K)) return false;
+  const GemmProblem pr = {nullptr, nullptr, nullptr, nullptr, M, N, K, K, N};
+  return !((K & 3) == 0 && plain_is_faster(false, true, EPI_STORE, tiles64_of(1, &pr), K)) &&
+         !((K & 3) && plain_is_faster(false, false, EPI_STORE, tiles64_of(1, &pr), K));
+}
+
 hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                            int K, int lda, int ldb, int ldc, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
-  if ((layout != GEMM_NT && layout != GEMM_TN) || epi < EPI_STORE || epi > EPI_STOREF) return hipErrorInvalidValue;
+  if ((layout != GEMM_NT && layout != GEMM_TN) || epi < EPI_STORE || epi > EPI_DSWIGLU || epi == EPI_ROPE || epi == EPI_SWIGLU)
+    return hipErrorInvalidValue;
+  if (epi >= EPI_GELU && (layout != GEMM_NT || lda != K || ldb != K || (ldc & 3) || !gemm_f32_act_applies(M, N, K))) return hipErrorInvalidValue;
   const bool tn = layout == GEMM_TN;
   const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
   float* c = (float*)C;
   const GemmProblem pr = {A, B, C, R, M, N, lda, ldb, ldc};
   const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
-  const bool plain = plain_is_faster(tn, vec && (ldc & 3) == 0, epi, tiles64_of(1, &pr), K) && (M + 63) / 64 < 65536;   // the second dimension of its grid
+  const bool plain = epi < EPI_GELU && plain_is_faster(tn, vec && (ldc & 3) == 0, epi, tiles64_of(1, &pr), K) && (M + 63) / 64 < 65536;   // the second dimension of its grid
   if (!plain && mfma_reaches(tn, K, lda, ldb)) {
     if (tn) return vec ? launch_sized<true, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
                        : launch_sized<true, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);

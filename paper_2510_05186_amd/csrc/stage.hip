@@ -51,7 +51,8 @@ uint64_t round_up(uint64_t n) { return (n + ALIGN - 1) / ALIGN * ALIGN; }
 struct Shape {
   int family, dtype, L, h, nq, nkv, d, f, seq, mb, tokens, qkv_w, up_w, e;
   int chunks, Lc;   // model chunks on this stage and layers per chunk (L = chunks * Lc)
-  bool fuse_rope, fuse_act;   // rotary in the QKV projection's epilogue, MLP activation in the gate / up projection's
+  bool fuse_rope, fuse_act;   // rotary in the QKV projection's epilogue, SwiGLU in the gate / up projection's
+  int epi_up, epi_da;         // epilogues of the up projection and of da = dy W_d: GELU, the activation's gradient, or plain
 };
 
 optstage_status shape_from_desc(const optstage_desc* d, Shape* s) {
@@ -81,6 +82,12 @@ optstage_status shape_from_desc(const optstage_desc* d, Shape* s) {
   // not in the recompute variant: B rebuilds the activation output from the stored gate / up tensor and has to arrive
   // at the very bits F multiplied with
   s->fuse_act = fusable && !d->recompute && (s->f % 128) == 0 && gemm_bf16_fused_applies(EPI_SWIGLU, s->tokens, s->up_w, s->h, s->h, 0);
+  const bool gpt = s->family == OPTSTAGE_GPT;
+  auto act = [&](int epi) {
+    return !d->no_fusion && (s->dtype == OPTSTAGE_BF16 ? gemm_bf16_act_applies(epi, s->tokens, s->f, s->h) : gemm_f32_act_applies(s->tokens, s->f, s->h)) ? epi : (int)EPI_STORE;
+  };
+  s->epi_up = gpt && !d->recompute ? act(EPI_GELU) : (int)EPI_STORE;
+  s->epi_da = act(gpt ? EPI_DGELU : EPI_DSWIGLU);
   return OPTSTAGE_OK;
 }
 
@@ -103,7 +110,7 @@ void kind_raw_bytes(const Shape& s, uint64_t raw[NK]) {
 
 struct WorkspaceLayout {
   uint64_t rope, wt_base, wt[OPTSTAGE_N_WEIGHTS], wf[OPTSTAGE_N_WEIGHTS], wt_layer_stride, da, dn, dout, dqkv, attn, partial,
-      csum, total;
+      partial_stride, csum, total;
 };
 
 uint64_t weight_elems(const Shape& s, int which) {
@@ -138,6 +145,9 @@ void slab_modes(const Shape& s, int which, bool* fwd, bool* bwd) {
   *bwd = gemm_bf16_slab_applies(s.tokens, cols, rows, rows);
 }
 
+// norms of a B op whose parameter gradients are summed in one launch
+int norm_group(const Shape& s) { return std::min(2 * s.Lc, (int)NormReduce::MAX); }
+
 WorkspaceLayout workspace_layout(const Shape& s) {
   WorkspaceLayout w;
   memset(&w, 0, sizeof w);
@@ -162,7 +172,8 @@ WorkspaceLayout workspace_layout(const Shape& s) {
   w.dout = take((uint64_t)s.tokens * s.nq * s.d * s.e);
   w.dqkv = take((uint64_t)s.tokens * s.qkv_w * s.e);
   w.attn = take(attn_bwd_ws_floats(s.seq, s.mb, s.nq, s.nkv, s.d) * 4);
-  w.partial = take((uint64_t)2 * norm_bwd_partial_rows(s.tokens) * s.h * 4);
+  w.partial_stride = round_up((uint64_t)2 * norm_bwd_partial_rows(s.tokens) * s.h * 4);
+  w.partial = take(w.partial_stride * norm_group(s));
   w.csum = take(16);
   w.total = off;
   return w;
@@ -506,12 +517,25 @@ optstage_status k_norm_fwd(optstage* st, const void* x, const void* g, const voi
       s.h, st->desc.norm_eps, st->cs, x_copy));
   return OPTSTAGE_OK;
 }
-optstage_status k_norm_bwd(optstage* st, const void* dn, const void* x, const float* stats, const void* g, const void* dres,
-    void* dx, float* dg, float* db, bool store, void* dres_copy = nullptr) {
+// sums of the norm parameters' gradients that wait for the end of a B op (with kernel timing on, each norm's come with it)
+struct NormSums { NormReduce list; bool store; };
+optstage_status flush_norm_sums(optstage* st, NormSums& q) {
   const Shape& s = st->sh;
-  KT(OPTSTAGE_KC_NORM_BWD, (dres_copy ? 5.0 : 4.0) * s.e * s.tokens * s.h, launch_norm_bwd(s.dtype, s.family, dn, x, stats, g, dres, dx,
-      (float*)(st->wsp() + st->ws.partial), dg, db, s.tokens, s.h, st->cs, store ? 1 : 0, dres_copy));
+  if (q.list.n) HIP_TRY(launch_norm_reduce(s.family, q.list, s.tokens, s.h, q.store ? 1 : 0, st->cs));
+  q.list.n = 0;
   return OPTSTAGE_OK;
+}
+optstage_status k_norm_bwd(optstage* st, const void* dn, const void* x, const float* stats, const void* g, const void* dres,
+    void* dx, float* dg, float* db, NormSums& q, void* dres_copy = nullptr) {
+  const Shape& s = st->sh;
+  float* partial = (float*)(st->wsp() + st->ws.partial + st->ws.partial_stride * q.list.n);
+  KT(OPTSTAGE_KC_NORM_BWD, (dres_copy ? 5.0 : 4.0) * s.e * s.tokens * s.h, launch_norm_bwd(s.dtype, s.family, dn, x, stats, g, dres, dx,
+      partial, dg, db, s.tokens, s.h, st->cs, q.store ? 1 : 0, dres_copy, st->ktiming));
+  if (st->ktiming) return OPTSTAGE_OK;
+  q.list.partial[q.list.n] = partial;
+  q.list.dgamma[q.list.n] = dg;
+  q.list.dbeta[q.list.n++] = db;
+  return q.list.n == norm_group(s) ? flush_norm_sums(st, q) : OPTSTAGE_OK;
 }
 optstage_status k_act_fwd(optstage* st, const void* gu, void* a) {
   const Shape& s = st->sh;
@@ -616,8 +640,9 @@ optstage_status exec_forward(optstage* st, int j, int c, const OpBufs& ob) {
       ex.a_out = a; ex.f = s.f;
       TRY(k_gemm_fused(st, GEMM_NT_SLAB, EPI_SWIGLU, n2, wgu, P(l, OPTSTAGE_K_GU), T, s.up_w, s.h, s.h, 64, s.up_w, ex));
     } else {
-      TRY(k_gemm(st, lay, EPI_STORE, n2, wgu, P(l, OPTSTAGE_K_GU), nullptr, T, s.up_w, s.h, s.h, s.h, s.up_w, OPTSTAGE_KC_GEMM_NT_GU));
-      TRY(k_act_fwd(st, P(l, OPTSTAGE_K_GU), a));
+      TRY(k_gemm(st, lay, s.epi_up, n2, wgu, P(l, OPTSTAGE_K_GU), s.epi_up == EPI_GELU ? a : nullptr, T, s.up_w, s.h, s.h, s.h, s.up_w,
+          OPTSTAGE_KC_GEMM_NT_GU));
+      if (s.epi_up != EPI_GELU) TRY(k_act_fwd(st, P(l, OPTSTAGE_K_GU), a));
     }
     void* y = l + 1 < l1 ? P(l + 1, OPTSTAGE_K_X_IN) : st->y_out[io];
     const void* wd = fwd_operand(st, l, OPTSTAGE_W_D, &lay);
@@ -656,7 +681,9 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
   const size_t io = (size_t)c * st->desc.n_microbatches + j;
   // B ops of a chunk run in micro-batch order, so micro-batch 0 is the iteration's first: in overwrite mode it
   // stores the norm parameters' gradients instead of adding to what the accumulators held
-  const bool store = st->overwrite && j == 0;
+  NormSums sums;
+  sums.list.n = 0;
+  sums.store = st->overwrite && j == 0;
   auto bit = [](int k) { return 1u << k; };
   for (int l = l1 - 1; l >= l0; --l) {
     TRY(wait_reload(st, j, l, bit(OPTSTAGE_K_GU), trace));
@@ -667,9 +694,13 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
     // da = dy W_d ; dgu = act'(gu) da (over gu) ; dn2 = dgu W_gu
     int lay;
     const void* wd = bwd_operand(st, l, OPTSTAGE_W_D, &lay);
-    TRY(k_gemm(st, lay, EPI_STORE, dy, wd, da, nullptr, T, s.f, s.h, s.h, s.h, s.f));
     if (rc) TRY(k_act_fwd(st, P(l, OPTSTAGE_K_GU), P(l, OPTSTAGE_K_A)));   // W's operand, before gu is overwritten
-    TRY(k_act_bwd(st, da, P(l, OPTSTAGE_K_GU), P(l, OPTSTAGE_K_GU)));
+    if (s.epi_da != EPI_STORE) {
+      TRY(k_gemm(st, lay, s.epi_da, dy, wd, P(l, OPTSTAGE_K_GU), nullptr, T, s.f, s.h, s.h, s.h, s.up_w));
+    } else {
+      TRY(k_gemm(st, lay, EPI_STORE, dy, wd, da, nullptr, T, s.f, s.h, s.h, s.h, s.f));
+      TRY(k_act_bwd(st, da, P(l, OPTSTAGE_K_GU), P(l, OPTSTAGE_K_GU)));
+    }
     const void* wgu = bwd_operand(st, l, OPTSTAGE_W_GU, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_GU), wgu, dn, nullptr, T, s.h, s.up_w, s.up_w, s.up_w, s.h));
     TRY(wait_reload(st, j, l, bit(OPTSTAGE_K_X_MID) | bit(OPTSTAGE_K_STATS), trace));
@@ -677,7 +708,7 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
         OPTSTAGE_K_N2), stats + (size_t)nstat * T));
     // dx_mid = dy + norm2'(dn2)
     TRY(k_norm_bwd(st, dn, P(l, OPTSTAGE_K_X_MID), stats + (size_t)nstat * T, W(st, l, OPTSTAGE_W_G2), dy, P(l,
-        OPTSTAGE_K_DX_MID), GW(st, l, OPTSTAGE_W_G2), GW(st, l, OPTSTAGE_W_B2), store, top ? P(l, OPTSTAGE_K_DY) : nullptr));
+        OPTSTAGE_K_DX_MID), GW(st, l, OPTSTAGE_W_G2), GW(st, l, OPTSTAGE_W_B2), sums, top ? P(l, OPTSTAGE_K_DY) : nullptr));
     // do = dx_mid W_o ; attention backward ; rotary backward into the qkv buffer
     const void* wo = bwd_operand(st, l, OPTSTAGE_W_O, &lay);
     TRY(k_gemm(st, lay, EPI_STORE, P(l, OPTSTAGE_K_DX_MID), wo, dout, nullptr, T, s.nq * s.d, s.h, s.h, s.h, s.nq * s.d));
@@ -690,9 +721,9 @@ optstage_status exec_backward_input(optstage* st, int j, int c, const OpBufs& ob
     if (rc) TRY(k_norm_fwd(st, P(l, OPTSTAGE_K_X_IN), W(st, l, OPTSTAGE_W_G1), W(st, l, OPTSTAGE_W_B1), P(l, OPTSTAGE_K_N1), stats));
     void* dx = l > l0 ? P(l - 1, OPTSTAGE_K_DY) : st->dx_in[io];
     TRY(k_norm_bwd(st, dn, P(l, OPTSTAGE_K_X_IN), stats, W(st, l, OPTSTAGE_W_G1), P(l, OPTSTAGE_K_DX_MID), dx, GW(st, l,
-        OPTSTAGE_W_G1), GW(st, l, OPTSTAGE_W_B1), store));
+        OPTSTAGE_W_G1), GW(st, l, OPTSTAGE_W_B1), sums));
   }
-  return OPTSTAGE_OK;
+  return flush_norm_sums(st, sums);
 }
 
 optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& ob) {

@@ -990,3 +990,39 @@ def test_reloads_arrive_before_the_kernels_that_read_them(duplex, seq, hidden):
         st.reset()
     st.close()
     ref.close()
+
+
+# tiles of 16 (fp32), 64 and 128 and the wave-split kernel (bf16); ragged tokens; ffn no multiple of a tile; more norms than one launch sums
+@pytest.mark.parametrize("family,dtype,hidden,ffn,seq,layers,recompute", [
+    (0, 0, 256, 1024, 128, 2, False), (1, 0, 128, 260, 61, 5, False), (0, 0, 512, 1000, 333, 1, True), (0, 1, 256, 520, 200, 2, False),
+    (1, 1, 1024, 1792, 320, 5, False), (1, 1, 256, 2056, 999, 1, True), (0, 1, 1024, 2048, 1000, 2, False), (0, 1, 768, 776, 65, 2, True)])
+def test_activation_in_the_products_epilogues(family, dtype, hidden, ffn, seq, layers, recompute):
+    """Products of the small kernels write GELU and the activation's gradient themselves: bit for bit what the separate kernels
+    write, and their norm parameters' gradients summed at the end of B those summed norm by norm.  Without fusion the rotary rotation
+    has a kernel of its own too (one rounding more), so that a Llama stage is compared up to the attention of its last layer."""
+    cfg = CFG.shrunken(CFG.CFG2 if family else CFG.CFG1, hidden=hidden, n_q=2, n_kv=2, ffn=ffn, seq=seq, n_layers=layers, n_microbatches=2, dtype=dtype)
+    ws, ref, top = T.stage_weights(cfg), None, layers - 1
+    for no_fusion in (False, True):
+        st = Stage(cfg, no_fusion=no_fusion, recompute=recompute, grad_overwrite=True)
+        st.set_weights(ws)
+        for j in range(2):
+            st.bind(j, T.stage_input(cfg, j), T.output_grad(cfg, j))
+        if no_fusion:
+            B.check(B.lib().optstage_set_kernel_timing(st.h, 1))
+        st.run([("F", 0), ("F", 1), ("B", 0)])
+        st.synchronize()
+        got = [st.y[j] for j in range(2)] + [st.grads[top]["g2"]] + [torch.from_numpy(st.read(0, top, k)[:seq * w * (4 - 2 * dtype)])
+                                                                            for k, w in (("A", ffn), ("GU", ffn * (1 + family)), ("DX_MID", hidden), ("N2", hidden))]
+        got = [t.clone() for t in got]
+        st.run([("W", 0), ("B", 1), ("W", 1)])
+        st.synchronize()
+        got.append(st.grads[top]["g2"].clone())
+        if not family:
+            got += [st.dx[j].clone() for j in range(2)] + [g[k].clone() for g in st.grads for k in sorted(g)]
+        n = dict(zip(B.KERNEL_CLASSES, st.stats().kernel_launches))
+        assert not no_fusion or (n["act_bwd"] == 2 * layers and n["norm_bwd"] == 4 * layers)
+        st.close()
+        if ref is None:
+            ref = got
+    for i, (a, b) in enumerate(zip(ref, got, strict=True)):
+        assert torch.equal(a, b), i
