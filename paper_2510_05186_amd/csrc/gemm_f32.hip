@@ -2,21 +2,25 @@
 // (Sec. 2.2: Y = X W^T, dX = dY W, dW += dY^T X), on the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (fp32 products and sums).
 //
 // What bounds it: an fp32 MFMA does 64 flop per cycle and SIMD, so operands are cheap to feed and what counts is how many compute
-// units have work.  A workgroup owns an RM x RN tile (64 x 64 to 16 x 16, see pick_tile), its four waves split the contraction in
-// steps of 16 k (wave w takes the steps w, w + 4, ...) and the four partial tiles are added through LDS in wave order.  No
-// operand is shared between waves, so nothing is staged through LDS: every lane loads its part of the fragments straight into
-// registers, 16 bytes at a time, several steps ahead (DEPTH), and the loop has no barrier.
-//  * NT (contiguous along k): lane = row (lane & 15), 4 consecutive k at 4 (lane >> 4); element e of the four goes to MFMA e of
-//    the step, the same k on both sides.  One load is 16 rows of 64 bytes.
-//  * TN (contiguous along the output index): a lane loads T = rows / 16 consecutive rows (columns) T r .. of one k, r = lane & 15,
-//    and element i belongs to MFMA tile i: tile i holds the rows T r + i, which costs nothing but the index in the epilogue.
-//    One load is 4 k-rows of 4 RM (RN) bytes.
-// Loads go through the buffer range check: rows past the operand and, by a lane offset out of range, k past K read as zero.
-// The loads ahead only help if every step waits for its own: the vectors that come back are kept as they are (as single floats, the
-// compiler copied them all at the top of the loop, behind one wait for every load in flight) and each step's loads are fenced in behind its
-// MFMAs.  That and the 64 x 32 and 16 x 32 tiles, us: NT 512 x 1024 x 4096 62.7 -> 45.5, 512 x 1024 x 1024 19.8 -> 14.2, 512 x 4096 x 1024 45.4 -> 40.2,
-// 128 x 768 x 256 4.9 -> 3.8, 2048 x 2048 x 2048 154 -> 138 (124 TFLOP/s); TN 1024 x 4096 x 512 45.8 -> 42.0; 80 products drawn between 100 and 2048
-// 1.26x (geometric mean; least .98, of 4 us).
+// units have work, and that nothing is issued while no MFMA runs.  A workgroup owns an RM x RN tile (64 x 64 to 16 x 16, see pick_tile), its
+// four waves split the contraction in steps of 16 k (wave w takes the steps w, w + 4, ...) and the four partial tiles are added through LDS
+// in wave order.  No operand is shared between waves, so the loop has no barrier.
+//  * NT (contiguous along k) with 16-byte rows: loads go straight into a ring in LDS, each wave's its own (staged_loop).
+//  * TN (contiguous along the output index): into registers, several steps ahead (DEPTH).  A lane loads T = rows / 16 consecutive
+//    rows (columns) T r .. of one k, r = lane & 15, and element i belongs to MFMA tile i: tile i holds the rows T r + i, which costs
+//    nothing but the index in the epilogue.  One load is 4 k-rows of 4 RM (RN) bytes.
+//  * rows that do not load 16 bytes at a time: the same into registers, element by element.
+// Loads go through the buffer range check: rows past the operand and k past K read as zero.
+// An MFMA takes 32 cycles and leaves room for other instructions of its wave, but only for those that stand between it and the next:
+// with a step's loads and their address arithmetic (some 90 instructions) in one place behind its MFMAs, 512 x 1024 x 4096 kept the matrix units
+// busy for 64 % of the time.  Now the loads and reads stand one by one between the MFMAs, their addresses are a scalar offset, and NT rows
+// go through LDS, where 16 lanes fetch four rows instead of sixteen (4 % of it).  us, before -> after: NT 512 x 1024 x 4096 45.7 -> 39.4,
+// 512 x 3072 x 1024 37.1 -> 32.4, 2048 x 2048 x 2048 135 -> 129 (133 TFLOP/s), 333 x 1000 x 512 8.7 -> 7.8, 128 x 256 x 1024 5.9 -> 4.6; TN 1024 x 1024 x
+// 1024 20.9 -> 19.1, 4096 x 1024 x 512 40.2 -> 38.5, 2048 x 2048 x 2048 134 -> 123.
+// The sums keep their registers and every step waits for its own loads: the vectors that come back are kept as they are (as single
+// floats the compiler copied them all at the top of the loop, behind one wait for every load in flight).
+#include <utility>
+
 #include "common.h"
 
 namespace {
@@ -24,6 +28,8 @@ namespace {
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 constexpr unsigned OUT_OF_RANGE = 0xFFFFFF00u;
 constexpr int STEP = 16;                                     // k per step
+// slots of a wave's ring: some 2000 cycles of MFMAs ahead (TA * TB of 128 cycles per step) within the LDS of two workgroups per compute unit
+constexpr int ring_slots(int rm, int rn) { return rm * rn >= 4096 ? 2 : rm * rn >= 2048 ? 3 : rm * rn >= 1024 ? 4 : rm * rn >= 512 ? 6 : 8; }
 
 // One operand: R rows of the tile (RM or RN) by 16 k per step, T = R / 16 MFMA tiles
 template <int R, bool TNL, bool VEC> struct Operand {
@@ -43,6 +49,10 @@ template <int R, bool TNL, bool VEC> struct Operand {
       k0 = g;                                                // rows g, g + 4, g + 8, g + 12 of a step
       kstep = (unsigned)ld * 4u;
       off[0] = first + r * T < extent ? (unsigned)(r * T) * 4u : OUT_OF_RANGE;
+      if constexpr (VEC) {                                   // for load_k: rows past the end take others in their place, and no sum of theirs is stored
+        if (off[0] == OUT_OF_RANGE) off[0] = 0;
+        off[0] += (unsigned)g * kstep;
+      }
     } else {
       k0 = 4 * g;
       kstep = 4u;
@@ -60,20 +70,24 @@ template <int R, bool TNL, bool VEC> struct Operand {
     // operand of MFMA e (k-set e) of tile i
     __device__ __forceinline__ float get(int i, int e) const { return TNL ? v[e][i] : v[i][e]; }
   };
+  // TN, 16-byte rows: k-set e of the step at k.  k-rows past K lie past the operand and read as zero.
+  __device__ __forceinline__ void load_k(Frag& f, int k, int e) const {
+    const unsigned at = (unsigned)(k + 4 * e) * kstep;
+    if constexpr (T == 4) f.v[e] = __builtin_bit_cast(typename Frag::vec_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[0], at, 0));
+    else if constexpr (T == 2) f.v[e] = __builtin_bit_cast(typename Frag::vec_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off[0], at, 0));
+    else f.v[e][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off[0], at, 0));
+  }
   __device__ __forceinline__ void load(Frag& f, int k, int K, int rows_left) const {
-    if constexpr (TNL) {
+    if constexpr (TNL && VEC) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) load_k(f, k, e);
+    } else if constexpr (TNL) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int kk = k + k0 + 4 * e;
         const unsigned o = kk < K && off[0] != OUT_OF_RANGE ? off[0] + (unsigned)kk * kstep : OUT_OF_RANGE;
-        if constexpr (VEC && T == 4) {
-          f.v[e] = __builtin_bit_cast(typename Frag::vec_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
-        } else if constexpr (VEC && T == 2) {
-          f.v[e] = __builtin_bit_cast(typename Frag::vec_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, o, 0, 0));
-        } else {
 #pragma unroll
-          for (int i = 0; i < T; ++i) f.v[e][i] = one(o != OUT_OF_RANGE && i < rows_left ? o + i * 4u : OUT_OF_RANGE);
-        }
+        for (int i = 0; i < T; ++i) f.v[e][i] = one(o != OUT_OF_RANGE && i < rows_left ? o + i * 4u : OUT_OF_RANGE);
       }
     } else {
       const int kk = k + k0;
@@ -92,12 +106,150 @@ template <int R, bool TNL, bool VEC> struct Operand {
   }
 };
 
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4_t;
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+
+// One NT operand by way of LDS: R rows of the tile, a step (64 bytes of each row) per slot, in the wave's own ring.  A load
+// takes 16 rows, four lanes to a row; the 16-byte chunk that lands at place p of its row is p ^ (row / 4 % 4), so that the 16 rows at
+// one k that an MFMA operand reads fall on all banks.
+template <int R> struct Staged {
+  static constexpr int T = R / 16;
+  // The range check adds the scalar offset (4 k) to the lane's, and the sum wraps: PAST + 4 k has to stay past the end (mfma_reaches)
+  static constexpr unsigned PAST = 0xF8000000u;
+  unsigned voff[T];            // this lane's byte offset within a step
+  unsigned frag;               // where it reads MFMA tile 0
+  int k0;                      // first k it fetches
+  i32x4_t desc;                // from the tile's corner to the operand's end: what lies past it reads as zero
+
+  __device__ __forceinline__ void init(const float* p, int ld, int first, int extent, int K, int lane) {
+    const unsigned long long at = (unsigned long long)(p + (size_t)first * ld), bytes = ((unsigned long long)(extent - 1 - first) * ld + K) * 4;
+    desc[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)at);
+    desc[1] = __builtin_amdgcn_readfirstlane((int)(unsigned)(at >> 32) & 0xffff);
+    desc[2] = __builtin_amdgcn_readfirstlane((int)(unsigned)(bytes > PAST ? PAST : bytes));
+    desc[3] = 0x00020000;
+    const int chunk = (lane & 3) ^ (lane >> 4);
+    k0 = chunk * 4;
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+      voff[i] = first + i * 16 + (lane >> 2) < extent ? (unsigned)(i * 16 + (lane >> 2)) * (unsigned)ld * 4u + (unsigned)chunk * 16u : PAST;
+    frag = (unsigned)((lane & 15) * 64 + (((lane >> 4) ^ ((lane >> 2) & 3)) << 4));
+  }
+  // the last step of a K that is no multiple of 16: chunks past K go out of range, for good
+  __device__ __forceinline__ void cut(int k, int K) {
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+      if (k + k0 >= K) voff[i] = PAST;
+  }
+  __device__ __forceinline__ void issue(unsigned slot, unsigned kbytes, int i) const {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(slot + i * 1024), "v"(voff[i]), "s"(desc), "s"(kbytes) : "memory", "m0");
+  }
+  __device__ __forceinline__ f32x4_t read(unsigned slot, int i) const { return *(const lds_f32x4_t*)(slot + frag + i * 1024); }
+};
+
+// f(0), f(1), ...: a loop that is unrolled at any length, its index a constant
+template <int... I, class F> __device__ __forceinline__ void each(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// The sums leave the matrix unit before a path ends: where paths meet, the compiler may copy them, and knows nothing of products in assembly
+template <int TA, int TB> __device__ __forceinline__ void drain(f32x4_t (&acc)[TA][TB]) {
+  asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc[0][0]) :: "memory");
+#pragma unroll
+  for (int i = 0; i < TA; ++i)
+#pragma unroll
+    for (int j = 0; j < TB; ++j) asm volatile("" : "+a"(acc[i][j]));
+}
+
+// acc[i][j] += this wave's share of the contraction (steps wave, wave + 4, ...)
+template <int RM, int RN>
+__device__ __forceinline__ void staged_loop(char* smem, f32x4_t (&acc)[RM / 16][RN / 16], const float* A, const float* B, int M, int N,
+                                            int K, int lda, int ldb, int m0, int n0, int wave, int lane) {
+  constexpr int TA = RM / 16, TB = RN / 16, L = TA + TB, NM = 4 * TA * TB, SLOTS = ring_slots(RM, RN), SLOT = L * 1024;
+  Staged<RM> a;
+  Staged<RN> b;
+  a.init(A, lda, m0, M, K, lane);
+  b.init(B, ldb, n0, N, K, lane);
+  const unsigned ring = (unsigned)(size_t)(lds_void_t*)smem + wave * (SLOTS * SLOT);
+  f32x4_t av[2][TA], bv[2][TB];
+  const int steps = (K + STEP - 1) / STEP, count = (steps - wave + 3) >> 2;
+  // Past its last step a wave loads the last of all again, which nobody reads: as many loads are in flight on every trip, and none
+  // reaches further.
+  auto first_k = [&](int n) __attribute__((always_inline)) {
+    const int k = min(wave + 4 * n, steps - 1) * STEP;
+    if (k + STEP > K) { a.cut(k, K); b.cut(k, K); }
+    return k;
+  };
+  auto issue = [&](unsigned slot, int k, int l) __attribute__((always_inline)) {
+    if (l < TA) a.issue(slot, k * 4u, l); else b.issue(slot + TA * 1024, k * 4u, l - TA);
+  };
+  auto read = [&](int set, unsigned slot, int q) __attribute__((always_inline)) {
+    if (q < TA) av[set][q] = a.read(slot, q); else bv[set][q - TA] = b.read(slot + TA * 1024, q - TA);
+  };
+#pragma unroll
+  for (int u = 0; u < SLOTS; ++u) {
+    const int k = first_k(u);
+#pragma unroll
+    for (int l = 0; l < L; ++l) issue(ring + u * SLOT, k, l);
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"((SLOTS - 1) * L) : "memory");
+#pragma unroll
+  for (int q = 0; q < L; ++q) read(0, ring, q);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  {
+    const int k = first_k(SLOTS);
+#pragma unroll
+    for (int l = 0; l < L; ++l) issue(ring, k, l);
+  }
+  unsigned slot = ring;
+  // A step: its MFMAs (fragment set `set`) in the order written.  Between those of the first half the next step's fragments are
+  // read, which have landed; between the others the slot that they have left is filled again.
+  auto trip = [&](int set, int n) __attribute__((always_inline)) {
+    slot = slot + SLOT == ring + SLOTS * SLOT ? ring : slot + SLOT;
+    const int k = first_k(n + 1 + SLOTS);
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((SLOTS - 1) * L) : "memory");
+    each(std::make_integer_sequence<int, NM>(), [&](auto at) __attribute__((always_inline)) {
+      constexpr int t = decltype(at)::value, H = NM / 2;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < L; ++q)
+        if (q * H / L == t) read(set ^ 1, slot, q);
+      if (t == H) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int l = 0; l < L; ++l)
+        if (H + l * H / L == t) issue(slot, k, l);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int e = t / (TA * TB), i = t / TB % TA, j = t % TB;
+      // in assembly the sums stay where they are (see f32_tile)
+      f32x4_t& sum = acc[i][j];
+      const float bf = bv[set][j][e], af = av[set][i][e];
+      asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(sum) : "v"(bf), "v"(af));
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int n = 0;
+  for (; n + 2 <= count; n += 2) {
+    trip(0, n);
+    trip(1, n + 1);
+  }
+  drain<TA, TB>(acc);
+  if (n < count) {
+    trip(0, n);
+    drain<TA, TB>(acc);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // nothing may land in LDS any more
+}
+
 template <int RM, int RN, bool TNL, bool VEC>
 __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C,
                                          const float* __restrict__ Res, int M, int N, int K, int lda, int ldb, int ldc, int id,
                                          int tiles_m, int tiles_n, int epi) {
   constexpr int TA = RM / 16, TB = RN / 16, DEPTH = TA * TB >= 16 ? 2 : TA * TB >= 8 ? 3 : TA * TB >= 4 ? 4 : 8;
-  __shared__ __attribute__((aligned(16))) float part[4][RM][RN + 4];
+  constexpr bool STAGED = !TNL && VEC;
+  constexpr int PART = 4 * RM * (RN + 4) * 4, RING = STAGED ? 4 * ring_slots(RM, RN) * (TA + TB) * 1024 : 0;
+  __shared__ __attribute__((aligned(1024))) char smem[PART > RING ? PART : RING];
+  float (&part)[4][RM][RN + 4] = *reinterpret_cast<float (*)[4][RM][RN + 4]>(smem);
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workgroup ids go to different XCDs: every XCD takes one contiguous eighth of the tiles, row by row
@@ -106,26 +258,36 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
   const int m0 = (id / tiles_n) * RM, n0 = (id % tiles_n) * RN;
   Operand<RM, TNL, VEC> a;
   Operand<RN, TNL, VEC> b;
-  a.init(A, lda, m0, M, K, lane);
-  b.init(B, ldb, n0, N, K, lane);
+  if constexpr (!STAGED) {
+    a.init(A, lda, m0, M, K, lane);
+    b.init(B, ldb, n0, N, K, lane);
+  }
   const int a_left = TNL ? M - m0 - r * TA : 0, b_left = TNL ? N - n0 - r * TB : 0;   // rows of this lane inside the operand
   f32x4_t acc[TA][TB];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
 #pragma unroll
     for (int j = 0; j < TB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  typename Operand<RM, TNL, VEC>::Frag av[DEPTH];
-  typename Operand<RN, TNL, VEC>::Frag bv[DEPTH];
-  const int steps = (K + STEP - 1) / STEP, count = (steps - wave + 3) >> 2;   // this wave's steps: wave + 4 s
+  if constexpr (VEC) {                                       // the zeros are in place, some cycles ahead of the first product
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) {
-    __builtin_amdgcn_sched_barrier(0);
-    a.load(av[d], (wave + 4 * d) * STEP, K, a_left);
-    b.load(bv[d], (wave + 4 * d) * STEP, K, b_left);
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int j = 0; j < TB; ++j) asm volatile("" : "+a"(acc[i][j]));
+    asm volatile("s_nop 3" ::: "memory");
   }
-  auto multiply = [&](int d) __attribute__((always_inline)) {
+  if constexpr (STAGED) {
+    staged_loop<RM, RN>(smem, acc, A, B, M, N, K, lda, ldb, m0, n0, wave, lane);
+  } else {
+    typename Operand<RM, TNL, VEC>::Frag av[DEPTH];
+    typename Operand<RN, TNL, VEC>::Frag bv[DEPTH];
+    const int steps = (K + STEP - 1) / STEP, count = (steps - wave + 3) >> 2;   // this wave's steps: wave + 4 s
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int d = 0; d < DEPTH; ++d) {
+      __builtin_amdgcn_sched_barrier(0);
+      a.load(av[d], (wave + 4 * d) * STEP, K, a_left);
+      b.load(bv[d], (wave + 4 * d) * STEP, K, b_left);
+    }
+    auto multiply_k = [&](int d, int e) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < TA; ++i)
 #pragma unroll
@@ -134,31 +296,45 @@ __device__ __forceinline__ void f32_tile(const float* __restrict__ A, const floa
           // round.  Its operands come straight from loads; no vector instruction writes them
           if constexpr (VEC) asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(bv[d].get(j, e)), "v"(av[d].get(i, e)));
           else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[d].get(j, e), av[d].get(i, e), acc[i][j], 0, 0, 0);
-  };
-  if constexpr (VEC) {                                       // the zeros are in place, some cycles ahead of the first product
+    };
+    auto multiply = [&](int d) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < TA; ++i)
+      for (int e = 0; e < 4; ++e) multiply_k(d, e);
+    };
+    int s = 0;
+    for (; s + DEPTH <= count; s += DEPTH) {
 #pragma unroll
-      for (int j = 0; j < TB; ++j) asm volatile("" : "+a"(acc[i][j]));
-    asm volatile("s_nop 3" ::: "memory");
-  }
-  int s = 0;
-  for (; s + DEPTH <= count; s += DEPTH) {
+      for (int d = 0; d < DEPTH; ++d) {
+        // a step's loads stay behind the MFMAs that free their registers: left alone the compiler gathers those of all DEPTH steps at the
+        // end of the loop, right ahead of one wait for all of them
+        const int k = (wave + 4 * (s + d + DEPTH)) * STEP;
+        if constexpr (TNL && VEC) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      // a step's loads stay behind its MFMAs: left alone the compiler gathers those of all DEPTH steps at the end of the loop, right ahead of
-      // one wait for all of them
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(d);
-      __builtin_amdgcn_sched_barrier(0);
-      a.load(av[d], (wave + 4 * (s + d + DEPTH)) * STEP, K, a_left);
-      b.load(bv[d], (wave + 4 * (s + d + DEPTH)) * STEP, K, b_left);
+          for (int e = 0; e < 4; ++e) {
+            __builtin_amdgcn_sched_barrier(0);
+            multiply_k(d, e);
+            __builtin_amdgcn_sched_barrier(0);
+            a.load_k(av[d], k, e);
+            b.load_k(bv[d], k, e);
+          }
+        } else {
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(d);
+          __builtin_amdgcn_sched_barrier(0);
+          a.load(av[d], k, K, a_left);
+          b.load(bv[d], k, K, b_left);
+        }
+      }
     }
-  }
+    if constexpr (VEC) drain<TA, TB>(acc);
 #pragma unroll
-  for (int d = 0; d < DEPTH - 1; ++d)                        // the steps left over are loaded
-    if (s + d < count) multiply(d);
-  if constexpr (VEC) asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");   // the last results have left the matrix unit
+    for (int d = 0; d < DEPTH - 1; ++d)                      // the steps left over are loaded
+      if (s + d < count) {
+        multiply(d);
+        if constexpr (VEC) drain<TA, TB>(acc);
+      }
+  }
+  if constexpr (STAGED) __syncthreads();                     // every wave's ring is read
   // partial tiles into LDS in the order of C: acc[i][j][v] is row r of tile i, column 4 g + v of tile j
 #pragma unroll
   for (int i = 0; i < TA; ++i) {
@@ -313,11 +489,12 @@ hipError_t launch_mfma(int epi, const float* A, const float* B, float* C, const 
 }
 
 // The tile that needs the least time.  Workgroups come to the compute units evenly, n = ceil(tiles / 256) to the fullest, and share its matrix
-// units: start, first loads and epilogue once, and n contractions.  Both from 256 and 1024 k and one to eight workgroups per unit, us:
-// 512 x 4096 x 1024 40.1 in tiles of 64 x 64, 48.0 of 64 x 32, 61.3 of 32 x 32; 512 x 3072 x 1024 39.4 / 37.0 / 46.8; 512 x 1024 x 4096 65.7 / 45.3 /
-// 58.9; 512 x 1024 x 1024 20.0 / 14.2 / 17.4; 128 x 768 x 256 8.2 / 5.7 / 4.3, of 16 x 32 3.7, of 16 x 16 4.1; 128 x 256 x 1024 19.7 / 13.7 / 9.4 / 7.8 / 5.9.
+// units: start, first loads and epilogue once, and n contractions.  Both from 256 to 4096 k and one to 32 workgroups per unit, us in tiles of
+// 64 x 64 / 64 x 32 / 32 x 32 / 16 x 32 / 16 x 16: 512 x 4096 x 1024 37.8 / 41.6 / 47.2 / 76 / 81; 512 x 3072 x 1024 36.0 / 32.4 / 37.8 / 59 / 63;
+// 512 x 1024 x 4096 67.7 / 39.3 / 41.5 / 75 / 83; 512 x 1024 x 1024 20.5 / 13.9 / 14.4 / 17.9 / 21.7; 800 x 800 x 800 17.9 / 18.4 / 16.0 / 17.3 / 22.0;
+// 200 x 512 x 512 11.5 / 7.5 / 5.0 / 4.3 / 4.6; 128 x 256 x 1024 19.4 / 11.9 / 7.4 / 5.5 / 4.6; TN within 10 %.
 struct TileShape { int rows, cols; double start_us, first_ns, next_ns; };   // ns per k: a unit's only workgroup, each of several
-constexpr TileShape TILES[] = {{64, 64, 4.0, 16.8, 16.8}, {64, 32, 3.0, 10.9, 11.2}, {32, 32, 2.6, 6.8, 7.2}, {16, 32, 2.6, 5.0, 5.7}, {16, 16, 2.6, 2.6, 3.75}};
+constexpr TileShape TILES[] = {{64, 64, 3.8, 15.3, 15.7}, {64, 32, 3.2, 8.8, 9.3}, {32, 32, 2.75, 5.0, 5.2}, {16, 32, 2.6, 3.0, 3.8}, {16, 16, 2.6, 2.0, 2.35}};
 int pick_tile(int n, const GemmProblem* pr, int K) {
   int best = 0;
   double least = 1e30;
@@ -370,7 +547,7 @@ namespace {
 bool mfma_reaches(bool tn, int K, int lda, int ldb) {
   const unsigned long long reach = 0xF0000000ull / 4;
   const unsigned long long span = (unsigned long long)(tn ? K + 64ull * 16 : 64ull) * (unsigned long long)(lda > ldb ? lda : ldb) + 64;
-  return span < reach && (tn || (unsigned long long)K < reach / 2);
+  return span < reach && (tn || K < 1 << 25);                // 4 k below 2^27 (Staged::PAST)
 }
 
 template <int RM, int RN>
