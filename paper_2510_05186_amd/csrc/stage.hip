@@ -517,6 +517,8 @@ optstage_status k_norm_fwd(optstage* st, const void* x, const void* g, const voi
       s.h, st->desc.norm_eps, st->cs, x_copy));
   return OPTSTAGE_OK;
 }
+// whether two accumulators (null: none) have a float in common: parameters may be given the same one (tied weights)
+bool shared(const float* a, uint64_t na, const float* b, uint64_t nb) { return a && b && a < b + nb && b < a + na; }
 // sums of the norm parameters' gradients that wait for the end of a B op (with kernel timing on, each norm's come with it)
 struct NormSums { NormReduce list; bool store; };
 optstage_status flush_norm_sums(optstage* st, NormSums& q) {
@@ -528,6 +530,13 @@ optstage_status flush_norm_sums(optstage* st, NormSums& q) {
 optstage_status k_norm_bwd(optstage* st, const void* dn, const void* x, const float* stats, const void* g, const void* dres,
     void* dx, float* dg, float* db, NormSums& q, void* dres_copy = nullptr) {
   const Shape& s = st->sh;
+  // the norms of one launch add at the same time: one whose accumulator the list already has waits for the next
+  for (int i = 0; i < q.list.n; ++i)
+    for (const float* acc : {q.list.dgamma[i], q.list.dbeta[i]})
+      if (shared(acc, s.h, dg, s.h) || shared(acc, s.h, db, s.h)) {
+        TRY(flush_norm_sums(st, q));
+        break;
+      }
   float* partial = (float*)(st->wsp() + st->ws.partial + st->ws.partial_stride * q.list.n);
   KT(OPTSTAGE_KC_NORM_BWD, (dres_copy ? 5.0 : 4.0) * s.e * s.tokens * s.h, launch_norm_bwd(s.dtype, s.family, dn, x, stats, g, dres, dx,
       partial, dg, db, s.tokens, s.h, st->cs, q.store ? 1 : 0, dres_copy, st->ktiming));

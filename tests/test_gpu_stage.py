@@ -721,6 +721,34 @@ def test_grad_overwrite_mode_needs_no_cleared_accumulators():
         ref.close()
 
 
+# more norms than one launch sums; both families
+@pytest.mark.parametrize("base,layers,names", [(CFG.CFG1, 5, ("g1", "b1", "g2", "b2")), (CFG.CFG2, 3, ("g1", "g2"))])
+@pytest.mark.parametrize("overwrite", [False, True])
+def test_layers_that_share_an_accumulator(base, layers, names, overwrite):
+    """Parameters tied over the layers have one accumulator: it receives every layer's gradient, one after the other in the order of B.
+    Storing (overwrite mode), the last one stands, as of two calls."""
+    cfg = CFG.shrunken(base, hidden=256, n_q=2, n_kv=2, ffn=512, seq=100, n_layers=layers, n_microbatches=1)
+    ws, own = T.stage_weights(cfg), None
+    for tied in (False, True):
+        st = Stage(cfg, grad_overwrite=overwrite)
+        st.set_weights(ws)
+        st.bind(0, T.stage_input(cfg, 0), T.output_grad(cfg, 0))
+        for l in range(layers if tied else 0):
+            for n in names:
+                B.check(B.lib().optstage_set_weight(st.h, l, B.WEIGHT_ID[n], st.weights[l][n].data_ptr(), st.grads[0][n].data_ptr()))
+        torch.cuda.synchronize()
+        st.run([("F", 0), ("B", 0), ("W", 0)])
+        st.synchronize()
+        if not tied:
+            own = [{n: g[n].clone() for n in names} for g in st.grads]
+        for n in names if tied else ():
+            ref = own[-1][n]
+            for l in reversed(range(layers - 1)):
+                ref = own[l][n] if overwrite else ref + own[l][n]
+            assert torch.equal(st.grads[0][n], ref), n
+        st.close()
+
+
 def _grouped(base, name, hidden, n_q, n_kv, ffn, seq, n_layers):
     return CFG.shrunken(base, hidden=hidden, n_q=n_q, n_kv=n_kv, ffn=ffn, seq=seq, n_layers=n_layers, n_microbatches=2, name=name)
 
