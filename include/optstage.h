@@ -183,7 +183,7 @@ void optstage_destroy(optstage_t* st);
 
 /* Registers layer `layer`'s parameter `which` (DEVICE, stage dtype) and its gradient accumulator
  * (DEVICE, fp32, same shape; B and W add into it, so the caller zeroes it, unless
- * optstage_set_grad_overwrite is on).  Norm parameters of several layers may be given one accumulator (tied
+ * optstage_set_grad_overwrite is on).  Parameters of several layers may be given one accumulator (tied
  * parameters): their gradients are added one after the other.  With optstage_set_grad_overwrite on, each needs its own
  * (stored ones replace each other).  For the four linear weights the
  * library also keeps a transposed copy in the workspace (enqueued on compute_stream) so that B's

@@ -753,12 +753,18 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
   // W ops of a chunk run in micro-batch order: in overwrite mode micro-batch 0 stores its products (no read of the
   // accumulators, and nobody has to clear them between iterations), the others add
   const int epi = st->overwrite && j == 0 ? EPI_STOREF : EPI_ACCUM;
-  for (size_t i0 = 0; i0 < pr.size(); i0 += 16) {
-    const int n = (int)std::min<size_t>(16, pr.size() - i0);
-    const bool grouped = s.dtype == OPTSTAGE_BF16 ? gemm_bf16_grouped_applies(GEMM_TN, n, &pr[i0], T) : gemm_f32_grouped_applies(n, &pr[i0], T);
-    if (grouped) TRY(k_gemm_grouped(st, GEMM_TN, epi, n, &pr[i0], T));
+  for (size_t i0 = 0, n; i0 < pr.size(); i0 += n) {
+    // the products of one call add at the same time: one whose accumulator an earlier product of the call has starts the next
+    auto alone = [&](const GemmProblem& q) {
+      for (size_t i = i0; i < i0 + n; ++i)
+        if (shared((const float*)pr[i].C, (uint64_t)pr[i].M * pr[i].ldc, (const float*)q.C, (uint64_t)q.M * q.ldc)) return false;
+      return true;
+    };
+    for (n = 1; n < 16 && i0 + n < pr.size() && alone(pr[i0 + n]); ++n) {}
+    const bool grouped = s.dtype == OPTSTAGE_BF16 ? gemm_bf16_grouped_applies(GEMM_TN, (int)n, &pr[i0], T) : gemm_f32_grouped_applies((int)n, &pr[i0], T);
+    if (grouped) TRY(k_gemm_grouped(st, GEMM_TN, epi, (int)n, &pr[i0], T));
     if (!grouped)
-      for (int i = 0; i < n; ++i) {
+      for (size_t i = 0; i < n; ++i) {
         const GemmProblem& q = pr[i0 + i];
         TRY(k_gemm(st, GEMM_TN, epi, q.A, q.B, q.C, nullptr, q.M, q.N, T, q.lda, q.ldb, q.ldc));
       }

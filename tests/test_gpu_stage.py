@@ -721,13 +721,15 @@ def test_grad_overwrite_mode_needs_no_cleared_accumulators():
         ref.close()
 
 
-# more norms than one launch sums; both families
-@pytest.mark.parametrize("base,layers,names", [(CFG.CFG1, 5, ("g1", "b1", "g2", "b2")), (CFG.CFG2, 3, ("g1", "g2"))])
+# more norms than one launch sums; linear weights of the fp32 and the bf16 grouped launch (136 tiles of 256 a layer), all of them and one
+@pytest.mark.parametrize("base,layers,hidden,ffn,names", [(CFG.CFG1, 5, 256, 512, ("g1", "b1", "g2", "b2")), (CFG.CFG2, 3, 256, 512, ("g1", "g2")),
+                                                          (CFG.CFG1, 3, 256, 512, ("wqkv", "wo", "wgu", "wd", "g1")), (CFG.CFG1, 5, 256, 512, ("wo",)),
+                                                          (CFG.CFG2, 2, 1024, 2048, ("wqkv", "wo", "wgu", "wd")), (CFG.CFG2, 3, 1024, 2048, ("wgu",))])
 @pytest.mark.parametrize("overwrite", [False, True])
-def test_layers_that_share_an_accumulator(base, layers, names, overwrite):
-    """Parameters tied over the layers have one accumulator: it receives every layer's gradient, one after the other in the order of B.
-    Storing (overwrite mode), the last one stands, as of two calls."""
-    cfg = CFG.shrunken(base, hidden=256, n_q=2, n_kv=2, ffn=512, seq=100, n_layers=layers, n_microbatches=1)
+def test_layers_that_share_an_accumulator(base, layers, hidden, ffn, names, overwrite):
+    """Parameters tied over the layers have one accumulator: it receives every layer's gradient, one after the other (norms from the
+    last layer down, in B, linear weights from the first up, in W).  Storing (overwrite mode), the last one stands."""
+    cfg = CFG.shrunken(base, hidden=hidden, n_q=hidden // 128, n_kv=2, ffn=ffn, seq=100, n_layers=layers, n_microbatches=1)
     ws, own = T.stage_weights(cfg), None
     for tied in (False, True):
         st = Stage(cfg, grad_overwrite=overwrite)
@@ -742,8 +744,9 @@ def test_layers_that_share_an_accumulator(base, layers, names, overwrite):
         if not tied:
             own = [{n: g[n].clone() for n in names} for g in st.grads]
         for n in names if tied else ():
-            ref = own[-1][n]
-            for l in reversed(range(layers - 1)):
+            order = list(range(layers)) if n[0] == "w" else list(reversed(range(layers)))
+            ref = own[order[0]][n]
+            for l in order[1:]:
                 ref = own[l][n] if overwrite else ref + own[l][n]
             assert torch.equal(st.grads[0][n], ref), n
         st.close()
