@@ -145,8 +145,15 @@ void slab_modes(const Shape& s, int which, bool* fwd, bool* bwd) {
   *bwd = gemm_bf16_slab_applies(s.tokens, cols, rows, rows);
 }
 
-// norms of a B op whose parameter gradients are summed in one launch
-int norm_group(const Shape& s) { return std::min(2 * s.Lc, (int)NormReduce::MAX); }
+// Norms of a B op whose parameter gradients are summed in one launch.  Their partial sums (up to 256 rows of two norm widths each) wait for
+// it side by side in the workspace, bounded because a launch saved is worth 4 us whatever they take.  us per iteration with a launch
+// per norm / this bound / up to eight norms: hidden 256, 2 layers 765 / 722 / 720; 1024, 4 layers 2130 / 2037 / 2025 (16 MiB); 4096, 3
+// layers, 300 tokens 2585 / 2560 / 2559 (48 MiB); 4096 tokens 8641 / 8635 / 8633.  At hidden 8192 eight are 128 MiB.
+constexpr uint64_t NORM_PARTIALS_MAX = 16 << 20;
+uint64_t norm_partial_bytes(const Shape& s) { return round_up((uint64_t)2 * norm_bwd_partial_rows(s.tokens) * s.h * 4); }
+int norm_group(const Shape& s) {
+  return std::max(1, std::min(std::min(2 * s.Lc, (int)NormReduce::MAX), (int)(NORM_PARTIALS_MAX / norm_partial_bytes(s))));
+}
 
 WorkspaceLayout workspace_layout(const Shape& s) {
   WorkspaceLayout w;
@@ -172,7 +179,7 @@ WorkspaceLayout workspace_layout(const Shape& s) {
   w.dout = take((uint64_t)s.tokens * s.nq * s.d * s.e);
   w.dqkv = take((uint64_t)s.tokens * s.qkv_w * s.e);
   w.attn = take(attn_bwd_ws_floats(s.seq, s.mb, s.nq, s.nkv, s.d) * 4);
-  w.partial_stride = round_up((uint64_t)2 * norm_bwd_partial_rows(s.tokens) * s.h * 4);
+  w.partial_stride = norm_partial_bytes(s);
   w.partial = take(w.partial_stride * norm_group(s));
   w.csum = take(16);
   w.total = off;

@@ -59,6 +59,16 @@ def test_memory_table_matches_oracle(cfg):
     assert ws > 0
 
 
+@pytest.mark.parametrize("hidden,tokens,norms", [(256, 128, 8), (1024, 320, 8), (2048, 300, 4), (4096, 300, 2), (8192, 4096, 1), (8192, 3, 8)])
+def test_workspace_for_waiting_norm_sums_is_bounded(hidden, tokens, norms):
+    """Partial sums of the norms of one launch (up to eight, of 2 hidden floats for each of up to 256 rows) stay within 16 MiB, or are one
+    norm's: what a layer adds to the workspace beyond its weight copies, by layer."""
+    sizes = [B.query_sizes(replace(CFG.shrunken(CFG.CFG4, hidden=hidden, n_q=2, n_kv=1, ffn=256, seq=tokens), n_layers=n))[0] for n in range(1, 8)]
+    one = 2 * min(tokens, 256) * hidden * 4
+    copies = sizes[-1] - sizes[-2]
+    assert [s - sizes[0] - copies * i for i, s in enumerate(sizes)] == [(min(2 * (i + 1), norms) - min(2, norms)) * one for i in range(7)]
+
+
 @pytest.mark.parametrize("cfg", [CFG.CFG1, CFG.CFG2, CFG.CFG4], ids=lambda c: c.name)
 def test_recompute_memory_table_matches_oracle(cfg):
     _, act, kinds = B.query_sizes(cfg, recompute=1)
