@@ -138,7 +138,9 @@ typedef struct {
   uint64_t bytes_offloaded, bytes_reloaded;
   uint64_t n_ops[6];                            /* count per optstage_op */
   double ms_ops[6];                             /* summed device time per optstage_op (F, B, W on the compute
-                                                   stream; O, R on the copy stream); valid after synchronize */
+                                                   stream; O, R on the copy stream); valid after synchronize.  An op
+                                                   of a list begins where the one before it on its stream ends, or
+                                                   when it is enqueued where the stream has run dry by then */
   uint64_t arena_high_water;                    /* highest physical arena offset ever used */
   /* per kernel class, filled only while kernel timing is on (optstage_set_kernel_timing): launches,
    * summed device time, and summed algorithmic work (flops for the GEMM / attention classes 0-4, 10, 11: 2*M*N*K, causal

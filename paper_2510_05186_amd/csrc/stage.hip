@@ -442,6 +442,19 @@ optstage_status record(optstage* st, hipStream_t s, hipEvent_t* out) {
   HIP_TRY(hipEventRecord(*out, s));
   return OPTSTAGE_OK;
 }
+// Whether stream s has yet to pass an event recorded on it: only then does what is enqueued next begin there.  Past it the stream waits
+// for the host, and that time is no op's.  (The query must not end a capture that another thread of the program is making.)
+bool ahead(hipEvent_t e, hipStream_t s) {
+  if (!e) return false;
+  hipStreamCaptureStatus capture;
+  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return true;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t q = hipEventQuery(e);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (q != hipSuccess) (void)hipGetLastError();
+  return q == hipErrorNotReady;
+}
 // begin: an event that already marks this point of the stream, or null to record one
 optstage_status span_begin(optstage* st, int op, hipStream_t s, TimedSpan* sp, int trace = -1, hipEvent_t begin = nullptr) {
   sp->op = op;
@@ -822,7 +835,7 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
     case OPTSTAGE_F:
     case OPTSTAGE_B:
     case OPTSTAGE_W:
-      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti, st->cs_waited ? nullptr : st->cs_tail)) != OPTSTAGE_OK) return rc;
+      if ((rc = span_begin(st, ev.op, st->cs, &sp, ti, !st->cs_waited && ahead(st->cs_tail, st->cs) ? st->cs_tail : nullptr)) != OPTSTAGE_OK) return rc;
       // B starts at once; every reload of its micro-batch has completed before the first kernel that reads what it brought
       rc = ev.op == OPTSTAGE_F ? exec_forward(st, j, c, ob) : ev.op == OPTSTAGE_B ? exec_backward_input(st, j, c, ob, ti)
                                                                                    : exec_backward_weight(st, j, c, ob);
@@ -851,7 +864,10 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
       // compute ops listed from here on may reuse the freed bytes: they start after the offload ended
       const hipEvent_t o = st->pending[(size_t)j * L + ev.layer].o;
       if (!o || o == st->cs_waited) break;
-      if (!st->cs_tail && (rc = record(st, st->cs, &st->cs_tail)) != OPTSTAGE_OK) return rc;
+      if (!ahead(st->cs_tail, st->cs) && !ahead(st->cs_waited, st->cs)) {
+        if ((rc = record(st, st->cs, &st->cs_tail)) != OPTSTAGE_OK) return rc;
+        st->cs_waited = nullptr;
+      }
       HIP_TRY(hipStreamWaitEvent(st->cs, o, 0));
       st->spans.push_back({SPAN_STALL, st->cs_tail, o, ti, st->cs_waited});
       st->cs_waited = o;
@@ -875,7 +891,7 @@ optstage_status exec_event(optstage* st, const optstage_event& ev, const OpBufs&
         HIP_TRY(hipStreamWaitEvent(st->rs, p.o, 0));
         st->rs_tail = nullptr;
       }
-      if ((rc = span_begin(st, ev.op, st->rs, &sp, ti, st->rs_tail)) != OPTSTAGE_OK) return rc;
+      if ((rc = span_begin(st, ev.op, st->rs, &sp, ti, ahead(st->rs_tail, st->rs) ? st->rs_tail : nullptr)) != OPTSTAGE_OK) return rc;
       if ((rc = transfer(st, ev, ob, st->rs)) != OPTSTAGE_OK) return rc;
       if ((rc = span_end(st, st->rs, sp)) != OPTSTAGE_OK) return rc;
       st->rs_tail = st->last_r = p.r = sp.b;

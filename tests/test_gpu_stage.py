@@ -848,6 +848,30 @@ def test_stats_report_the_trace_the_live_levels_and_the_stalls():
     st.close()
 
 
+def test_time_in_which_the_stream_waits_for_the_host_is_no_op_s():
+    """Eighty offloads are enqueued between two forward ops of a tiny stage, which takes the host far longer than the first op the
+    device: the second op begins when it is enqueued, not where the first ended."""
+    cfg = CFG.shrunken(CFG.CFG1, hidden=64, n_q=1, n_kv=1, ffn=64, seq=16, n_layers=8, n_microbatches=2)
+    ws, t = T.stage_weights(cfg), oracle_table(cfg)
+    moves = [(0, l, (k,)) for l in range(cfg.n_layers) for k in S.F_KINDS]
+    st = Stage(cfg, host_pool_bytes=sum(t[k] for k in S.F_KINDS) * cfg.n_layers)
+    st.set_weights(ws)
+    for j in range(2):
+        st.bind(j, T.stage_input(cfg, j), T.output_grad(cfg, j))
+    for _ in range(2):                                           # the first pass loads the kernels
+        st.reset()
+        st.run([("F", 0)] + [("O", *m) for m in moves] + [("F", 1)])
+        st.synchronize()
+    first, second = [e for e in st.trace() if e[0] == "F"]
+    assert second[5] - first[6] > 0.05 and st.stats().ms_ops[0] == pytest.approx(first[6] - first[5] + second[6] - second[5], rel=1e-3)
+    # the reloads come in one group, each begins where the one before ended, or later
+    st.run([("OWAIT", *m) for m in moves] + [("R", *m) for m in moves])
+    st.synchronize()
+    spans = sorted(e[5:7] for e in st.trace() if e[0] == "R")
+    assert len(spans) == len(moves) and all(b[0] >= a[1] - 1e-3 for a, b in zip(spans, spans[1:]))
+    st.close()
+
+
 def test_fused_epilogues_against_the_oracle_and_the_separate_kernels():
     """A stage large enough for the direct GEMM kernel, so that rotary runs in the QKV projection's epilogue and SwiGLU
     in the gate / up projection's: results against the oracle, and against the same stage with no_fusion (separate
