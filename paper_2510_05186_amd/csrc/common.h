@@ -105,7 +105,7 @@ hipError_t launch_gemm_bf16_grouped(int layout, int epi, int n, const GemmProble
 hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
                             int K, int lda, int ldb, int ldc, hipStream_t s, const GemmExtra* extra = nullptr);
 // whether a product y = x W^T (dense operands) is served with the activation in its epilogue (EPI_GELU, EPI_DGELU, EPI_DSWIGLU)
-bool gemm_bf16_act_applies(int epi, int M, int N, int K);
+bool gemm_bf16_act_applies(int M, int N, int K);
 bool gemm_f32_act_applies(int M, int N, int K);
 // tiles of 128 or 64, for products of up to 256 tiles of 128 x 128 and for what is cut off a grouped TN set; bf16 alignment rules as
 // for launch_gemm_bf16

@@ -1004,8 +1004,9 @@ bool gemm_bf16_fused_applies(int epi, int M, int N, int K, int lda, int head_dim
 
 // The activation runs in the epilogue of the small kernels: at their sizes its own pass is a launch of 4 us, most of it start and end
 // (320 tokens, hidden 1024, ffn 1792, SwiGLU backward 4.8 us of 13 with its product).
-bool gemm_bf16_act_applies(int epi, int M, int N, int K) {
-  if (M <= 0 || N <= 0 || K <= 0 || (K & 7) || (N & 3)) return false;
+// The product's weight must have its plain layout: not at a size where it is kept in slabs.
+bool gemm_bf16_act_applies(int M, int N, int K) {
+  if (M <= 0 || N <= 0 || K <= 0 || (K & 7) || (N & 3) || gemm_bf16_slab_applies(M, N, K, K)) return false;
   return route(false, EPI_STORE, M, N, K, K, K) == ROUTE_SMALL;
 }
 
@@ -1040,7 +1041,7 @@ hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, v
   }
   if ((lda & 7) || (ldb & 7) || (ldc & 3) || (N & 3)) return hipErrorInvalidValue;
   if (epi == EPI_GELU || epi == EPI_DGELU || epi == EPI_DSWIGLU) {
-    if (layout != GEMM_NT || lda != K || ldb != K || !gemm_bf16_act_applies(epi, M, N, K)) return hipErrorInvalidValue;
+    if (layout != GEMM_NT || lda != K || ldb != K || !gemm_bf16_act_applies(M, N, K)) return hipErrorInvalidValue;
     return launch_gemm_bf16_small(GEMM_NT, epi, GemmProblem{A, B, C, R, M, N, lda, ldb, ldc}, K, s);
   }
   if (layout == GEMM_NT) {

@@ -84,7 +84,7 @@ optstage_status shape_from_desc(const optstage_desc* d, Shape* s) {
   s->fuse_act = fusable && !d->recompute && (s->f % 128) == 0 && gemm_bf16_fused_applies(EPI_SWIGLU, s->tokens, s->up_w, s->h, s->h, 0);
   const bool gpt = s->family == OPTSTAGE_GPT;
   auto act = [&](int epi) {
-    return !d->no_fusion && (s->dtype == OPTSTAGE_BF16 ? gemm_bf16_act_applies(epi, s->tokens, s->f, s->h) : gemm_f32_act_applies(s->tokens, s->f, s->h)) ? epi : (int)EPI_STORE;
+    return !d->no_fusion && (s->dtype == OPTSTAGE_BF16 ? gemm_bf16_act_applies(s->tokens, s->f, s->h) : gemm_f32_act_applies(s->tokens, s->f, s->h)) ? epi : (int)EPI_STORE;
   };
   s->epi_up = gpt && !d->recompute ? act(EPI_GELU) : (int)EPI_STORE;
   s->epi_da = act(gpt ? EPI_DGELU : EPI_DSWIGLU);

@@ -45,6 +45,20 @@ def test_matrix_unit_attention_takes_what_its_grid_and_offsets_reach():
     assert takes(128, 4096, 32, 8) and not takes(128, 4096, 32, 8, 4098) and not takes(64, 4096, 32, 8, 4104) and not takes(96, 4096, 32, 8)
 
 
+def test_activation_epilogues_leave_weights_in_slabs_alone():
+    """gemm_bf16_act_applies(M, N, K) chooses the activation's epilogue, which reads a plain weight, gemm_bf16_slab_applies(M, N, K, lda) keeps the
+    weight in slabs: never both.  At hidden 8192 the two reach their 32-bit limits one ffn apart (959 row tiles)."""
+    lib = ctypes.CDLL(B.LIB_PATH)
+    act, slab = lib["_Z21gemm_bf16_act_appliesiii"], lib["_Z22gemm_bf16_slab_appliesiiii"]
+    for f in (act, slab):
+        f.restype = ctypes.c_bool
+    assert act(320, 1792, 1024) and not slab(320, 1792, 1024, 1024) and slab(4096, 11008, 4096, 4096)
+    assert slab(4096, 245504, 8192, 8192) and not slab(4096, 245512, 8192, 8192)
+    rng = random.Random(3)
+    sizes = [(4096, n, 8192) for n in range(245248, 245768, 8)] + [(int(2 ** rng.uniform(0, 17)), 8 * int(2 ** rng.uniform(3, 16)), 64 * int(2 ** rng.uniform(0, 7))) for _ in range(3000)]
+    assert not any(act(*s) and slab(*s, s[2]) for s in sizes)
+
+
 def oracle_table(cfg):
     return S.memory_table(cfg.family, cfg.hidden, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.ffn,
                           cfg.seq * cfg.micro_batch, cfg.elem_size)
