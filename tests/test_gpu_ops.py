@@ -170,6 +170,24 @@ def test_gemm_fp32_tiles_of_every_size(M, N, K, pad):
         del ops
 
 
+# Operands that are the leading rows of larger tensors, NaN behind them as far as any prefetch goes: TN contractions whose last step of 16 and
+# whose loads ahead lie past the operand (up to 576 rows), NT rows past it, on every tile shape.
+@pytest.mark.parametrize("M,N,K", [(1000, 1004, 1001), (508, 1020, 1037), (1020, 252, 133), (124, 764, 259), (60, 44, 1027), (20, 36, 13), (64, 64, 1), (1004, 1000, 17)])
+def test_gemm_fp32_reads_nothing_behind_its_operands(M, N, K):
+    a, w = q(RNG.standard_normal((K, M)), FP32), q(RNG.standard_normal((K, N)), FP32)
+    ref, bound = a.T @ w, (K + 1) * 2.0 ** -24 * (np.abs(a).T @ np.abs(w))
+    for layout, x, y in ((B.GEMM_TN, a, w), (B.GEMM_NT, a.T, w.T)):
+        ops = []
+        for part in (x, y):
+            t = torch.full((part.shape[0] + 640, part.shape[1]), float("nan"), dtype=torch.float32, device="cuda")
+            t[:part.shape[0]] = dev(part, FP32)
+            ops.append(t)
+        C = torch.full((M, N), 3.0, dtype=torch.float32, device="cuda")
+        ok(lib().optstage_op_gemm(FP32, layout, 3, ops[0].data_ptr(), ops[1].data_ptr(), C.data_ptr(), 0, M, N, K, ops[0].shape[1], ops[1].shape[1], N, stream()))
+        torch.cuda.synchronize()
+        assert np.all(np.abs(host(C) - ref) <= bound), layout
+
+
 def test_gemm_with_rows_further_apart_than_a_tile_can_address():
     """Leading dimensions of 2^23 elements: the kernel that stages its tiles through registers."""
     ld, n, k = 1 << 23, 16, 72
@@ -662,14 +680,15 @@ def attention_by_rows(qkv, do, seq, nq, nkv, d):
 
 # A value that is not finite stays with the rows that depend on it: a later token's with the later rows (forward, dQ), an earlier
 # one's with the earlier keys (dK, dV).  The poisoned token sits inside a tile of 16 and of 32 rows, and at the end of a cut
-# one, whose last row stands in for the rows past it.  Infinity and NaN themselves only have to be where the reference has either.
-@pytest.mark.parametrize("dtype,d", [(BF16, 64), (FP32, 64), (FP32, 128)])
+# one, whose last row stands in for the rows past it; 300 tokens are divided over two groups of waves (bf16), of which either may have
+# it.  Infinity and NaN themselves only have to be where the reference has either.
+@pytest.mark.parametrize("dtype,d,seq", [(BF16, 64, 75), (BF16, 64, 300), (FP32, 64, 75), (FP32, 128, 75)])
 @pytest.mark.parametrize("what", ["q", "k", "v", "do"])
-def test_attention_keeps_what_is_not_finite_to_the_rows_that_depend_on_it(dtype, d, what):
-    seq, nq, nkv = 75, 2, 1
+def test_attention_keeps_what_is_not_finite_to_the_rows_that_depend_on_it(dtype, d, seq, what):
+    nq, nkv = 2, 1
     w, tol = (nq + 2 * nkv) * d, {BF16: 2.0 ** -7, FP32: 1e-5}[dtype]
     clean, do0 = q(RNG.standard_normal((seq, w)), dtype), q(RNG.standard_normal((seq, nq * d)), dtype)
-    for row, value in ((36, np.inf), (36, np.nan), (seq - 1, np.inf)):
+    for row, value in ((36, np.inf), (36, np.nan), (seq - 1, np.inf), (seq // 2 - 5, np.inf)):
         qkv, do = clean.copy(), do0.copy()
         if what == "do":
             do[row, 5] = value
