@@ -757,28 +757,36 @@ def _grouped(base, name, hidden, n_q, n_kv, ffn, seq, n_layers):
 
 
 # Weight-gradient products of a W op in grouped launches of up to 16.  bf16: token counts that are no multiple of 64, 136 tiles of 256
-# (one layer) and 272, whose last round of 16 is cut off.  fp32: the tile that a set picks (estimated time: rounds of 256
-# workgroups times 2.3 / 3.8, 7.8 and 21 for tiles of 16 (up to 256 / more), 32 and 64), edges that are no multiple of it next to the
-# next product's first tile, 20 products in two launches.
+# (one layer) and 272, whose last round of 16 is cut off.  fp32: the tile that a set picks (estimated us: start, and ns per token
+# of a compute unit's only workgroup or of each of several), edges that are no multiple of it next to the next product's first tile, 20
+# products in two launches on different tiles, token counts that are no multiple of a step of 16.
+FP32_TILES = {(64, 64): (3.8, 15.3, 15.7), (64, 32): (3.2, 8.8, 9.3), (32, 32): (2.75, 5.0, 5.2), (16, 32): (2.6, 3.0, 3.8), (16, 16): (2.6, 2.0, 2.35)}
+
+
 @pytest.mark.parametrize("cfg,tiles", [(_grouped(CFG.CFG4, "one_token", 1024, 8, 2, 2048, 1, 1), [256]), (_grouped(CFG.CFG4, "tokens_63", 1024, 8, 2, 2048, 63, 1), [256]),
                                        (_grouped(CFG.CFG4, "tokens_65_cut", 1024, 8, 2, 2048, 65, 2), [256]),
                                        (_grouped(CFG.CFG4, "tokens_200_cut", 1024, 8, 2, 2048, 200, 2), [256]),
-                                       (_grouped(CFG.CFG1, "fp32_16", 64, 1, 1, 100, 38, 1), [16]),
-                                       (_grouped(CFG.CFG1, "fp32_32_and_16", 64, 1, 1, 132, 38, 5), [32, 16]),
-                                       (_grouped(CFG.CFG1, "fp32_32", 132, 2, 1, 260, 45, 1), [32]),
-                                       (_grouped(CFG.CFG1, "fp32_64", 260, 4, 2, 1028, 51, 2), [64])], ids=lambda c: getattr(c, "name", ""))
+                                       (_grouped(CFG.CFG1, "fp32_16", 64, 1, 1, 100, 38, 1), [(16, 16)]),
+                                       (_grouped(CFG.CFG1, "fp32_16_of_20_products", 64, 1, 1, 132, 38, 5), [(16, 16), (16, 16)]),
+                                       (_grouped(CFG.CFG1, "fp32_32_and_16", 64, 1, 1, 132, 206, 5), [(32, 32), (16, 16)]),
+                                       (_grouped(CFG.CFG1, "fp32_16x32", 132, 2, 1, 516, 45, 1), [(16, 32)]),
+                                       (_grouped(CFG.CFG1, "fp32_32", 260, 4, 2, 1028, 51, 2), [(32, 32)]),
+                                       (_grouped(CFG.CFG1, "fp32_64x32", 516, 4, 2, 260, 77, 4), [(64, 32)]),
+                                       (_grouped(CFG.CFG1, "fp32_64", 516, 2, 1, 1540, 77, 2), [(64, 64)])], ids=lambda c: getattr(c, "name", ""))
 def test_grouped_weight_gradients(cfg, tiles):
     ws = T.stage_weights(cfg)
     h, f, q = cfg.hidden, cfg.ffn, cfg.n_q_heads * cfg.head_dim
     up = 2 * f if cfg.family == O.LLAMA else f
     products = [(h, f), (up, h), (h, q), (q + 2 * cfg.n_kv_heads * cfg.head_dim, h)] * cfg.n_layers
-    count = lambda group, r: sum(-(-a // r) * -(-b // r) for a, b in group)  # noqa: E731
+    count = lambda group, r, c: sum(-(-a // r) * -(-b // c) for a, b in group)  # noqa: E731
     groups = [products[i:i + 16] for i in range(0, len(products), 16)]
     if cfg.dtype == CFG.BF16:
-        assert len(groups) == 1 and count(products, 256) == 136 * cfg.n_layers and cfg.seq % 64
+        assert len(groups) == 1 and count(products, 256, 256) == 136 * cfg.n_layers and cfg.seq % 64
     else:
-        cost = lambda group, r: -(-count(group, r) // 256) * {64: 21.0, 32: 7.8, 16: 2.3 if count(group, 16) <= 256 else 3.8}[r]  # noqa: E731
-        assert [min((64, 32, 16), key=lambda r, g=g: cost(g, r)) for g in groups] == tiles
+        def cost(group, tile):
+            n, (start, only, each) = count(group, *tile), FP32_TILES[tile]
+            return start + 1e-3 * cfg.seq * (only if n <= 256 else -(-n // 256) * each)
+        assert [min(FP32_TILES, key=lambda tile, g=g: cost(g, tile)) for g in groups] == tiles
     events = [("F", 0), ("F", 1), ("B", 0), ("W", 0), ("B", 1), ("W", 1)]
     ref, runs = oracle_run(cfg, ws), []
     for overwrite in (False, True):
@@ -790,6 +798,7 @@ def test_grouped_weight_gradients(cfg, tiles):
             for g in st.grads:
                 for v in g.values():
                     v.fill_(float("nan"))
+        st.arena.fill_(255)                                      # NaN behind every operand that is not followed by another
         B.check(B.lib().optstage_set_kernel_timing(st.h, 1))
         st.run(events)
         st.synchronize()
@@ -957,54 +966,105 @@ def test_every_forward_kind_survives_offload_and_reload():
     ref.close()
 
 
-# one workgroup per kv head and several (split partials), one 32-row tile per wave and two (more than 320 wide workgroups), ragged rows, the
-# general kernels (a few tokens), both families and both types
+# Every division of the rows that the gradient in place is served by, W = heads x sequences x blocks of 128 rows: (waves, groups) of dQ / (key
+# tiles, groups) of dK / dV; ragged rows, both families and both types; the general kernels (a few tokens), which keep the slot's copy
 @pytest.mark.parametrize("family,dtype,n_q,n_kv,d,seq,mb", [
-    (0, 1, 4, 4, 128, 129, 1), (1, 1, 8, 2, 128, 257, 2), (0, 1, 36, 36, 128, 2305, 1), (1, 1, 36, 36, 128, 2305, 1), (0, 1, 4, 2, 64, 191, 2), (1, 1, 4, 4, 64, 65, 1),
+    (0, 1, 4, 4, 128, 129, 1), (1, 1, 4, 4, 128, 150, 2),                       # (2, 1) / (1, 1)
+    (1, 1, 24, 24, 128, 900, 2),                                                # (2, 1) / (1, 2), W 384
+    (0, 1, 2, 2, 128, 705, 1), (1, 1, 8, 2, 128, 257, 2),                       # (2, 2) / (1, 2), the second with split partials
+    (0, 1, 14, 14, 128, 2600, 1), (1, 1, 14, 14, 128, 2600, 1),                 # (4, 2) / (1, 2), W 294
+    (0, 1, 36, 36, 128, 2305, 1), (1, 1, 22, 22, 128, 1990, 2),                 # (8, 1) / (1, 2), W 684 and 704
+    (0, 1, 30, 30, 128, 1990, 2), (1, 1, 30, 30, 128, 1990, 2),                 # (8, 1) / (2, 1), W 960
+    (1, 1, 32, 4, 128, 1990, 2),                                                # the same with split partials, W 1024
+    (1, 1, 4, 4, 64, 65, 1),                                                    # heads of 64: (2, 1) / (1, 1)
+    (0, 1, 4, 2, 64, 191, 2), (1, 1, 4, 2, 64, 191, 2),                         # (2, 2) / (1, 2)
+    (0, 1, 32, 32, 64, 520, 4), (1, 1, 32, 32, 64, 520, 4),                     # (4, 1) / (1, 1), W 640
     (1, 0, 4, 2, 64, 33, 2), (0, 0, 2, 2, 128, 17, 1), (1, 0, 2, 2, 128, 47, 1), (1, 0, 2, 2, 64, 4, 1), (0, 1, 2, 2, 64, 5, 3)])
 def test_attention_gradient_takes_its_operands_place(family, dtype, n_q, n_kv, d, seq, mb):
     """After B the QKV slot holds the attention gradient that the single-kernel call gives for the same operands: bit for bit
     without rotary, and turned back by the rotary angle with one rounding more on the side of the two separate kernels."""
-    cfg = replace(CFG.shrunken(CFG.CFG2 if family else CFG.CFG1, hidden=256, n_q=n_q, n_kv=n_kv, ffn=512, seq=seq, n_layers=1, n_microbatches=1,
+    got, dqkv = gradient_slot(family, dtype, n_q, n_kv, d, seq, mb, None)
+    if family == 0:
+        assert torch.equal(got, dqkv)
+    else:
+        n_rot = (n_q + n_kv) * d
+        ref, bound = turned_back(dqkv[:, :n_rot], d, seq)
+        assert torch.equal(got[:, n_rot:], dqkv[:, n_rot:])
+        assert bool(((got[:, :n_rot].double() - ref).abs() <= bound).all())
+
+
+# one group of waves and two (bf16, from 110 tokens on), a workgroup per kv head and per two query heads, the poisoned token in either half of a
+# block of 64
+@pytest.mark.parametrize("family,dtype,n_q,n_kv,d,seq,row", [(0, 0, 2, 1, 64, 75, 36), (1, 0, 2, 2, 64, 75, 36), (1, 0, 2, 1, 128, 75, 36), (0, 1, 2, 2, 64, 75, 36),
+                                                             (1, 1, 2, 1, 64, 75, 36), (0, 1, 2, 2, 64, 300, 150), (1, 1, 2, 1, 64, 300, 110), (1, 1, 2, 2, 64, 300, 150)])
+@pytest.mark.parametrize("what", ["x", "dy"])
+def test_attention_gradient_in_place_keeps_what_is_not_finite_to_its_rows(family, dtype, n_q, n_kv, d, seq, row, what):
+    """A token of x that is not finite makes NaN of its Q, K and V rows: dQ of the tokens before it stays finite.  One of dy: dQ of all others does,
+    dK and dV of the keys behind it.  Those rows are redone one by one, in place and rotated, and agree with the single-kernel call's."""
+    got, dqkv = gradient_slot(family, dtype, n_q, n_kv, d, seq, 1, (what, row))
+    n_rot, token = (n_q + n_kv) * d, torch.arange(seq, device="cuda")
+    fine = torch.empty_like(got, dtype=torch.bool)
+    fine[:, :n_q * d] = (token < row if what == "x" else token != row)[:, None]
+    fine[:, n_q * d:] = (token < 0 if what == "x" else token > row)[:, None]
+    assert torch.equal(torch.isfinite(dqkv), fine) and torch.equal(torch.isfinite(got), fine)
+    if family:
+        ref, bound = turned_back(dqkv[:, :n_rot], d, seq)
+        assert bool(((got[:, :n_rot].double() - ref).abs() <= bound)[fine[:, :n_rot]].all())
+        got, dqkv, fine = got[:, n_rot:], dqkv[:, n_rot:], fine[:, n_rot:]
+    assert torch.equal(got[fine], dqkv[fine])
+
+
+def gradient_slot(family, dtype, n_q, n_kv, d, seq, mb, poison):
+    """The QKV slot after B of a one-layer stage, and what the single-kernel call gives for the same operands.  poison: ("x" or "dy", token)
+    or None."""
+    hidden = 264                       # no multiple of 64: no product keeps its weight in slabs or takes rotary into its epilogue
+    cfg = replace(CFG.shrunken(CFG.CFG2 if family else CFG.CFG1, hidden=hidden, n_q=n_q, n_kv=n_kv, ffn=512, seq=seq, n_layers=1, n_microbatches=1,
                                dtype=dtype), head_dim=d, micro_batch=mb)
     tdt, rows = (torch.float32, torch.bfloat16)[dtype], seq * mb
-    ws = T.stage_weights(cfg)
+    ws, io = T.stage_weights(cfg), {"x": T.stage_input(cfg, 0).copy(), "dy": T.output_grad(cfg, 0).copy()}
+    if poison:
+        io[poison[0]][poison[1], 5] = np.inf
     st = Stage(cfg)
     st.set_weights(ws)
-    st.bind(0, T.stage_input(cfg, 0), T.output_grad(cfg, 0))
+    st.bind(0, io["x"], io["dy"])
+    B.check(B.lib().optstage_set_kernel_timing(st.h, 1))
     dev = lambda kind, dt, *shape: torch.from_numpy(st.read(0, 0, kind).copy()).view(dt)[:int(np.prod(shape))].reshape(shape).cuda()  # noqa: E731
     st.run([("F", 0)])
     st.synchronize()
     width = (n_q + 2 * n_kv) * d
     qkv, o, lse = dev("QKV", tdt, rows, width), dev("O", tdt, rows, n_q * d), dev("LSE", torch.float32, mb, n_q, seq)
-    assert torch.equal(dev("X_IN", tdt, rows, 256), st.x[0])
+    assert torch.equal(dev("X_IN", tdt, rows, hidden), st.x[0])
     st.run([("B", 0)])
     st.synchronize()
-    assert torch.equal(dev("DY", tdt, rows, 256), st.dy[0])
-    dx_mid, got = dev("DX_MID", tdt, rows, 256), dev("QKV", tdt, rows, width)
+    assert torch.equal(dev("DY", tdt, rows, hidden), st.dy[0])
+    # F's rotary pass, and B's where the gradient was not turned in place
+    assert st.stats().kernel_launches[B.KERNEL_CLASSES.index("rope")] == family * (1 if seq > 5 else 2)
+    dx_mid, got = dev("DX_MID", tdt, rows, hidden), dev("QKV", tdt, rows, width)
     lib, p, s = B.lib(), lambda t: t.data_ptr(), torch.cuda.current_stream().cuda_stream  # noqa: E731
     wt = st.weights[0]["wo"].t().contiguous()
     dout, dqkv = torch.empty_like(o), torch.empty_like(qkv)
     scratch = torch.empty(max(1, lib.optstage_op_attn_bwd_ws_floats(seq, mb, n_q, n_kv, d)), dtype=torch.float32, device="cuda")
-    B.check(lib.optstage_op_gemm(dtype, B.GEMM_NT, B.EPI_STORE, p(dx_mid), p(wt), p(dout), 0, rows, n_q * d, 256, 256, 256, n_q * d, s))
+    B.check(lib.optstage_op_gemm(dtype, B.GEMM_NT, B.EPI_STORE, p(dx_mid), p(wt), p(dout), 0, rows, n_q * d, hidden, hidden, hidden, n_q * d, s))
     B.check(lib.optstage_op_attn_bwd(dtype, p(qkv), p(o), p(dout), p(lse), p(dqkv), p(scratch), seq, mb, n_q, n_kv, d, s))
-    if family == 0:
-        assert torch.equal(got, dqkv)
-    else:
-        n_rot = (n_q + n_kv) * d
-        assert torch.equal(got[:, n_rot:], dqkv[:, n_rot:])
-        heads = dqkv[:, :n_rot].double().reshape(rows, -1, d)
-        pos = (torch.arange(rows, device="cuda") % seq).double()
-        ang = pos[:, None] * cfg.rope_base ** (-2.0 * torch.arange(d // 2, device="cuda").double() / d)[None, :]
-        cos, sin = ang.cos()[:, None, :], ang.sin()[:, None, :]
-        lo, hi = heads[..., :d // 2], heads[..., d // 2:]
-        ref = torch.cat((lo * cos + hi * sin, hi * cos - lo * sin), dim=-1).reshape(rows, n_rot)
-        # per element: the rounding of the two operands and of the result (half an ulp, 2^-9 in bf16, each of the pair's magnitude),
-        # in fp32 the four operations and the table's rounding as well
-        size = torch.maximum(lo.abs(), hi.abs()).repeat(1, 1, 2).reshape(rows, n_rot)
-        bound = (2.0 ** -9 * 3 if dtype else 2.0 ** -24 * 12) * 1.5 * size + 1e-30
-        assert bool(((got[:, :n_rot].double() - ref).abs() <= bound).all())
+    torch.cuda.synchronize()
     st.close()
+    return got, dqkv
+
+
+def turned_back(heads, d, seq, rope_base=CFG.CFG2.rope_base):
+    """The q and k head columns of a gradient turned back by the rotary angle, in fp64, and how far the kernels' may be from it, per
+    element.  bf16: the two operands here are rounded, by up to 2^-8 of their magnitude (half an ulp just above a power of two), which the
+    rotation passes on with cos and sin, together at most sqrt(2) times that of the larger one; the result, at most sqrt(2) times the larger
+    one, is rounded too.  fp32: the same, the four operations and the table's rounding."""
+    rows, n_rot = heads.shape
+    x = heads.double().reshape(rows, -1, d)
+    pos = (torch.arange(rows, device="cuda") % seq).double()
+    ang = pos[:, None] * rope_base ** (-2.0 * torch.arange(d // 2, device="cuda").double() / d)[None, :]
+    cos, sin = ang.cos()[:, None, :], ang.sin()[:, None, :]
+    lo, hi = x[..., :d // 2], x[..., d // 2:]
+    ref = torch.cat((lo * cos + hi * sin, hi * cos - lo * sin), dim=-1).reshape(rows, n_rot)
+    size = torch.maximum(lo.abs(), hi.abs()).repeat(1, 1, 2).reshape(rows, n_rot)
+    return ref, (2.0 ** -8 * 2.9 if heads.dtype == torch.bfloat16 else 2.0 ** -24 * 18) * size + 1e-30
 
 
 # transfers below and above the size up to which one kernel moves all kinds of an item; an odd number of tokens, whose statistics are no
