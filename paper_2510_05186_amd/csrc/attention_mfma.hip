@@ -603,7 +603,7 @@ __global__ __launch_bounds__(64 * NW * NG) void attn_bwd_dq_mfma(const bf16_t* q
   };
   const i32x4_t rs = make_desc(base, (unsigned)seq * ld * 2u);
   const unsigned k_off = (unsigned)(n_q + kvh) * D * 2u, v_off = (unsigned)(n_q + n_kv + kvh) * D * 2u;
-  // All offsets go through the lane offset, which is what the range check sees: rows at or past seq read zero.
+  // All offsets are the lane's (the range check would count a scalar one too): rows at or past seq read zero.
   auto issue_block = [&](int kb, int stage) {
     const unsigned rowoff = (unsigned)(64 * kb) * (unsigned)ld * 2u;
     const unsigned dst = lds0 + stage * DQ_STAGE + (WROWS * id) * ROWB;
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(256 * NG) void attn_bwd_dkv_mfma(const bf16_t* qkv,
   const int rep = n_q / n_kv / split;                          // query heads of the group handled here
   const int qb0 = k0 / 64, nqb = (seq + 63) / 64 - qb0;       // query blocks at or after the first key
   const int iters = rep * nqb;
-  // All offsets go through the lane offset, which is what the range check sees: rows at or past seq read zero.
+  // All offsets are the lane's (the range check would count a scalar one too): rows at or past seq read zero.
   auto issue_block = [&](int it, int stage) {
     const int a = (kvh * split + part) * rep + it / nqb;
     const int r0 = 64 * (qb0 + it % nqb);

@@ -70,7 +70,8 @@ template <int R, bool TNL, bool VEC> struct Operand {
     // operand of MFMA e (k-set e) of tile i
     __device__ __forceinline__ float get(int i, int e) const { return TNL ? v[e][i] : v[i][e]; }
   };
-  // TN, 16-byte rows: k-set e of the step at k.  k-rows past K lie past the operand and read as zero.
+  // TN, 16-byte rows: k-set e of the step at k.  k-rows past K lie past the operand and read as zero: the range check adds the scalar offset to the
+  // lane's, also where the scalar one is past the end by itself.
   __device__ __forceinline__ void load_k(Frag& f, int k, int e) const {
     const unsigned at = (unsigned)(k + 4 * e) * kstep;
     if constexpr (T == 4) f.v[e] = __builtin_bit_cast(typename Frag::vec_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[0], at, 0));

@@ -141,7 +141,7 @@ def test_gemm_fp32_tile_shapes_and_remainders(M, N, K):
 # Bound: K + 1 roundings of 2^-24 on sums of magnitudes.
 @pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (16, 16, 4, 0), (17, 20, 15, 3), (130, 36, 68, 4), (200, 500, 200, 0), (201, 499, 77, 1),
                                        (1000, 1100, 132, 0), (1001, 1023, 67, 2), (8, 8, 16, 1 << 24),
-                                       # short contractions of many tiles (the plain kernel) and the first past each limit, 16-byte rows and others
+                                       # contractions of a few steps on many tiles, 16-byte rows and others
                                        (2048, 2040, 32, 0), (2048, 2040, 36, 0), (4052, 2048, 76, 0), (4052, 2048, 80, 0), (1760, 1262, 60, 0),
                                        (1760, 1262, 61, 0), (1760, 1262, 64, 0), (1760, 1262, 130, 0), (1760, 1262, 131, 0), (1001, 1023, 20, 0), (1001, 1023, 33, 0),
                                        (301, 499, 16, 0), (301, 499, 17, 0)])
@@ -479,10 +479,10 @@ def test_attention_fwd_bwd(dtype, seq, batch, nq, nkv, d):
             assert rel_err(dq_g[sl, lo:hi], ref[:, lo:hi]) < TOL[dtype], (lo, hi)
 
 
-# Both tile counts of the kernels for heads of 128: one 32-row tile per wave while there is at most a workgroup of 256 rows per
-# compute unit, two above; ragged ends, grouped heads (partials of several workgroups per kv head), several sequences.
+# Heads of 128 from a workgroup or two to several per compute unit: ragged ends, grouped heads (partials of several workgroups per kv
+# head), several sequences.
 @pytest.mark.parametrize("seq,batch,nq,nkv", [(127, 1, 2, 2), (129, 2, 4, 1), (257, 1, 256, 256), (257, 1, 64, 8), (33, 5, 64, 64), (257, 3, 128, 128)])
-def test_attention_with_one_and_two_tiles_per_wave(seq, batch, nq, nkv):
+def test_attention_of_few_and_of_many_workgroups(seq, batch, nq, nkv):
     d, rows, w = 128, seq * batch, (nq + 2 * nkv) * 128
     g = torch.Generator(device="cuda")
     g.manual_seed(seq)
