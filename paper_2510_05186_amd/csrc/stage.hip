@@ -794,9 +794,12 @@ optstage_status exec_backward_weight(optstage* st, int j, int c, const OpBufs& o
 
 // Transfer of an event's kinds between the arena and the pinned pool: small ones in one kernel, large ones in a copy call per kind.
 // A call costs 14 us beside its bytes' time on the link; the kernel holds compute units that the compute stream's products
-// then wait for.  Two layers, five micro-batches, three kinds of every item moved, one event's MB and us per iteration, calls /
-// kernel: .3 1869 / 1595, .6 2181 / 2004, 1.0 2360 / 2291, 1.3 2448 / 2467, 2.8 3115 / 3298, 109 56230 / 68431.
-constexpr uint64_t COPY_KERNEL_MAX = 1 << 20;
+// then wait for, and that grows with the bytes.  So the limit goes by the number of calls saved.  us per iteration of a Llama stage of hidden 1024,
+// calls / kernel: one kind, KB 32 2569 / 2472, 128 2828 / 2764, 256 3013 / 3034, 512 3248 / 3404, 1024 3694 / 3994; two kinds, KB 256 2941 / 2859, 512 3196 /
+// 3193, 1024 3436 / 3644; three, KB 384 3000 / 2868, 768 3237 / 3272 (two layers, 770 2148 / 2064), 1001 3277 / 3358 (2236 / 2190); five, KB 640 3193 / 2991.
+// Two layers, five micro-batches, three kinds, MB 1.3 2448 / 2467, 2.8 3115 / 3298, 109 56230 / 68431.  Beside products that fill the chip neither is the
+// faster one (LSE and STATS, .6 MB, of hidden 4096, 4096 tokens 36657 / 36584; LSE, 1 MB, of hidden 8192 66295 / 66299).
+uint64_t copy_kernel_limit(int kinds) { return std::min<uint64_t>((uint64_t)kinds << 18, 1 << 20); }
 optstage_status transfer(optstage* st, const optstage_event& ev, const OpBufs& ob, hipStream_t s) {
   const bool out = ev.op == OPTSTAGE_O;
   uint64_t total = 0;
@@ -812,7 +815,7 @@ optstage_status transfer(optstage* st, const optstage_event& ev, const OpBufs& o
       total += st->raw[k];
     }
   (out ? st->stats.bytes_offloaded : st->stats.bytes_reloaded) += total;
-  if (st->pool_dev && total <= COPY_KERNEL_MAX) {
+  if (st->pool_dev && total <= copy_kernel_limit(list.n)) {
     HIP_TRY(launch_copy_list(list, s));
     return OPTSTAGE_OK;
   }

@@ -1067,10 +1067,10 @@ def turned_back(heads, d, seq, rope_base=CFG.CFG2.rope_base):
     return ref, (2.0 ** -8 * 2.9 if heads.dtype == torch.bfloat16 else 2.0 ** -24 * 18) * size + 1e-30
 
 
-# transfers below and above the size up to which one kernel moves all kinds of an item; an odd number of tokens, whose statistics are no
+# transfers below and above the size up to which one kernel moves all kinds of an item (401 tokens: of some items and not of others); an odd number of tokens, whose statistics are no
 # multiple of 16 bytes; the reloads on the offloads' channel and on one of their own
 @pytest.mark.parametrize("duplex", [False, True])
-@pytest.mark.parametrize("seq,hidden", [(101, 256), (640, 512)])
+@pytest.mark.parametrize("seq,hidden", [(101, 256), (401, 256), (640, 512)])
 def test_reloads_arrive_before_the_kernels_that_read_them(duplex, seq, hidden):
     """The whole list enqueued at once, reloads right before their B in ascending layer order (the channel takes them from the last
     layer down), each layer's kinds such that B's wait comes at another kernel: results bitwise those without transfers."""
