@@ -95,12 +95,17 @@ typedef struct {
                                            chunk c is layers c * n_layers / n_chunks onwards.  Every chunk has its
                                            own F / B / W per micro-batch and its own boundary tensors; arena,
                                            budget and transfer channel are shared */
-  uint32_t no_fusion;                   /* 0: where the shapes allow it (bf16 LLAMA, head_dim 128, ffn % 128 == 0, products
-                                           large enough for the direct GEMM kernel) the rotary embedding runs in the
-                                           epilogue of the QKV projection and the MLP activation in the epilogue of the
-                                           gate / up projection, each from the fp32 accumulators (one rounding to the
-                                           storage type less than the separate kernels; the stored kinds and their
-                                           bytes are the same).  1: always the separate kernels */
+  uint32_t no_fusion;                   /* 0: where the shapes allow it, pointwise work runs in a kernel that holds its operand:
+                                           - large products (bf16 LLAMA on the direct GEMM kernel; head_dim 128 / ffn % 128 ==
+                                             0): rotary in the epilogue of the QKV projection, SwiGLU in that of the
+                                             gate / up projection (not with recompute), each from the fp32 accumulators:
+                                             one rounding to the storage type less than the separate kernels;
+                                           - small products (bf16 on the small-tile kernels, fp32; both families): GELU in
+                                             the epilogue of the up projection (not with recompute), the gradient of GELU
+                                             or SwiGLU in that of da = dy W_d: bit for bit the separate kernels' results;
+                                           - LLAMA, where rotary is not in the QKV projection's epilogue: rotary backward in
+                                             the attention gradient, in fp32 ahead of its one rounding: one rounding less.
+                                           The stored kinds and their bytes are the same.  1: always the separate kernels */
   uint32_t reserved;                    /* 0 */
   uint64_t hbm_budget_bytes;            /* M_limit_i for activations (Eq. 7); 0 = unlimited */
   void* arena; uint64_t arena_bytes;          /* DEVICE block for activations, 256-byte aligned */
@@ -124,12 +129,13 @@ typedef struct {
 } optstage_event;
 
 typedef enum {
-  OPTSTAGE_KC_GEMM_NT_STORE = 0 /* the four dX products of B (C = A B^T, plain store) */,
+  OPTSTAGE_KC_GEMM_NT_STORE = 0 /* the four dX products of B (C = A B^T; da with the activation's gradient when fused) */,
   OPTSTAGE_KC_GEMM_NT_RESID = 1 /* output and down projection, residual added */, OPTSTAGE_KC_GEMM_TN_ACCUM = 2,
   OPTSTAGE_KC_ATTN_FWD = 3, OPTSTAGE_KC_ATTN_BWD = 4, OPTSTAGE_KC_NORM_FWD = 5, OPTSTAGE_KC_NORM_BWD = 6,
   OPTSTAGE_KC_ACT_FWD = 7, OPTSTAGE_KC_ACT_BWD = 8, OPTSTAGE_KC_ROPE = 9,
   OPTSTAGE_KC_GEMM_NT_QKV = 10 /* QKV projection (rotary in its epilogue when fused) */,
   OPTSTAGE_KC_GEMM_NT_GU = 11 /* gate / up projection (activation in its epilogue when fused) */,
+  /* what runs in another kernel counts no launch, time or work in ACT_FWD, ACT_BWD or ROPE */
   OPTSTAGE_N_KERNEL_CLASSES = 12
 } optstage_kernel_class;
 
@@ -145,7 +151,8 @@ typedef struct {
   /* per kernel class, filled only while kernel timing is on (optstage_set_kernel_timing): launches,
    * summed device time, and summed algorithmic work (flops for the GEMM / attention classes 0-4, 10, 11: 2*M*N*K, causal
    * attention 2*s^2*n_q*d forward and 5*s^2*n_q*d backward; bytes for the elementwise classes: norm
-   * forward 2e per element, norm backward 4e, activation forward 3e per output element, backward 5e,
+   * forward 2e per element, norm backward 4e (one e more in the first norm of F and the last layer's second norm of B,
+   * which also store X_IN / DY), activation forward 3e per output element (GELU 2e), backward 5e (3e),
    * rotary 2e over the q and k heads; e = element size) */
   uint64_t kernel_launches[OPTSTAGE_N_KERNEL_CLASSES];
   double kernel_ms[OPTSTAGE_N_KERNEL_CLASSES];
@@ -163,7 +170,8 @@ typedef struct {
 
 /* One executed event: what was enqueued, the live activation bytes after it (list-order accounting), and, once
  * optstage_synchronize() has returned, its device times in ms since the first event after the last reset: F, B, W
- * on the compute stream, O and R on their transfer stream; -1 for OWAIT, which takes no time of its own.
+ * on the compute stream, O and R on their transfer stream (start as for ms_ops); -1 for OWAIT, which takes no time of
+ * its own.
  * stall_ms: how long the compute stream waited at this event (OWAIT: for the offload; B: for the reloads, within its
  * start and end). */
 typedef struct {
@@ -227,7 +235,8 @@ optstage_status optstage_synchronize(optstage_t* st);
  * cleared).  Requires that nothing is in flight (call after optstage_synchronize). */
 optstage_status optstage_reset(optstage_t* st);
 optstage_status optstage_get_stats(optstage_t* st, optstage_stats* out /* HOST */);
-/* The executed trace since the last reset, in enqueue order: copies min(capacity, total) entries to out (HOST,
+/* The executed trace since the last reset, in list order (reloads of one micro-batch that follow each other in a list run
+ * last layer first, as B needs them, and their times say so): copies min(capacity, total) entries to out (HOST,
  * may be null when capacity is 0) and writes the total to *n_total (may be null). */
 optstage_status optstage_get_trace(optstage_t* st, optstage_trace_entry* out /* HOST */, size_t capacity,
                                    size_t* n_total);
