@@ -599,9 +599,9 @@ optstage_status k_attn_bwd(optstage* st, const void* qkv, const void* o, const v
 // Attention backward into the QKV slot, rotary backward included: the gradient takes qkv's place (the executor's table has one slot for
 // both).  `scratch` is a packed [tokens, qkv] transient.  Where the tile kernels serve the call they write the slot themselves,
 // rotated, and keep Q in the scratch meanwhile: no pass over the gradient follows.  Otherwise it goes to the scratch and a kernel moves
-// it into the slot (rotary, or a plain copy for the family without).  Layers of the size that takes rotary into the QKV
-// projection's epilogue keep the rotary kernel here: their per-class kernel timing counts its launches, and it is .4 % of such a
-// layer (4096 tokens, hidden 4096, two micro-batches 8865 us: 35 us); one of hidden 1024 and 320 tokens, where the launch is most of it, 1.5 %.
+// it into the slot (rotary, or a plain copy for the family without).  Layers whose size takes rotary into the QKV projection's
+// epilogue keep the rotary kernel here: it is .4 % of such a layer (4096 tokens, hidden 4096, two micro-batches 8865 us: 35 us) against 1.5 %
+// of one of hidden 1024 and 320 tokens, where the launch is most of it; the gradient in place has not been timed on them.
 optstage_status k_attn_bwd_slot(optstage* st, void* qkv, const void* o, const void* dout, const float* lse, void* scratch) {
   const Shape& s = st->sh;
   const bool rotate = s.family == OPTSTAGE_LLAMA;
