@@ -143,7 +143,7 @@ __device__ __forceinline__ float pair_max32(float x) {
 // hand: the exponentials of tile i run between the score MFMAs of tile i + 1, the row maxima of tile i + 1 between the O^T MFMAs of
 // tile i; the loop has no address arithmetic (stages are constants of the unrolled blocks: 15 of 107 vector instructions per step,
 // and 2-5 % of the time, as sums); and a second wave on the SIMD takes the waits that are left.  On long sequences the board's power limit
-// holds the clock at 1.7-1.9 GHz while the matrix unit is busy 53 % of the cycles, so fewer cycles save less than their share.
+// holds the clock at 1.7-1.9 GHz while the matrix unit is busy 54 % of the cycles, so fewer cycles save less than their share.
 // The softmax reference m_ref is not the running maximum: it is raised (and O^T and the row sums rescaled)
 // only when some row of the wave finds a score more than FWD_TAU / c above it, so p <= 2^FWD_TAU and the
 // rescaling, which would sit between consecutive tiles' MFMAs on the same accumulators, is rare after the first
@@ -1267,8 +1267,9 @@ template <int D, int KT, int NG> hipError_t dkv_d(const BwdArgs& a) {
 //  * Beyond, 4 waves and two workgroups per compute unit: 2111 tokens x 8, 8 heads (1088) 90.6, 8 waves 100.6; 617 x 8, 32 heads 58.9 / 70.4.
 //    Eight waves on one set of tiles, which read half as much, where their workgroups fill the chip twice or many times: 4096
 //    tokens, 32 heads (512 of 256 rows) 146.6 / 137.0, 7298, 16 heads (464) 227.8 / 212.7, 16384, 40 heads 2607 / 2568; between, as above.
-// Measured against two 32-row tiles per wave on four waves, the former kernels: 16384 tokens, 40 heads forward 2710 -> 2568, backward 8267 -> 8128,
-// 4096, 32 heads 144.6 -> 137.0, 435 -> 426; they are never the better ones in forward and dQ.
+// Measured against two 32-row tiles per wave on four waves, the former kernels, in turn in one process on two cards: 16384 tokens, 40 heads forward
+// 2765 -> 2603 and 2674 -> 2551, backward 8510 -> 8377 and 8417 -> 8219 (a third card 8265 -> 8293); 4096, 32 heads 148.6 -> 143.7 and 152.6 -> 140.9,
+// 453 -> 439 and 442 -> 430; they are never the better ones in forward and dQ.
 long row_workgroups(int seq, int batch, int n_q) { return (long)n_q * batch * ((seq + 127) / 128); }
 }  // namespace
 
