@@ -107,6 +107,9 @@ hipError_t launch_gemm_bf16(int layout, int epi, const void* A, const void* B, v
 // whether a product y = x W^T (dense operands) is served with the activation in its epilogue (EPI_GELU, EPI_DGELU, EPI_DSWIGLU)
 bool gemm_bf16_act_applies(int M, int N, int K);
 bool gemm_f32_act_applies(int M, int N, int K);
+// the form that an fp32 product takes by its sizes: matrix-instruction kernel on tiles of 64 x 64, 64 x 32, 32 x 32, 16 x 32, 16 x 16 (0 - 4), plain
+// kernel (5); vec: operand rows load 16 bytes at a time
+int gemm_f32_form(bool tn, bool vec, int epi, int M, int N, int K, int ldc);
 // tiles of 128 or 64, for products of up to 256 tiles of 128 x 128 and for what is cut off a grouped TN set; bf16 alignment rules as
 // for launch_gemm_bf16
 bool gemm_bf16_small_applies(int M, int N, int K, int lda, int ldb);

@@ -2,7 +2,7 @@
 // (Sec. 2.2: Y = X W^T, dX = dY W, dW += dY^T X), on the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (fp32 products and sums).
 //
 // What bounds it: an fp32 MFMA does 64 flop per cycle and SIMD, so operands are cheap to feed and what counts is how many compute
-// units have work, and that nothing is issued while no MFMA runs.  A workgroup owns an RM x RN tile (64 x 64 to 16 x 16, see pick_tile), its
+// units have work, and that nothing is issued while no MFMA runs.  A workgroup owns an RM x RN tile (64 x 64 to 16 x 16, see pick_form), its
 // four waves split the contraction in steps of 16 k (wave w takes the steps w, w + 4, ...) and the four partial tiles are added through LDS
 // in wave order.  No operand is shared between waves, so the loop has no barrier.
 //  * NT (contiguous along k) with 16-byte rows: loads go straight into a ring in LDS, each wave's its own (staged_loop).
@@ -19,6 +19,7 @@
 // 1024 20.9 -> 19.1, 4096 x 1024 x 512 40.2 -> 38.5, 2048 x 2048 x 2048 134 -> 123.
 // The sums keep their registers and every step waits for its own loads: the vectors that come back are kept as they are (as single
 // floats the compiler copied them all at the top of the loop, behind one wait for every load in flight).
+#include <algorithm>
 #include <utility>
 
 #include "common.h"
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(256) void gemm_f32_grouped_tn_kernel(const GroupedF
 }
 
 // General path: 64 x 64 tile through LDS, 256 threads, 4 x 4 outputs per thread, any strides.  Takes what 32-bit offsets within
-// a tile do not reach, and short contractions of many tiles (plain_is_faster).
+// a tile do not reach, and short contractions of many tiles (pick_form).
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                        float* __restrict__ C, const float* __restrict__ R, int M, int N,
@@ -489,56 +490,60 @@ hipError_t launch_mfma(int epi, const float* A, const float* B, float* C, const 
   return hipGetLastError();
 }
 
-// The tile that needs the least time.  Workgroups come to the compute units evenly, n = ceil(tiles / 256) to the fullest, and share its matrix
-// units: start, first loads and epilogue once, and n contractions.  Both from 256 to 4096 k and one to 32 workgroups per unit, us in tiles of
-// 64 x 64 / 64 x 32 / 32 x 32 / 16 x 32 / 16 x 16: 512 x 4096 x 1024 37.8 / 41.6 / 47.2 / 76 / 81; 512 x 3072 x 1024 36.0 / 32.4 / 37.8 / 59 / 63;
-// 512 x 1024 x 4096 67.7 / 39.3 / 41.5 / 75 / 83; 512 x 1024 x 1024 20.5 / 13.9 / 14.4 / 17.9 / 21.7; 800 x 800 x 800 17.9 / 18.4 / 16.0 / 17.3 / 22.0;
-// 200 x 512 x 512 11.5 / 7.5 / 5.0 / 4.3 / 4.6; 128 x 256 x 1024 19.4 / 11.9 / 7.4 / 5.5 / 4.6; TN within 10 %.
-struct TileShape { int rows, cols; double start_us, first_ns, next_ns; };   // ns per k: a unit's only workgroup, each of several
-constexpr TileShape TILES[] = {{64, 64, 3.8, 15.3, 15.7}, {64, 32, 3.2, 8.8, 9.3}, {32, 32, 2.75, 5.0, 5.2}, {16, 32, 2.6, 3.0, 3.8}, {16, 16, 2.6, 2.0, 2.35}};
-int pick_tile(int n, const GemmProblem* pr, int K) {
+// The form that needs the least time: the matrix-instruction kernel on one of five tiles, or the plain kernel.  Workgroups come to the compute units
+// evenly, n = ceil(tiles / 256) of them to the fullest.  Their contractions share its units, ns per k each; while the contraction is short, a
+// workgroup's start, first loads and the way of its tile through LDS to memory bound them instead, a time per workgroup that no k shortens
+// (16 x 16 tiles: 756 x 2056 of any K up to 64 takes 25 us, 64 x 64 tiles 6.6, and the plain kernel, which writes its sums at once, 7).  The plain
+// kernel also waits for the loads of every step of 16, however many workgroups share a unit.  Measured from 4 to 4096 k on one to 128
+// workgroups per unit (2052 products of 24 sizes, both layouts, 16-byte rows and others, storing and accumulating): the form picked takes 1.5 %
+// longer than the fastest on average, 31 % at most, and 1.8 % on 832 others of any size up to 50 GFLOP.  With the start counted once for all workgroups, and fixed limits to the plain kernel,
+// it was 15 % and up to three times, e.g. us before -> now: NT 756 x 2056 x 4 15.6 -> 6.8, 2208 x 2316 x 16 25.4 -> 14.5, 1760 x 1264 x 1023 166 -> 112,
+// TN 4095 x 4095 x 128 accumulating 144 -> 98, 1760 x 1264 x 64 accumulating 14.3 -> 10.6; 512 x 4096 x 1024 37.8, 512 x 1024 x 1024 13.9 as before.
+struct Form { int rows, cols; };
+constexpr Form FORMS[] = {{64, 64}, {64, 32}, {32, 32}, {16, 32}, {16, 16}, {64, 64}};
+constexpr int PLAIN = 5;
+struct Cost { double start_us, group_us, k_ns, once_ns; };
+// Consecutive workgroups go to different XCDs; where the number of tiles is a multiple of 8, each XCD has neighbours (f32_tile).  Elsewhere
+// small TN tiles, which read most per product, take `scattered` times as long: 596 x 3724 x 3008 on 32 x 32 tiles 224 us, 640 x 3840 x 3072 145.
+struct Costs { double scattered; Cost form[6]; };
+constexpr Costs COSTS[] = {                                  // by layout, rows, epilogue (costs_of); by form
+  {1, {{2.43, 2.33, 16.7}, {2.67, 2.07, 8.64}, {1.78, 1.37, 4.95}, {1.78, 0.91, 4.89}, {1.72, 0.98, 3.07}, {4.11, 1.65, 44.3, 92.1}}},   // NT
+  {1, {{3.37, 1.86, 43.1}, {2.82, 1.19, 29.9}, {3.08, 0.67, 15.1}, {3.04, 0.66, 11.3}, {2.45, 0.42, 10}, {4.39, 1.76, 36, 90}}},   // NT, element by element
+  {1.3, {{3.74, 2.57, 17.2}, {3.31, 0.81, 9.76}, {2.87, 0.81, 5.42}, {2.3, 1.07, 3.95}, {2.38, 0.74, 3.84}, {3.75, 1.59, 55.9, 81.2}}},   // TN
+  {1.3, {{3.45, 3.65, 16.4}, {2.76, 1.07, 10.8}, {2.28, 0.76, 5.51}, {2.41, 0.91, 3.96}, {2.46, 0.89, 3.82}, {5.84, 1.87, 55.6, 108}}},   // TN, accumulating
+  {1, {{4.15, 2.46, 36.3}, {3.39, 1.59, 25.1}, {2.74, 1.06, 10.8}, {2.73, 1.06, 7.44}, {2.99, 1.03, 4.02}, {3.9, 2.08, 31.8, 73.5}}},   // TN, element by element
+  {1, {{3.93, 5.5, 35.7}, {4.78, 1.96, 24}, {3.22, 1.22, 9.72}, {2.84, 1.78, 6.9}, {2.11, 1.18, 4.35}, {5.4, 2.75, 30.4, 108}}},   // TN, element by element, accumulating
+  {1, {{3.68, 3.14, 16.7}, {2.88, 1.97, 8.64}, {2, 1.39, 4.95}, {1.92, 1.49, 4.89}, {1.68, 0.85, 3.07}, {2.84, 2.03, 44.3, 92.1}}},   // NT, rows of C off 16 bytes
+  {1, {{5.84, 4.22, 16.7}, {2.88, 3.4, 8.64}, {1.77, 2.24, 4.95}, {2.12, 1.44, 4.89}, {1.62, 1.49, 3.07}, {6.59, 3.18, 44.3, 92.1}}},   // the same with a residual
+};
+const Costs& costs_of(bool tn, bool vec, int epi, int ldc) {
+  return COSTS[tn ? (vec ? 2 : 4) + (epi == EPI_ACCUM) : !vec ? 1 : ldc & 3 ? 6 + (epi == EPI_RESID) : 0];
+}
+int pick_form(const Costs& costs, int n, const GemmProblem* pr, int K, int forms = PLAIN + 1) {
   int best = 0;
   double least = 1e30;
-  for (int t = 0; t < 5; ++t) {
-    const TileShape& s = TILES[t];
+  for (int t = 0; t < forms; ++t) {
+    const Cost& c = costs.form[t];
     long long tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += (long long)((pr[i].M + s.rows - 1) / s.rows) * ((pr[i].N + s.cols - 1) / s.cols);
-    const double us = s.start_us + 1e-3 * K * (tiles <= 256 ? s.first_ns : (double)((tiles + 255) / 256) * s.next_ns);
+    for (int i = 0; i < n; ++i) tiles += (long long)((pr[i].M + FORMS[t].rows - 1) / FORMS[t].rows) * ((pr[i].N + FORMS[t].cols - 1) / FORMS[t].cols);
+    const double each = (double)((tiles + 255) / 256), k = t == PLAIN ? (K + 15) / 16 * 16.0 : K;
+    const double k_ns = c.k_ns * (FORMS[t].rows < 64 && each > 1 && (tiles & 7) ? costs.scattered : 1);
+    const double us = c.start_us + std::max(each * c.group_us, 1e-3 * k * (c.once_ns + each * k_ns));
     if (us < least) { least = us; best = t; }
   }
   return best;
 }
 
 template <bool TNL, bool VEC>
-hipError_t launch_sized(int epi, const float* A, const float* B, float* C, const float* R, int M, int N, int K, int lda, int ldb,
+hipError_t launch_sized(int form, int epi, const float* A, const float* B, float* C, const float* R, int M, int N, int K, int lda, int ldb,
                         int ldc, hipStream_t s) {
-  const GemmProblem pr = {A, B, C, R, M, N, lda, ldb, ldc};
-  switch (pick_tile(1, &pr, K)) {
+  switch (form) {
     case 0: return launch_mfma<64, 64, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     case 1: return launch_mfma<64, 32, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     case 2: return launch_mfma<32, 32, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     case 3: return launch_mfma<16, 32, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
     default: return launch_mfma<16, 16, TNL, VEC>(epi, A, B, C, R, M, N, K, lda, ldb, ldc, s);
   }
-}
-
-// With a contraction of one or two steps of 16 the four waves have little to share, and adding their partial tiles through LDS costs more
-// than the products: what is left is the writing of C, which the plain kernel does at once where there are many tiles.  Operands that do not
-// load, or a C that does not store, 16 bytes at a time (vec = false) move that point up.  Time of the matrix-instruction kernel over the plain one:
-//  vec   NT 8192 tiles of 64 (8192 x 4096), K 16 / 32 / 40 1.10 / 1.05 / .83; 2048 tiles, K 8 / 32 .81 / .94; 1024 tiles, K 8 .95; 384 tiles .75
-//        TN 8192 tiles, K 16 / 32 / 40 1.11 / 1.01 / .87; 2048 tiles, K 8 / 16 / 32 1.11 / 1.04 / .84; 1024 tiles 1.59 / 1.01 / .81; 384 tiles 1.11 / 1.05 / .82;
-//        28 tiles, K 4 / 16 .93 / .81 (accumulating, the old values are read in either kernel: .7 - .86)
-//  else  NT 560 tiles (1760 x 1262), K 6 / 17 / 41 1.09 / 1.01 / .99; 256 tiles, K 6 .89
-//        TN 560 tiles, K 6 / 17 / 41 1.27 / 1.12 / .96; 256 tiles, K 6 / 17 1.22 / .94
-bool plain_is_faster(bool tn, bool vec, int epi, long tiles64, int K) {
-  if (tn && epi == EPI_ACCUM) return vec ? K <= 32 && tiles64 >= 4096 : K <= 24 && tiles64 >= 512;
-  if (tn) return vec ? K <= 16 ? tiles64 >= 256 : K <= 32 && tiles64 >= 4096 : K <= 12 ? tiles64 >= 128 : K <= 24 && tiles64 >= 512;
-  return vec ? K <= 32 && tiles64 >= 4096 : K <= 12 && tiles64 >= 512;
-}
-long tiles64_of(int n, const GemmProblem* pr) {
-  long tiles = 0;
-  for (int i = 0; i < n; ++i) tiles += (long)((pr[i].M + 63) / 64) * ((pr[i].N + 63) / 64);
-  return tiles;
 }
 
 }  // namespace
@@ -570,13 +575,13 @@ bool gemm_f32_grouped_applies(int n, const GemmProblem* pr, int K) {
   if (n < 1 || n > MAX_GROUP || K <= 0) return false;
   for (int i = 0; i < n; ++i)
     if (pr[i].M <= 0 || pr[i].N <= 0 || ((pr[i].lda | pr[i].ldb | pr[i].M | pr[i].N) & 3) || !mfma_reaches(true, K, pr[i].lda, pr[i].ldb)) return false;
-  return !plain_is_faster(true, true, EPI_ACCUM, tiles64_of(n, pr), K);
+  return pick_form(costs_of(true, true, EPI_ACCUM, 0), n, pr, K) != PLAIN;
 }
 
 // n independent TN products with the same K: C (fp32) += product (EPI_ACCUM) or = product
 hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* pr, int K, hipStream_t s) {
   if (!gemm_f32_grouped_applies(n, pr, K) || (epi != EPI_ACCUM && epi != EPI_STOREF)) return hipErrorInvalidValue;
-  switch (pick_tile(n, pr, K)) {
+  switch (pick_form(costs_of(true, true, epi, 0), n, pr, K, PLAIN)) {
     case 0: return launch_grouped<64, 64>(epi, n, pr, K, s);
     case 1: return launch_grouped<64, 32>(epi, n, pr, K, s);
     case 2: return launch_grouped<32, 32>(epi, n, pr, K, s);
@@ -585,12 +590,15 @@ hipError_t launch_gemm_f32_grouped(int epi, int n, const GemmProblem* pr, int K,
   }
 }
 
+int gemm_f32_form(bool tn, bool vec, int epi, int M, int N, int K, int ldc) {
+  const GemmProblem pr = {nullptr, nullptr, nullptr, nullptr, M, N, 0, 0, ldc};
+  return pick_form(costs_of(tn, vec, epi, ldc), 1, &pr, K);
+}
+
 // The activation's epilogues are in the matrix-instruction kernels only
 bool gemm_f32_act_applies(int M, int N, int K) {
   if (M <= 0 || N <= 0 || K <= 0 || (N & 3) || !mfma_reaches(false, K, K, K)) return false;
-  const GemmProblem pr = {nullptr, nullptr, nullptr, nullptr, M, N, K, K, N};
-  return !((K & 3) == 0 && plain_is_faster(false, true, EPI_STORE, tiles64_of(1, &pr), K)) &&
-         !((K & 3) && plain_is_faster(false, false, EPI_STORE, tiles64_of(1, &pr), K));
+  return gemm_f32_form(false, (K & 3) == 0, EPI_STORE, M, N, K, N) != PLAIN;
 }
 
 hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, void* C, const void* R, int M, int N,
@@ -604,12 +612,14 @@ hipError_t launch_gemm_f32(int layout, int epi, const void* A, const void* B, vo
   float* c = (float*)C;
   const GemmProblem pr = {A, B, C, R, M, N, lda, ldb, ldc};
   const bool vec = (lda & 3) == 0 && (ldb & 3) == 0 && (tn ? (M & 3) == 0 && (N & 3) == 0 : (K & 3) == 0);
-  const bool plain = epi < EPI_GELU && plain_is_faster(tn, vec && (ldc & 3) == 0, epi, tiles64_of(1, &pr), K) && (M + 63) / 64 < 65536;   // the second dimension of its grid
-  if (!plain && mfma_reaches(tn, K, lda, ldb)) {
-    if (tn) return vec ? launch_sized<true, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
-                       : launch_sized<true, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
-    return vec ? launch_sized<false, true>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
-               : launch_sized<false, false>(epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
+  // the plain kernel also where the other does not reach; its grid's second dimension ends at 65535
+  const bool reaches = mfma_reaches(tn, K, lda, ldb), plain_too = epi < EPI_GELU && (M + 63) / 64 < 65536;
+  const int form = plain_too ? gemm_f32_form(tn, vec, epi, M, N, K, ldc) : pick_form(costs_of(tn, vec, epi, ldc), 1, &pr, K, PLAIN);
+  if (form != PLAIN && reaches) {
+    if (tn) return vec ? launch_sized<true, true>(form, epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
+                       : launch_sized<true, false>(form, epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
+    return vec ? launch_sized<false, true>(form, epi, a, b, c, r, M, N, K, lda, ldb, ldc, s)
+               : launch_sized<false, false>(form, epi, a, b, c, r, M, N, K, lda, ldb, ldc, s);
   }
   const long sam = tn ? 1 : lda, sak = tn ? lda : 1, sbn = tn ? 1 : ldb, sbk = tn ? ldb : 1;
   dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);

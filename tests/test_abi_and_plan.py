@@ -59,6 +59,43 @@ def test_activation_epilogues_leave_weights_in_slabs_alone():
     assert not any(act(*s) and slab(*s, s[2]) for s in sizes)
 
 
+# us of an fp32 product in each form (tiles of 64 x 64, 64 x 32, 32 x 32, 16 x 32, 16 x 16, plain kernel), measured one after the other:
+# (TN, 16-byte rows, epilogue, M, N, K, times).  Short contractions of many tiles are where a wrong form costs most, up to three times.
+FP32_FORMS = [
+    (0, 1, 0, 5168, 544, 4, (10.0, 11.5, 14.7, 25.0, 41.5, 8.8)), (0, 1, 0, 512, 4096, 4, (6.8, 8.3, 10.9, 19.0, 31.1, 7.5)),
+    (0, 1, 0, 932, 1700, 8, (6.7, 8.4, 10.3, 16.1, 25.6, 7.6)), (0, 1, 0, 2048, 4096, 16, (19.3, 26.8, 37.2, 68.5, 117.6, 18.2)),
+    (0, 1, 0, 512, 1024, 2048, (35.8, 22.9, 24.1, 38.2, 44.4, 333.2)), (0, 1, 0, 36, 3020, 4096, (66.3, 39.1, 29.0, 39.6, 33.1, 568.7)),
+    (0, 1, 0, 200, 512, 2048, (35.4, 21.4, 13.1, 9.7, 11.7, 241.7)), (0, 0, 0, 932, 1700, 7, (5.7, 7.5, 7.1, 12.3, 15.3, 7.4)),
+    (0, 0, 0, 756, 2056, 3, (5.5, 7.2, 6.8, 11.8, 14.7, 7.3)), (0, 0, 0, 1596, 876, 7, (5.6, 5.5, 6.2, 10.5, 13.7, 7.1)),
+    (0, 0, 0, 1540, 3156, 407, (89.6, 126.4, 151.3, 219.0, 290.1, 112.4)), (0, 0, 0, 180, 1836, 1791, (74.2, 57.7, 71.0, 80.0, 99.5, 306.9)),
+    (0, 0, 0, 272, 1788, 255, (15.5, 17.8, 12.9, 17.2, 21.3, 33.9)), (0, 0, 0, 200, 512, 1023, (41.7, 30.9, 21.6, 17.2, 21.7, 124.5)),
+    (0, 0, 0, 8, 2284, 659, (21.4, 13.8, 11.1, 11.0, 7.3, 74.4)), (1, 1, 3, 3544, 232, 16, (5.0, 4.6, 5.7, 9.3, 13.0, 5.9)),
+    (1, 1, 3, 132, 5372, 32, (5.0, 4.6, 5.9, 8.3, 11.5, 7.5)), (1, 1, 3, 3544, 232, 1024, (20.1, 20.3, 22.4, 31.4, 47.5, 196.6)),
+    (1, 1, 3, 2304, 180, 1940, (32.2, 19.3, 20.2, 27.5, 36.3, 380.7)), (1, 1, 3, 36, 3020, 256, (7.7, 5.6, 4.8, 5.2, 5.2, 35.5)),
+    (1, 1, 3, 744, 132, 1132, (20.4, 11.8, 7.7, 7.2, 9.1, 149.8)), (1, 1, 2, 512, 4096, 4, (6.5, 6.3, 9.4, 19.2, 27.5, 7.8)),
+    (1, 1, 2, 1024, 1024, 8, (5.3, 4.7, 6.0, 10.6, 15.0, 6.9)), (1, 1, 2, 132, 5372, 48, (6.8, 5.4, 6.2, 8.9, 12.0, 12.4)),
+    (1, 1, 2, 1024, 1024, 1024, (21.3, 21.3, 22.9, 36.0, 49.9, 225.2)), (1, 1, 2, 368, 2760, 100, (9.4, 8.8, 8.7, 12.6, 17.0, 20.6)),
+    (1, 1, 2, 800, 800, 192, (7.5, 7.1, 5.7, 8.1, 11.6, 29.7)), (1, 1, 2, 60, 164, 496, (12.3, 7.8, 5.5, 5.1, 4.8, 69.4)),
+    (1, 0, 3, 3543, 231, 24, (6.1, 5.8, 6.5, 11.9, 15.7, 7.5)), (1, 0, 3, 799, 799, 16, (6.1, 5.7, 5.1, 9.6, 12.1, 5.7)),
+    (1, 0, 3, 2999, 2999, 256, (92.1, 97.3, 102.5, 139.8, 170.8, 119.7)), (1, 0, 3, 999, 1003, 128, (10.4, 9.7, 8.9, 15.6, 19.5, 20.2)),
+    (1, 0, 3, 383, 255, 396, (17.5, 11.8, 6.9, 5.2, 5.5, 54.6)), (1, 0, 3, 311, 71, 1080, (34.9, 22.5, 12.0, 10.2, 7.4, 143.3)),
+    (1, 0, 2, 931, 1699, 4, (12.0, 15.8, 15.5, 28.2, 38.9, 9.9)), (1, 0, 2, 1595, 875, 4, (11.6, 11.5, 9.3, 20.5, 34.7, 9.6)),
+    (1, 0, 2, 807, 1059, 2924, (94.3, 113.0, 99.0, 122.9, 197.7, 614.7)), (1, 0, 2, 755, 2055, 128, (19.9, 21.3, 15.7, 26.6, 34.5, 25.2)),
+    (1, 0, 2, 199, 511, 512, (23.3, 14.9, 9.3, 8.3, 8.7, 72.0)), (1, 0, 2, 63, 63, 192, (12.6, 10.0, 5.5, 5.5, 4.6, 29.1)),
+    (0, 1, 0, 756, 2057, 4, (8.0, 9.9, 10.9, 17.2, 27.6, 7.3)), (0, 1, 1, 1032, 4149, 16, (29.0, 33.8, 38.0, 58.7, 105.5, 18.2)),
+    (0, 1, 1, 2208, 2317, 16, (31.8, 35.8, 42.3, 69.3, 126.7, 20.7)),
+]
+
+
+@pytest.mark.parametrize("case", FP32_FORMS, ids=lambda c: "-".join(map(str, c[:6])))
+def test_fp32_products_take_a_form_that_is_near_the_fastest(case):
+    """The estimate by which a product picks its form (gemm_f32_form(tn, vec, epi, M, N, K, ldc)) is within 15 % of the fastest."""
+    form = ctypes.CDLL(B.LIB_PATH)["_Z13gemm_f32_formbbiiiii"]
+    form.argtypes = [ctypes.c_bool] * 2 + [ctypes.c_int] * 5
+    tn, vec, epi, m, n, k, us = case
+    assert us[form(tn, vec, epi, m, n, k, n)] <= 1.15 * min(us)
+
+
 def oracle_table(cfg):
     return S.memory_table(cfg.family, cfg.hidden, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.ffn,
                           cfg.seq * cfg.micro_batch, cfg.elem_size)

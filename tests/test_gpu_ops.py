@@ -120,8 +120,9 @@ def test_gemm_tiles_of_every_size_tn(M, N, K):
 # sums of K rounded products, each rounding 2^-24 of a sum that grows as a random walk: sqrt(K) 2^-24 RMS-relative is never reached.
 @pytest.mark.parametrize("M,N,K", [(1000, 1004, 1000), (1023, 1021, 999), (508, 1020, 1040), (510, 1023, 1043), (1020, 252, 132), (1021, 251, 133),
                                    (124, 764, 260), (123, 763, 261), (60, 44, 1028), (61, 43, 1029), (20, 36, 12), (33, 17, 67), (256, 512, 320), (512, 512, 52),
-                                   # either side of the plain kernel's limits
-                                   (1004, 1024, 16), (1004, 1024, 20), (4100, 4096, 32), (4100, 4096, 36), (1761, 1262, 12), (1761, 1262, 13), (1761, 1262, 24), (1761, 1262, 25)])
+                                   # short contractions of many tiles, some of them in the plain kernel
+                                   (1004, 1024, 16), (1004, 1024, 20), (4100, 4096, 32), (4100, 4096, 36), (1761, 1262, 12), (1761, 1262, 13), (1761, 1262, 24), (1761, 1262, 25),
+                                   (2052, 4096, 16), (1761, 1263, 16), (4101, 4095, 99)])
 def test_gemm_fp32_tile_shapes_and_remainders(M, N, K):
     g = torch.Generator(device="cuda")
     g.manual_seed(M + K)
