@@ -1278,30 +1278,39 @@ hipError_t launch_attn_fwd_mfma(const void* qkv, void* o, float* lse, int seq, i
   // heads of 64: three workgroups of four waves fit a compute unit; 246 tokens x 2, 16 heads (64) 9.3 -> 8.4 us, 1993, 16 heads (256) 42.5 -> 41.3,
   // 5661 x 8, one head (360) 108.7 -> 115.6
   if (d == 64) return W <= 256 ? fwd_d<64, 2, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s) : fwd_d<64, 4, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s);
-  if (W <= 256 && seq <= 128) return fwd_d<128, 2, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s);
+  // one group of 2 waves over two where the compute units are full of rows of a few tiles: 192 tokens, W = 256 9.1 / 9.7 us, 256 10.9 / 11.2; W = 128 8.4 / 7.9, 9.4 /
+  // 8.7; 320 tokens, W = 192 11.5 / 10.3
+  if (W <= 256 && seq <= (W > 192 ? 256 : 128)) return fwd_d<128, 2, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s);
   if (W <= 256 || (W <= 448 && seq > 640)) return fwd_d<128, 2, 2>(qkv, o, lse, seq, batch, n_q, n_kv, s);
   if (W > 448 && W <= 512 && seq > 1600) return fwd_d<128, 4, 2>(qkv, o, lse, seq, batch, n_q, n_kv, s);
   return (wide > 416 && wide <= 512) || wide >= 2048 ? fwd_d<128, 8, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s)
                                                      : fwd_d<128, 4, 1>(qkv, o, lse, seq, batch, n_q, n_kv, s);
 }
 
+// Heads of 64, dK / dV: groups of waves that share a workgroup's keys.  WK = workgroups.  Up to two of them per compute unit two groups pay, with
+// grouped heads also on short sequences, since a workgroup has all of a group's queries; us, one group -> two: 7298 tokens, 16 / 4 heads 1020 ->
+// 887, 100 x 8, 16 / 4 26.2 -> 23.9, 1000 x 4, 64 / 8 (256) 325 -> 281, 1600 x 4, 32 / 8 (416) 289 -> 252.  Not beyond: 256 x 16, 32 / 16 (512) 62.1 -> 73.5,
+// 640 x 16, 32 / 8 (640) 175 -> 199, 3000 x 4, 32 / 8 (768) 746 -> 809, 2048 x 8, 64 / 8 (1024) 1479 -> 1602; at 512 from some 1000 tokens on: 4096 x 2,
+// 32 / 8 790 -> 688.  Without grouped heads 6426, 8 heads (408) 326 -> 293, 1024 x 4, 16 heads (512) 65.7 -> 66.8, 2111 x 8, 8 heads (1088) 205 ->
+// 223, 128 x 16, 16 heads (256) 16.1 -> 17.1.
+int attn_d64_key_groups(int seq, int batch, int n_q, int n_kv) {
+  const long WK = row_workgroups(seq, batch, n_kv);
+  return WK <= 480 ? (n_q > n_kv || seq > 128 ? 2 : 1) : n_q > n_kv && WK <= 512 && seq > 640 ? 2 : 1;
+}
+
 hipError_t launch_attn_bwd_mfma(const void* qkv, const void* o, const void* dout, const float* lse, void* dqkv, float* ws,
                                 int seq, int batch, int n_q, int n_kv, int d, hipStream_t s, void* qcopy, const float2* rope) {
-  const long W = row_workgroups(seq, batch, n_q), WK = row_workgroups(seq, batch, n_kv);
+  const long W = row_workgroups(seq, batch, n_q);
   const BwdArgs a = {qkv, o, dout, lse, dqkv, ws, seq, batch, n_q, n_kv, s, qcopy, rope};
   hipError_t e;
   if (d == 64) {
     // dQ as in the forward pass: 1993 tokens, 16 heads (256) 101.2 -> 87.5 of both kernels' time, 6408, 8 heads (408) 418.6 -> 387.2, 361 x 3, 32 heads
-    // (288) 37.2 -> 38.8, 1108, 64 heads (576) 138.7 -> 144.1
-    if (W <= 256 && seq < (W > 128 ? 160 : 110)) e = dq_d<64, 2, 1>(a);
+    // (288) 37.2 -> 38.8, 1108, 64 heads (576) 138.7 -> 144.1; 192 tokens x 4, 32 heads (256) 18.6 -> 19.2
+    if (W <= 256 && seq < (W > 128 ? 200 : 110)) e = dq_d<64, 2, 1>(a);
     else if (W <= 256 || (W <= 448 && seq > 640)) e = dq_d<64, 2, 2>(a);
     else e = dq_d<64, 4, 1>(a);
     if (e != hipSuccess) return e;
-    // dK / dV, one group -> two: with grouped heads a workgroup has all of a group's queries, 7298 tokens, 16 / 4 heads 1020 -> 887, 100 x 8,
-    // 16 / 4 26.2 -> 23.9; without, 6426, 8 heads (408) 326 -> 293, 1024 x 4, 16 heads (512) 65.7 -> 66.8, 2111 x 8, 8 heads (1088) 205 -> 223,
-    // 128 x 16, 16 heads (256) 16.1 -> 17.1
-    const bool two = n_q > n_kv ? WK <= 1024 : WK <= 480 && seq > 128;
-    return two ? dkv_d<64, 1, 2>(a) : dkv_d<64, 1, 1>(a);
+    return attn_d64_key_groups(seq, batch, n_q, n_kv) == 2 ? dkv_d<64, 1, 2>(a) : dkv_d<64, 1, 1>(a);
   }
   // dQ: 5661 tokens x 8, one head (360) 2 waves 271.6, 4 x 2 254.2, 2 x 2 275.5; 671 x 3, 16 heads (288) 48.2 / 54.7 / 54.5; 2048, 32 heads (512) 133.7 /
   // 137.3; 5096 x 8, 2 heads (640) 404 / 395, 8 waves 402; 2742 x 2, 16 heads (704) 265 / 265, 8 waves 254; 4096, 32 heads (1024) 474 / 459, 8 waves 426

@@ -171,3 +171,5 @@ bool attn_bwd_inplace_applies(int dtype, int d, int seq, int batch, int n_q, int
 hipError_t launch_attn_bwd_inplace(int dtype, void* qkv, const void* o, const void* dout, const float* lse, void* qcopy, const float* rope_table,
                                    float* ws, int seq, int batch, int n_q, int n_kv, int d, hipStream_t s);
 uint64_t attn_bwd_ws_floats(int seq, int batch, int n_q, int n_kv, int d);
+// heads of 64: how many groups of waves share the keys of a dK / dV workgroup
+int attn_d64_key_groups(int seq, int batch, int n_q, int n_kv);

@@ -96,6 +96,18 @@ def test_fp32_products_take_a_form_that_is_near_the_fastest(case):
     assert us[form(tn, vec, epi, m, n, k, n)] <= 1.15 * min(us)
 
 
+# us of the attention gradient, heads of 64, with one group of waves on a dK / dV workgroup's keys and with two: (tokens, sequences, n_q, n_kv, times)
+D64_GROUPS = [(400, 4, 32, 8, (72.2, 62.1)), (1000, 4, 64, 8, (324.6, 281.2)), (1600, 4, 32, 8, (289.3, 251.8)), (4096, 2, 32, 8, (789.8, 688.4)), (256, 16, 32, 16, (62.1, 73.4)),
+              (400, 16, 32, 16, (113.2, 127.1)), (640, 16, 32, 8, (175.0, 198.2)), (3000, 4, 32, 8, (745.9, 810.0)), (2048, 8, 64, 8, (1479.0, 1601.7)),
+              (1300, 8, 16, 8, (171.2, 184.8)), (65, 8, 64, 8, (46.9, 39.2)), (640, 16, 8, 8, (56.6, 62.9)), (1000, 2, 8, 8, (48.0, 44.3))]
+
+
+@pytest.mark.parametrize("case", D64_GROUPS, ids=lambda c: "-".join(map(str, c[:4])))
+def test_attention_of_64_wide_heads_divides_its_keys_the_faster_way(case):
+    groups = ctypes.CDLL(B.LIB_PATH)["_Z19attn_d64_key_groupsiiii"]
+    assert case[4][groups(*case[:4]) - 1] <= 1.02 * min(case[4])
+
+
 def oracle_table(cfg):
     return S.memory_table(cfg.family, cfg.hidden, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.ffn,
                           cfg.seq * cfg.micro_batch, cfg.elem_size)
