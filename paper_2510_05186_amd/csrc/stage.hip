@@ -600,8 +600,9 @@ optstage_status k_attn_bwd(optstage* st, const void* qkv, const void* o, const v
 // both).  `scratch` is a packed [tokens, qkv] transient.  Where the tile kernels serve the call they write the slot themselves,
 // rotated, and keep Q in the scratch meanwhile: no pass over the gradient follows.  Otherwise it goes to the scratch and a kernel moves
 // it into the slot (rotary, or a plain copy for the family without).  Layers whose size takes rotary into the QKV projection's
-// epilogue keep the rotary kernel here: it is .4 % of such a layer (4096 tokens, hidden 4096, two micro-batches 8865 us: 35 us) against 1.5 %
-// of one of hidden 1024 and 320 tokens, where the launch is most of it; the gradient in place has not been timed on them.
+// epilogue still use the rotary kernel here, not because it is faster: the gradient in place would take .2 to .5 % off them (4096 tokens, two
+// micro-batches, us, kernel / in place: hidden 4096 8628 / 8592 and 8640 / 8599, hidden 8192 31574 / 31491 and 31515 / 31459) and round their
+// dQ and dK once less.  At hidden 1024 and 320 tokens, where the launch is most of the kernel, it is 1.5 %.
 optstage_status k_attn_bwd_slot(optstage* st, void* qkv, const void* o, const void* dout, const float* lse, void* scratch) {
   const Shape& s = st->sh;
   const bool rotate = s.family == OPTSTAGE_LLAMA;
